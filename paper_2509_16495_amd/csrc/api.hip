@@ -401,14 +401,12 @@ int shiftattn_unpack_o_proj(const void* recv, const void* w_o, void* out, int32_
 
 size_t shiftattn_proj_workspace_bytes(int32_t rows, int32_t n_features, int32_t k) {
     if (rows < 1 || n_features < 1 || k < 1 || force_generic()) return 0;
-    if (proj_stream_takes(rows, n_features, k, false, static_cast<size_t>(-1))) return proj_stream_workspace(rows, n_features, k, false);
-    return proj_gemm_workspace(rows, n_features, k, false);
+    return proj_workspace(rows, n_features, k, false);
 }
 
 size_t shiftattn_proj_workspace_bytes_fp8(int32_t rows, int32_t n_features, int32_t k) {
     if (rows < 1 || n_features < 1 || k < 1 || force_generic()) return 0;
-    if (proj_stream_takes(rows, n_features, k, true, static_cast<size_t>(-1))) return proj_stream_workspace(rows, n_features, k, true);
-    return proj_gemm_workspace(rows, n_features, k, true);
+    return proj_workspace(rows, n_features, k, true);
 }
 
 int shiftattn_quantize_rows_fp8(const void* x, void* codes, float* scales, int32_t rows, int32_t cols, void* stream) {

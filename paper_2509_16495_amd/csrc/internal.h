@@ -158,9 +158,12 @@ hipError_t launch_unpack_o_proj(const void* recv, const void* w_o, void* out, in
                                 hipStream_t st);
 // bytes of workspace that let the large-batch kernel split k over workgroups for its last (or only) round of tiles; 0: no split
 size_t proj_gemm_workspace(int M_out, int N, int K, bool fp8);
+// what the large-batch kernel is expected to take with a workspace of this size, in microseconds
+double proj_gemm_us(int M_out, int N, int K, bool fp8, size_t workspace_bytes);
 // proj_stream.hip : the same two products for up to 64 token rows, organised around one pass over the weights
-size_t proj_stream_workspace(int M_out, int N, int K, bool fp8);
 bool proj_stream_takes(int M_out, int N, int K, bool fp8, size_t workspace_bytes);
+// the workspace that the size query names (shiftattn_proj_workspace_bytes)
+size_t proj_workspace(int M_out, int N, int K, bool fp8);
 hipError_t launch_qkv_proj_stream(const void* x, const void* w_qkv, void* send, int d_model, const XchgShape& s,
                                   const float* x_scales, const float* w_scales, void* workspace, hipStream_t st);
 hipError_t launch_o_proj_stream(const void* recv, const void* w_o, void* out, int d_model, const XchgShape& s,

@@ -306,6 +306,7 @@ __global__ __launch_bounds__(kSThreads) void proj_stream_kernel(StreamParams p) 
 
 // kg > 1: result[t][f .. f + 3] = sum over the k groups in group order, rounded once
 // (row_base: partial row r is row row_base + r of the result)
+constexpr int kFinishAhead = 4;
 __global__ __launch_bounds__(256) void proj_stream_finish_kernel(StreamParams p, int t_rows, int row_base) {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
     const int quads = p.N / 4;
@@ -315,10 +316,21 @@ __global__ __launch_bounds__(256) void proj_stream_finish_kernel(StreamParams p,
     f32x4 sum = {0.f, 0.f, 0.f, 0.f};
     if (t < p.M) {
         sum = *reinterpret_cast<const f32x4*>(p.partial + static_cast<size_t>(r) * p.N + f);
-        for (int c = 1; c < p.kg; ++c) {
-            const f32x4 v = *reinterpret_cast<const f32x4*>(p.partial + (static_cast<size_t>(c) * t_rows + r) * p.N + f);
+        // four ranges are requested at a time: added one by one, each would be a round trip to memory of its own
+        const float* src = p.partial + static_cast<size_t>(r) * p.N + f;
+        const size_t range = static_cast<size_t>(t_rows) * p.N;
+        for (int c = 1; c < p.kg; c += kFinishAhead) {
+            f32x4 v[kFinishAhead];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) sum[e] += v[e];
+            for (int x = 0; x < kFinishAhead; ++x)
+                if (c + x < p.kg) v[x] = *reinterpret_cast<const f32x4*>(src + (c + x) * range);
+#pragma unroll
+            for (int x = 0; x < kFinishAhead; ++x) {
+                if (c + x < p.kg) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) sum[e] += v[x][e];
+                }
+            }
         }
         if (p.xs) {   // the scales of FP8 operands, applied as the unsplit kernel applies them
             const float row_scale = p.xs[t];
@@ -333,23 +345,6 @@ __global__ __launch_bounds__(256) void proj_stream_finish_kernel(StreamParams p,
 struct StreamPlan {
     int tb, kwb, kg;   // token blocks of 16, steps per wavefront's k slice, k groups; tb == 0: not served
 };
-
-// The largest k slice per wavefront that fits the registers decides how many workgroups must share a block of features.
-StreamPlan plan_stream(int M_out, int K, bool fp8) {
-    StreamPlan pl = {0, 0, 0};
-    const int step_k = kStepRowBytes / (fp8 ? 1 : 2);
-    if (M_out < 1 || M_out > 64 || K % (kSWaves * step_k) != 0) return pl;
-    const int tb = M_out <= 16 ? 1 : M_out <= 32 ? 2 : 4;
-    const int per_wave = K / (kSWaves * step_k);   // steps per wavefront if one workgroup covered all of k
-    for (int kwb = 16 / tb; kwb >= 1; kwb /= 2) {
-        if (per_wave % kwb != 0) continue;
-        const int kg = per_wave / kwb;
-        if (kg > 8 || kSGrid % kg != 0) continue;
-        pl = {tb, kwb, kg};
-        return pl;
-    }
-    return pl;
-}
 
 template <int TB>
 constexpr int stream_stages() { return TB == 1 ? 9 : TB == 2 ? 8 : 7; }
@@ -369,9 +364,24 @@ hipError_t init_stream() {
                                hipFuncAttributeMaxDynamicSharedMemorySize, stream_lds<TB>());
 }
 
-// the instantiated (token blocks, steps per k slice) pairs: X(tb, kwb)
+// the instantiated (token blocks, steps per k slice) pairs: X(tb, kwb), largest slices first (10 and 5: k = 5120)
 #define SHIFTATTN_STREAM_SHAPES(X) \
-    X(1, 16) X(1, 8) X(1, 4) X(1, 2) X(1, 1) X(2, 8) X(2, 4) X(2, 2) X(2, 1) X(4, 4) X(4, 2) X(4, 1)
+    X(1, 16) X(1, 10) X(1, 8) X(1, 5) X(1, 4) X(1, 2) X(1, 1) X(2, 8) X(2, 5) X(2, 4) X(2, 2) X(2, 1) X(4, 4) X(4, 2) X(4, 1)
+
+// The largest k slice per wavefront that is built decides how many workgroups (at most eight) must share a block of
+// features.
+StreamPlan plan_stream(int M_out, int K, bool fp8) {
+    StreamPlan pl = {0, 0, 0};
+    const int step_k = kStepRowBytes / (fp8 ? 1 : 2);
+    if (M_out < 1 || M_out > 64 || K % (kSWaves * step_k) != 0) return pl;
+    const int tb = M_out <= 16 ? 1 : M_out <= 32 ? 2 : 4;
+    const int per_wave = K / (kSWaves * step_k);   // steps per wavefront if one workgroup covered all of k
+#define SHIFTATTN_STREAM_TRY(tb_, kwb_) \
+    if (pl.tb == 0 && tb == tb_ && per_wave % kwb_ == 0 && per_wave / kwb_ <= 8) pl = {tb_, kwb_, per_wave / kwb_};
+    SHIFTATTN_STREAM_SHAPES(SHIFTATTN_STREAM_TRY)
+#undef SHIFTATTN_STREAM_TRY
+    return pl;
+}
 
 hipError_t run_stream(StreamParams p, const StreamPlan& pl, void* workspace, hipStream_t st) {
     p.kg = pl.kg;
@@ -423,16 +433,41 @@ hipError_t proj_stream_init() {
     return e;
 }
 
-// bytes of workspace the streaming kernel needs for M_out token rows (0: none, or the shape is not served by it)
-size_t proj_stream_workspace(int M_out, int N, int K, bool fp8) {
-    const StreamPlan pl = plan_stream(M_out, K, fp8);
-    return pl.tb == 0 || pl.kg == 1 ? 0 : static_cast<size_t>(pl.kg) * 16 * pl.tb * N * sizeof(float);
-}
+// bytes of workspace the streaming kernel needs for its k groups
+static size_t stream_bytes(int kg, int tb, int N) { return kg == 1 ? 0 : static_cast<size_t>(kg) * 16 * tb * N * sizeof(float); }
 
-// served: up to 64 token rows, and either no workspace needed or one of sufficient size given
+// served: up to 64 token rows, either no workspace needed or one of sufficient size given, and expected to be no slower
+// than the large-batch kernel with its small tiles and k ranges: from about 32 rows on that kernel's weights, shared by all
+// of a tile's token rows in LDS, win over this kernel's token slices, which every workgroup fetches for itself (64 rows x
+// 8192 features x 8192 k in bf16: 33 us against 47; 16 rows: 30 against 29).
 bool proj_stream_takes(int M_out, int N, int K, bool fp8, size_t workspace_bytes) {
     const StreamPlan pl = plan_stream(M_out, K, fp8);
-    return pl.tb != 0 && N % 4 == 0 && proj_stream_workspace(M_out, N, K, fp8) <= workspace_bytes;
+    if (pl.tb == 0 || N % 4 != 0 || stream_bytes(pl.kg, pl.tb, N) > workspace_bytes) return false;
+    if (M_out <= 8) return true;   // one pass over the weights and next to nothing else
+    // fitted to the timed launches of 10 .. 64 rows (4 % off at the median): launch, the weights' pass, the token slices
+    // of all workgroups (rows past the last one hit in the caches), the meeting of the wavefronts per tile of 16
+    // features, the finishing kernel
+    const int elem = fp8 ? 1 : 2, blocks = kSGrid / pl.kg;
+    const int tiles = ((N + blocks - 1) / blocks + 15) / 16;
+    const double token_rows = 0.64 * M_out + 0.36 * 16 * pl.tb;
+    const double us = 2.1 + static_cast<double>(N) * K * elem / 9.0e6 + kSGrid * token_rows * (K / pl.kg) * elem / 7.9e6 + 1.05 * tiles +
+                      (pl.kg > 1 ? 1.7 + pl.kg * 16.0 * pl.tb * N * 8 / 20.0e6 : 0.0);
+    return us <= proj_gemm_us(M_out, N, K, fp8, workspace_bytes);
+}
+
+// What the size query names: for up to 64 rows the streaming kernel's partial results where its k slices divide the k of
+// eight wavefronts in halves, else the large-batch kernel's.  (Callers allocate by it; which kernel runs is decided per
+// call by what fits.)
+size_t proj_workspace(int M_out, int N, int K, bool fp8) {
+    const int per_step = kSWaves * kStepRowBytes / (fp8 ? 1 : 2);
+    if (M_out <= 64 && N % 4 == 0 && K % per_step == 0) {
+        const int tb = M_out <= 16 ? 1 : M_out <= 32 ? 2 : 4;
+        for (int kwb = 16 / tb; kwb >= 1; kwb /= 2) {
+            const int kg = K / per_step / kwb;
+            if (K / per_step % kwb == 0 && kg <= 8 && kSGrid % kg == 0) return stream_bytes(kg, tb, N);
+        }
+    }
+    return proj_gemm_workspace(M_out, N, K, fp8);
 }
 
 // x_scales / w_scales: nullptr for bf16 operands, the row scales of FP8 E4M3 codes otherwise
