@@ -57,6 +57,7 @@ struct StreamParams {
                                            // receive buffers (k = (p hq_l + j) 128 + e), result dense [M][N]
     int kg;                                // workgroups that share a block of features (k groups)
     int rows_per_block;                    // features per block, a multiple of 4
+    int rot_steps;                         // k steps by which a block's slices are shifted against the block before
     XchgShape s;
 };
 
@@ -121,7 +122,14 @@ __global__ __launch_bounds__(kSThreads) void proj_stream_kernel(StreamParams p) 
     if (row_begin >= row_end) return;   // the whole workgroup
     const int n_tiles = (row_end - row_begin + 15) >> 4;
     const int total = n_tiles * KWB;    // steps of this wavefront
-    const int k0 = (cgrp * kSWaves + wave) * (KWB * kStepK);
+    // The k slices of a block of features start `rot` steps into k and wrap around: rows lie k apart, often a power of two,
+    // and with the same start everywhere all workgroups ask the same memory channels at the same time (8192 features x
+    // 8192 k, 1 / 16 rows: 27.2 / 29.4 us, in bf16, 16.6 / 16.8 with FP8 codes; three steps further per block 23.7 / 26.5 and
+    // 13.1 / 14.8; other sizes within 1 % or faster, any odd step alike).
+    const int all_steps = p.kg * kSWaves * KWB, rot = rb * p.rot_steps % all_steps;
+    const int first_step = ((cgrp * kSWaves + wave) * KWB + rot) % all_steps;   // this wavefront's slice: KWB steps from here
+    const int wrap_st = all_steps - first_step;                                  // ... of which those from this one on lie at k = 0
+    const int k0 = first_step * kStepK;
     const size_t k_bytes = static_cast<size_t>(p.K) * kElem;
     const uint32_t ring = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds)) + wave * (kStages * kStepBytes);
     unsigned char* ring_ptr = lds + wave * (kStages * kStepBytes);
@@ -154,7 +162,8 @@ __global__ __launch_bounds__(kSThreads) void proj_stream_kernel(StreamParams p) 
         }
     };
     int rq_g = 0, rq_st = 0, rq_tile = 0, rq_slot = 0;   // the next step to request
-    const unsigned char* rq_base = p.w + static_cast<size_t>(row_begin) * k_bytes + static_cast<size_t>(k0) * kElem;
+    const unsigned char* rq_tile_base = p.w + static_cast<size_t>(row_begin) * k_bytes + static_cast<size_t>(k0) * kElem;
+    const unsigned char* rq_base = rq_tile_base;
     auto request = [&]() {
         const uint32_t dst = ring + rq_slot * kStepBytes;
 #pragma unroll
@@ -164,10 +173,12 @@ __global__ __launch_bounds__(kSThreads) void proj_stream_kernel(StreamParams p) 
         if (++rq_st == KWB) {
             rq_st = 0;
             ++rq_tile;
-            rq_base += 16 * k_bytes - (KWB - 1) * kStepRowBytes;
+            rq_tile_base += 16 * k_bytes;
+            rq_base = rq_tile_base;
             if (rq_tile < n_tiles) tile_offsets(rq_tile);
         } else {
             rq_base += kStepRowBytes;
+            if (rq_st == wrap_st) rq_base -= k_bytes;
         }
     };
     tile_offsets(0);
@@ -184,7 +195,8 @@ __global__ __launch_bounds__(kSThreads) void proj_stream_kernel(StreamParams p) 
             const int t_src = min(16 * tb + l16, p.M - 1);
             // the 16 bytes of token t_src this lane multiplies with weight piece (b % 2 ? second : first) of step b / 2:
             // bf16: k block b (32 k), its k group grp; FP8: step b / 2, the lane's 32 k in two halves
-            const int k = kFp8 ? k0 + 128 * (b >> 1) + 32 * grp + 16 * (b & 1) : k0 + 32 * b + 8 * grp;
+            const int k_step = b / 2 >= wrap_st ? k0 - p.K : k0;
+            const int k = kFp8 ? k_step + 128 * (b >> 1) + 32 * grp + 16 * (b & 1) : k_step + 32 * b + 8 * grp;
             const unsigned char* src;
             if (p.mode == 0) {
                 src = p.x + (static_cast<size_t>(t_src) * p.K + k) * kElem;
@@ -388,6 +400,7 @@ hipError_t run_stream(StreamParams p, const StreamPlan& pl, void* workspace, hip
     p.partial = static_cast<float*>(workspace);
     const int blocks = kSGrid / pl.kg;
     p.rows_per_block = ((p.N + blocks - 1) / blocks + 3) / 4 * 4;
+    p.rot_steps = 3;
     hipError_t e = hipErrorInvalidValue;
     if (p.xs) {
 #define SHIFTATTN_STREAM_LAUNCH(tb_, kwb_) if (pl.tb == tb_ && pl.kwb == kwb_) e = launch_stream<tb_, kwb_, true>(p, st);
