@@ -36,6 +36,9 @@ __device__ inline float wave_sum(float v) {
     return v;
 }
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
 constexpr int kWaves = 4;
 constexpr int kMaxD = 256;
 
@@ -210,6 +213,9 @@ __global__ __launch_bounds__(kCombineThreads) void combine_kernel(const float* _
 // Merge of a split prefill (bf16 output, D = 128, every row has the same few parts): many rows, few parts, so a row
 // takes 32 threads (four head-dim elements each, 16-byte loads of a part's row, one 8-byte store) and a workgroup eight
 // rows; the parts are added in part order with the arithmetic of combine_kernel, so both give the same bits.
+// What bounds it is the chain of loads a row waits for, not the bytes: lane c of a row fetches the (max, sum) pair of part
+// c and the weights go round by cross-lane reads, so a row waits for memory once (twice beyond eight parts), where a walk
+// over the pairs waited once per part: 2048 tokens x 8 heads, 4 parts 10.4 -> 9.1 us; 1000 x 8, 8 parts 9.2 -> 8.0.
 constexpr int kSplitRowsPerWg = 8;
 __global__ __launch_bounds__(32 * kSplitRowsPerWg) void combine_splits_kernel(const float* __restrict__ o_part,
                                                                               const float* __restrict__ ml_part,
@@ -217,34 +223,54 @@ __global__ __launch_bounds__(32 * kSplitRowsPerWg) void combine_splits_kernel(co
                                                                               uint16_t* __restrict__ out, int64_t out_stride,
                                                                               float out_scale) {
     constexpr int D = 128;
-    typedef float f32x4 __attribute__((ext_vector_type(4)));
-    typedef float f32x2 __attribute__((ext_vector_type(2)));
-    const int64_t row = static_cast<int64_t>(blockIdx.x) * kSplitRowsPerWg + (threadIdx.x >> 5);
-    if (row >= rows) return;
+    const int64_t row_raw = static_cast<int64_t>(blockIdx.x) * kSplitRowsPerWg + (threadIdx.x >> 5);
+    const int64_t row = row_raw < rows ? row_raw : rows - 1;  // (every lane stays for the cross-lane reads)
     const int q4 = threadIdx.x & 31;
     const float* o_row = o_part + row * D + 4 * q4;
     const size_t part_stride = static_cast<size_t>(rows) * D;
     // the first parts' rows are requested before the weights are known
-    constexpr int kEarly = 4;
+    constexpr int kEarly = 8;
     f32x4 early[kEarly];
 #pragma unroll
     for (int c = 0; c < kEarly; ++c) early[c] = c < n_parts ? *reinterpret_cast<const f32x4*>(o_row + c * part_stride) : f32x4{0.f, 0.f, 0.f, 0.f};
-    float m_star = -INFINITY;
-    for (int c = 0; c < n_parts; ++c) m_star = fmaxf(m_star, ml_part[(c * rows + row) * 2]);
+    auto pair_of = [&](int c) -> f32x2 {
+        return c < n_parts ? *reinterpret_cast<const f32x2*>(ml_part + (static_cast<size_t>(c) * rows + row) * 2) : f32x2{-INFINITY, 0.f};
+    };
+    const f32x2 ml0 = pair_of(q4);
+    float m_star = ml0[0];
+    for (int c = q4 + 32; c < n_parts; c += 32) m_star = fmaxf(m_star, pair_of(c)[0]);
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1) m_star = fmaxf(m_star, __shfl_xor(m_star, o));
     float l_star = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    auto add_part = [&](int c, f32x4 v) {
-        const f32x2 ml = *reinterpret_cast<const f32x2*>(ml_part + (c * rows + row) * 2);
-        const float w = (ml[0] == -INFINITY) ? 0.f : exp2f(ml[0] - m_star);
-        l_star = fmaf(ml[1], w, l_star);
+    for (int c0 = 0; c0 < n_parts; c0 += 32) {   // uniform
+        const f32x2 ml = c0 == 0 ? ml0 : pair_of(c0 + q4);
+        const float w_lane = (ml[0] == -INFINITY) ? 0.f : exp2f(ml[0] - m_star);
+        auto add_part = [&](int c, f32x4 v) {
+            const float w = __shfl(w_lane, c, 32);
+            l_star = fmaf(__shfl(ml[1], c, 32), w, l_star);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc[e] = fmaf(v[e], w, acc[e]);
-    };
+            for (int e = 0; e < 4; ++e) acc[e] = fmaf(v[e], w, acc[e]);
+        };
+        int c = 0;
+        if (c0 == 0) {
 #pragma unroll
-    for (int c = 0; c < kEarly; ++c)
-        if (c < n_parts) add_part(c, early[c]);
-#pragma unroll 4
-    for (int c = kEarly; c < n_parts; ++c) add_part(c, *reinterpret_cast<const f32x4*>(o_row + c * part_stride));
+            for (int x = 0; x < kEarly; ++x)
+                if (x < n_parts) add_part(x, early[x]);
+            c = kEarly;
+        }
+        const int c_end = min(32, n_parts - c0);
+        for (; c < c_end; c += kEarly) {
+            f32x4 v[kEarly];
+#pragma unroll
+            for (int x = 0; x < kEarly; ++x)
+                if (c + x < c_end) v[x] = *reinterpret_cast<const f32x4*>(o_row + (c0 + c + x) * part_stride);
+#pragma unroll
+            for (int x = 0; x < kEarly; ++x)
+                if (c + x < c_end) add_part(c + x, v[x]);
+        }
+    }
+    if (row_raw >= rows) return;
     const float inv = l_star > 0.f ? out_scale / l_star : 0.f;
     const int64_t tok = row / hq_l;
     const int head = static_cast<int>(row - tok * hq_l);
@@ -257,78 +283,101 @@ __global__ __launch_bounds__(32 * kSplitRowsPerWg) void combine_splits_kernel(co
                                                static_cast<uint32_t>(h[2]) | (static_cast<uint32_t>(h[3]) << 16)};
 }
 
-// Merge for the flat decode kernel (bf16 output, D = 128; out_scale = v_scale of an FP8 cache, else 1): one workgroup of one or four thread groups
-// per output row; group pg sums the parts c = pg, pg + groups, ... for its 128 head-dim elements (with
-// four groups sixteen partial rows are in flight per element) and the sums are added in group order.
-// Four groups pay off when rows are few and parts many (small batches), one when it is the reverse.  The parts of a
-// row are the partial rows (plan[pair].x + c) * G + head % G, c < plan[pair].y.
-template <int kFlatCombineGroups>
-__global__ __launch_bounds__(128 * kFlatCombineGroups) void combine_flat_kernel(
+// Merge for the flat decode kernel (bf16 output, D = 128; out_scale = v_scale of an FP8 cache, else 1): one workgroup per
+// output row.  The parts of a row are the partial rows (plan[pair].x + c) * G + head % G, c < plan[pair].y.  32 threads
+// (four head-dim elements each) form a group; group pg sums the parts c = pg, pg + groups, ... and the groups' sums are
+// added in group order.  As above the time is the chain of dependent loads: the first four parts of every group are
+// requested together with the (max, sum) pairs, which up to 64 parts sit one per lane, so every wavefront has all weights
+// after one cross-lane reduction, without LDS or barriers.  Sixteen groups where rows are few and parts many (small
+// batches: 64 parts in flight per row), four where it is the reverse.  Against one element per thread
+// and the weights through LDS: 2048 rows of 9 parts 5.9 -> 5.3 us, 32 rows of 65 parts 5.5 -> 4.6.
+template <int kGroups>
+__global__ __launch_bounds__(32 * kGroups) void combine_flat_kernel(
     const float* __restrict__ o_part, const float* __restrict__ ml_part, const int2* __restrict__ plan, int hq_l, int G,
     uint16_t* __restrict__ out, int64_t out_stride, float out_scale) {
-    constexpr int D = 128, kThreadsF = 128 * kFlatCombineGroups;
+    constexpr int D = 128, kThreadsF = 32 * kGroups, kEarly = 4;
     __shared__ float w_s[kCombineMaxParts];
-    __shared__ float l_s[kCombineMaxParts];
-    __shared__ float red_s[kThreadsF / 64];
-    __shared__ float acc_s[kFlatCombineGroups][D];
-    __shared__ float lsum_s[kFlatCombineGroups];
+    __shared__ float red_s[2][kThreadsF / 64];
+    __shared__ __attribute__((aligned(16))) float acc_s[kGroups / 2][D];
     const int row = blockIdx.x;  // sequence * hq_l + head
     const int tok = row / hq_l, head = row % hq_l;
     const int2 e = plan[tok * (hq_l / G) + head / G];
     const int np = min(e.y, kCombineMaxParts);
     const size_t row0 = static_cast<size_t>(e.x) * G + head % G;
-    const int tid = threadIdx.x, d = tid & (D - 1), pg = tid >> 7;
-    // this thread's first four parts are requested before the weights are known
-    float early[4];
+    const int tid = threadIdx.x, pg = tid >> 5, lane = tid & 63;
+    const float* o_row = o_part + row0 * D + 4 * (tid & 31);
+    const size_t part_stride = static_cast<size_t>(G) * D;
+    auto pair_of = [&](int c) -> f32x2 {
+        return c < np ? *reinterpret_cast<const f32x2*>(ml_part + (row0 + static_cast<size_t>(c) * G) * 2) : f32x2{-INFINITY, 0.f};
+    };
+    // this thread's first parts are requested before the weights are known
+    f32x4 early[kEarly];
 #pragma unroll
-    for (int x = 0; x < 4; ++x) {
-        const int c = pg + kFlatCombineGroups * x;
-        early[x] = c < np ? o_part[(row0 + static_cast<size_t>(c) * G) * D + d] : 0.f;
+    for (int x = 0; x < kEarly; ++x) {
+        const int c = pg + kGroups * x;
+        early[x] = c < np ? *reinterpret_cast<const f32x4*>(o_row + c * part_stride) : f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    float m_loc = -INFINITY;
-    for (int c = tid; c < np; c += kThreadsF) {
-        const float m_c = ml_part[(row0 + static_cast<size_t>(c) * G) * 2];
-        w_s[c] = m_c;
-        l_s[c] = ml_part[(row0 + static_cast<size_t>(c) * G) * 2 + 1];
-        m_loc = fmaxf(m_loc, m_c);
-    }
-    m_loc = wave_max(m_loc);
-    if ((tid & 63) == 0) red_s[tid >> 6] = m_loc;
-    __syncthreads();
-    float m_star = red_s[0];
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    auto add_part = [&](float w, f32x4 v) {
 #pragma unroll
-    for (int w = 1; w < kThreadsF / 64; ++w) m_star = fmaxf(m_star, red_s[w]);
-    for (int c = tid; c < np; c += kThreadsF) {
-        const float m_c = w_s[c];
-        w_s[c] = (m_c == -INFINITY) ? 0.f : exp2f(m_c - m_star);
-    }
-    __syncthreads();
-    float acc = 0.f, lsum = 0.f;
+        for (int x = 0; x < 4; ++x) acc[x] = fmaf(v[x], w, acc[x]);
+    };
+    float l_star;
+    if (np <= 64) {   // uniform
+        const f32x2 ml = pair_of(lane);
+        const float m_star = wave_max(ml[0]);
+        const float w_lane = (ml[0] == -INFINITY) ? 0.f : exp2f(ml[0] - m_star);
+        l_star = wave_sum(ml[1] * w_lane);
 #pragma unroll
-    for (int x = 0; x < 4; ++x) {
-        const int c = pg + kFlatCombineGroups * x;
-        if (c < np) {
-            acc = fmaf(early[x], w_s[c], acc);
-            lsum = fmaf(l_s[c], w_s[c], lsum);
+        for (int x = 0; x < kEarly; ++x)
+            if (pg + kGroups * x < 64) add_part(__shfl(w_lane, pg + kGroups * x), early[x]);
+        // (a group's further parts: a lane pair of groups may differ in count, the cross-lane read stays uniform)
+        for (int c = kEarly * kGroups; c < np; c += kGroups) {
+            const float w = __shfl(w_lane, min(c + pg, 63));
+            if (c + pg < np) add_part(w, *reinterpret_cast<const f32x4*>(o_row + (c + pg) * part_stride));
         }
-    }
+    } else {
+        float m_loc = -INFINITY;
+        for (int c = tid; c < np; c += kThreadsF) {
+            w_s[c] = pair_of(c)[0];
+            m_loc = fmaxf(m_loc, w_s[c]);
+        }
+        m_loc = wave_max(m_loc);
+        if (lane == 0) red_s[0][tid >> 6] = m_loc;
+        __syncthreads();
+        float m_star = red_s[0][0];
+#pragma unroll
+        for (int w = 1; w < kThreadsF / 64; ++w) m_star = fmaxf(m_star, red_s[0][w]);
+        float l_loc = 0.f;
+        for (int c = tid; c < np; c += kThreadsF) {
+            const float m_c = w_s[c];  // each slot is read and rewritten by the same thread
+            const float w = (m_c == -INFINITY) ? 0.f : exp2f(m_c - m_star);
+            w_s[c] = w;
+            l_loc = fmaf(pair_of(c)[1], w, l_loc);
+        }
+        l_loc = wave_sum(l_loc);
+        if (lane == 0) red_s[1][tid >> 6] = l_loc;
+        __syncthreads();
+        l_star = red_s[1][0];
+#pragma unroll
+        for (int w = 1; w < kThreadsF / 64; ++w) l_star += red_s[1][w];
+#pragma unroll
+        for (int x = 0; x < kEarly; ++x)
+            if (pg + kGroups * x < np) add_part(w_s[pg + kGroups * x], early[x]);
 #pragma unroll 4
-    for (int c = pg + 4 * kFlatCombineGroups; c < np; c += kFlatCombineGroups) {
-        acc = fmaf(o_part[(row0 + static_cast<size_t>(c) * G) * D + d], w_s[c], acc);
-        lsum = fmaf(l_s[c], w_s[c], lsum);
+        for (int c = pg + kEarly * kGroups; c < np; c += kGroups)
+            add_part(w_s[c], *reinterpret_cast<const f32x4*>(o_row + c * part_stride));
     }
-    acc_s[pg][d] = acc;
-    if (d == 0) lsum_s[pg] = lsum;
-    __syncthreads();
-    if (pg == 0) {
-        float a = acc_s[0][d], l = lsum_s[0];
 #pragma unroll
-        for (int g2 = 1; g2 < kFlatCombineGroups; ++g2) {
-            a += acc_s[g2][d];
-            l += lsum_s[g2];
-        }
-        const float inv = l > 0.f ? out_scale / l : 0.f;
-        store_elem(out + static_cast<size_t>(tok) * out_stride + static_cast<size_t>(head) * D + d, a * inv);
+    for (int x = 0; x < 4; ++x) acc[x] += __shfl_xor(acc[x], 32);
+    if (lane < 32) *reinterpret_cast<f32x4*>(&acc_s[pg >> 1][4 * lane]) = acc;
+    __syncthreads();
+    if (tid < D) {
+        float a = acc_s[0][tid];
+#pragma unroll
+        for (int g2 = 1; g2 < kGroups / 2; ++g2) a += acc_s[g2][tid];
+        const float inv = l_star > 0.f ? out_scale / l_star : 0.f;
+        store_elem(out + static_cast<size_t>(tok) * out_stride + static_cast<size_t>(head) * D + tid, a * inv);
     }
 }
 
@@ -339,10 +388,10 @@ hipError_t launch_combine_flat(const float* o_part, const float* ml_part, const 
     const int64_t rows = static_cast<int64_t>(num_seqs) * hq_l;
     if (rows == 0) return hipSuccess;
     if (rows >= 1024)
-        combine_flat_kernel<1><<<static_cast<unsigned>(rows), 128, 0, st>>>(o_part, ml_part, plan, hq_l, G,
+        combine_flat_kernel<4><<<static_cast<unsigned>(rows), 128, 0, st>>>(o_part, ml_part, plan, hq_l, G,
                                                                             static_cast<uint16_t*>(out), out_stride, out_scale);
     else
-        combine_flat_kernel<4><<<static_cast<unsigned>(rows), 512, 0, st>>>(o_part, ml_part, plan, hq_l, G,
+        combine_flat_kernel<16><<<static_cast<unsigned>(rows), 512, 0, st>>>(o_part, ml_part, plan, hq_l, G,
                                                                             static_cast<uint16_t*>(out), out_stride, out_scale);
     return hipGetLastError();
 }
