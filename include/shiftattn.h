@@ -336,8 +336,8 @@ int32_t shiftattn_use_base_config(int32_t n_tokens, int32_t threshold);
  *   SHIFTATTN_OPT_PREFILL_TILE   128 | 256: which prefill kernel takes bf16 / head_dim 128 launches
  *   SHIFTATTN_OPT_PREFILL_SPLITS 1 .. 64: key ranges per column tile of those kernels
  *   SHIFTATTN_OPT_GENERIC_ONLY   1: every attention call runs the general kernel (any type / head_dim)
- *   SHIFTATTN_OPT_PREFILL_PAIRING 1 | 2: the 256-column prefill kernel takes a sequence's column tiles two per
- *                                workgroup, heaviest with lightest (1), or one per workgroup, heaviest first (2)
+ *   SHIFTATTN_OPT_PREFILL_PAIRING 1 | 2: the prefill kernels take a sequence's column tiles two per workgroup,
+ *                                heaviest with lightest (1), or one per workgroup, heaviest first (2)
  *   SHIFTATTN_OPT_PREFILL_SCALED_Q 1: the 256-column prefill kernel multiplies Q by the softmax scale when a tile
  *                                fetches it, rounds it to bf16 again and takes its softmax without a reference,
  *                                so that its loop spends no instruction on scaling and shifting logits (about

@@ -539,7 +539,7 @@ int shiftattn_prefill(const void* q, const void* k_new, const void* v_new, const
         return rc;
     if (num_seqs == 0 || total_q == 0) return SHIFTATTN_OK;
     const bool mfma = use_prefill_mfma(s, num_seqs, max_seq_len);
-    const size_t need = mfma ? prefill_mfma_workspace(num_seqs, total_q, max_q_len, max_seq_len, s) : 0;
+    const size_t need = mfma ? prefill_mfma_least_workspace(num_seqs, total_q, max_q_len, max_seq_len, s) : 0;
     if (need > 0 && (!workspace || workspace_bytes < need || !aligned16(workspace)))
         return fail(SHIFTATTN_EWORKSPACE, "prefill needs %zu workspace bytes, got %zu", need,
                     workspace ? workspace_bytes : static_cast<size_t>(0));
@@ -553,7 +553,7 @@ int shiftattn_prefill(const void* q, const void* k_new, const void* v_new, const
     }
     if (mfma)
         e = launch_prefill_mfma(q, kv_cache, block_table, cu_seqlens_q, seq_lens, num_seqs, total_q, max_q_len,
-                                max_seq_len, out, workspace, s, st);
+                                max_seq_len, out, workspace, workspace && aligned16(workspace) ? workspace_bytes : 0, s, st);
     else
         e = launch_attn_generic(q, kv_cache, block_table, cu_seqlens_q, seq_lens, num_seqs, total_q, out, s, st);
     return e == hipSuccess ? SHIFTATTN_OK : hip_fail(e, "prefill launch");
@@ -638,8 +638,10 @@ int shiftattn_mixed(const void* q, const void* k_new, const void* v_new, const i
     if (rows == 0) return SHIFTATTN_OK;
     if (!q || !kv_cache || !block_table || !seq_lens || !out || (num_prefill_seqs > 0 && !cu_seqlens_q))
         return fail(SHIFTATTN_EINVAL, "a required pointer is NULL");
-    const size_t need = shiftattn_mixed_workspace_bytes(num_prefill_seqs, total_prefill_q, max_q_len, max_prefill_seq_len,
-                                                        num_decode_seqs, max_decode_seq_len, a);
+    const size_t need_p = num_prefill_seqs > 0 && total_prefill_q > 0 && use_prefill_mfma(s, num_prefill_seqs, max_prefill_seq_len)
+                              ? prefill_mfma_least_workspace(num_prefill_seqs, total_prefill_q, max_q_len, max_prefill_seq_len, s) : 0;
+    const size_t need_d = shiftattn_decode_workspace_bytes(num_decode_seqs, max_decode_seq_len, a);
+    const size_t need = need_p > need_d ? need_p : need_d;
     if (need > 0 && (!workspace || workspace_bytes < need || !aligned16(workspace)))
         return fail(SHIFTATTN_EWORKSPACE, "mixed batch needs %zu workspace bytes, got %zu", need,
                     workspace ? workspace_bytes : static_cast<size_t>(0));

@@ -39,10 +39,12 @@
 // the load.  Stage `par` of a group is filled during an iteration of parity `par` and read during
 // the next one; one barrier per iteration.
 //
-// Scheduling.  Tiles of a sequence are processed in pairs (heaviest with lightest) by one
-// workgroup so every workgroup of a causal prefill does the same amount of work; the long
-// contexts of chunked prefill are additionally split into key ranges whose partial results are
-// merged by launch_combine.
+// Scheduling.  Either tiles of a sequence are processed in pairs (heaviest with lightest) by one
+// workgroup, so that every workgroup of a causal prefill does the same amount of work, or one tile
+// per workgroup, heaviest first: half the latency where the tiles do not fill the chip (eleven
+// prompts of 149 to 1097 tokens, 5 heads: 34.6 -> 28.2 us a call).  The long contexts of chunked
+// prefill are additionally split into key ranges whose partial results are merged by launch_combine.
+// plan_within() below prices the plans of both prefill kernels.
 #include "internal.h"
 
 #include <utility>
@@ -94,6 +96,7 @@ struct PrefillParams {
     int gs_log2;      // log2 of heads stacked per token in the column index
     int head_slots;   // hq_l >> gs_log2
     int n_splits;     // key ranges per tile
+    int paired;       // tiles of a sequence taken two per workgroup (heaviest with lightest), else one
     int rotate;       // the (sequence, head slot) index is rotated by the (pair rank, key range) index (see internal.h)
     int max_blocks;
     float c;          // softmax_scale * log2(e) (times k_scale for a cache widened from FP8)
@@ -116,7 +119,7 @@ __global__ __launch_bounds__(kThreads, 2) void prefill_kernel(PrefillParams p) {
     item -= rank * (n_sh * p.n_splits);
     const int split = item / n_sh;
     item -= split * n_sh;
-    if (p.rotate) item = (item + n_sh - static_cast<int>((blockIdx.x / n_sh) % n_sh)) % n_sh;
+    if (p.rotate) item = (item + n_sh - static_cast<int>((blockIdx.x / max(n_sh, 8)) % n_sh)) % n_sh;
     const int s = item / p.head_slots;
     const int hs = item - s * p.head_slots;
 
@@ -126,8 +129,8 @@ __global__ __launch_bounds__(kThreads, 2) void prefill_kernel(PrefillParams p) {
     const int tile_tokens = kCols >> p.gs_log2;
     const int n_tiles = (q_len + tile_tokens - 1) / tile_tokens;
     const int hi_tile = n_tiles - 1 - rank;
-    if (rank > hi_tile) return;  // uniform
-    const int n_pass = (hi_tile == rank) ? 1 : 2;
+    if (p.paired ? rank > hi_tile : hi_tile < 0) return;  // uniform
+    const int n_pass = (!p.paired || hi_tile == rank) ? 1 : 2;
     const int gs_mask = (1 << p.gs_log2) - 1;
     const int g = (hs << p.gs_log2) / p.G;  // KV head of every column of this workgroup
     const int32_t* __restrict__ table = p.block_table + static_cast<size_t>(s) * p.max_blocks;
@@ -647,7 +650,7 @@ constexpr double kPassSeconds = 7e-6;  // what a pass of this kernel costs aroun
 
 struct Plan {
     int gs_log2, head_slots, tile_tokens, pair_ranks, n_splits;
-    bool rotate;
+    bool paired, rotate;
 };
 
 Plan make_plan(int num_seqs, int total_q, int max_q_len, int max_seq_len, const AttnShape& a) {
@@ -659,7 +662,8 @@ Plan make_plan(int num_seqs, int total_q, int max_q_len, int max_seq_len, const 
     pl.head_slots = a.hq_l >> pl.gs_log2;
     pl.tile_tokens = 128 >> pl.gs_log2;
     const int tiles = (max_q_len + pl.tile_tokens - 1) / pl.tile_tokens;
-    pl.pair_ranks = (tiles + 1) / 2;
+    pl.paired = option_prefill_pairing() != 2;
+    pl.pair_ranks = pl.paired ? (tiles + 1) / 2 : tiles;
     // Key ranges per column tile: the count that minimises the model of a launch that also decides between the two
     // kernels - more ranges when the tiles alone cannot fill the chip (long cached context, short chunk) or fill it
     // with a ragged last round (320 equal workgroups on 256 compute units), as long as the merge does not eat the gain.
@@ -754,21 +758,120 @@ Choice choose(int num_seqs, int total_q, int max_q_len, int max_seq_len, const A
     return c;
 }
 
+size_t split_bytes(int n_splits, int total_q, const AttnShape& a) {
+    return n_splits == 1 ? 0 : static_cast<size_t>(n_splits) * total_q * a.hq_l * (kD + 2) * sizeof(float);
+}
+
 size_t split_bytes_of(const Choice& c, int total_q, const AttnShape& a) {
-    if (c.wide) return prefill_mfma64_workspace(total_q, c.w, a);
-    return c.narrow.n_splits == 1 ? 0 : static_cast<size_t>(c.narrow.n_splits) * total_q * a.hq_l * (kD + 2) * sizeof(float);
+    return split_bytes(c.wide ? c.w.n_splits : c.narrow.n_splits, total_q, a);
+}
+
+// ---- the launch within the workspace given --------------------------------------------------------------------
+// choose() above plans tiles in pairs for the 128-column kernel and at least 1024 keys per range: right where the tiles
+// fill the chip, and a chip left idle where they do not (a few prompts of some hundred tokens, a short chunk behind a
+// long context: 47 tokens on 9062 cached, 4 heads, were one workgroup per key range that walked its range twice).  Its
+// plan stays the least workspace a call is accepted with and the plan of a caller that brings no more; beyond it, one
+// tile or two per workgroup and 1 to 32 key ranges of both kernels are priced with the model below.  Constants in
+// microseconds, fitted to 140 launches times about 40 plans each (prompts of 7 .. 16384 tokens, chunks behind 100 ..
+// 131072 cached, 1 .. 12 sequences, all head geometries): the fit is 5 % off (root mean square of the logarithm), its
+// choices 1 % slower than the best plan measured, where choose() alone was 45 % slower.
+struct TileKernel {
+    double pass, second_pass;  // around the key loop: set-up, Q, first and last tile, write-out
+    double step, step_full;    // one step of the key loop, and what it costs more once every compute unit is busy
+    int keys_per_step;
+};
+constexpr TileKernel kNarrowCost = {2.65, 3.1, 1.4, 0.335, 2 * kKvTile};   // two groups of wavefronts, a tile of 64 keys each
+constexpr TileKernel kWideCost = {10.1, 9.5, 0.77, 0.03, 32};
+
+double launch_us(const TileKernel& k, bool paired, int splits, int tile_tokens, int heads, int num_seqs, int total_q,
+                 int max_q_len, int max_seq_len, int hq_l) {
+    constexpr double kCus = 256, kSlack = 1.13;  // slack: how far a chip full of unequal workgroups stays from level
+    constexpr double kMergeUs = 4.5, kMergeBytesPerUs = 5.8e6, kRowBytes = 1040;  // partials of a (token, head) written and read
+    const int tiles = (max_q_len + tile_tokens - 1) / tile_tokens, ranks = paired ? (tiles + 1) / 2 : tiles;
+    const double seqs = longest_chunk_equivalents(num_seqs, total_q, max_q_len);
+    const double wgs = ranks * seqs * heads * splits, grid = static_cast<double>(ranks) * num_seqs * heads * splits;
+    const int q = max_q_len < max_seq_len ? max_q_len : max_seq_len;
+    auto steps = [&](int keys) {   // of the range a workgroup takes of a tile that sees `keys` keys
+        const int range = k.keys_per_step * splits;
+        return static_cast<double>((keys + range - 1) / range);
+    };
+    const double heavy = steps(max_seq_len), light = steps(max_seq_len - q + (tile_tokens < q ? tile_tokens : q));
+    const double step = k.step + k.step_full * (wgs < kCus ? wgs / kCus : 1.0);
+    double d_hi, d_lo;             // longest and shortest workgroup
+    if (paired) d_hi = d_lo = k.pass + heavy * step + (tiles > 1 ? k.second_pass + light * step : 0.0);
+    else d_hi = k.pass + heavy * step, d_lo = k.pass + light * step;
+    // A grid beyond the chip takes whole rounds of its shortest workgroup at least.  Workgroups of sequences shorter than
+    // the longest leave at once, but up to two rounds their places are not free soon enough: the dispatcher hands
+    // workgroups to shader engines in turn (measured: 204 busy of 288 workgroups took 37 us, 170 of 240 took 25).
+    const double counted = grid <= 2 * kCus ? grid : wgs;
+    const double rounds = static_cast<double>(static_cast<long>((counted + kCus - 1) / kCus));
+    double span = (grid > kCus ? kSlack : 1.0) * (d_hi + d_lo) / 2 * wgs / kCus;
+    if (span < d_hi) span = d_hi;
+    if (span < rounds * d_lo) span = rounds * d_lo;
+    if (splits > 1) span += kMergeUs + splits * static_cast<double>(total_q) * hq_l * kRowBytes / kMergeBytesPerUs;
+    return (span + 6.6) * (1.0 + 0.008 * splits);   // (launch; among equals the plan with fewer ranges)
+}
+
+Choice plan_within(size_t split_budget, int num_seqs, int total_q, int max_q_len, int max_seq_len, const AttnShape& a) {
+    Choice best = choose(num_seqs, total_q, max_q_len, max_seq_len, a);
+    AttnShape b = a;
+    b.kv_elem = b.elem;
+    const int forced_tile = option_prefill_tile(), forced_splits = option_prefill_splits(), forced_pairing = option_prefill_pairing();
+    const bool wide_ok = prefill_mfma64_supported(b);
+    auto priced = [&](const Choice& c) {
+        return c.wide ? launch_us(kWideCost, c.w.paired, c.w.n_splits, c.w.tile_tokens, a.hkv_l, num_seqs, total_q, max_q_len, max_seq_len, a.hq_l)
+                      : launch_us(kNarrowCost, c.narrow.paired, c.narrow.n_splits, c.narrow.tile_tokens, c.narrow.head_slots, num_seqs,
+                                  total_q, max_q_len, max_seq_len, a.hq_l);
+    };
+    double best_us = 0.97 * priced(best);   // (what is left of choose()'s plan only for a gain beyond the model's error)
+    Choice c = best;
+    auto try_ranges = [&](int splits) {
+        if (split_bytes(splits, total_q, a) > split_budget) return;
+        for (int wide = 0; wide < 2; ++wide) {
+            if (wide ? !wide_ok || forced_tile == 128 : wide_ok && forced_tile == 256) continue;
+            for (int paired = 0; paired < 2; ++paired) {
+                if (forced_pairing != 0 && paired != (forced_pairing == 1)) continue;
+                c.wide = wide != 0;
+                const int tile_tokens = wide ? c.w.tile_tokens : c.narrow.tile_tokens;
+                const int tiles = (max_q_len + tile_tokens - 1) / tile_tokens, ranks = paired ? (tiles + 1) / 2 : tiles;
+                if (wide) {
+                    c.w.paired = paired != 0, c.w.pair_ranks = ranks, c.w.n_splits = splits;
+                    c.w.workgroups = static_cast<long>(ranks) * splits * num_seqs * a.hkv_l;
+                } else {
+                    c.narrow.paired = paired != 0, c.narrow.pair_ranks = ranks, c.narrow.n_splits = splits;
+                }
+                const double us = priced(c);
+                if (us < best_us) best = c, best_us = us;
+            }
+        }
+    };
+    if (forced_splits > 0) {
+        try_ranges(forced_splits);
+    } else {
+        for (int splits : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 24, 32})
+            if (splits == 1 || max_seq_len >= splits * 2 * kKvTile) try_ranges(splits);
+    }
+    return best;
+}
+
+size_t with_fp8_scratch(size_t bytes, int num_seqs, int max_seq_len, const AttnShape& a) {
+    if (!a.kv_fp8()) return bytes;
+    const Fp8Scratch f = fp8_scratch(num_seqs, max_seq_len, a);
+    return (bytes + 255) / 256 * 256 + f.cache_bytes + f.table_bytes;
 }
 
 }  // namespace
 
-size_t prefill_mfma_workspace(int num_seqs, int total_q, int max_q_len, int max_seq_len, const AttnShape& a) {
+size_t prefill_mfma_least_workspace(int num_seqs, int total_q, int max_q_len, int max_seq_len, const AttnShape& a) {
     const Choice c = choose(num_seqs, total_q, max_q_len, max_seq_len, a);
-    size_t bytes = split_bytes_of(c, total_q, a);
-    if (a.kv_fp8()) {
-        const Fp8Scratch f = fp8_scratch(num_seqs, max_seq_len, a);
-        bytes = (bytes + 255) / 256 * 256 + f.cache_bytes + f.table_bytes;
-    }
-    return bytes;
+    return with_fp8_scratch(split_bytes_of(c, total_q, a), num_seqs, max_seq_len, a);
+}
+
+size_t prefill_mfma_workspace(int num_seqs, int total_q, int max_q_len, int max_seq_len, const AttnShape& a) {
+    const size_t least = prefill_mfma_least_workspace(num_seqs, total_q, max_q_len, max_seq_len, a);
+    const Choice c = plan_within(SIZE_MAX, num_seqs, total_q, max_q_len, max_seq_len, a);
+    const size_t best = with_fp8_scratch(split_bytes_of(c, total_q, a), num_seqs, max_seq_len, a);
+    return best > least ? best : least;
 }
 
 hipError_t prefill_mfma_init() {
@@ -778,10 +881,13 @@ hipError_t prefill_mfma_init() {
 
 hipError_t launch_prefill_mfma(const void* q, const void* cache, const int32_t* block_table,
                                const int32_t* cu_seqlens_q, const int32_t* seq_lens, int num_seqs, int total_q,
-                               int max_q_len, int max_seq_len, void* out, void* workspace, const AttnShape& a,
-                               hipStream_t st) {
+                               int max_q_len, int max_seq_len, void* out, void* workspace, size_t workspace_bytes,
+                               const AttnShape& a, hipStream_t st) {
     if (num_seqs == 0 || total_q == 0 || max_q_len <= 0) return hipSuccess;
-    const Choice ch = choose(num_seqs, total_q, max_q_len, max_seq_len, a);
+    const size_t fixed = with_fp8_scratch(0, num_seqs, max_seq_len, a);
+    // (an FP8 cache's scratch lies behind the partials, at a multiple of 256 bytes)
+    const size_t budget = workspace_bytes < fixed ? 0 : a.kv_fp8() ? (workspace_bytes - fixed) / 256 * 256 : workspace_bytes;
+    const Choice ch = plan_within(budget, num_seqs, total_q, max_q_len, max_seq_len, a);
     int max_blocks = a.max_blocks;
     if (a.kv_fp8()) {  // widen into the scratch cache behind the split partials, then attend over that
         const Fp8Scratch f = fp8_scratch(num_seqs, max_seq_len, a);
@@ -820,6 +926,7 @@ hipError_t launch_prefill_mfma(const void* q, const void* cache, const int32_t* 
     p.gs_log2 = pl.gs_log2;
     p.head_slots = pl.head_slots;
     p.n_splits = pl.n_splits;
+    p.paired = pl.paired ? 1 : 0;
     p.rotate = pl.rotate ? 1 : 0;
     p.max_blocks = max_blocks;
     p.c = c;

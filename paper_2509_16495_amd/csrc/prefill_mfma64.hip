@@ -195,7 +195,7 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
     item -= rank * (n_sg * p.n_splits);
     const int split = item / n_sg;
     item -= split * n_sg;
-    if (p.rotate) item = (item + n_sg - static_cast<int>((blockIdx.x / n_sg) % n_sg)) % n_sg;
+    if (p.rotate) item = (item + n_sg - static_cast<int>((blockIdx.x / max(n_sg, 8)) % n_sg)) % n_sg;
     const int s = item / p.hkv_l;
     const int g = item - s * p.hkv_l;
 
