@@ -554,6 +554,8 @@ int shiftattn_prefill(const void* q, const void* k_new, const void* v_new, const
     if (mfma)
         e = launch_prefill_mfma(q, kv_cache, block_table, cu_seqlens_q, seq_lens, num_seqs, total_q, max_q_len,
                                 max_seq_len, out, workspace, workspace && aligned16(workspace) ? workspace_bytes : 0, s, st);
+    else if (!force_generic() && prefill_f32_supported(s))
+        e = launch_prefill_f32(q, kv_cache, block_table, cu_seqlens_q, seq_lens, num_seqs, total_q, out, s, st);
     else
         e = launch_attn_generic(q, kv_cache, block_table, cu_seqlens_q, seq_lens, num_seqs, total_q, out, s, st);
     return e == hipSuccess ? SHIFTATTN_OK : hip_fail(e, "prefill launch");

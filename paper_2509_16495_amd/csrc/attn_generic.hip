@@ -4,7 +4,8 @@
 // boundary accepts, for prefill chunks and decode rows alike: one wavefront per (token, query head)
 // row, lanes spread over 64 keys for q.k, then over the head dimension for p.V, online softmax in
 // fp32 (Algorithm 1, boxed attention line; Sec. 2.2).  It is the reference-grade path for shapes
-// the MFMA kernels do not take (fp32 tensors, head_dim != 128) and is not tuned for speed.
+// the MFMA kernels do not take (fp32 decode rows, fp32 and bf16 at other head_dims, FP8 caches of either) and is not tuned
+// for speed.
 #include "internal.h"
 
 namespace shiftattn {

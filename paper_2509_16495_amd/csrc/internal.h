@@ -136,6 +136,11 @@ hipError_t launch_prefill_mfma64(const void* q, const void* cache, const int32_t
                                  const Prefill64Plan& pl, void* out, void* workspace, const AttnShape& a, float c,
                                  float out_scale, hipStream_t st);
 
+// prefill_f32.hip : fp32 tensors and cache, D = 64 or 128, hq_l / hkv_l <= 16
+bool prefill_f32_supported(const AttnShape& a);
+hipError_t launch_prefill_f32(const void* q, const void* cache, const int32_t* block_table, const int32_t* cu_seqlens_q,
+                              const int32_t* seq_lens, int num_seqs, int total_q, void* out, const AttnShape& a, hipStream_t st);
+
 // Per-device set-up of the kernels that need more dynamic LDS than the default limit (each sets the attribute of its
 // kernels on the current device).  api.hip calls them once per device, under a lock, before the first launch there.
 hipError_t prefill_mfma_init();
