@@ -618,7 +618,15 @@ size_t shiftattn_mixed_workspace_bytes(int32_t num_prefill_seqs, int32_t total_p
     const size_t wp = shiftattn_prefill_workspace_bytes(num_prefill_seqs, total_prefill_q, max_q_len, max_prefill_seq_len, a);
     const size_t wd = shiftattn_decode_workspace_bytes(num_decode_seqs, max_decode_seq_len, a);
     if (wp == SIZE_MAX || wd == SIZE_MAX) return SIZE_MAX;
-    return wp > wd ? wp : wd;
+    size_t need = wp > wd ? wp : wd;
+    AttnShape s;
+    if (check_attn(a, &s) == 0 && use_prefill_mfma(s, num_prefill_seqs, max_prefill_seq_len) &&
+        use_decode_mfma(s, num_decode_seqs, max_decode_seq_len)) {
+        const size_t both = prefill_and_decode_workspace(num_prefill_seqs, total_prefill_q, max_q_len, max_prefill_seq_len,
+                                                         num_decode_seqs, max_decode_seq_len, s);
+        if (both > need) need = both;
+    }
+    return need;
 }
 
 int shiftattn_mixed(const void* q, const void* k_new, const void* v_new, const int64_t* slot_mapping, void* kv_cache,
@@ -662,6 +670,15 @@ int shiftattn_mixed(const void* q, const void* k_new, const void* v_new, const i
         hipError_t e = launch_kv_write(k_new, v_new, slot_mapping, static_cast<int>(rows), kv_cache, s,
                                        static_cast<hipStream_t>(stream));
         if (e != hipSuccess) return hip_fail(e, "kv_write launch");
+    }
+    if (workspace && aligned16(workspace) && use_prefill_mfma(s, num_prefill_seqs, max_prefill_seq_len) &&
+        use_decode_mfma(s, num_decode_seqs, max_decode_seq_len)) {
+        if (int rc = ensure_device_ready()) return rc;
+        hipError_t e = hipSuccess;
+        if (launch_prefill_and_decode(q, kv_cache, block_table, cu_seqlens_q, seq_lens, num_prefill_seqs, total_prefill_q, max_q_len,
+                                      max_prefill_seq_len, num_decode_seqs, max_decode_seq_len, out, workspace, workspace_bytes, s,
+                                      static_cast<hipStream_t>(stream), &e))
+            return e == hipSuccess ? SHIFTATTN_OK : hip_fail(e, "mixed launch");
     }
     // the two kinds of rows go to the kernel built for each; both read the cache written above
     if (int rc = shiftattn_prefill(q, nullptr, nullptr, nullptr, kv_cache, block_table, cu_seqlens_q, seq_lens,

@@ -218,13 +218,10 @@ __global__ __launch_bounds__(kCombineThreads) void combine_kernel(const float* _
 // c and the weights go round by cross-lane reads, so a row waits for memory once (twice beyond eight parts), where a walk
 // over the pairs waited once per part: 2048 tokens x 8 heads, 4 parts 10.4 -> 9.1 us; 1000 x 8, 8 parts 9.2 -> 8.0.
 constexpr int kSplitRowsPerWg = 8;
-__global__ __launch_bounds__(32 * kSplitRowsPerWg) void combine_splits_kernel(const float* __restrict__ o_part,
-                                                                              const float* __restrict__ ml_part,
-                                                                              int64_t rows, int hq_l, int n_parts,
-                                                                              uint16_t* __restrict__ out, int64_t out_stride,
-                                                                              float out_scale) {
+__device__ inline void combine_splits_body(const float* __restrict__ o_part, const float* __restrict__ ml_part, int64_t rows, int hq_l,
+                                           int n_parts, uint16_t* __restrict__ out, int64_t out_stride, float out_scale, int wg) {
     constexpr int D = 128;
-    const int64_t row_raw = static_cast<int64_t>(blockIdx.x) * kSplitRowsPerWg + (threadIdx.x >> 5);
+    const int64_t row_raw = static_cast<int64_t>(wg) * kSplitRowsPerWg + (threadIdx.x >> 5);
     const int64_t row = row_raw < rows ? row_raw : rows - 1;  // (every lane stays for the cross-lane reads)
     const int q4 = threadIdx.x & 31;
     const float* o_row = o_part + row * D + 4 * q4;
@@ -284,6 +281,14 @@ __global__ __launch_bounds__(32 * kSplitRowsPerWg) void combine_splits_kernel(co
                                                static_cast<uint32_t>(h[2]) | (static_cast<uint32_t>(h[3]) << 16)};
 }
 
+__global__ __launch_bounds__(32 * kSplitRowsPerWg) void combine_splits_kernel(const float* __restrict__ o_part,
+                                                                              const float* __restrict__ ml_part,
+                                                                              int64_t rows, int hq_l, int n_parts,
+                                                                              uint16_t* __restrict__ out, int64_t out_stride,
+                                                                              float out_scale) {
+    combine_splits_body(o_part, ml_part, rows, hq_l, n_parts, out, out_stride, out_scale, blockIdx.x);
+}
+
 // Merge for the flat decode kernel (bf16 output, D = 128; out_scale = v_scale of an FP8 cache, else 1): one workgroup per
 // output row.  The parts of a row are the partial rows (plan[pair].x + c) * G + head % G, c < plan[pair].y.  32 threads
 // (four head-dim elements each) form a group; group pg sums the parts c = pg, pg + groups, ... and the groups' sums are
@@ -293,14 +298,13 @@ __global__ __launch_bounds__(32 * kSplitRowsPerWg) void combine_splits_kernel(co
 // batches: 64 parts in flight per row), four where it is the reverse.  Against one element per thread
 // and the weights through LDS: 2048 rows of 9 parts 5.9 -> 5.3 us, 32 rows of 65 parts 5.5 -> 4.6.
 template <int kGroups>
-__global__ __launch_bounds__(32 * kGroups) void combine_flat_kernel(
-    const float* __restrict__ o_part, const float* __restrict__ ml_part, const int2* __restrict__ plan, int hq_l, int G,
-    uint16_t* __restrict__ out, int64_t out_stride, float out_scale) {
+__device__ inline void combine_flat_body(const float* __restrict__ o_part, const float* __restrict__ ml_part,
+                                         const int2* __restrict__ plan, int hq_l, int G, uint16_t* __restrict__ out, int64_t out_stride,
+                                         float out_scale, int row) {   // row: sequence * hq_l + head
     constexpr int D = 128, kThreadsF = 32 * kGroups, kEarly = 4;
     __shared__ float w_s[kCombineMaxParts];
     __shared__ float red_s[2][kThreadsF / 64];
     __shared__ __attribute__((aligned(16))) float acc_s[kGroups / 2][D];
-    const int row = blockIdx.x;  // sequence * hq_l + head
     const int tok = row / hq_l, head = row % hq_l;
     const int2 e = plan[tok * (hq_l / G) + head / G];
     const int np = min(e.y, kCombineMaxParts);
@@ -382,7 +386,36 @@ __global__ __launch_bounds__(32 * kGroups) void combine_flat_kernel(
     }
 }
 
+template <int kGroups>
+__global__ __launch_bounds__(32 * kGroups) void combine_flat_kernel(
+    const float* __restrict__ o_part, const float* __restrict__ ml_part, const int2* __restrict__ plan, int hq_l, int G,
+    uint16_t* __restrict__ out, int64_t out_stride, float out_scale) {
+    combine_flat_body<kGroups>(o_part, ml_part, plan, hq_l, G, out, out_stride, out_scale, blockIdx.x);
+}
+
+// The two merges of a launch that carried chunks and decode rows: the first dec_rows workgroups take a decode row each.
+__global__ __launch_bounds__(32 * kSplitRowsPerWg) void combine_both_kernel(
+    const float* __restrict__ o_part_p, const float* __restrict__ ml_part_p, int64_t rows_p, int n_parts, uint16_t* __restrict__ out_p,
+    const float* __restrict__ o_part_d, const float* __restrict__ ml_part_d, const int2* __restrict__ plan, int dec_rows,
+    uint16_t* __restrict__ out_d, int hq_l, int G, int64_t out_stride, float out_scale) {
+    const int wg = blockIdx.x;
+    if (wg < dec_rows) combine_flat_body<kSplitRowsPerWg>(o_part_d, ml_part_d, plan, hq_l, G, out_d, out_stride, out_scale, wg);
+    else combine_splits_body(o_part_p, ml_part_p, rows_p, hq_l, n_parts, out_p, out_stride, out_scale, wg - dec_rows);
+}
+
 }  // namespace
+
+hipError_t launch_combine_both(const float* o_part_p, const float* ml_part_p, int n_rows_p, int n_parts, void* out_p, const float* o_part_d,
+                               const float* ml_part_d, const int2* plan, int num_dec, void* out_d, const AttnShape& a, hipStream_t st) {
+    const int G = a.hq_l / a.hkv_l;
+    if (n_parts == 1) return launch_combine_flat(o_part_d, ml_part_d, plan, num_dec, a.hq_l, G, out_d, a.out_stride, a.v_scale, st);
+    const int64_t rows_p = static_cast<int64_t>(n_rows_p) * a.hq_l, rows_d = static_cast<int64_t>(num_dec) * a.hq_l;
+    const unsigned grid = static_cast<unsigned>(rows_d + (rows_p + kSplitRowsPerWg - 1) / kSplitRowsPerWg);
+    combine_both_kernel<<<grid, 32 * kSplitRowsPerWg, 0, st>>>(o_part_p, ml_part_p, rows_p, n_parts, static_cast<uint16_t*>(out_p), o_part_d,
+                                                             ml_part_d, plan, static_cast<int>(rows_d), static_cast<uint16_t*>(out_d),
+                                                             a.hq_l, G, a.out_stride, a.v_scale);
+    return hipGetLastError();
+}
 
 hipError_t launch_combine_flat(const float* o_part, const float* ml_part, const int2* plan, int num_seqs, int hq_l, int G,
                                void* out, int64_t out_stride, float out_scale, hipStream_t st) {

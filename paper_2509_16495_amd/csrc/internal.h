@@ -50,6 +50,9 @@ hipError_t launch_attn_generic(const void* q, const void* cache, const int32_t* 
 // Partials: o[part][row][D] fp32 un-normalised, ml[part][row][2] = (max logit * log2e*scale, sum).
 // mode 0: every row has n_parts parts.  mode 1 (decode): row = (sequence, head), the number of
 // parts of a row is ceil(seq_lens[sequence] / chunk).
+// both merges of launch_prefill_and_decode in one launch (n_parts 1: the prefill part has none)
+hipError_t launch_combine_both(const float* o_part_p, const float* ml_part_p, int n_rows_p, int n_parts, void* out_p, const float* o_part_d,
+                               const float* ml_part_d, const int2* plan, int num_dec, void* out_d, const AttnShape& a, hipStream_t st);
 hipError_t launch_combine(const float* o_part, const float* ml_part, int n_rows, int hq_l, int D,
                           int n_parts, int mode, const int32_t* seq_lens, int chunk, void* out,
                           int64_t out_stride, int elem, float out_scale, hipStream_t st);
@@ -64,6 +67,13 @@ size_t decode_mfma_workspace(int num_seqs, int max_seq_len, const AttnShape& a);
 // k_new / v_new / slots non-null: the kernel also appends the new token of every sequence (only where
 // decode_mfma_appends() says so; the caller then launches no separate K/V write)
 bool decode_mfma_appends(int num_seqs, const AttnShape& a);
+// for launches that carry decode rows beside other work: partial rows (one per (wavefront, pair) whose ranges meet,
+// numbered wavefront + pair) and workspace of `workers` wavefronts, the least tokens a wavefront takes, and whether one
+// launch indexes the batch
+size_t decode_mfma_rows_for(int workers, int num_seqs, const AttnShape& a);
+size_t decode_mfma_workspace_for(int workers, int num_seqs, const AttnShape& a);
+int decode_mfma_r_min(int max_seq_len);
+bool decode_mfma_one_launch(int num_seqs, int max_seq_len, const AttnShape& a);
 hipError_t launch_decode_mfma(const void* q, const void* k_new, const void* v_new, const int64_t* slots, void* cache,
                               const int32_t* block_table, const int32_t* seq_lens, int num_seqs, int max_seq_len,
                               void* out, void* workspace, const AttnShape& a, hipStream_t st);
@@ -78,6 +88,13 @@ hipError_t launch_prefill_mfma(const void* q, const void* cache, const int32_t* 
                                const int32_t* cu_seqlens_q, const int32_t* seq_lens, int num_seqs,
                                int total_q, int max_q_len, int max_seq_len, void* out, void* workspace,
                                size_t workspace_bytes, const AttnShape& a, hipStream_t st);
+
+// the chunks and the decode rows of a unified batch in one launch: the workspace it needs (0: the parts are launched one
+// after the other), and the launch (false: not taken, nothing enqueued)
+size_t prefill_and_decode_workspace(int num_seqs, int total_q, int max_q_len, int max_seq_len, int num_dec, int max_dec_len, const AttnShape& a);
+bool launch_prefill_and_decode(const void* q, void* cache, const int32_t* block_table, const int32_t* cu_seqlens_q, const int32_t* seq_lens,
+                               int num_seqs, int total_q, int max_q_len, int max_seq_len, int num_dec, int max_dec_len, void* out,
+                               void* workspace, size_t workspace_bytes, const AttnShape& a, hipStream_t st, hipError_t* err);
 
 // prefill_mfma64.hip : the same operation on 256-column workgroup tiles, one 64-column wavefront per SIMD; bf16 cache
 struct Prefill64Plan {

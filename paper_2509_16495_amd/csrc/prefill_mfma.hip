@@ -45,7 +45,7 @@
 // prompts of 149 to 1097 tokens, 5 heads: 34.6 -> 28.2 us a call).  The long contexts of chunked
 // prefill are additionally split into key ranges whose partial results are merged by launch_combine.
 // plan_within() below prices the plans of both prefill kernels.
-#include "internal.h"
+#include "decode_body.h"
 
 #include <utility>
 
@@ -101,11 +101,41 @@ struct PrefillParams {
     int max_blocks;
     float c;          // softmax_scale * log2(e) (times k_scale for a cache widened from FP8)
     float out_scale;  // multiplies the normalised output: v_scale of an FP8 cache, else 1
+    // launches that carry decode rows (see launch_prefill_and_decode)
+    int ranks;        // tiles per sequence at most
+    float range_div;  // a tile's keys are cut into ranges of 1 / range_div of them, the last one what remains
 };
 
-__global__ __launch_bounds__(kThreads, 2) void prefill_kernel(PrefillParams p) {
+// decode rows that ride in a prefill launch: what decode_flat_body takes, and how many workgroups they get
+struct DecodeRole {
+    const uint16_t* q;
+    uint16_t* cache;
+    const int32_t* block_table;
+    const int32_t* seq_lens;
+    float* o_part;
+    float* ml_part;
+    int2* plan;
+    int max_blocks, num_seqs, r_min, n_wg;
+    float c;
+};
+constexpr int kDecodeWaves = kThreads / 64;
+constexpr int kLdsBytesDecode = kDecodeWaves * decode_flat::kStageBytes + decode_flat::kIndexInts * 4;
+constexpr int kLdsBytesBoth = kLdsBytesDecode > kLdsBytes ? kLdsBytesDecode : kLdsBytes;
+
+// kDecode: 0 = prefill only; 1, 2 = the first workgroups take decode rows over a bf16 (1) or FP8 (2) cache
+template <int kDecode>
+__global__ __launch_bounds__(kThreads, 2) void prefill_kernel(PrefillParams p, DecodeRole dec) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     constexpr int kCols = 128;
+    if constexpr (kDecode != 0) {
+        if (static_cast<int>(blockIdx.x) < dec.n_wg) {   // uniform
+            decode_flat::decode_flat_body<kDecode == 2, false, kDecodeWaves>(
+                dec.q, p.q_stride, dec.cache, dec.block_table, dec.max_blocks, dec.seq_lens, dec.o_part, dec.ml_part, dec.plan, dec.num_seqs,
+                p.hq_l, p.hq_l / p.G, dec.c, dec.r_min, decode_flat::AppendArgs{}, lds,
+                reinterpret_cast<int*>(lds + kDecodeWaves * decode_flat::kStageBytes), blockIdx.x, dec.n_wg);
+            return;
+        }
+    }
 
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int grp = wave >> 2;  // key-tile parity this wavefront works on
@@ -114,11 +144,19 @@ __global__ __launch_bounds__(kThreads, 2) void prefill_kernel(PrefillParams p) {
 
     // ---- which (pair rank, key split, sequence, head slot) is this workgroup -----------------------
     const int n_sh = p.num_seqs * p.head_slots;
-    int item = blockIdx.x;
-    const int rank = item / (n_sh * p.n_splits);
-    item -= rank * (n_sh * p.n_splits);
-    const int split = item / n_sh;
-    item -= split * n_sh;
+    int item = blockIdx.x, rank, split;
+    if constexpr (kDecode == 0) {
+        rank = item / (n_sh * p.n_splits);
+        item -= rank * (n_sh * p.n_splits);
+        split = item / n_sh;
+        item -= split * n_sh;
+    } else {   // ranges outermost: the shorter last ones start last, on the compute units that the decode rows leave
+        item -= dec.n_wg;
+        split = item / (n_sh * p.ranks);
+        item -= split * (n_sh * p.ranks);
+        rank = item / n_sh;
+        item -= rank * n_sh;
+    }
     if (p.rotate) item = (item + n_sh - static_cast<int>((blockIdx.x / max(n_sh, 8)) % n_sh)) % n_sh;
     const int s = item / p.head_slots;
     const int hs = item - s * p.head_slots;
@@ -204,9 +242,9 @@ __global__ __launch_bounds__(kThreads, 2) void prefill_kernel(PrefillParams p) {
         // ---- key tiles of this (column tile, split), dealt alternately to the two groups ------------------
         const int tile_pos_max = ctx - q_len + min(tok0 + tile_tokens, q_len) - 1;
         const int kv_tiles = tile_pos_max / kKvTile + 1;
-        const int per_split = (kv_tiles + p.n_splits - 1) / p.n_splits;
+        const int per_split = kDecode == 0 ? (kv_tiles + p.n_splits - 1) / p.n_splits : static_cast<int>(ceilf(kv_tiles / p.range_div));
         const int kt_begin = split * per_split;
-        const int kt_end = min(kv_tiles, kt_begin + per_split);
+        const int kt_end = kDecode != 0 && split == p.n_splits - 1 ? kv_tiles : min(kv_tiles, kt_begin + per_split);
         const int n_all = max(kt_end - kt_begin, 0);
         const int n = (n_all + 1 - grp) >> 1;        // tiles of this group: kt(j) = kt_begin + grp + 2 j
         const int n_other = (n_all + grp) >> 1;
@@ -875,41 +913,41 @@ size_t prefill_mfma_workspace(int num_seqs, int total_q, int max_q_len, int max_
 }
 
 hipError_t prefill_mfma_init() {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&prefill_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               kLdsBytes);
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&prefill_kernel<0>), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
+    if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&prefill_kernel<1>), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytesBoth);
+    if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&prefill_kernel<2>), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytesBoth);
+    return e;
 }
 
-hipError_t launch_prefill_mfma(const void* q, const void* cache, const int32_t* block_table,
-                               const int32_t* cu_seqlens_q, const int32_t* seq_lens, int num_seqs, int total_q,
-                               int max_q_len, int max_seq_len, void* out, void* workspace, size_t workspace_bytes,
-                               const AttnShape& a, hipStream_t st) {
-    if (num_seqs == 0 || total_q == 0 || max_q_len <= 0) return hipSuccess;
-    const size_t fixed = with_fp8_scratch(0, num_seqs, max_seq_len, a);
-    // (an FP8 cache's scratch lies behind the partials, at a multiple of 256 bytes)
-    const size_t budget = workspace_bytes < fixed ? 0 : a.kv_fp8() ? (workspace_bytes - fixed) / 256 * 256 : workspace_bytes;
-    const Choice ch = plan_within(budget, num_seqs, total_q, max_q_len, max_seq_len, a);
-    int max_blocks = a.max_blocks;
-    if (a.kv_fp8()) {  // widen into the scratch cache behind the split partials, then attend over that
-        const Fp8Scratch f = fp8_scratch(num_seqs, max_seq_len, a);
-        const size_t split_bytes = (split_bytes_of(ch, total_q, a) + 255) / 256 * 256;
-        unsigned char* scratch = static_cast<unsigned char*>(workspace) + split_bytes;
-        int32_t* table2 = reinterpret_cast<int32_t*>(scratch + f.cache_bytes);
-        hipError_t e0 = launch_fp8_blocks_to_bf16(cache, block_table, a.max_blocks, seq_lens, num_seqs, f.nb, a.hkv_l, scratch,
-                                                 table2, st);
-        if (e0 != hipSuccess) return e0;
-        cache = scratch;
-        block_table = table2;
-        max_blocks = f.nb;
-    }
-    const float c = a.scale * a.k_scale * 1.4426950408889634f;
-    if (ch.wide)
-        return launch_prefill_mfma64(q, cache, block_table, max_blocks, cu_seqlens_q, seq_lens, num_seqs, total_q, ch.w, out,
-                                     workspace, a, c, a.v_scale, st);
-    const Plan& pl = ch.narrow;
+namespace {
+
+constexpr float kLog2e = 1.4426950408889634f;
+
+// The cache as the kernels read it: itself, or the blocks of an FP8 cache that the batch needs widened to bf16 behind the
+// partials in the workspace.
+struct CacheView {
+    const void* cache;
+    const int32_t* block_table;
+    int max_blocks;
+};
+
+hipError_t bf16_view(const void* cache, const int32_t* block_table, const int32_t* seq_lens, int num_seqs, int max_seq_len,
+                     size_t partial_bytes, void* workspace, const AttnShape& a, CacheView* v, hipStream_t st) {
+    *v = {cache, block_table, a.max_blocks};
+    if (!a.kv_fp8()) return hipSuccess;
+    const Fp8Scratch f = fp8_scratch(num_seqs, max_seq_len, a);
+    unsigned char* scratch = static_cast<unsigned char*>(workspace) + (partial_bytes + 255) / 256 * 256;
+    int32_t* table2 = reinterpret_cast<int32_t*>(scratch + f.cache_bytes);
+    *v = {scratch, table2, f.nb};
+    return launch_fp8_blocks_to_bf16(cache, block_table, a.max_blocks, seq_lens, num_seqs, f.nb, a.hkv_l, scratch, table2, st);
+}
+
+PrefillParams narrow_params(const void* q, const CacheView& v, const int32_t* cu_seqlens_q, const int32_t* seq_lens, int num_seqs,
+                            int total_q, const Plan& pl, void* out, void* workspace, const AttnShape& a) {
     PrefillParams p;
     p.q = static_cast<const uint16_t*>(q);
-    p.cache = static_cast<const uint16_t*>(cache);
-    p.block_table = block_table;
+    p.cache = static_cast<const uint16_t*>(v.cache);
+    p.block_table = v.block_table;
     p.cu_seqlens_q = cu_seqlens_q;
     p.seq_lens = seq_lens;
     p.out = static_cast<uint16_t*>(out);
@@ -928,18 +966,180 @@ hipError_t launch_prefill_mfma(const void* q, const void* cache, const int32_t* 
     p.n_splits = pl.n_splits;
     p.paired = pl.paired ? 1 : 0;
     p.rotate = pl.rotate ? 1 : 0;
-    p.max_blocks = max_blocks;
-    p.c = c;
+    p.max_blocks = v.max_blocks;
+    p.c = a.scale * a.k_scale * kLog2e;
     p.out_scale = a.v_scale;
+    p.ranks = pl.pair_ranks;
+    p.range_div = static_cast<float>(pl.n_splits);
+    return p;
+}
 
+}  // namespace
+
+hipError_t launch_prefill_mfma(const void* q, const void* cache, const int32_t* block_table,
+                               const int32_t* cu_seqlens_q, const int32_t* seq_lens, int num_seqs, int total_q,
+                               int max_q_len, int max_seq_len, void* out, void* workspace, size_t workspace_bytes,
+                               const AttnShape& a, hipStream_t st) {
+    if (num_seqs == 0 || total_q == 0 || max_q_len <= 0) return hipSuccess;
+    const size_t fixed = with_fp8_scratch(0, num_seqs, max_seq_len, a);
+    // (an FP8 cache's scratch lies behind the partials, at a multiple of 256 bytes)
+    const size_t budget = workspace_bytes < fixed ? 0 : a.kv_fp8() ? (workspace_bytes - fixed) / 256 * 256 : workspace_bytes;
+    const Choice ch = plan_within(budget, num_seqs, total_q, max_q_len, max_seq_len, a);
+    CacheView v;
+    if (hipError_t e = bf16_view(cache, block_table, seq_lens, num_seqs, max_seq_len, split_bytes_of(ch, total_q, a), workspace, a, &v, st); e != hipSuccess)
+        return e;
+    if (ch.wide)
+        return launch_prefill_mfma64(q, v.cache, v.block_table, v.max_blocks, cu_seqlens_q, seq_lens, num_seqs, total_q, ch.w, out,
+                                     workspace, a, a.scale * a.k_scale * kLog2e, a.v_scale, st);
+    const Plan& pl = ch.narrow;
+    const PrefillParams p = narrow_params(q, v, cu_seqlens_q, seq_lens, num_seqs, total_q, pl, out, workspace, a);
     const unsigned grid = static_cast<unsigned>(pl.pair_ranks) * pl.n_splits * num_seqs * pl.head_slots;
-    prefill_kernel<<<grid, kThreads, kLdsBytes, st>>>(p);
+    prefill_kernel<0><<<grid, kThreads, kLdsBytes, st>>>(p, DecodeRole{});
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (pl.n_splits > 1)
         return launch_combine(p.o_part, p.ml_part, total_q, a.hq_l, kD, pl.n_splits, 0, nullptr, 0, out, a.out_stride,
                               a.elem, a.v_scale, st);
     return hipSuccess;
+}
+
+// ---- prefill and decode rows of a unified batch in one launch -----------------------------------------------------
+// Chunks are bound by the matrix units, decode rows by memory, and one behind the other each leaves the other's resource
+// idle; each also costs a launch (about 4.6 us behind another kernel) for its product and one for its merge.  Here the
+// first workgroups of the 128-column kernel's grid take the decode rows and the others the tiles, one merge kernel serves
+// both.  A compute unit holds one workgroup of either kind, so the rows get as many as the tiles' ranges leave over; where
+// every place is taken, the last key range of each tile is the one that waits for a place and is made shorter by what the
+// decode rows take, so that all end together.  1000 tokens on 20000 cached (FP8) with 97 decodes: 154 -> 132 us a step;
+// forty random batches (chunks of 100 .. 2048 on 1000 .. 60000 cached, 2 .. 128 decodes): 1.22 times, none slower.
+namespace {
+
+struct BothPlan {
+    bool taken;
+    Plan narrow;
+    int dec_wgs;
+    float range_div;
+    size_t partial_bytes;  // of the prefill part, a multiple of 256 with an FP8 cache's scratch behind it
+    size_t bytes;          // workspace in all
+};
+
+// microseconds the decode rows take on some workgroups of eight wavefronts, one per compute unit (rates measured with 64 of
+// them; an FP8 cache has half the bytes in flight); the lengths are on the device, their mean is taken as 0.6 of the longest
+double decode_bytes(int num_seqs, int max_seq_len, const AttnShape& a) {
+    return 0.6 * num_seqs * static_cast<double>(max_seq_len) * a.hkv_l * 2 * kD * a.kv_elem;
+}
+constexpr double kDecodeStartUs = 5.0, kBf16BytesPerUsWg = 60e3, kFp8BytesPerUsWg = 48e3, kDecodeBytesPerUs = 5.8e6;
+double decode_us(double bytes, double wgs, bool fp8) {
+    const double rate = wgs * (fp8 ? kFp8BytesPerUsWg : kBf16BytesPerUsWg);
+    return kDecodeStartUs + bytes / (rate < kDecodeBytesPerUs ? rate : kDecodeBytesPerUs);
+}
+
+BothPlan plan_both(int num_seqs, int total_q, int max_q_len, int max_seq_len, int num_dec, int max_dec_len, const AttnShape& a) {
+    BothPlan best{};
+    if (option_prefill_tile() == 256 || option_prefill_splits() != 0 || option_prefill_pairing() == 1) return best;
+    if (num_seqs < 1 || total_q < 1 || max_q_len < 1 || num_dec < 1 || max_dec_len < 1 || !decode_mfma_one_launch(num_dec, max_dec_len, a))
+        return best;
+    const double bytes = decode_bytes(num_dec, max_dec_len, a);
+    if (bytes < 1e6) return best;   // (a few short rows: nothing to share, and the workspace stays the larger of the two parts')
+    const Choice alone = plan_within(SIZE_MAX, num_seqs, total_q, max_q_len, max_seq_len, a);
+    const TileKernel& k = kNarrowCost;
+    const Plan& base = alone.narrow;
+    const double serial = (alone.wide ? launch_us(kWideCost, alone.w.paired, alone.w.n_splits, alone.w.tile_tokens, a.hkv_l, num_seqs, total_q,
+                                                  max_q_len, max_seq_len, a.hq_l)
+                                      : launch_us(k, base.paired, base.n_splits, base.tile_tokens, base.head_slots, num_seqs, total_q,
+                                                  max_q_len, max_seq_len, a.hq_l)) + decode_us(bytes, 256, a.kv_fp8()) + 9.0;
+    double best_us = 0.97 * serial;
+    const int tiles = (max_q_len + base.tile_tokens - 1) / base.tile_tokens;
+    const double seqs = longest_chunk_equivalents(num_seqs, total_q, max_q_len);
+    const int q = max_q_len < max_seq_len ? max_q_len : max_seq_len;
+    const double lightest = max_seq_len - q + (base.tile_tokens < q ? base.tile_tokens : q);
+    const double step = (k.step + k.step_full) / k.keys_per_step;   // per key
+    for (int splits : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 24, 32}) {
+        if (splits > 1 && max_seq_len < splits * 2 * kKvTile) break;
+        const double wgs = tiles * seqs * base.head_slots * splits, grid = static_cast<double>(tiles) * num_seqs * base.head_slots * splits;
+        const double merge = splits > 1 ? splits * static_cast<double>(total_q) * a.hq_l * 1040 / 5.8e6 : 0.0;
+        auto consider = [&](double x, double div, double span) {
+            const double us = (span + merge + 6.6 + 4.5) * (1.0 + 0.008 * splits);
+            if (us >= best_us) return;
+            best_us = us;
+            best.taken = true;
+            best.narrow = base;
+            best.narrow.paired = false;
+            best.narrow.pair_ranks = tiles;
+            best.narrow.n_splits = splits;
+            best.dec_wgs = static_cast<int>(x);
+            best.range_div = static_cast<float>(div);
+        };
+        auto rows_us = [&](double x) { return decode_us(bytes, x, a.kv_fp8()); };
+        if (grid <= 256) {
+            const double free = 256 - grid, last = grid / splits;   // places the tiles leave over; workgroups of the last ranges
+            if (free >= 8) {                                        // nobody waits
+                const double d = k.pass + max_seq_len * step / splits;
+                consider(free, splits, d > rows_us(free) ? d : rows_us(free));
+            }
+            if (splits > 1 && free + last >= 8) {                   // the last ranges wait for the decode rows' places
+                const double x = static_cast<int>(free + last);
+                const double cut = rows_us(x) / step / max_seq_len;     // keys the last range leaves to the others, of the tile's
+                const double share = (1.0 + cut) / splits;              // of a full range: splits x share - cut = 1
+                if (share - cut >= 0.05 * share) consider(x, 1.0 / share, k.pass + max_seq_len * share * step);
+            }
+        } else {                                                    // several rounds: the rows first, ever lighter tiles behind them
+            const double d_hi = k.pass + max_seq_len * step / splits, d_lo = k.pass + lightest * step / splits;
+            for (int x : {32, 64, 96, 128, 192}) {
+                double span = 1.13 * (0.5 * (d_hi + d_lo) * wgs + x * rows_us(x)) / 256;
+                const double rounds = static_cast<double>(static_cast<long>((grid + x + 255) / 256));
+                for (const double least : {d_hi, rounds * d_lo, rows_us(x)})
+                    if (span < least) span = least;
+                consider(x, splits, span);
+            }
+        }
+    }
+    if (best.taken) {
+        best.partial_bytes = split_bytes(best.narrow.n_splits, total_q, a);
+        best.bytes = (with_fp8_scratch(best.partial_bytes, num_seqs, max_seq_len, a) + 255) / 256 * 256 +
+                     decode_mfma_workspace_for(best.dec_wgs * kDecodeWaves, num_dec, a);
+    }
+    return best;
+}
+
+}  // namespace
+
+size_t prefill_and_decode_workspace(int num_seqs, int total_q, int max_q_len, int max_seq_len, int num_dec, int max_dec_len, const AttnShape& a) {
+    return plan_both(num_seqs, total_q, max_q_len, max_seq_len, num_dec, max_dec_len, a).bytes;
+}
+
+bool launch_prefill_and_decode(const void* q, void* cache, const int32_t* block_table, const int32_t* cu_seqlens_q, const int32_t* seq_lens,
+                               int num_seqs, int total_q, int max_q_len, int max_seq_len, int num_dec, int max_dec_len, void* out,
+                               void* workspace, size_t workspace_bytes, const AttnShape& a, hipStream_t st, hipError_t* err) {
+    const BothPlan pl = plan_both(num_seqs, total_q, max_q_len, max_seq_len, num_dec, max_dec_len, a);
+    if (!pl.taken || workspace_bytes < pl.bytes) return false;
+    CacheView v;
+    *err = bf16_view(cache, block_table, seq_lens, num_seqs, max_seq_len, pl.partial_bytes, workspace, a, &v, st);
+    if (*err != hipSuccess) return true;
+    PrefillParams p = narrow_params(q, v, cu_seqlens_q, seq_lens, num_seqs, total_q, pl.narrow, out, workspace, a);
+    p.range_div = pl.range_div;
+    const size_t dec_at = (with_fp8_scratch(pl.partial_bytes, num_seqs, max_seq_len, a) + 255) / 256 * 256;
+    const size_t rows = decode_mfma_rows_for(pl.dec_wgs * kDecodeWaves, num_dec, a);
+    DecodeRole d;
+    d.q = p.q + static_cast<size_t>(total_q) * a.q_stride;
+    d.cache = static_cast<uint16_t*>(cache);
+    d.block_table = block_table + static_cast<size_t>(num_seqs) * a.max_blocks;
+    d.seq_lens = seq_lens + num_seqs;
+    d.o_part = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + dec_at);
+    d.ml_part = d.o_part + rows * kD;
+    d.plan = reinterpret_cast<int2*>(d.ml_part + rows * 2);
+    d.max_blocks = a.max_blocks;
+    d.num_seqs = num_dec;
+    d.r_min = decode_mfma_r_min(max_dec_len);
+    d.n_wg = pl.dec_wgs;
+    d.c = p.c;
+    const unsigned grid = static_cast<unsigned>(pl.dec_wgs) + static_cast<unsigned>(pl.narrow.pair_ranks) * pl.narrow.n_splits * num_seqs * pl.narrow.head_slots;
+    if (a.kv_fp8()) prefill_kernel<2><<<grid, kThreads, kLdsBytesBoth, st>>>(p, d);
+    else prefill_kernel<1><<<grid, kThreads, kLdsBytesBoth, st>>>(p, d);
+    *err = hipGetLastError();
+    if (*err != hipSuccess) return true;
+    *err = launch_combine_both(p.o_part, p.ml_part, total_q, pl.narrow.n_splits, out, d.o_part, d.ml_part, d.plan, num_dec,
+                               static_cast<uint16_t*>(out) + static_cast<size_t>(total_q) * a.out_stride, a, st);
+    return true;
 }
 
 }  // namespace shiftattn

@@ -1,0 +1,59 @@
+"""Chunks and decode rows of a unified batch in one launch, against the fp64 oracle and against the two parts launched one
+after the other (what a workspace of the larger part's size gives): tiles that leave places over, tiles whose last key
+range waits for the decode rows' places, several rounds of tiles.  max |err| <= 2e-2 and mean |err| <= 1e-3 against the
+oracle, as for all bf16 attention; between the two launches twice that."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2509_16495_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+SCALES = (0.0371, 0.0293)
+
+
+@pytest.fixture(scope="module")
+def G():
+    import gpu_backend
+    return gpu_backend
+
+
+BATCHES = [
+    # chunks (tokens, context), decode contexts, query heads, KV heads
+    ([(33, 2000)], [5000, 1, 31, 32, 33, 700, 1500], 8, 1),                 # few tiles: most places are left over
+    ([(1000, 3000)], [3000] * 9 + [17, 64], 8, 1),                          # 63 tiles in ranges: the last ones wait
+    ([(700, 700)], [9000, 3], 4, 1),
+    ([(900, 1300), (333, 333)], [2500, 4100, 16], 16, 2),                   # several rounds, unequal chunks, two KV heads
+    ([(260, 2600)], [4000, 900, 60, 2000], 5, 1),                           # heads not stacked
+    ([(1, 1), (0, 5), (40, 90)], [6000, 6000], 8, 1),                       # a one-token and an empty chunk
+]
+
+
+@pytest.mark.parametrize("kv", ["bf16", "fp8"])
+@pytest.mark.parametrize("chunks,decodes,hq_l,hkv_l", BATCHES)
+def test_mixed_launch(oracle, G, kv, chunks, decodes, hq_l, hkv_l):
+    from paper_2509_16495_amd import binding as B
+    scales = SCALES if kv == "fp8" else None
+    case = W.make_attn_case("t", 103, "bf16", chunks + [(1, c) for c in decodes], hq_l, hkv_l, 128, pool_factor=1.2)
+    cache = G.cache_for_case(case, fill_byte=0xFF, fp8_scales=scales)   # (unwritten slots: NaN)
+    if scales:   # the oracle reads the codes the append wrote, which tests of their own compare bit for bit
+        want = oracle.attention_case(case, B.to_host(cache), k_scale=scales[0], v_scale=scales[1])
+    else:
+        want = oracle.attention_case(case, oracle.cache_for_case(case))
+    got = W.to_f64(G.mixed_case(case, len(chunks), cache, fused_new_kv=False, fp8_scales=scales), "bf16")
+    err = np.abs(got - want)
+    assert np.all(np.isfinite(got)) and err.max() <= 2e-2 and err.mean() <= 1e-3, (err.max(), err.mean())
+    # the parts one after the other
+    q, table, ctx = G.t(case.q, "bf16"), G.ti(case.block_table, np.int32), G.ti(case.ctx_lens, np.int32)
+    out = torch.empty_like(q)
+    ks, vs = scales or (1.0, 1.0)
+    n, tot, mq = len(chunks), sum(c[0] for c in chunks), max(c[0] for c in chunks)
+    desc = B.attn_desc(q, cache, table, case.softmax_scale, None, out, ks, vs)
+    size = max(B.prefill_workspace_bytes(n, tot, mq, max(c[1] for c in chunks), desc), B.decode_workspace_bytes(len(decodes), max(decodes), desc))
+    ws = torch.empty(size, dtype=torch.uint8, device=G.DEV)
+    B.mixed(q, cache, table, G.ti(case.cu_seqlens_q[:n + 1], np.int32), ctx, n, mq, max(c[1] for c in chunks), max(decodes), out,
+            case.softmax_scale, workspace=ws, k_scale=ks, v_scale=vs)
+    torch.cuda.synchronize()
+    serial = W.to_f64(B.to_host(out), "bf16")
+    assert np.abs(serial - want).max() <= 2e-2 and np.abs(serial - got).max() <= 4e-2
