@@ -39,6 +39,19 @@
 
 namespace shiftattn {
 
+// Decode rows that ride in a prefill launch: what decode_flat_body takes, and how many workgroups they get
+// (the first ones of the grid)
+struct DecodeRole {
+    const uint16_t* q;
+    uint16_t* cache;
+    const int32_t* block_table;
+    const int32_t* seq_lens;
+    float* o_part;
+    float* ml_part;
+    int2* plan;
+    int max_blocks, num_seqs, r_min, n_wg;
+    float c;
+};
 namespace decode_flat {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -466,6 +479,15 @@ __device__ __attribute__((always_inline)) inline void decode_flat_body(
     }
     flush(pair);
 }
+
+// the role's body in a kernel with LDS of its own layout: lds holds kWaves x kStageBytes and then kIndexInts ints
+template <bool kFp8, int kWaves>
+__device__ __attribute__((always_inline)) inline void decode_role(const DecodeRole& d, int64_t q_stride, int hq_l, int hkv_l, unsigned char* lds, int wg) {
+    decode_flat_body<kFp8, false, kWaves>(d.q, q_stride, d.cache, d.block_table, d.max_blocks, d.seq_lens, d.o_part, d.ml_part, d.plan, d.num_seqs,
+                                          hq_l, hkv_l, d.c, d.r_min, AppendArgs{}, lds, reinterpret_cast<int*>(lds + kWaves * kStageBytes), wg, d.n_wg);
+}
+template <int kWaves>
+constexpr int kRoleLdsBytes = kWaves * kStageBytes + kIndexInts * 4;
 
 }  // namespace decode_flat
 

@@ -143,6 +143,8 @@ inline bool rotate_sequences_over_dies(int num_seqs, int heads, int total_q, int
     return num_seqs > 1 && (static_cast<long>(num_seqs) * heads) % 4 == 0 &&
            longest_chunk_equivalents(num_seqs, total_q, max_q_len) < 0.9 * num_seqs;
 }
+constexpr int kPrefill64Waves = 4;  // per workgroup
+struct DecodeRole;                  // decode_body.h
 bool prefill_mfma64_supported(const AttnShape& a);
 Prefill64Plan prefill_mfma64_plan(int num_seqs, int total_q, int max_q_len, int max_seq_len, const AttnShape& a,
                                   int forced_splits);
@@ -157,6 +159,13 @@ hipError_t launch_prefill_mfma64(const void* q, const void* cache, const int32_t
 bool prefill_f32_supported(const AttnShape& a);
 hipError_t launch_prefill_f32(const void* q, const void* cache, const int32_t* block_table, const int32_t* cu_seqlens_q,
                               const int32_t* seq_lens, int num_seqs, int total_q, void* out, const AttnShape& a, hipStream_t st);
+
+// the same with decode rows in the grid's first workgroups, without the merge; the last of a tile's key ranges is what
+// 1 / range_div of its keys per range in front of it leave
+hipError_t launch_prefill64_and_decode(const void* q, const void* cache, const int32_t* block_table, int max_blocks,
+                                       const int32_t* cu_seqlens_q, const int32_t* seq_lens, int num_seqs, int total_q,
+                                       const Prefill64Plan& pl, float range_div, const DecodeRole& dec, void* out, void* workspace,
+                                       const AttnShape& a, float c, float out_scale, hipStream_t st);
 
 // Per-device set-up of the kernels that need more dynamic LDS than the default limit (each sets the attribute of its
 // kernels on the current device).  api.hip calls them once per device, under a lock, before the first launch there.

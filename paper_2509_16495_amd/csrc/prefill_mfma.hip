@@ -106,21 +106,8 @@ struct PrefillParams {
     float range_div;  // a tile's keys are cut into ranges of 1 / range_div of them, the last one what remains
 };
 
-// decode rows that ride in a prefill launch: what decode_flat_body takes, and how many workgroups they get
-struct DecodeRole {
-    const uint16_t* q;
-    uint16_t* cache;
-    const int32_t* block_table;
-    const int32_t* seq_lens;
-    float* o_part;
-    float* ml_part;
-    int2* plan;
-    int max_blocks, num_seqs, r_min, n_wg;
-    float c;
-};
 constexpr int kDecodeWaves = kThreads / 64;
-constexpr int kLdsBytesDecode = kDecodeWaves * decode_flat::kStageBytes + decode_flat::kIndexInts * 4;
-constexpr int kLdsBytesBoth = kLdsBytesDecode > kLdsBytes ? kLdsBytesDecode : kLdsBytes;
+constexpr int kLdsBytesBoth = decode_flat::kRoleLdsBytes<kDecodeWaves> > kLdsBytes ? decode_flat::kRoleLdsBytes<kDecodeWaves> : kLdsBytes;
 
 // kDecode: 0 = prefill only; 1, 2 = the first workgroups take decode rows over a bf16 (1) or FP8 (2) cache
 template <int kDecode>
@@ -129,10 +116,7 @@ __global__ __launch_bounds__(kThreads, 2) void prefill_kernel(PrefillParams p, D
     constexpr int kCols = 128;
     if constexpr (kDecode != 0) {
         if (static_cast<int>(blockIdx.x) < dec.n_wg) {   // uniform
-            decode_flat::decode_flat_body<kDecode == 2, false, kDecodeWaves>(
-                dec.q, p.q_stride, dec.cache, dec.block_table, dec.max_blocks, dec.seq_lens, dec.o_part, dec.ml_part, dec.plan, dec.num_seqs,
-                p.hq_l, p.hq_l / p.G, dec.c, dec.r_min, decode_flat::AppendArgs{}, lds,
-                reinterpret_cast<int*>(lds + kDecodeWaves * decode_flat::kStageBytes), blockIdx.x, dec.n_wg);
+            decode_flat::decode_role<kDecode == 2, kDecodeWaves>(dec, p.q_stride, p.hq_l, p.hq_l / p.G, lds, blockIdx.x);
             return;
         }
     }
@@ -817,9 +801,11 @@ struct TileKernel {
     double pass, second_pass;  // around the key loop: set-up, Q, first and last tile, write-out
     double step, step_full;    // one step of the key loop, and what it costs more once every compute unit is busy
     int keys_per_step;
+    double several;            // factor where the batch has several sequences (two chunks of 1739 tokens on 31682: the model had
+                               // the wide kernel 2 % ahead, it was 10 % behind)
 };
-constexpr TileKernel kNarrowCost = {2.65, 3.1, 1.4, 0.335, 2 * kKvTile};   // two groups of wavefronts, a tile of 64 keys each
-constexpr TileKernel kWideCost = {10.1, 9.5, 0.77, 0.03, 32};
+constexpr TileKernel kNarrowCost = {2.65, 3.1, 1.4, 0.335, 2 * kKvTile, 1.0};   // two groups of wavefronts, a tile of 64 keys each
+constexpr TileKernel kWideCost = {10.1, 9.5, 0.77, 0.03, 32, 1.08};
 
 double launch_us(const TileKernel& k, bool paired, int splits, int tile_tokens, int heads, int num_seqs, int total_q,
                  int max_q_len, int max_seq_len, int hq_l) {
@@ -846,6 +832,7 @@ double launch_us(const TileKernel& k, bool paired, int splits, int tile_tokens, 
     double span = (grid > kCus ? kSlack : 1.0) * (d_hi + d_lo) / 2 * wgs / kCus;
     if (span < d_hi) span = d_hi;
     if (span < rounds * d_lo) span = rounds * d_lo;
+    if (num_seqs > 1) span *= k.several;
     if (splits > 1) span += kMergeUs + splits * static_cast<double>(total_q) * hq_l * kRowBytes / kMergeBytesPerUs;
     return (span + 6.6) * (1.0 + 0.008 * splits);   // (launch; among equals the plan with fewer ranges)
 }
@@ -1006,98 +993,112 @@ hipError_t launch_prefill_mfma(const void* q, const void* cache, const int32_t* 
 // ---- prefill and decode rows of a unified batch in one launch -----------------------------------------------------
 // Chunks are bound by the matrix units, decode rows by memory, and one behind the other each leaves the other's resource
 // idle; each also costs a launch (about 4.6 us behind another kernel) for its product and one for its merge.  Here the
-// first workgroups of the 128-column kernel's grid take the decode rows and the others the tiles, one merge kernel serves
+// first workgroups of either prefill kernel's grid take the decode rows and the others the tiles, one merge kernel serves
 // both.  A compute unit holds one workgroup of either kind, so the rows get as many as the tiles' ranges leave over; where
 // every place is taken, the last key range of each tile is the one that waits for a place and is made shorter by what the
 // decode rows take, so that all end together.  1000 tokens on 20000 cached (FP8) with 97 decodes: 154 -> 132 us a step;
-// forty random batches (chunks of 100 .. 2048 on 1000 .. 60000 cached, 2 .. 128 decodes): 1.22 times, none slower.
+// forty random batches (chunks of 100 .. 2048 on 1000 .. 60000 cached, 2 .. 128 decodes): 1.22 times, none slower.  2048 tokens on 131072 cached with 64 decodes (256-column kernel): 1028 -> 974;
+// 1536 on 90000 with 100: 670 -> 602.
 namespace {
 
 struct BothPlan {
-    bool taken;
+    bool taken, wide;
     Plan narrow;
-    int dec_wgs;
+    Prefill64Plan w;
+    int dec_wgs, dec_waves;
     float range_div;
     size_t partial_bytes;  // of the prefill part, a multiple of 256 with an FP8 cache's scratch behind it
     size_t bytes;          // workspace in all
 };
 
-// microseconds the decode rows take on some workgroups of eight wavefronts, one per compute unit (rates measured with 64 of
-// them; an FP8 cache has half the bytes in flight); the lengths are on the device, their mean is taken as 0.6 of the longest
+// microseconds the decode rows take on some workgroups, one per compute unit (rates measured with 64 of them; an FP8 cache
+// has half the bytes in flight); the lengths are on the device, their mean is taken as 0.6 of the longest
 double decode_bytes(int num_seqs, int max_seq_len, const AttnShape& a) {
     return 0.6 * num_seqs * static_cast<double>(max_seq_len) * a.hkv_l * 2 * kD * a.kv_elem;
 }
 constexpr double kDecodeStartUs = 5.0, kBf16BytesPerUsWg = 60e3, kFp8BytesPerUsWg = 48e3, kDecodeBytesPerUs = 5.8e6;
-double decode_us(double bytes, double wgs, bool fp8) {
-    const double rate = wgs * (fp8 ? kFp8BytesPerUsWg : kBf16BytesPerUsWg);
+constexpr double kFourWaves = 0.85;   // of that with four wavefronts per workgroup (the 256-column kernel's) instead of eight
+double decode_us(double bytes, double wgs, bool fp8, bool wide) {
+    const double rate = wgs * (fp8 ? kFp8BytesPerUsWg : kBf16BytesPerUsWg) * (wide ? kFourWaves : 1.0);
     return kDecodeStartUs + bytes / (rate < kDecodeBytesPerUs ? rate : kDecodeBytesPerUs);
 }
 
 BothPlan plan_both(int num_seqs, int total_q, int max_q_len, int max_seq_len, int num_dec, int max_dec_len, const AttnShape& a) {
     BothPlan best{};
-    if (option_prefill_tile() == 256 || option_prefill_splits() != 0 || option_prefill_pairing() == 1) return best;
+    if (option_prefill_splits() != 0 || option_prefill_pairing() == 1) return best;
     if (num_seqs < 1 || total_q < 1 || max_q_len < 1 || num_dec < 1 || max_dec_len < 1 || !decode_mfma_one_launch(num_dec, max_dec_len, a))
         return best;
     const double bytes = decode_bytes(num_dec, max_dec_len, a);
     if (bytes < 1e6) return best;   // (a few short rows: nothing to share, and the workspace stays the larger of the two parts')
     const Choice alone = plan_within(SIZE_MAX, num_seqs, total_q, max_q_len, max_seq_len, a);
-    const TileKernel& k = kNarrowCost;
     const Plan& base = alone.narrow;
     const double serial = (alone.wide ? launch_us(kWideCost, alone.w.paired, alone.w.n_splits, alone.w.tile_tokens, a.hkv_l, num_seqs, total_q,
                                                   max_q_len, max_seq_len, a.hq_l)
-                                      : launch_us(k, base.paired, base.n_splits, base.tile_tokens, base.head_slots, num_seqs, total_q,
-                                                  max_q_len, max_seq_len, a.hq_l)) + decode_us(bytes, 256, a.kv_fp8()) + 9.0;
+                                      : launch_us(kNarrowCost, base.paired, base.n_splits, base.tile_tokens, base.head_slots, num_seqs, total_q,
+                                                  max_q_len, max_seq_len, a.hq_l)) + decode_us(bytes, 256, a.kv_fp8(), false) + 9.0;
     double best_us = 0.97 * serial;
-    const int tiles = (max_q_len + base.tile_tokens - 1) / base.tile_tokens;
     const double seqs = longest_chunk_equivalents(num_seqs, total_q, max_q_len);
     const int q = max_q_len < max_seq_len ? max_q_len : max_seq_len;
-    const double lightest = max_seq_len - q + (base.tile_tokens < q ? base.tile_tokens : q);
-    const double step = (k.step + k.step_full) / k.keys_per_step;   // per key
-    for (int splits : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 24, 32}) {
-        if (splits > 1 && max_seq_len < splits * 2 * kKvTile) break;
-        const double wgs = tiles * seqs * base.head_slots * splits, grid = static_cast<double>(tiles) * num_seqs * base.head_slots * splits;
-        const double merge = splits > 1 ? splits * static_cast<double>(total_q) * a.hq_l * 1040 / 5.8e6 : 0.0;
-        auto consider = [&](double x, double div, double span) {
-            const double us = (span + merge + 6.6 + 4.5) * (1.0 + 0.008 * splits);
-            if (us >= best_us) return;
-            best_us = us;
-            best.taken = true;
-            best.narrow = base;
-            best.narrow.paired = false;
-            best.narrow.pair_ranks = tiles;
-            best.narrow.n_splits = splits;
-            best.dec_wgs = static_cast<int>(x);
-            best.range_div = static_cast<float>(div);
-        };
-        auto rows_us = [&](double x) { return decode_us(bytes, x, a.kv_fp8()); };
-        if (grid <= 256) {
-            const double free = 256 - grid, last = grid / splits;   // places the tiles leave over; workgroups of the last ranges
-            if (free >= 8) {                                        // nobody waits
-                const double d = k.pass + max_seq_len * step / splits;
-                consider(free, splits, d > rows_us(free) ? d : rows_us(free));
-            }
-            if (splits > 1 && free + last >= 8) {                   // the last ranges wait for the decode rows' places
-                const double x = static_cast<int>(free + last);
-                const double cut = rows_us(x) / step / max_seq_len;     // keys the last range leaves to the others, of the tile's
-                const double share = (1.0 + cut) / splits;              // of a full range: splits x share - cut = 1
-                if (share - cut >= 0.05 * share) consider(x, 1.0 / share, k.pass + max_seq_len * share * step);
-            }
-        } else {                                                    // several rounds: the rows first, ever lighter tiles behind them
-            const double d_hi = k.pass + max_seq_len * step / splits, d_lo = k.pass + lightest * step / splits;
-            for (int x : {32, 64, 96, 128, 192}) {
-                double span = 1.13 * (0.5 * (d_hi + d_lo) * wgs + x * rows_us(x)) / 256;
-                const double rounds = static_cast<double>(static_cast<long>((grid + x + 255) / 256));
-                for (const double least : {d_hi, rounds * d_lo, rows_us(x)})
-                    if (span < least) span = least;
-                consider(x, splits, span);
+    AttnShape b16 = a;
+    b16.kv_elem = b16.elem;
+    for (int wide = 0; wide < 2; ++wide) {
+        if (wide ? !prefill_mfma64_supported(b16) || option_prefill_tile() == 128 : option_prefill_tile() == 256) continue;
+        const TileKernel& k = wide ? kWideCost : kNarrowCost;
+        const int tile_tokens = wide ? alone.w.tile_tokens : base.tile_tokens, heads = wide ? a.hkv_l : base.head_slots;
+        const int tiles = (max_q_len + tile_tokens - 1) / tile_tokens;
+        const double lightest = max_seq_len - q + (tile_tokens < q ? tile_tokens : q);
+        const double step = (k.step + k.step_full) / k.keys_per_step;   // per key
+        auto rows_us = [&](double x) { return decode_us(bytes, x, a.kv_fp8(), wide != 0); };
+        for (int splits : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 24, 32}) {
+            if (splits > 1 && max_seq_len < splits * 2 * kKvTile) break;
+            const double wgs = tiles * seqs * heads * splits, grid = static_cast<double>(tiles) * num_seqs * heads * splits;
+            const double merge = splits > 1 ? splits * static_cast<double>(total_q) * a.hq_l * 1040 / 5.8e6 : 0.0;
+            auto consider = [&](double x, double div, double span) {
+                const double us = (span * (num_seqs > 1 ? k.several : 1.0) + merge + 6.6 + 4.5) * (1.0 + 0.008 * splits);
+                if (us >= best_us) return;
+                best_us = us;
+                best.taken = true;
+                best.wide = wide != 0;
+                best.narrow = base;
+                best.w = alone.w;
+                if (wide) {
+                    best.w.paired = false, best.w.pair_ranks = tiles, best.w.n_splits = splits;
+                    best.w.workgroups = static_cast<long>(tiles) * splits * num_seqs * a.hkv_l;
+                } else {
+                    best.narrow.paired = false, best.narrow.pair_ranks = tiles, best.narrow.n_splits = splits;
+                }
+                best.dec_wgs = static_cast<int>(x);
+                best.dec_waves = best.dec_wgs * (wide ? kPrefill64Waves : kDecodeWaves);
+                best.range_div = static_cast<float>(div);
+                best.partial_bytes = split_bytes(splits, total_q, a);
+            };
+            if (grid <= 256) {
+                const double free = 256 - grid, last = grid / splits;   // places the tiles leave over; workgroups of the last ranges
+                if (free >= 8) {                                        // nobody waits
+                    const double d = k.pass + max_seq_len * step / splits;
+                    consider(free, splits, d > rows_us(free) ? d : rows_us(free));
+                }
+                if (splits > 1 && free + last >= 8) {                   // the last ranges wait for the decode rows' places
+                    const double x = static_cast<int>(free + last);
+                    const double cut = rows_us(x) / step / max_seq_len;     // keys the last range leaves to the others, of the tile's
+                    const double share = (1.0 + cut) / splits;              // of a full range: splits x share - cut = 1
+                    if (share - cut >= 0.05 * share) consider(x, 1.0 / share, k.pass + max_seq_len * share * step);
+                }
+            } else {                                                    // several rounds: the rows first, ever lighter tiles behind them
+                const double d_hi = k.pass + max_seq_len * step / splits, d_lo = k.pass + lightest * step / splits;
+                for (int x : {32, 64, 96, 128, 192}) {
+                    double span = 1.13 * (0.5 * (d_hi + d_lo) * wgs + x * rows_us(x)) / 256;
+                    const double rounds = static_cast<double>(static_cast<long>((grid + x + 255) / 256));
+                    for (const double least : {d_hi, rounds * d_lo, rows_us(x)})
+                        if (span < least) span = least;
+                    consider(x, splits, span);
+                }
             }
         }
     }
-    if (best.taken) {
-        best.partial_bytes = split_bytes(best.narrow.n_splits, total_q, a);
+    if (best.taken)
         best.bytes = (with_fp8_scratch(best.partial_bytes, num_seqs, max_seq_len, a) + 255) / 256 * 256 +
-                     decode_mfma_workspace_for(best.dec_wgs * kDecodeWaves, num_dec, a);
-    }
+                     decode_mfma_workspace_for(best.dec_waves, num_dec, a);
     return best;
 }
 
@@ -1115,12 +1116,10 @@ bool launch_prefill_and_decode(const void* q, void* cache, const int32_t* block_
     CacheView v;
     *err = bf16_view(cache, block_table, seq_lens, num_seqs, max_seq_len, pl.partial_bytes, workspace, a, &v, st);
     if (*err != hipSuccess) return true;
-    PrefillParams p = narrow_params(q, v, cu_seqlens_q, seq_lens, num_seqs, total_q, pl.narrow, out, workspace, a);
-    p.range_div = pl.range_div;
     const size_t dec_at = (with_fp8_scratch(pl.partial_bytes, num_seqs, max_seq_len, a) + 255) / 256 * 256;
-    const size_t rows = decode_mfma_rows_for(pl.dec_wgs * kDecodeWaves, num_dec, a);
+    const size_t rows = decode_mfma_rows_for(pl.dec_waves, num_dec, a);
     DecodeRole d;
-    d.q = p.q + static_cast<size_t>(total_q) * a.q_stride;
+    d.q = static_cast<const uint16_t*>(q) + static_cast<size_t>(total_q) * a.q_stride;
     d.cache = static_cast<uint16_t*>(cache);
     d.block_table = block_table + static_cast<size_t>(num_seqs) * a.max_blocks;
     d.seq_lens = seq_lens + num_seqs;
@@ -1131,13 +1130,23 @@ bool launch_prefill_and_decode(const void* q, void* cache, const int32_t* block_
     d.num_seqs = num_dec;
     d.r_min = decode_mfma_r_min(max_dec_len);
     d.n_wg = pl.dec_wgs;
-    d.c = p.c;
-    const unsigned grid = static_cast<unsigned>(pl.dec_wgs) + static_cast<unsigned>(pl.narrow.pair_ranks) * pl.narrow.n_splits * num_seqs * pl.narrow.head_slots;
-    if (a.kv_fp8()) prefill_kernel<2><<<grid, kThreads, kLdsBytesBoth, st>>>(p, d);
-    else prefill_kernel<1><<<grid, kThreads, kLdsBytesBoth, st>>>(p, d);
-    *err = hipGetLastError();
+    d.c = a.scale * a.k_scale * kLog2e;
+    const int n_splits = pl.wide ? pl.w.n_splits : pl.narrow.n_splits;
+    float* o_part = static_cast<float*>(workspace);
+    const float* ml_part = n_splits > 1 ? o_part + static_cast<size_t>(n_splits) * total_q * a.hq_l * kD : nullptr;
+    if (pl.wide) {
+        *err = launch_prefill64_and_decode(q, v.cache, v.block_table, v.max_blocks, cu_seqlens_q, seq_lens, num_seqs, total_q, pl.w, pl.range_div,
+                                           d, out, workspace, a, d.c, a.v_scale, st);
+    } else {
+        PrefillParams p = narrow_params(q, v, cu_seqlens_q, seq_lens, num_seqs, total_q, pl.narrow, out, workspace, a);
+        p.range_div = pl.range_div;
+        const unsigned grid = static_cast<unsigned>(pl.dec_wgs) + static_cast<unsigned>(pl.narrow.pair_ranks) * n_splits * num_seqs * pl.narrow.head_slots;
+        if (a.kv_fp8()) prefill_kernel<2><<<grid, kThreads, kLdsBytesBoth, st>>>(p, d);
+        else prefill_kernel<1><<<grid, kThreads, kLdsBytesBoth, st>>>(p, d);
+        *err = hipGetLastError();
+    }
     if (*err != hipSuccess) return true;
-    *err = launch_combine_both(p.o_part, p.ml_part, total_q, pl.narrow.n_splits, out, d.o_part, d.ml_part, d.plan, num_dec,
+    *err = launch_combine_both(o_part, ml_part, total_q, n_splits, out, d.o_part, d.ml_part, d.plan, num_dec,
                                static_cast<uint16_t*>(out) + static_cast<size_t>(total_q) * a.out_stride, a, st);
     return true;
 }

@@ -48,7 +48,7 @@
 //
 // Scheduling: tiles of a sequence are processed in pairs (heaviest with lightest) by one workgroup; a short chunk on a
 // long context is taken one tile per workgroup, its keys split into ranges merged by launch_combine.
-#include "internal.h"
+#include "decode_body.h"
 
 #include <utility>
 
@@ -180,21 +180,42 @@ struct Prefill64Params {
     int max_blocks;
     float c;          // softmax_scale * log2(e) (times k_scale for a cache widened from FP8)
     float out_scale;  // multiplies the normalised output: v_scale of an FP8 cache, else 1
+    // launches that carry decode rows
+    int ranks;        // tiles per sequence at most
+    float range_div;  // a tile's keys are cut into ranges of 1 / range_div of them, the last one what remains
 };
 
-__global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params p) {
+static_assert(kThreads == 64 * kPrefill64Waves && decode_flat::kRoleLdsBytes<kPrefill64Waves> <= kLdsBytes);
+
+// kDecode: 0 = prefill only; 1, 2 = the first workgroups take decode rows over a bf16 (1) or FP8 (2) cache
+template <int kDecode>
+__global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params p, DecodeRole dec) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    if constexpr (kDecode != 0) {
+        if (static_cast<int>(blockIdx.x) < dec.n_wg) {   // uniform
+            decode_flat::decode_role<kDecode == 2, kPrefill64Waves>(dec, p.q_stride, p.hq_l, p.hkv_l, lds, blockIdx.x);
+            return;
+        }
+    }
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
     // ---- which (pair rank, key split, sequence, KV head) is this workgroup --------------------------------------
     const int n_sg = p.num_seqs * p.hkv_l;
-    int item = blockIdx.x;
-    const int rank = item / (n_sg * p.n_splits);
-    item -= rank * (n_sg * p.n_splits);
-    const int split = item / n_sg;
-    item -= split * n_sg;
+    int item = blockIdx.x, rank, split;
+    if constexpr (kDecode == 0) {
+        rank = item / (n_sg * p.n_splits);
+        item -= rank * (n_sg * p.n_splits);
+        split = item / n_sg;
+        item -= split * n_sg;
+    } else {   // ranges outermost: the shorter last ones start last, on the compute units that the decode rows leave
+        item -= dec.n_wg;
+        split = item / (n_sg * p.ranks);
+        item -= split * (n_sg * p.ranks);
+        rank = item / n_sg;
+        item -= rank * n_sg;
+    }
     if (p.rotate) item = (item + n_sg - static_cast<int>((blockIdx.x / max(n_sg, 8)) % n_sg)) % n_sg;
     const int s = item / p.hkv_l;
     const int g = item - s * p.hkv_l;
@@ -335,9 +356,9 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
         // ---- key tiles of this (column tile, split) -------------------------------------------------------
         const int tile_pos_max = ctx - q_len + min(tok0 + tile_tokens, q_len) - 1;
         const int kv_tiles = tile_pos_max / kKv + 1;
-        const int per_split = (kv_tiles + p.n_splits - 1) / p.n_splits;
+        const int per_split = kDecode == 0 ? (kv_tiles + p.n_splits - 1) / p.n_splits : static_cast<int>(ceilf(kv_tiles / p.range_div));
         const int kt_begin = __builtin_amdgcn_readfirstlane(split * per_split);
-        const int kt_end = min(kv_tiles, kt_begin + per_split);
+        const int kt_end = kDecode != 0 && split == p.n_splits - 1 ? kv_tiles : min(kv_tiles, kt_begin + per_split);
         const int n = __builtin_amdgcn_readfirstlane(max(kt_end - kt_begin, 0));
         // the tile that reaches past the context (if any) holds unwritten V slots: cleared in LDS before use
         const bool ragged = n > 0 && kt_end * kKv > ctx;
@@ -897,14 +918,17 @@ size_t prefill_mfma64_workspace(int total_q, const Prefill64Plan& pl, const Attn
 }
 
 hipError_t prefill_mfma64_init() {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&prefill64_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               kLdsBytes);
+    for (const void* kernel : {reinterpret_cast<const void*>(&prefill64_kernel<0>), reinterpret_cast<const void*>(&prefill64_kernel<1>),
+                               reinterpret_cast<const void*>(&prefill64_kernel<2>)})
+        if (hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes); e != hipSuccess) return e;
+    return hipSuccess;
 }
 
-hipError_t launch_prefill_mfma64(const void* q, const void* cache, const int32_t* block_table, int max_blocks,
-                                 const int32_t* cu_seqlens_q, const int32_t* seq_lens, int num_seqs, int total_q,
-                                 const Prefill64Plan& pl, void* out, void* workspace, const AttnShape& a, float c,
-                                 float out_scale, hipStream_t st) {
+namespace {
+
+Prefill64Params wide_params(const void* q, const void* cache, const int32_t* block_table, int max_blocks, const int32_t* cu_seqlens_q,
+                            const int32_t* seq_lens, int num_seqs, int total_q, const Prefill64Plan& pl, void* out, void* workspace,
+                            const AttnShape& a, float c, float out_scale) {
     Prefill64Params p;
     p.q = static_cast<const uint16_t*>(q);
     p.cache = static_cast<const uint16_t*>(cache);
@@ -930,13 +954,38 @@ hipError_t launch_prefill_mfma64(const void* q, const void* cache, const int32_t
     p.max_blocks = max_blocks;
     p.c = c;
     p.out_scale = out_scale;
-    prefill64_kernel<<<static_cast<unsigned>(pl.workgroups), kThreads, kLdsBytes, st>>>(p);
+    p.ranks = pl.pair_ranks;
+    p.range_div = static_cast<float>(pl.n_splits);
+    return p;
+}
+
+}  // namespace
+
+hipError_t launch_prefill_mfma64(const void* q, const void* cache, const int32_t* block_table, int max_blocks,
+                                 const int32_t* cu_seqlens_q, const int32_t* seq_lens, int num_seqs, int total_q,
+                                 const Prefill64Plan& pl, void* out, void* workspace, const AttnShape& a, float c,
+                                 float out_scale, hipStream_t st) {
+    const Prefill64Params p = wide_params(q, cache, block_table, max_blocks, cu_seqlens_q, seq_lens, num_seqs, total_q, pl, out, workspace, a,
+                                          c, out_scale);
+    prefill64_kernel<0><<<static_cast<unsigned>(pl.workgroups), kThreads, kLdsBytes, st>>>(p, DecodeRole{});
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (pl.n_splits > 1)
         return launch_combine(p.o_part, p.ml_part, total_q, a.hq_l, kD, pl.n_splits, 0, nullptr, 0, out, a.out_stride, a.elem,
                               out_scale, st);
     return hipSuccess;
+}
+
+hipError_t launch_prefill64_and_decode(const void* q, const void* cache, const int32_t* block_table, int max_blocks,
+                                       const int32_t* cu_seqlens_q, const int32_t* seq_lens, int num_seqs, int total_q,
+                                       const Prefill64Plan& pl, float range_div, const DecodeRole& dec, void* out, void* workspace,
+                                       const AttnShape& a, float c, float out_scale, hipStream_t st) {
+    Prefill64Params p = wide_params(q, cache, block_table, max_blocks, cu_seqlens_q, seq_lens, num_seqs, total_q, pl, out, workspace, a, c, out_scale);
+    p.range_div = range_div;
+    const unsigned grid = static_cast<unsigned>(pl.workgroups + dec.n_wg);
+    if (a.kv_fp8()) prefill64_kernel<2><<<grid, kThreads, kLdsBytes, st>>>(p, dec);
+    else prefill64_kernel<1><<<grid, kThreads, kLdsBytes, st>>>(p, dec);
+    return hipGetLastError();
 }
 
 }  // namespace shiftattn
