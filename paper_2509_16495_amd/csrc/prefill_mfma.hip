@@ -997,9 +997,9 @@ hipError_t launch_prefill_mfma(const void* q, const void* cache, const int32_t* 
 // both.  A compute unit holds one workgroup of either kind, so the rows get as many as the tiles' ranges leave over; where
 // every place is taken, the last key range of each tile is the one that waits for a place and is made shorter by what the
 // decode rows take, so that all end together.  1000 tokens on 20000 cached (FP8) with 97 decodes: 154 -> 132 us a step;
-// forty random batches (chunks of 100 .. 2048 on 1000 .. 60000 cached, 2 .. 128 decodes): 1.22 times, none slower.  2048
-// tokens on 131072 cached with 64 decodes (256-column kernel): 1028 -> 974;
-// 1536 on 90000 with 100: 670 -> 602.
+// forty random batches (chunks of 100 .. 2048 on 1000 .. 60000 cached, 2 .. 128 decodes): 1.22 times, none slower; where all
+// rows are as long as the longest 1.18, where one is and the others have a 25th 1.12.  2048 tokens on 131072 cached with 64
+// decodes (256-column kernel): 1028 -> 974; 1536 on 90000 with 100: 670 -> 602.
 namespace {
 
 struct BothPlan {
