@@ -167,7 +167,11 @@ __device__ __attribute__((always_inline)) inline void decode_flat_body(
             plan[i] = e;
         }
     }
-    const int wk = wg * kWaves + wave;
+    // Short ranges are dealt to the workgroups in turn: a batch with fewer ranges than wavefronts has one wavefront on each of
+    // many compute units then, instead of four on a quarter of them (call in a graph, before and after: 4 sequences of about
+    // 4000 tokens 11.9 -> 11.0 us, 14 of 400 12.1 -> 10.5, 10 of 8000 18.5 -> 16.7).  Longer ones stay side by side in a
+    // workgroup: with every wavefront at work for four groups and more that is up to 2 % faster (64 of 9000: 57.2 against 58.5).
+    const int wk = R <= 3 * kGroup ? wave * n_wg + wg : wg * kWaves + wave;
     const int64_t start64 = static_cast<int64_t>(wk) * R;
     if (start64 >= total) return;  // no barrier below this line
     const int start = static_cast<int>(start64);
