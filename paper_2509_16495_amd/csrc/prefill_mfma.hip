@@ -46,6 +46,7 @@
 // prefill are additionally split into key ranges whose partial results are merged by launch_combine.
 // plan_within() below prices the plans of both prefill kernels.
 #include "decode_body.h"
+#include "tile_order.h"
 
 #include <utility>
 
@@ -128,22 +129,10 @@ __global__ __launch_bounds__(kThreads, 2) void prefill_kernel(PrefillParams p, D
 
     // ---- which (pair rank, key split, sequence, head slot) is this workgroup -----------------------
     const int n_sh = p.num_seqs * p.head_slots;
-    int item = blockIdx.x, rank, split;
-    if constexpr (kDecode == 0) {
-        rank = item / (n_sh * p.n_splits);
-        item -= rank * (n_sh * p.n_splits);
-        split = item / n_sh;
-        item -= split * n_sh;
-    } else {   // ranges outermost: the shorter last ones start last, on the compute units that the decode rows leave
-        item -= dec.n_wg;
-        split = item / (n_sh * p.ranks);
-        item -= split * (n_sh * p.ranks);
-        rank = item / n_sh;
-        item -= rank * n_sh;
-    }
-    if (p.rotate) item = (item + n_sh - static_cast<int>((blockIdx.x / max(n_sh, 8)) % n_sh)) % n_sh;
-    const int s = item / p.head_slots;
-    const int hs = item - s * p.head_slots;
+    const TileItem ti = tile_item(blockIdx.x, kDecode == 0 ? 0 : dec.n_wg, n_sh, p.ranks, p.n_splits, kDecode != 0, p.rotate != 0);
+    const int rank = ti.rank, split = ti.split;
+    const int s = ti.sh / p.head_slots;
+    const int hs = ti.sh - s * p.head_slots;
 
     const int q_begin = p.cu_seqlens_q[s];
     const int q_len = p.cu_seqlens_q[s + 1] - q_begin;

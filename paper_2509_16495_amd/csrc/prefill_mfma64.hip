@@ -49,6 +49,7 @@
 // Scheduling: tiles of a sequence are processed in pairs (heaviest with lightest) by one workgroup; a short chunk on a
 // long context is taken one tile per workgroup, its keys split into ranges merged by launch_combine.
 #include "decode_body.h"
+#include "tile_order.h"
 
 #include <utility>
 
@@ -203,22 +204,10 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
 
     // ---- which (pair rank, key split, sequence, KV head) is this workgroup --------------------------------------
     const int n_sg = p.num_seqs * p.hkv_l;
-    int item = blockIdx.x, rank, split;
-    if constexpr (kDecode == 0) {
-        rank = item / (n_sg * p.n_splits);
-        item -= rank * (n_sg * p.n_splits);
-        split = item / n_sg;
-        item -= split * n_sg;
-    } else {   // ranges outermost: the shorter last ones start last, on the compute units that the decode rows leave
-        item -= dec.n_wg;
-        split = item / (n_sg * p.ranks);
-        item -= split * (n_sg * p.ranks);
-        rank = item / n_sg;
-        item -= rank * n_sg;
-    }
-    if (p.rotate) item = (item + n_sg - static_cast<int>((blockIdx.x / max(n_sg, 8)) % n_sg)) % n_sg;
-    const int s = item / p.hkv_l;
-    const int g = item - s * p.hkv_l;
+    const TileItem ti = tile_item(blockIdx.x, kDecode == 0 ? 0 : dec.n_wg, n_sg, p.ranks, p.n_splits, kDecode != 0, p.rotate != 0);
+    const int rank = ti.rank, split = ti.split;
+    const int s = ti.sh / p.hkv_l;
+    const int g = ti.sh - s * p.hkv_l;
 
     const int q_begin = p.cu_seqlens_q[s];
     const int q_len = p.cu_seqlens_q[s + 1] - q_begin;

@@ -57,3 +57,60 @@ def test_mixed_launch(oracle, G, kv, chunks, decodes, hq_l, hkv_l):
     torch.cuda.synchronize()
     serial = W.to_f64(B.to_host(out), "bf16")
     assert np.abs(serial - want).max() <= 2e-2 and np.abs(serial - got).max() <= 4e-2
+
+
+# Several chunks of unequal length, so that the (sequence, head) pairs are rotated over the dies, n of them per run of
+# workgroups, in launches whose decode workgroups are no multiple of n; a tile that no workgroup takes shows as NaN.
+UNEQUAL = [
+    # chunks, decode contexts, query heads, KV heads, columns of the prefill kernel
+    ([(150, 750), (131, 131), (67, 67), (50, 50)], [5000, 17, 4900], 5, 1, 128),                                                 # n = 20
+    ([(150, 750), (35, 35), (39, 39), (18, 18), (6, 498), (48, 48)], [3000, 1, 2900, 33], 16, 2, 128),                           # 12
+    ([(150, 750), (19, 19), (53, 53), (138, 138), (53, 53), (79, 82)], [3000, 3000, 64, 640, 31], 16, 2, 256),                   # 12
+    ([(150, 750), (33, 33), (36, 36), (20, 449), (29, 148), (42, 42), (120, 193), (9, 9), (71, 71), (15, 123), (55, 55), (38, 440)],
+     [9000, 777], 8, 1, 128),                                                                                                    # 12
+    ([(150, 750), (142, 142), (105, 105), (28, 28), (20, 20), (42, 42), (73, 76), (18, 361), (95, 95), (85, 85), (118, 118), (90, 90)],
+     [3000, 2999, 31, 700, 3000, 48, 1, 1600], 8, 1, 256),                                                                       # 12
+    ([(150, 750), (12, 159), (26, 262), (48, 408), (31, 233), (9, 258), (11, 11), (11, 342), (20, 355), (89, 89), (44, 44), (60, 60)],
+     [5000, 5000, 2, 640, 4999, 33, 1000], 16, 2, 128),                                                                          # 24
+    ([(150, 750), (50, 50), (79, 79), (113, 145)], [3000, 700, 2100], 10, 2, 128),                                               # 40
+    ([(150, 750), (77, 103), (38, 38), (66, 66)], [3000, 64], 12, 3, 256),                                                       # 12
+    ([(150, 750), (69, 69)], [3000, 16, 2990], 10, 2, 128),                                                                      # 20
+]
+ONE_RANGE = ([(300, 300), (150, 150), (70, 70), (50, 50)], [3500, 2, 3499, 700, 700, 48, 3500], 10, 2, 128)                        # 40
+
+
+@pytest.mark.parametrize("kv", ["bf16", "fp8"])
+@pytest.mark.parametrize("chunks,decodes,hq_l,hkv_l,tile", UNEQUAL + [ONE_RANGE])
+def test_mixed_launch_of_unequal_chunks(oracle, G, kv, chunks, decodes, hq_l, hkv_l, tile):
+    from paper_2509_16495_amd import binding as B
+    scales = SCALES if kv == "fp8" else None
+    case = W.make_attn_case("t", 104, "bf16", chunks + [(1, c) for c in decodes], hq_l, hkv_l, 128, pool_factor=1.2)
+    cache = G.cache_for_case(case, fill_byte=0xFF, fp8_scales=scales)
+    ks, vs = scales or (1.0, 1.0)
+    if scales:
+        want = oracle.attention_case(case, B.to_host(cache), k_scale=ks, v_scale=vs)
+    else:
+        want = oracle.attention_case(case, oracle.cache_for_case(case))
+    q, table, ctx = G.t(case.q, "bf16"), G.ti(case.block_table, np.int32), G.ti(case.ctx_lens, np.int32)
+    n, tot, mq, mp = len(chunks), sum(c[0] for c in chunks), max(c[0] for c in chunks), max(c[1] for c in chunks)
+    cu, out = G.ti(case.cu_seqlens_q[:n + 1], np.int32), torch.empty_like(q)
+    desc = B.attn_desc(q, cache, table, case.softmax_scale, None, out, ks, vs)
+    try:
+        B.set_option(B.OPT_PREFILL_TILE, tile)
+        size = B.mixed_workspace_bytes(n, tot, mq, mp, len(decodes), max(decodes), desc)
+        parts = max(B.prefill_workspace_bytes(n, tot, mq, mp, desc), B.decode_workspace_bytes(len(decodes), max(decodes), desc))
+        # one launch for both parts holds the partial results of both at once: it shows in the size (with one key range the
+        # chunks have none)
+        assert size > parts or (chunks, decodes, hq_l, hkv_l, tile) == ONE_RANGE
+        ws, got = torch.empty(size, dtype=torch.uint8, device=G.DEV), []
+        for _ in range(2):
+            ws.fill_(0xFF)
+            out.view(torch.uint8).fill_(0xFF)
+            B.mixed(q, cache, table, cu, ctx, n, mq, mp, max(decodes), out, case.softmax_scale, workspace=ws, k_scale=ks, v_scale=vs)
+            torch.cuda.synchronize()
+            got.append(B.to_host(out))
+    finally:
+        B.set_option(B.OPT_PREFILL_TILE, 0)
+    assert got[0].tobytes() == got[1].tobytes()
+    err = np.abs(W.to_f64(got[0], "bf16") - want)
+    assert np.all(np.isfinite(err)) and err.max() <= 2e-2 and err.mean() <= 1e-3, (err.max(), err.mean())

@@ -1,0 +1,67 @@
+"""Host-side walk (no GPU) of the index functions the kernels share with it: every work item of a launch is taken exactly
+once, whatever stands in front of it in the grid."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2509_16495_amd import build as BLD
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++ to compile the index functions for the host")
+
+SOURCE = r"""
+#include "tile_order.h"
+#include <vector>
+using namespace shiftattn;
+// work items (tile rank, key range, (sequence, head)) of a grid that are out of range or not taken exactly once
+extern "C" int items_missed(int decode_wgs, int n_sh, int ranks, int n_splits, int range_major, int rotate) {
+    const int items = n_sh * ranks * n_splits;
+    std::vector<int> taken(items, 0);
+    int bad = 0;
+    for (int block = decode_wgs; block < decode_wgs + items; ++block) {
+        const TileItem t = tile_item(block, decode_wgs, n_sh, ranks, n_splits, range_major != 0, rotate != 0);
+        if (t.rank < 0 || t.rank >= ranks || t.split < 0 || t.split >= n_splits || t.sh < 0 || t.sh >= n_sh) ++bad;
+        else ++taken[(t.rank * n_splits + t.split) * n_sh + t.sh];
+    }
+    for (const int n : taken) bad += n != 1;
+    return bad;
+}
+// (sequence, head) of one workgroup
+extern "C" int sh_of(int block, int decode_wgs, int n_sh, int ranks, int n_splits, int range_major, int rotate) {
+    return tile_item(block, decode_wgs, n_sh, ranks, n_splits, range_major != 0, rotate != 0).sh;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def maps(tmp_path_factory):
+    d = tmp_path_factory.mktemp("maps")
+    src, lib = os.path.join(str(d), "maps.cpp"), os.path.join(str(d), "maps.so")
+    with open(src, "w") as f:
+        f.write(SOURCE)
+    subprocess.check_call(["g++", "-std=c++20", "-O1", "-shared", "-fPIC", "-I", BLD.CSRC, src, "-o", lib])
+    return ctypes.CDLL(lib)
+
+
+@pytest.mark.parametrize("n_sh", [1, 2, 3, 4, 5, 6, 7, 8, 12, 16, 20, 24, 28, 40, 44, 48, 100])
+def test_prefill_grids_take_every_work_item_once(maps, n_sh):
+    """With and without decode workgroups in front: counts that divide the runs of n_sh workgroups and counts that do not
+    (the planner hands out what the tiles leave of 256, or 32 to 192)."""
+    for decode_wgs in (0, 8, 32, 64, 96, 128, 192, 196, 201, 255):
+        for ranks in (1, 2, 3, 8, 57):
+            for n_splits in (1, 2, 3, 16):
+                for range_major in (0, 1):
+                    for rotate in (0, 1):
+                        args = (decode_wgs, n_sh, ranks, n_splits, range_major, rotate)
+                        assert maps.items_missed(*args) == 0, args
+
+
+@pytest.mark.parametrize("n_sh", [4, 8, 12, 24])
+def test_rotation_shows_every_die_all_sequences(maps, n_sh):
+    """Workgroup i runs on die i % 8: with a rotation a die meets every (sequence, head) within a few rounds."""
+    for decode_wgs in (0, 96, 196):
+        for die in range(8):
+            blocks = [b for b in range(decode_wgs, decode_wgs + n_sh * 64) if b % 8 == die]
+            assert {maps.sh_of(b, decode_wgs, n_sh, 64, 1, 0, 1) for b in blocks} == set(range(n_sh))
