@@ -29,6 +29,7 @@
 //     has a slot of its own behind an MFMA;
 //   * workgroups on different XCDs start their walk over k at different places (see rot0 below).
 #include "internal.h"
+#include "token_rows.h"
 
 #include <math.h>
 
@@ -169,8 +170,8 @@ __device__ __attribute__((always_inline)) void proj_gemm_tile(const GemmParams& 
     for (int j = 0; j < kLoadsM; ++j) {
         const int row = S_::kRowsM * wave + 8 * j + ld_row;
         const int piece = ld_pos ^ ((row >> 1) & 7);
-        const int m = min(m0 + row, p.M - 1) - m0;   // rows past the end re-read the last one; they are not stored
-        x_off[j] = static_cast<uint32_t>(static_cast<size_t>(m) * seg_bytes + piece * 16);
+        // (rows past the end re-read the last one; they are not stored)
+        x_off[j] = static_cast<uint32_t>(static_cast<size_t>(tile_row(m0, row, p.M)) * seg_bytes + piece * 16);
     }
     // A half-filled last stage: the lanes of pieces 4..7 (past the end of the row) fetch pieces 0..3 once more.  The
     // key of row (32 or 64) wave + 8 j + lane / 8 has bit 2 equal to j % 2, so which lanes those are depends on j % 2 only.
@@ -178,7 +179,7 @@ __device__ __attribute__((always_inline)) void proj_gemm_tile(const GemmParams& 
 #pragma unroll
     for (int jp = 0; jp < 2; ++jp) tail_fix[jp] = (((ld_pos >> 2) ^ jp) & 1) ? 64u : 0u;
     const unsigned char* w_tile = p.w + static_cast<size_t>(n0) * k_bytes;
-    const unsigned char* x_tile = p.x + static_cast<size_t>(m0) * seg_bytes;
+    const unsigned char* x_tile = p.x + static_cast<size_t>(tile_origin(m0, p.M)) * seg_bytes;
     // A token row's k runs contiguously through the hq_l heads that one source rank returned, then jumps to the
     // next rank's buffer (mode 1); in mode 0 it is contiguous throughout.
     const int seg_tiles = max(static_cast<int>(seg_bytes / kRowBytes), 1);

@@ -49,3 +49,24 @@ def test_qkv(oracle, G, case, give_workspace):
 def test_o(oracle, G, case, give_workspace):
     _o_bf16(oracle, G, *case, give_workspace)
     _o_fp8(oracle, G, *case, give_workspace)
+
+
+# Token tiles that hold padding rows only (of 128 rows, of 256, or both): their loads count from a row that exists, their
+# result is zeros.
+PADDING = [
+    # P, h, h_kv, d_model, T, T_pad
+    (8, 64, 8, 512, 128, 129),
+    (8, 32, 4, 2048, 384, 385),    # KV replication
+    (1, 4, 1, 512, 256, 257),
+    (4, 8, 1, 192, 128, 700),      # several tiles behind the last token; half a last stage with FP8
+    (2, 8, 4, 448, 1, 300),
+    (8, 8, 8, 4096, 130, 520),     # k ranges: the tiles leave no partial results
+    (8, 64, 8, 512, 1700, 2300),   # rounds of whole tiles, the rest behind them
+]
+
+
+@pytest.mark.parametrize("give_workspace", [True, False])
+@pytest.mark.parametrize("case", PADDING)
+def test_tiles_of_padding_rows(oracle, G, case, give_workspace):
+    _qkv_bf16(oracle, G, *case, give_workspace)
+    _qkv_fp8(oracle, G, *case, give_workspace)

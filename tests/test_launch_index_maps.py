@@ -13,6 +13,7 @@ pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++ t
 
 SOURCE = r"""
 #include "tile_order.h"
+#include "token_rows.h"
 #include <vector>
 using namespace shiftattn;
 // work items (tile rank, key range, (sequence, head)) of a grid that are out of range or not taken exactly once
@@ -31,6 +32,17 @@ extern "C" int items_missed(int decode_wgs, int n_sh, int ranks, int n_splits, i
 // (sequence, head) of one workgroup
 extern "C" int sh_of(int block, int decode_wgs, int n_sh, int ranks, int n_splits, int range_major, int rotate) {
     return tile_item(block, decode_wgs, n_sh, ranks, n_splits, range_major != 0, rotate != 0).sh;
+}
+// rows of the token tiles of a result of M_out rows, M of which are tokens, whose load would leave the M rows, go backwards
+// from the tile's origin, or fetch another token than the row's own (the last one for padding rows)
+extern "C" int rows_wrong(int M, int M_out, int tile) {
+    int bad = 0;
+    for (int m0 = 0; m0 < M_out; m0 += tile)
+        for (int row = 0; row < tile; ++row) {
+            const int from = tile_origin(m0, M), behind = tile_row(m0, row, M), token = from + behind;
+            bad += behind < 0 || from < 0 || token >= M || token != (m0 + row < M ? m0 + row : M - 1);
+        }
+    return bad;
 }
 """
 
@@ -65,3 +77,11 @@ def test_rotation_shows_every_die_all_sequences(maps, n_sh):
         for die in range(8):
             blocks = [b for b in range(decode_wgs, decode_wgs + n_sh * 64) if b % 8 == die]
             assert {maps.sh_of(b, decode_wgs, n_sh, 64, 1, 0, 1) for b in blocks} == set(range(n_sh))
+
+
+@pytest.mark.parametrize("tile", [128, 256])
+def test_projection_tiles_load_rows_that_exist(maps, tile):
+    """Tiles that end in padding rows and tiles of padding rows only, whose origin lies past the last token."""
+    for M in (1, 2, 127, 128, 129, 255, 256, 257, 384, 512, 701):
+        for M_out in (M, M + 1, M + 7, M + tile - 1, M + tile, M + tile + 1, M + 3 * tile):
+            assert maps.rows_wrong(M, M_out, tile) == 0, (M, M_out)
