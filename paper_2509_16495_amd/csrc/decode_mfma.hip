@@ -21,7 +21,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void decode_flat_kernel(
     float c, int r_min, AppendArgs ap) {
     __shared__ __attribute__((aligned(16))) unsigned char smem[kWaves * kStageBytes];
     __shared__ int index[kIndexInts];
-    decode_flat_body<kFp8, kAppend, kWaves>(q, q_stride, cache, block_table, max_blocks, seq_lens, o_part, ml_part, plan, num_seqs, hq_l,
+    decode_flat_body<kFp8, kAppend, kWaves, false>(q, q_stride, cache, block_table, max_blocks, seq_lens, o_part, ml_part, plan, num_seqs, hq_l,
                                             hkv_l, c, r_min, ap, smem, index, blockIdx.x, kFlatWorkgroups);
 }
 
