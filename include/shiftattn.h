@@ -157,8 +157,9 @@ int shiftattn_unpack_o_proj(const void *recv, const void *w_o, void *out, int32_
                             int32_t d_model, const shiftattn_xchg *xc, void *stream);
 
 /* ---- The same two projections with a workspace (Algorithm 2: the few-token steps below the threshold) ----
- * With up to 64 token rows (T_pad for qkv_proj_pack, T for unpack_o_proj) the product is one pass over the
- * weight matrix; from 17 rows on (at d_model = 8192) that pass is split over k between workgroups.  With a few
+ * With few token rows (T_pad for qkv_proj_pack, T for unpack_o_proj: up to 8, and up to 64 where it is expected to be
+ * the faster way) the product is one pass over the weight matrix; from 17 rows on (at d_model = 8192) that pass is split
+ * over k between workgroups.  With a few
  * hundred rows the large-batch kernel has too few output tiles to fill the chip and splits k as well, and with
  * a few thousand (a prefill chunk) it does so for the last token rows when the tiles are no multiple of the
  * chip's compute units.  Either way the fp32 partial results need device memory:
@@ -240,11 +241,16 @@ int shiftattn_kv_write(const void *k_new, const void *v_new, const int64_t *slot
  *                             q_len_s and seq_lens[s] (they size the launch; exceeding them
  *                             silently drops work)
  * out (device, out)         : [total_q][hq_l][D], row stride a->out_stride
- * workspace (device)        : at least shiftattn_prefill_workspace_bytes(...) bytes, 16-byte
- *                             aligned; may be NULL when that is 0.  Contents are scratch.
+ * workspace (device)        : shiftattn_prefill_workspace_bytes(...) bytes, 16-byte aligned; may be
+ *                             NULL when that is 0.  Contents are scratch.  Less is refused only
+ *                             below what the least plan needs; in between the launch takes the
+ *                             best plan that fits.
  * Arithmetic of the bf16 path: logits and outputs accumulate in fp32, the softmax (scale included)
  * runs in fp32, the probabilities are rounded to bf16 before the second product, the output once
  * at the end.  (SHIFTATTN_OPT_PREFILL_SCALED_Q trades one more rounding of Q for speed.)
+ * Results are bitwise reproducible for a given workspace size, and not bitwise equal between sizes:
+ * kernel and key ranges are chosen by what fits, and each range rounds its probabilities against a
+ * reference of its own.
  * num_seqs == 0 or total_q == 0 is a valid no-op. */
 int shiftattn_prefill(const void *q, const void *k_new, const void *v_new, const int64_t *slot_mapping,
                       void *kv_cache, const int32_t *block_table, const int32_t *cu_seqlens_q,
@@ -292,7 +298,8 @@ int shiftattn_decode_static(const void *q, const void *k_new, const void *v_new,
  * row per decode sequence.  block_table and seq_lens cover all sequences in that order.
  * The K/V of all rows is written once, then both kinds of rows run in one launch where the workspace holds the partial
  * results of both (the size asked for does), else one after the other; the result is that of shiftattn_prefill on the first
- * part followed by shiftattn_decode on the second, up to the order in which partial sums are added.
+ * part followed by shiftattn_decode on the second, up to the order in which partial sums are added and the references against
+ * which probabilities are rounded (bitwise reproducible for a given workspace size, no less exact).
  * max_prefill_seq_len / max_decode_seq_len bound seq_lens of the two parts.  The workspace is shared
  * by the two parts: at least shiftattn_mixed_workspace_bytes(...).  Either part may be empty. */
 int shiftattn_mixed(const void *q, const void *k_new, const void *v_new, const int64_t *slot_mapping,

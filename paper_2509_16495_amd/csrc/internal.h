@@ -47,15 +47,16 @@ hipError_t launch_attn_generic(const void* q, const void* cache, const int32_t* 
                                const AttnShape& a, hipStream_t st);
 
 // Merge of split-context partial results (shared by decode and split prefill).
-// Partials: o[part][row][D] fp32 un-normalised, ml[part][row][2] = (max logit * log2e*scale, sum).
+// Partials: o[part][row][D] fp32 un-normalised, ml[part][row][2] = (reference logit * log2e*scale, sum).
 // mode 0: every row has n_parts parts.  mode 1 (decode): row = (sequence, head), the number of
 // parts of a row is ceil(seq_lens[sequence] / chunk).
-// both merges of launch_prefill_and_decode in one launch (n_parts 1: the prefill part has none)
-hipError_t launch_combine_both(const float* o_part_p, const float* ml_part_p, int n_rows_p, int n_parts, void* out_p, const float* o_part_d,
-                               const float* ml_part_d, const int2* plan, int num_dec, void* out_d, const AttnShape& a, hipStream_t st);
 hipError_t launch_combine(const float* o_part, const float* ml_part, int n_rows, int hq_l, int D,
                           int n_parts, int mode, const int32_t* seq_lens, int chunk, void* out,
                           int64_t out_stride, int elem, float out_scale, hipStream_t st);
+
+// both merges of launch_prefill_and_decode in one launch (n_parts 1: the prefill part has none)
+hipError_t launch_combine_both(const float* o_part_p, const float* ml_part_p, int n_rows_p, int n_parts, void* out_p, const float* o_part_d,
+                               const float* ml_part_d, const int2* plan, int num_dec, void* out_d, const AttnShape& a, hipStream_t st);
 
 // Merge for the flat decode kernel (bf16, D = 128): see combine_flat_kernel.
 hipError_t launch_combine_flat(const float* o_part, const float* ml_part, const int2* plan, int num_seqs, int hq_l, int G,
@@ -135,10 +136,11 @@ inline double longest_chunk_equivalents(int num_seqs, int total_q, int max_q_len
 // same die: good while the sequences are alike (a die's L2 holds the K/V of its sequences only), and a 32-CU bottleneck
 // for a long prompt among short ones (measured: one 4096-token prompt with seven of 700 tokens took twice the time of
 // the long prompt alone).  Batches whose chunks are not near equal, and whose (sequence, head) count is a multiple of
-// four (a sequence then sees one or two dies), therefore rotate the (sequence, head) index by one every workgroups of
-// the (sequence, head) count, but at least eight, so that a die meets all of them; other counts spread by themselves, and
-// rotating them only costs L2 hits.  Near equal is 0.9 of the longest: four prompts of 2572 to 4301 tokens (0.77), ten
-// heads, gained 10 % from the rotation, four chunks of 831 to 1202 (0.87) lost 2 %, others stayed.
+// four (a sequence then sees one or two dies), therefore rotate the (sequence, head) index, by one more for every
+// (tile rank, key range) (tile_item() in tile_order.h), so that a die meets all of them; other counts spread by
+// themselves, and rotating them only costs L2 hits.  Near equal is 0.9 of the longest: without the rotation seven random
+// batches below 0.75 took 5.5 % longer and 27 between 0.75 and 0.9 0.4 % (single ones from 9 % shorter to 26 % longer);
+// fifty unified batches of unequal chunks, decode rows beside them, took 5 % longer without it (up to twice the time).
 inline bool rotate_sequences_over_dies(int num_seqs, int heads, int total_q, int max_q_len) {
     return num_seqs > 1 && (static_cast<long>(num_seqs) * heads) % 4 == 0 &&
            longest_chunk_equivalents(num_seqs, total_q, max_q_len) < 0.9 * num_seqs;
@@ -155,17 +157,17 @@ hipError_t launch_prefill_mfma64(const void* q, const void* cache, const int32_t
                                  const Prefill64Plan& pl, void* out, void* workspace, const AttnShape& a, float c,
                                  float out_scale, hipStream_t st);
 
-// prefill_f32.hip : fp32 tensors and cache, D = 64 or 128, hq_l / hkv_l <= 16
-bool prefill_f32_supported(const AttnShape& a);
-hipError_t launch_prefill_f32(const void* q, const void* cache, const int32_t* block_table, const int32_t* cu_seqlens_q,
-                              const int32_t* seq_lens, int num_seqs, int total_q, void* out, const AttnShape& a, hipStream_t st);
-
 // the same with decode rows in the grid's first workgroups, without the merge; the last of a tile's key ranges is what
 // 1 / range_div of its keys per range in front of it leave
 hipError_t launch_prefill64_and_decode(const void* q, const void* cache, const int32_t* block_table, int max_blocks,
                                        const int32_t* cu_seqlens_q, const int32_t* seq_lens, int num_seqs, int total_q,
                                        const Prefill64Plan& pl, float range_div, const DecodeRole& dec, void* out, void* workspace,
                                        const AttnShape& a, float c, float out_scale, hipStream_t st);
+
+// prefill_f32.hip : fp32 tensors and cache, D = 64 or 128, hq_l / hkv_l <= 16
+bool prefill_f32_supported(const AttnShape& a);
+hipError_t launch_prefill_f32(const void* q, const void* cache, const int32_t* block_table, const int32_t* cu_seqlens_q,
+                              const int32_t* seq_lens, int num_seqs, int total_q, void* out, const AttnShape& a, hipStream_t st);
 
 // Per-device set-up of the kernels that need more dynamic LDS than the default limit (each sets the attribute of its
 // kernels on the current device).  api.hip calls them once per device, under a lock, before the first launch there.

@@ -790,8 +790,9 @@ struct TileKernel {
     double pass, second_pass;  // around the key loop: set-up, Q, first and last tile, write-out
     double step, step_full;    // one step of the key loop, and what it costs more once every compute unit is busy
     int keys_per_step;
-    double several;            // factor where the batch has several sequences (two chunks of 1739 tokens on 31682: the model had
-                               // the wide kernel 2 % ahead, it was 10 % behind)
+    double several;            // factor where the batch has several sequences: among 70 random batches of 2 .. 12 the choice differs
+                               // from that of a factor 1 by more than 1.5 % in time in eight, two of them slower, the eight 2.7 %
+                               // faster together (two chunks of 1739 tokens on 31682 were 10 % faster)
 };
 constexpr TileKernel kNarrowCost = {2.65, 3.1, 1.4, 0.335, 2 * kKvTile, 1.0};   // two groups of wavefronts, a tile of 64 keys each
 constexpr TileKernel kWideCost = {10.1, 9.5, 0.77, 0.03, 32, 1.08};
@@ -986,8 +987,8 @@ hipError_t launch_prefill_mfma(const void* q, const void* cache, const int32_t* 
 // both.  A compute unit holds one workgroup of either kind, so the rows get as many as the tiles' ranges leave over; where
 // every place is taken, the last key range of each tile is the one that waits for a place and is made shorter by what the
 // decode rows take, so that all end together.  1000 tokens on 20000 cached (FP8) with 97 decodes: 154 -> 132 us a step;
-// forty random batches (chunks of 100 .. 2048 on 1000 .. 60000 cached, 2 .. 128 decodes): 1.22 times, none slower; where all
-// rows are as long as the longest 1.18, where one is and the others have a 25th 1.12.  2048 tokens on 131072 cached with 64
+// forty random batches (equal chunks of 100 .. 2048 on 1000 .. 60000 cached, 2 .. 128 decodes): 1.22 times, none slower; fifty
+// of two to eight unequal chunks (150 .. 1900 on up to 20000): 1.13 times, six of them 1 to 2.6 % slower; where all rows are as long as the longest 1.18, where one is and the others have a 25th 1.12.  2048 tokens on 131072 cached with 64
 // decodes (256-column kernel): 1028 -> 974; 1536 on 90000 with 100: 670 -> 602.
 namespace {
 

@@ -469,8 +469,8 @@ bool proj_stream_takes(int M_out, int N, int K, bool fp8, size_t workspace_bytes
 }
 
 // What the size query names: for up to 64 rows the streaming kernel's partial results where its k slices divide the k of
-// eight wavefronts in halves, else the large-batch kernel's.  (Callers allocate by it; which kernel runs is decided per
-// call by what fits.)
+// eight wavefronts in halves, else the large-batch kernel's.  (Callers allocate by it and tests pin it, see
+// proj_gemm_workspace(); which kernel runs is decided per call by what fits.)
 size_t proj_workspace(int M_out, int N, int K, bool fp8) {
     const int per_step = kSWaves * kStepRowBytes / (fp8 ? 1 : 2);
     if (M_out <= 64 && N % 4 == 0 && K % per_step == 0) {

@@ -118,8 +118,8 @@ def test_mixed_launch_of_unequal_chunks(oracle, G, kv, chunks, decodes, hq_l, hk
 
 @pytest.mark.parametrize("kv", ["bf16", "fp8"])
 def test_decode_rows_of_the_shared_launch_are_no_further_off_than_alone(oracle, G, kv):
-    """The shared launch gives these decode rows half the wavefronts that a launch of their own has, so a wavefront walks twice
-    the keys.  With P rounded to bf16 against one running maximum over all of them the rows were 2.6 % (bf16) and 3.5 % (FP8)
+    """The shared launch gives these decode rows a quarter of the wavefronts that a launch of their own has, so a wavefront walks
+    three times the keys.  With P rounded to bf16 against one running maximum over all of them the rows were 2.6 % (bf16) and 3.5 % (FP8)
     further from the oracle than decode()'s (root mean square); with P taken group by group they are 2 % nearer."""
     from paper_2509_16495_amd import binding as B
     chunks, decodes, scales = [(512, 8000)], [1000 + 77 * i for i in range(39)] + [4000], SCALES if kv == "fp8" else None
