@@ -296,8 +296,8 @@ int shiftattn_decode_static(const void *q, const void *k_new, const void *v_new,
  * [num_prefill_seqs + 1]); the num_decode_seqs sequences after them carry one new token each.
  * Row order of q, out, k_new, v_new, slot_mapping: the total_prefill_q rows of the chunks, then one
  * row per decode sequence.  block_table and seq_lens cover all sequences in that order.
- * The K/V of all rows is written once, then both kinds of rows run in one launch where the workspace holds the partial
- * results of both (the size asked for does), else one after the other; the result is that of shiftattn_prefill on the first
+ * The K/V of all rows is written once, then both kinds of rows run in one launch where that is expected to be faster and
+ * the workspace holds the partial results of both (the size asked for does), else one after the other; the result is that of shiftattn_prefill on the first
  * part followed by shiftattn_decode on the second, up to the order in which partial sums are added and the references against
  * which probabilities are rounded (bitwise reproducible for a given workspace size, no less exact).
  * max_prefill_seq_len / max_decode_seq_len bound seq_lens of the two parts.  The workspace is shared

@@ -987,8 +987,8 @@ hipError_t launch_prefill_mfma(const void* q, const void* cache, const int32_t* 
 // both.  A compute unit holds one workgroup of either kind, so the rows get as many as the tiles' ranges leave over; where
 // every place is taken, the last key range of each tile is the one that waits for a place and is made shorter by what the
 // decode rows take, so that all end together.  1000 tokens on 20000 cached (FP8) with 97 decodes: 154 -> 132 us a step;
-// forty random batches (equal chunks of 100 .. 2048 on 1000 .. 60000 cached, 2 .. 128 decodes): 1.22 times, none slower; fifty
-// of two to eight unequal chunks (150 .. 1900 on up to 20000): 1.13 times, six of them 1 to 2.6 % slower; where all rows are as long as the longest 1.18, where one is and the others have a 25th 1.12.  2048 tokens on 131072 cached with 64
+// 200 random batches (1 .. 8 equal or unequal chunks of 100 .. 2048 on up to 60000 cached, 2 .. 128 decodes, 80 of the batches with
+// decode rows that weigh more than the chunks) against two launches: 1.20 times, five of them 2 to 6.5 % slower; where all rows are as long as the longest 1.18, where one is and the others have a 25th 1.12.  2048 tokens on 131072 cached with 64
 // decodes (256-column kernel): 1028 -> 974; 1536 on 90000 with 100: 670 -> 602.
 namespace {
 
@@ -1014,6 +1014,21 @@ double decode_us(double bytes, double wgs, bool fp8, bool wide) {
     return kDecodeStartUs + bytes / (rate < kDecodeBytesPerUs ? rate : kDecodeBytesPerUs);
 }
 
+// What the rows take on that many workgroups if the tiles take nothing from them: bytes per microsecond and workgroup from 16 ..
+// 250 workgroups over 117 .. 760 MB of K/V (a workgroup keeps a fixed number of bytes in flight, half of them with an FP8 cache or
+// in the 256-column kernel, and the trip to memory gets longer the more of them ask).  The rates above shape the plans well
+// where tiles run beside the rows to the end, but promise too much where the rows outlast them.  kBothLimit: 176 random unified
+// batches, half of them with decode rows that weigh more than the chunks.  Ten were slower shared, by 1 to 28 % (2 x 567 tokens
+// x 16 heads with 73 rows of up to 17881: 204 us, 159 one after the other), all at 0.89 of the two launches' time or more by
+// this figure; below 0.88 none was, and the two that the line gives away had gained 3 and 6 %.
+double decode_us_at_least(double bytes, double wgs, bool fp8, bool wide) {
+    const double per_wg = fp8 ? (wide ? 28.3e3 : 43e3) : (wide ? 57e3 - 150.0 * wgs : 56.6e3 - 125.0 * wgs);
+    const double rate = wgs * per_wg;
+    return kDecodeStartUs + bytes / (rate < 6.4e6 ? rate : 6.4e6);
+}
+constexpr double kDecodeAloneBytesPerUs = 6.1e6;   // of a launch of their own
+constexpr double kBothLimit = 0.88;
+
 BothPlan plan_both(int num_seqs, int total_q, int max_q_len, int max_seq_len, int num_dec, int max_dec_len, const AttnShape& a) {
     BothPlan best{};
     if (option_prefill_splits() != 0 || option_prefill_pairing() == 1) return best;
@@ -1023,11 +1038,11 @@ BothPlan plan_both(int num_seqs, int total_q, int max_q_len, int max_seq_len, in
     if (bytes < 1e6) return best;   // (a few short rows: nothing to share, and the workspace stays the larger of the two parts')
     const Choice alone = plan_within(SIZE_MAX, num_seqs, total_q, max_q_len, max_seq_len, a);
     const Plan& base = alone.narrow;
-    const double serial = (alone.wide ? launch_us(kWideCost, alone.w.paired, alone.w.n_splits, alone.w.tile_tokens, a.hkv_l, num_seqs, total_q,
-                                                  max_q_len, max_seq_len, a.hq_l)
-                                      : launch_us(kNarrowCost, base.paired, base.n_splits, base.tile_tokens, base.head_slots, num_seqs, total_q,
-                                                  max_q_len, max_seq_len, a.hq_l)) + decode_us(bytes, 256, a.kv_fp8(), false) + 9.0;
-    double best_us = 0.97 * serial;
+    const double chunks_us = alone.wide ? launch_us(kWideCost, alone.w.paired, alone.w.n_splits, alone.w.tile_tokens, a.hkv_l, num_seqs, total_q,
+                                                    max_q_len, max_seq_len, a.hq_l)
+                                        : launch_us(kNarrowCost, base.paired, base.n_splits, base.tile_tokens, base.head_slots, num_seqs, total_q,
+                                                    max_q_len, max_seq_len, a.hq_l);
+    double best_us = 0.97 * (chunks_us + decode_us(bytes, 256, a.kv_fp8(), false) + 9.0), at_least_us = 0.0;
     const double seqs = longest_chunk_equivalents(num_seqs, total_q, max_q_len);
     const int q = max_q_len < max_seq_len ? max_q_len : max_seq_len;
     AttnShape b16 = a;
@@ -1048,6 +1063,7 @@ BothPlan plan_both(int num_seqs, int total_q, int max_q_len, int max_seq_len, in
                 const double us = (span * (num_seqs > 1 ? k.several : 1.0) + merge + 6.6 + 4.5) * (1.0 + 0.008 * splits);
                 if (us >= best_us) return;
                 best_us = us;
+                at_least_us = decode_us_at_least(bytes, x, a.kv_fp8(), wide != 0) + merge + 6.6 + 4.5;
                 best.taken = true;
                 best.wide = wide != 0;
                 best.narrow = base;
@@ -1087,6 +1103,7 @@ BothPlan plan_both(int num_seqs, int total_q, int max_q_len, int max_seq_len, in
             }
         }
     }
+    if (at_least_us > kBothLimit * (chunks_us + kDecodeStartUs + bytes / kDecodeAloneBytesPerUs + 9.0)) return BothPlan{};
     if (best.taken)
         best.bytes = (with_fp8_scratch(best.partial_bytes, num_seqs, max_seq_len, a) + 255) / 256 * 256 +
                      decode_mfma_workspace_for(best.dec_waves, num_dec, a);

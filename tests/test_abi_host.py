@@ -354,3 +354,22 @@ def test_fp8_projection_entry_points_reject_bad_arguments(B):
         assert B.last_error()
     assert q8(None, None, None, None, None, 0, 0, 8192, ctypes.byref(x), None) == B.OK
     assert o8(None, None, None, None, None, 0, 8, 8192, ctypes.byref(xo), None) == B.OK
+
+
+def test_unified_batches_whose_decode_rows_outweigh_the_chunks_take_two_launches(B):
+    """One launch for both kinds of rows holds the partial results of both, two launches share the workspace: where the key
+    ranges of the chunks have partial results, the size shows which it is.  With decode rows that outlast the tiles on the
+    workgroups that the tiles leave them, one launch took up to 28 % longer than two."""
+    def sizes(chunks, num_dec, max_dec, hq, hkv):
+        a = _attn(B, num_q_heads=hq, num_kv_heads=hkv, max_blocks_per_seq=(max(max_dec, max(c[1] for c in chunks)) + 15) // 16)
+        n, tot, mq, mp = len(chunks), sum(c[0] for c in chunks), max(c[0] for c in chunks), max(c[1] for c in chunks)
+        return (B.mixed_workspace_bytes(n, tot, mq, mp, num_dec, max_dec, a),
+                max(B.prefill_workspace_bytes(n, tot, mq, mp, a), B.decode_workspace_bytes(num_dec, max_dec, a)))
+
+    for chunks, num_dec, max_dec, hq, hkv in [([(367, 867)] * 4, 115, 12474, 16, 2), ([(968, 968)] * 2, 64, 22991, 16, 2),
+                                              ([(263, 2263)] * 6, 105, 19047, 16, 2)]:
+        both, larger = sizes(chunks, num_dec, max_dec, hq, hkv)
+        assert both == larger, (chunks, num_dec)
+    for chunks, num_dec, max_dec, hq, hkv in [([(2048, 133120)], 64, 32768, 8, 1), ([(33, 2000)], 7, 5000, 8, 1)]:
+        both, larger = sizes(chunks, num_dec, max_dec, hq, hkv)
+        assert both > larger, (chunks, num_dec)

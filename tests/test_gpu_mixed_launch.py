@@ -71,7 +71,7 @@ UNEQUAL = [
     ([(150, 750), (142, 142), (105, 105), (28, 28), (20, 20), (42, 42), (73, 76), (18, 361), (95, 95), (85, 85), (118, 118), (90, 90)],
      [3000, 2999, 31, 700, 3000, 48, 1, 1600], 8, 1, 256),                                                                       # 12
     ([(150, 750), (12, 159), (26, 262), (48, 408), (31, 233), (9, 258), (11, 11), (11, 342), (20, 355), (89, 89), (44, 44), (60, 60)],
-     [5000, 5000, 2, 640, 4999, 33, 1000], 16, 2, 128),                                                                          # 24
+     [4000, 4000, 2, 640, 3999, 33, 1000], 16, 2, 128),                                                                          # 24
     ([(150, 750), (50, 50), (79, 79), (113, 145)], [3000, 700, 2100], 10, 2, 128),                                               # 40
     ([(150, 750), (77, 103), (38, 38), (66, 66)], [3000, 64], 12, 3, 256),                                                       # 12
     ([(150, 750), (69, 69)], [3000, 16, 2990], 10, 2, 128),                                                                      # 20
