@@ -68,7 +68,13 @@ constexpr int kKBytes = kKvTile * kD * 2;      // 16384: K tile, 64 rows of 256 
 constexpr int kVBytes = kD * kKvTile * 2;      // 16384: V^T tile, 4 blocks of [128 rows][32 B]
 constexpr int kStageBytes = kKBytes + kVBytes; // 32768
 constexpr int kGroupBytes = 2 * kStageBytes;   // two stages per wavefront group
-constexpr int kLdsBytes = 2 * kGroupBytes;     // 131072
+// The merge of the two groups at the end of a pass: parked accumulators, the staged rows and the (max, sum) pairs lie
+// beside stage 0 of K of both groups, which the next pass's first tiles are loaded into meanwhile.
+constexpr int kPitch = 272;                    // staging row pitch in bytes (256 + 16)
+constexpr int kStagedAt = kKBytes;             // [128 columns][kPitch], then [2 groups][2][256] floats
+constexpr int kParkAt = kGroupBytes + kKBytes; // [2 groups][32 values][256 lanes] floats
+constexpr int kLdsBytes = kParkAt + 2 * 32 * 256 * 4;  // 147456
+static_assert(kStagedAt + 128 * kPitch + 2 * 2 * 256 * 4 <= kGroupBytes && kLdsBytes >= 2 * kGroupBytes);
 constexpr int kBlockBytes = kBlockSize * kD * 2;  // 4096: K (or V^T) of one cache block and head
 
 __device__ inline bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
@@ -128,21 +134,31 @@ __global__ __launch_bounds__(kThreads, 2) void prefill_kernel(PrefillParams p, D
     const int l32 = lane & 31, half = lane >> 5;
 
     // ---- which (pair rank, key split, sequence, head slot) is this workgroup -----------------------
+    const int tile_tokens = kCols >> p.gs_log2;
+    const int gs_mask = (1 << p.gs_log2) - 1;
+    // a pass of this workgroup: the key tiles [kt_begin, kt_end) of a tile
+    struct Part {
+        int tile, kt_begin, kt_end;
+    };
     const int n_sh = p.num_seqs * p.head_slots;
     const TileItem ti = tile_item(blockIdx.x, kDecode == 0 ? 0 : dec.n_wg, n_sh, p.ranks, p.n_splits, kDecode != 0, p.rotate != 0);
     const int rank = ti.rank, split = ti.split;
     const int s = ti.sh / p.head_slots;
     const int hs = ti.sh - s * p.head_slots;
-
-    const int q_begin = p.cu_seqlens_q[s];
-    const int q_len = p.cu_seqlens_q[s + 1] - q_begin;
-    const int ctx = p.seq_lens[s];
-    const int tile_tokens = kCols >> p.gs_log2;
+    // (uniform values, said so: kept in vector registers through the key loop they would be spilled)
+    const int q_begin = __builtin_amdgcn_readfirstlane(p.cu_seqlens_q[s]);
+    const int q_len = __builtin_amdgcn_readfirstlane(p.cu_seqlens_q[s + 1]) - q_begin;
+    const int ctx = __builtin_amdgcn_readfirstlane(p.seq_lens[s]);
     const int n_tiles = (q_len + tile_tokens - 1) / tile_tokens;
-    const int hi_tile = n_tiles - 1 - rank;
-    if (p.paired ? rank > hi_tile : hi_tile < 0) return;  // uniform
-    const int n_pass = (!p.paired || hi_tile == rank) ? 1 : 2;
-    const int gs_mask = (1 << p.gs_log2) - 1;
+    if (p.paired ? rank > n_tiles - 1 - rank : n_tiles - 1 - rank < 0) return;  // uniform
+    auto part_of = [&](int tile) SHIFTATTN_INLINE -> Part {
+        const int tile_pos_max = ctx - q_len + min((tile + 1) * tile_tokens, q_len) - 1;
+        const int kv_tiles = tile_pos_max / kKvTile + 1;
+        const int per_split = kDecode == 0 ? (kv_tiles + p.n_splits - 1) / p.n_splits : static_cast<int>(ceilf(kv_tiles / p.range_div));
+        const int begin = split * per_split;
+        return Part{tile, begin, kDecode != 0 && split == p.n_splits - 1 ? kv_tiles : min(kv_tiles, begin + per_split)};
+    };
+    Part cur = part_of(n_tiles - 1 - rank), next{};
     const int g = (hs << p.gs_log2) / p.G;  // KV head of every column of this workgroup
     const int32_t* __restrict__ table = p.block_table + static_cast<size_t>(s) * p.max_blocks;
     const int last_block = (ctx - 1) / kBlockSize;
@@ -179,8 +195,6 @@ __global__ __launch_bounds__(kThreads, 2) void prefill_kernel(PrefillParams p, D
         const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(a >> 32));
         return reinterpret_cast<const unsigned char*>((static_cast<uint64_t>(hi) << 32) | lo);
     };
-    const unsigned char* cache_g =
-        uniform_ptr(reinterpret_cast<const unsigned char*>(p.cache) + static_cast<size_t>(g) * 2 * kBlockBytes);
 
     typedef __attribute__((address_space(3))) void* lds_ptr;
     typedef const __attribute__((address_space(1))) void* glb_ptr;
@@ -190,36 +204,88 @@ __global__ __launch_bounds__(kThreads, 2) void prefill_kernel(PrefillParams p, D
     ones[1] = static_cast<__bf16>(1.0f);
     const float thr = 8.0f / p.c;
 
-    for (int pass = 0; pass < n_pass; ++pass) {
-        const int tile = pass == 0 ? hi_tile : rank;
+    // 1 KiB from src (wavefront-uniform, in scalar registers) + a 32-bit byte offset per lane + kImm into LDS at dst + kImm
+    // (dst uniform): written as assembly so that the address is formed by the load itself (scalar base + vector offset)
+    // instead of a 64-bit vector addition per load, which would cost MFMA issue time like any vector instruction.
+    // The loads are waited for with explicit vmcnt(0) waits (wait_vm0) only.
+    auto dma_1k = [&](const unsigned char* src, uint32_t lane_off, auto imm_c, unsigned char* dst) SHIFTATTN_INLINE {
+        constexpr int kImm = decltype(imm_c)::value;
+        const uint32_t m0v = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(dst));
+        // (M0 is reserved by the compiler - it sets it right before each use of its own and keeps no value in it,
+        // and rejects it on a clobber list - so writing it here needs no clobber.)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3"
+                     :: "s"(m0v), "v"(lane_off), "s"(src), "n"(kImm) : "memory");
+    };
+    // the base must sit in scalar registers for the assembly above: said explicitly (it is wavefront-uniform, but the
+    // register allocator may keep a uniform pointer in vector registers)
+    auto scalar_ptr = [](const unsigned char* ptr) SHIFTATTN_INLINE -> const unsigned char* {
+        const uint64_t a = reinterpret_cast<uint64_t>(ptr);
+        const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(a));
+        const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(a >> 32));
+        return reinterpret_cast<const unsigned char*>((static_cast<uint64_t>(hi) << 32) | lo);
+    };
+    auto load_k = [&](const unsigned char* src_any, int stage) SHIFTATTN_INLINE {
+        const unsigned char* src = scalar_ptr(src_any);
+        unsigned char* dst = ld_base + stage * kStageBytes;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) dma_1k(src, static_cast<uint32_t>(k_ld[j]), IC<0>{}, dst + j * 1024);
+    };
+    auto load_v = [&](const unsigned char* src_any, int stage) SHIFTATTN_INLINE {
+        const unsigned char* src = scalar_ptr(src_any);
+        unsigned char* dst = ld_base + stage * kStageBytes + kKBytes;
+        // the instruction's immediate offset moves the LDS destination along with the source
+        dma_1k(src, static_cast<uint32_t>(v_ld), IC<0>{}, dst);
+        dma_1k(src, static_cast<uint32_t>(v_ld), IC<1024>{}, dst);
+        dma_1k(src, static_cast<uint32_t>(v_ld), IC<2048>{}, dst);
+        dma_1k(src, static_cast<uint32_t>(v_ld), IC<3072>{}, dst);
+    };
+    typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
+    const const_i32_ptr table_c =
+        (const_i32_ptr)reinterpret_cast<const int32_t*>(uniform_ptr(reinterpret_cast<const unsigned char*>(table)));
+    const unsigned char* cache_g =
+        uniform_ptr(reinterpret_cast<const unsigned char*>(p.cache) + static_cast<size_t>(g) * 2 * kBlockBytes);
+    auto block_base = [&](int id) SHIFTATTN_INLINE -> const unsigned char* {
+        return cache_g + static_cast<int64_t>(id) * blk_bytes;
+    };
+    // What the first iterations of a pass wait for is requested while the pass before merges its groups and writes its rows
+    // out: the block ids of the first three tiles, K of the first, Q^T - a chain of two round trips to memory that a
+    // workgroup of two tiles otherwise waits for twice (4 x 4096 tokens, 4 heads: 76.8 -> 76.0 us a call).
+    bf16x8 qf[8];
+    int id0 = 0, id1 = 0, id2 = 0;  // ids of tiles j, j+1, j+2 at the top of iteration j (uniform)
+    auto load_q = [&](const Part& of) SHIFTATTN_INLINE {
+        const int c = wg * 32 + l32, tok = of.tile * tile_tokens + (c >> p.gs_log2);
+        const uint16_t* qp = p.q + static_cast<size_t>(q_begin + tok) * p.q_stride + ((hs << p.gs_log2) + (c & gs_mask)) * kD + half * 8;
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) {
+            u32x4 v = {0u, 0u, 0u, 0u};
+            if (tok < q_len) v = *reinterpret_cast<const u32x4*>(qp + ks * 16);
+            qf[ks] = as_bf16x8(v);
+        }
+    };
+    auto group_tiles = [&](const Part& of) SHIFTATTN_INLINE { return (max(of.kt_end - of.kt_begin, 0) + 1 - grp) >> 1; };
+    auto request_first = [&](const Part& of) SHIFTATTN_INLINE {   // the ids, and K of the first tile into stage 0
+        const int n = __builtin_amdgcn_readfirstlane(group_tiles(of));
+        if (n == 0) return;
+        auto id_of = [&](int j) SHIFTATTN_INLINE { return table_c[min((of.kt_begin + grp_u + 2 * min(j, n - 1)) * 4 + wg_u, last_block)]; };
+        id0 = id_of(0), id1 = id_of(1), id2 = id_of(2);
+        load_k(block_base(id0), 0);
+    };
+    load_q(cur);
+    request_first(cur);
+    for (;;) {
+        const int tile = cur.tile;
+        const int kt_begin = cur.kt_begin, kt_end = cur.kt_end;
         const int tok0 = tile * tile_tokens;
         const int cw = wg * 32 + l32;
         const int tok = tok0 + (cw >> p.gs_log2);
         const bool valid = tok < q_len;
-        const int head_col = (hs << p.gs_log2) + (cw & gs_mask);
-        const int row_col = q_begin + tok;
         const int pos_col = valid ? ctx - q_len + tok : -1;
-        bf16x8 qf[8];
-        {
-            const uint16_t* qp = p.q + static_cast<size_t>(row_col) * p.q_stride + head_col * kD + half * 8;
-#pragma unroll
-            for (int ks = 0; ks < 8; ++ks) {
-                u32x4 v = {0u, 0u, 0u, 0u};
-                if (valid) v = *reinterpret_cast<const u32x4*>(qp + ks * 16);
-                qf[ks] = as_bf16x8(v);
-            }
-        }
         const int w_tok_first = tok0 + ((wg * 32) >> p.gs_log2);
         const int w_pos_min = __builtin_amdgcn_readfirstlane(w_tok_first < q_len ? ctx - q_len + w_tok_first : -1);
 
         // ---- key tiles of this (column tile, split), dealt alternately to the two groups ------------------
-        const int tile_pos_max = ctx - q_len + min(tok0 + tile_tokens, q_len) - 1;
-        const int kv_tiles = tile_pos_max / kKvTile + 1;
-        const int per_split = kDecode == 0 ? (kv_tiles + p.n_splits - 1) / p.n_splits : static_cast<int>(ceilf(kv_tiles / p.range_div));
-        const int kt_begin = split * per_split;
-        const int kt_end = kDecode != 0 && split == p.n_splits - 1 ? kv_tiles : min(kv_tiles, kt_begin + per_split);
         const int n_all = max(kt_end - kt_begin, 0);
-        const int n = (n_all + 1 - grp) >> 1;        // tiles of this group: kt(j) = kt_begin + grp + 2 j
+        const int n = group_tiles(cur);              // tiles of this group: kt(j) = kt_begin + grp + 2 j
         const int n_other = (n_all + grp) >> 1;
         // The tile that reaches past the context (if any) holds unwritten V slots; its owner clears them
         // in LDS before use, which costs one extra barrier that the other group mirrors.
@@ -240,55 +306,12 @@ __global__ __launch_bounds__(kThreads, 2) void prefill_kernel(PrefillParams p, D
         // whole iteration later: loads return in order, so a wait right behind the direct-to-LDS loads
         // (or right after the barrier) would stall for a full memory round trip every iteration.
         const int n_u = __builtin_amdgcn_readfirstlane(n);
-        const int32_t* table_u = reinterpret_cast<const int32_t*>(uniform_ptr(reinterpret_cast<const unsigned char*>(table)));
-        typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
-        const const_i32_ptr table_c = (const_i32_ptr)table_u;
         auto fetch_id = [&](int j) SHIFTATTN_INLINE -> int {
             // every term of the address is uniform, and the table is read through the constant address space: the
             // compiler issues a scalar load, the id arrives in a scalar register without a vector instruction, and the
             // compiler itself places the wait in front of the first use (the bottom of the iteration, see below)
             const int idx = min((kt_begin + grp_u + 2 * min(j, max(n_u - 1, 0))) * 4 + wg_u, last_block);
             return table_c[idx];
-        };
-        auto id_arrived = [](int&) SHIFTATTN_INLINE {};   // the use itself waits
-        auto block_base = [&](int id) SHIFTATTN_INLINE -> const unsigned char* {
-            return cache_g + static_cast<int64_t>(id) * blk_bytes;
-        };
-        int id0 = 0, id1 = 0, id2 = 0;  // ids of tiles j, j+1, j+2 at the top of iteration j (uniform)
-        // 1 KiB from src (wavefront-uniform, in scalar registers) + a 32-bit byte offset per lane + kImm into LDS at dst + kImm
-        // (dst uniform): written as assembly so that the address is formed by the load itself (scalar base + vector offset)
-        // instead of a 64-bit vector addition per load, which would cost MFMA issue time like any vector instruction.
-        // The loads are waited for with explicit vmcnt(0) waits (wait_vm0) only.
-        auto dma_1k = [&](const unsigned char* src, uint32_t lane_off, auto imm_c, unsigned char* dst) SHIFTATTN_INLINE {
-            constexpr int kImm = decltype(imm_c)::value;
-            const uint32_t m0v = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(dst));
-            // (M0 is reserved by the compiler - it sets it right before each use of its own and keeps no value in it,
-            // and rejects it on a clobber list - so writing it here needs no clobber.)
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3"
-                         :: "s"(m0v), "v"(lane_off), "s"(src), "n"(kImm) : "memory");
-        };
-        // the base must sit in scalar registers for the assembly above: said explicitly (it is wavefront-uniform, but the
-        // register allocator may keep a uniform pointer in vector registers)
-        auto scalar_ptr = [](const unsigned char* ptr) SHIFTATTN_INLINE -> const unsigned char* {
-            const uint64_t a = reinterpret_cast<uint64_t>(ptr);
-            const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(a));
-            const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(a >> 32));
-            return reinterpret_cast<const unsigned char*>((static_cast<uint64_t>(hi) << 32) | lo);
-        };
-        auto load_k = [&](const unsigned char* src_any, int stage) SHIFTATTN_INLINE {
-            const unsigned char* src = scalar_ptr(src_any);
-            unsigned char* dst = ld_base + stage * kStageBytes;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) dma_1k(src, static_cast<uint32_t>(k_ld[j]), IC<0>{}, dst + j * 1024);
-        };
-        auto load_v = [&](const unsigned char* src_any, int stage) SHIFTATTN_INLINE {
-            const unsigned char* src = scalar_ptr(src_any);
-            unsigned char* dst = ld_base + stage * kStageBytes + kKBytes;
-            // the instruction's immediate offset moves the LDS destination along with the source
-            dma_1k(src, static_cast<uint32_t>(v_ld), IC<0>{}, dst);
-            dma_1k(src, static_cast<uint32_t>(v_ld), IC<1024>{}, dst);
-            dma_1k(src, static_cast<uint32_t>(v_ld), IC<2048>{}, dst);
-            dma_1k(src, static_cast<uint32_t>(v_ld), IC<3072>{}, dst);
         };
         // zero the V^T entries of keys at or past the context in the given stage (tile kt)
         auto clear_ragged_v = [&](int kt, int stage) SHIFTATTN_INLINE {
@@ -467,25 +490,19 @@ __global__ __launch_bounds__(kThreads, 2) void prefill_kernel(PrefillParams p, D
             wait_vm0();  // this wavefront's loads have landed before it reaches the next barrier
             id0 = id1;
             id1 = id2;
-            id_arrived(id3_v);
             id2 = id3_v;
         };
 
         int barriers = 0;  // barriers this group executes in the pass; both groups must end up equal
         if (n > 0) {
             // prologue: K of the first two tiles, S^T of the first
-            {
-                int a0 = fetch_id(0), a1 = fetch_id(1), a2 = fetch_id(2);
-                id_arrived(a0);
-                id_arrived(a1);
-                id_arrived(a2);
-                id0 = a0;
-                id1 = a1;
-                id2 = a2;
-                load_k(block_base(id0), 0);
-                if (n > 1) load_k(block_base(id1), 1);
+            // (K of the second is waited for behind the products on the first)
+            if (n > 1) {
+                load_k(block_base(id1), 1);
+                __builtin_amdgcn_s_waitcnt(0x0F74);   // vmcnt(4): all but these four
+            } else {
+                wait_vm0();
             }
-            wait_vm0();
             __syncthreads();
 #pragma unroll
             for (int sub = 0; sub < 2; ++sub) {
@@ -497,6 +514,7 @@ __global__ __launch_bounds__(kThreads, 2) void prefill_kernel(PrefillParams p, D
                     sbuf[0][sub] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(a), qf[ks], sbuf[0][sub], 0, 0, 0);
                 }
             }
+            wait_vm0();
             if (n == 1) {
                 body(IC<0>{}, IC<0>{}, IC<0>{}, 0);
             } else {
@@ -544,34 +562,40 @@ __global__ __launch_bounds__(kThreads, 2) void prefill_kernel(PrefillParams p, D
         // ---- merge the two groups -------------------------------------------------------------------------
         float l_tot = l_run + __shfl_xor(l_run, 32);
         __syncthreads();  // every wavefront is done with the tile stages
+        // the pass that follows: its first K tiles go to stage 0 of either group, where nothing of the merge lies
+        const bool more = p.paired && cur.tile != rank;   // (the second of a pair is the last)
+        if (more) {
+            next = part_of(rank);
+            request_first(next);
+        }
         // the thread index is read through an opaque copy: addresses derived from the plain value are loop
         // invariants that the optimiser computes before the key loop and then spills around it
         int tid_m = tid;
         asm volatile("" : "+v"(tid_m));
         const int t4 = tid_m & 255;
+        // Each group finishes one half of the head dimension (group 0 rows 0..63, group 1 rows 64..127): it parks the other half
+        // of its accumulators for the other group and folds in what that group parked.
+        float* park = reinterpret_cast<float*>(lds + kParkAt);        // [2 groups][32 values][256 lanes]
+        float* x_ml = reinterpret_cast<float*>(lds + kStagedAt + kCols * kPitch);  // [2 groups][2][256]
+        // (register arrays are indexed with compile-time constants only: one copy of the code per group)
+        auto park_half = [&](auto g_c) SHIFTATTN_INLINE {
+            constexpr int GRP = decltype(g_c)::value;
+            float* mine = park + GRP * (32 * 256);
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) mine[(k * 16 + r) * 256 + t4] = oacc[2 * (1 - GRP) + k][r];
+            x_ml[(GRP * 2) * 256 + t4] = m_used;
+            x_ml[(GRP * 2 + 1) * 256 + t4] = l_tot;
+        };
+        if (grp == 0) park_half(IC<0>{});
+        else park_half(IC<1>{});
+        __syncthreads();
+        if (more) load_q(next);
         if (p.n_splits == 1) {
-            // Each group finishes one half of the head dimension (group 0 rows 0..63, group 1 rows 64..127): it parks
-            // the other half of its accumulators for the other group, folds in what that group parked, normalises,
-            // and puts bf16 rows into an LDS staging tile; then all eight wavefronts write the tile out in whole
-            // 256-byte rows (one 16-byte piece per lane, 1 KiB of consecutive output per instruction per 4 rows).
-            float* park = reinterpret_cast<float*>(lds);                 // [2 groups][32 values][256 lanes]
-            float* x_ml = park + 2 * 32 * 256;                            // [2 groups][2][256]
-            constexpr int kPitch = 272;                                   // staging row pitch in bytes (256 + 16)
-            unsigned char* stage = lds + (2 * 32 * 256 + 2 * 2 * 256) * 4;  // [128 columns][kPitch]
-            // (register arrays are indexed with compile-time constants only: one copy of the code per group)
-            auto park_half = [&](auto g_c) SHIFTATTN_INLINE {
-                constexpr int GRP = decltype(g_c)::value;
-                float* mine = park + GRP * (32 * 256);
-#pragma unroll
-                for (int k = 0; k < 2; ++k)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) mine[(k * 16 + r) * 256 + t4] = oacc[2 * (1 - GRP) + k][r];
-                x_ml[(GRP * 2) * 256 + t4] = m_used;
-                x_ml[(GRP * 2 + 1) * 256 + t4] = l_tot;
-            };
-            if (grp == 0) park_half(IC<0>{});
-            else park_half(IC<1>{});
-            __syncthreads();
+            // it normalises and puts bf16 rows into an LDS staging tile; then all eight wavefronts write the tile out in whole
+            // 256-byte rows (one 16-byte piece per lane, 1 KiB of consecutive output per instruction per 4 rows)
+            unsigned char* stage = lds + kStagedAt;                       // [128 columns][kPitch]
             auto finish_half = [&](auto g_c) SHIFTATTN_INLINE {
                 constexpr int grp = decltype(g_c)::value;  // shadows the runtime value
                 const float* theirs = park + (1 - grp) * (32 * 256);
@@ -610,50 +634,43 @@ __global__ __launch_bounds__(kThreads, 2) void prefill_kernel(PrefillParams p, D
                 }
             }
         } else {
-            // key ranges split over workgroups: group 1 parks (m, l, O) in LDS, group 0 folds it in and writes the
-            // un-normalised partial of this range
-            float* x_o = reinterpret_cast<float*>(lds);                   // [64 values][256 lanes of a group]
-            float* x_ml = x_o + 64 * 256;                                  // [2][256]
-            if (grp == 1) {
+            // key ranges split over workgroups: the un-normalised partial of this range, each group one half of the head
+            // dimension of it
+            auto fold_half = [&](auto g_c) SHIFTATTN_INLINE {
+                constexpr int grp = decltype(g_c)::value;  // shadows the runtime value
+                const float* theirs = park + (1 - grp) * (32 * 256);
+                const float m_o = x_ml[((1 - grp) * 2) * 256 + t4], l_o = x_ml[((1 - grp) * 2 + 1) * 256 + t4];
+                const float m_star = fmaxf(m_used, m_o);
+                const float w_me = m_used == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_used - m_star) * p.c);
+                const float w_o = m_o == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_o - m_star) * p.c);
+                const int cw_m = ((tid_m >> 6) & 3) * 32 + (tid_m & 31), half_m = (tid_m >> 5) & 1, tok_m = tok0 + (cw_m >> p.gs_log2);
+                if (tok_m >= q_len || ctx - q_len + tok_m < 0) return;
+                // accumulator register r of row tile mt is head-dim 32*mt + 8*(r/4) + 4*half + r%4
+                const size_t prow = (static_cast<size_t>(split) * p.total_q + q_begin + tok_m) * p.hq_l + (hs << p.gs_log2) + (cw_m & gs_mask);
+                float* op = p.o_part + prow * kD + 64 * grp + 4 * half_m;
 #pragma unroll
-                for (int mt = 0; mt < 4; ++mt)
+                for (int k = 0; k < 2; ++k)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) x_o[(mt * 16 + r) * 256 + t4] = oacc[mt][r];
-                x_ml[t4] = m_used;
-                x_ml[256 + t4] = l_tot;
-            }
-            __syncthreads();
-            if (grp == 0) {
-                const float m1 = x_ml[t4], l1 = x_ml[256 + t4];
-                const float m_star = fmaxf(m_used, m1);
-                const float w0 = m_used == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_used - m_star) * p.c);
-                const float w1 = m1 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m1 - m_star) * p.c);
-                l_tot = l_tot * w0 + l1 * w1;
+                    for (int r4 = 0; r4 < 4; ++r4) {
+                        f32x4 v;
 #pragma unroll
-                for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) oacc[mt][r] = oacc[mt][r] * w0 + x_o[(mt * 16 + r) * 256 + t4] * w1;
-                if (pos_col >= 0) {
-                    // accumulator register r of row tile mt is head-dim 32*mt + 8*(r/4) + 4*half + r%4
-                    const size_t prow = (static_cast<size_t>(split) * p.total_q + row_col) * p.hq_l + head_col;
-                    float* op = p.o_part + prow * kD + 4 * half;
-#pragma unroll
-                    for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-                        for (int r4 = 0; r4 < 4; ++r4) {
-                            f32x4 v;
-#pragma unroll
-                            for (int x = 0; x < 4; ++x) v[x] = oacc[mt][r4 * 4 + x];
-                            *reinterpret_cast<f32x4*>(op + 32 * mt + 8 * r4) = v;
-                        }
-                    if (half == 0) {
-                        p.ml_part[prow * 2] = m_star * p.c;  // -inf when this key range held no visible key
-                        p.ml_part[prow * 2 + 1] = l_tot;
+                        for (int x = 0; x < 4; ++x)
+                            v[x] = oacc[2 * grp + k][r4 * 4 + x] * w_me + theirs[(k * 16 + r4 * 4 + x) * 256 + t4] * w_o;
+                        *reinterpret_cast<f32x4*>(op + 32 * k + 8 * r4) = v;
                     }
+                if (grp == 0 && half_m == 0) {
+                    p.ml_part[prow * 2] = m_star * p.c;  // -inf when this key range held no visible key
+                    p.ml_part[prow * 2 + 1] = l_tot * w_me + l_o * w_o;
                 }
-            }
+            };
+            if (grp == 0) fold_half(IC<0>{});
+            else fold_half(IC<1>{});
         }
-        __syncthreads();  // the next pass reuses LDS
+        if (!more) break;
+        // The next pass reuses LDS.  A bare barrier: __syncthreads() would also wait until the rows just written out and the
+        // requests of the next pass have come back.
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        cur = next;
     }
 }
 
