@@ -136,14 +136,15 @@ inline double longest_chunk_equivalents(int num_seqs, int total_q, int max_q_len
 // same die: good while the sequences are alike (a die's L2 holds the K/V of its sequences only), and a 32-CU bottleneck
 // for a long prompt among short ones (measured: one 4096-token prompt with seven of 700 tokens took twice the time of
 // the long prompt alone).  Batches whose chunks are not near equal, and whose (sequence, head) count is a multiple of
-// four (a sequence then sees one or two dies), therefore rotate the (sequence, head) index, by one more for every
-// (tile rank, key range) (tile_item() in tile_order.h), so that a die meets all of them; other counts spread by
-// themselves, and rotating them only costs L2 hits.  Near equal is 0.9 of the longest: without the rotation seven random
-// batches below 0.75 took 5.5 % longer and 27 between 0.75 and 0.9 0.4 % (single ones from 9 % shorter to 26 % longer);
-// fifty unified batches of unequal chunks, decode rows beside them, took 5 % longer without it (up to twice the time).
+// four (a sequence then sees one or two dies), therefore rotate the (sequence, head) index from one (tile rank, key range)
+// to the next (rotation() in tile_order.h), so that a die meets all of them; other counts spread by
+// themselves, and rotating them only costs L2 hits.  Near equal is 0.9 of the longest (between 0.9 and 0.98 twelve
+// (sequence, head) or more were 3 to 5 % slower rotated), 0.98 where there are four, each on two dies only (21 batches between 0.9
+// and 0.98 1.8 % faster, two of 6754 and 5424 tokens x 2 heads 367 -> 318 us).  Fifty unified batches of unequal chunks, decode
+// rows beside them, took 5 % longer without a rotation (up to twice the time).
 inline bool rotate_sequences_over_dies(int num_seqs, int heads, int total_q, int max_q_len) {
     return num_seqs > 1 && (static_cast<long>(num_seqs) * heads) % 4 == 0 &&
-           longest_chunk_equivalents(num_seqs, total_q, max_q_len) < 0.9 * num_seqs;
+           longest_chunk_equivalents(num_seqs, total_q, max_q_len) < (num_seqs * heads == 4 ? 0.98 : 0.9) * num_seqs;
 }
 constexpr int kPrefill64Waves = 4;  // per workgroup
 struct DecodeRole;                  // decode_body.h

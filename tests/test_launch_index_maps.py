@@ -85,3 +85,15 @@ def test_projection_tiles_load_rows_that_exist(maps, tile):
     for M in (1, 2, 127, 128, 129, 255, 256, 257, 384, 512, 701):
         for M_out in (M, M + 1, M + 7, M + tile - 1, M + tile, M + tile + 1, M + 3 * tile):
             assert maps.rows_wrong(M, M_out, tile) == 0, (M, M_out)
+
+
+@pytest.mark.parametrize("n_sh", [4, 8, 12, 16])
+def test_rotation_shows_every_engine_all_sequences(maps, n_sh):
+    """Workgroup i runs on die i % 8, shader engine (i / 8) % 4 of it: with a rotation each of the 32 meets every (sequence, head)
+    about equally often, whatever decode workgroups stand in front and in either order of the grid."""
+    for decode_wgs in (0, 67, 96):
+        for ranks, n_splits, range_major in ((32 * n_sh, 1, 0), (8 * n_sh, 4, 0), (8 * n_sh, 4, 1)):
+            seen = [[0] * n_sh for _ in range(32)]
+            for b in range(decode_wgs, decode_wgs + n_sh * 32 * n_sh):
+                seen[b % 32][maps.sh_of(b, decode_wgs, n_sh, ranks, n_splits, range_major, 1)] += 1
+            assert min(min(x) for x in seen) >= 0.6 * n_sh and max(max(x) for x in seen) <= 1.6 * n_sh, (decode_wgs, ranks, n_splits)
