@@ -9,6 +9,7 @@ __graft_entry__.build()), loading raises.
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
 from typing import Optional
 
@@ -46,11 +47,16 @@ KV_SAME, KV_FP8_E4M3 = 0, 1
 
 
 _lib: Optional[ctypes.CDLL] = None
+_calls = None  # csrc/python_calls.cpp, bound to _lib
+# the functions that _calls takes the addresses of, in its order
+_BOUND = ("pack_seq2head", "unpack_head2seq", "prefill", "decode", "decode_static", "mixed", "kv_write", "qkv_proj_pack_ws",
+          "unpack_o_proj_ws", "qkv_proj_pack", "unpack_o_proj", "qkv_proj_pack_fp8_ws", "unpack_o_proj_fp8_ws", "quantize_rows_fp8",
+          "quantize_recv_fp8")
 
 
 def lib() -> ctypes.CDLL:
     """The loaded C library.  Raises if it was never built: there is no other implementation."""
-    global _lib
+    global _lib, _calls
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(f"{LIB_PATH} is missing: build it with `python -m paper_2509_16495_amd.build`")
@@ -100,6 +106,8 @@ def lib() -> ctypes.CDLL:
         L.shiftattn_get_option.argtypes = [i32]
         L.shiftattn_get_option.restype = i32
         L.shiftattn_last_error.restype = ctypes.c_char_p
+        _calls = importlib.import_module("._calls", __package__)
+        _calls.bind(*[ctypes.cast(getattr(L, "shiftattn_" + name), ctypes.c_void_p).value for name in _BOUND])
         _lib = L
     return _lib
 
@@ -128,10 +136,15 @@ def _check(rc: int) -> None:
         raise ShiftAttnError(rc, last_error())
 
 
-# Small calls are bound by what the host does per launch, so the functions below ask a tensor for its shape and its
-# strides once each (every access is a call into torch), hand pointers to the library as plain integers and leave the
-# workspace query to calls that bring none (the library checks the size by itself).  A call over four
-# sequences costs the host 11.7 us instead of 17.1, a pack 5.3 instead of 8.
+# Small calls are bound by what the host does per launch, so the functions of the path hand their arguments to
+# csrc/python_calls.cpp, which checks them and calls the library, and leave the workspace query to calls that bring none
+# (the library checks the size by itself).
+def _native():
+    if _lib is None:
+        lib()
+    return _calls
+
+
 _DTYPE_CODES = {torch.bfloat16: BF16, torch.float32: F32}
 
 
@@ -218,22 +231,12 @@ def local_kv_heads(P: int, h_kv: int) -> int:
 # ---- exchange pack / unpack -----------------------------------------------------------------------
 def pack_seq2head(qkv: torch.Tensor, send: torch.Tensor, P: int, h: int, h_kv: int) -> None:
     """qkv [T, h+2*h_kv, D] -> send [P, T_pad, h/P + 2*hkv_l, D] (pad rows zeroed)."""
-    T, w, D = qkv.shape
-    assert w == h + 2 * h_kv and qkv.is_contiguous() and send.is_contiguous() and send.dtype == qkv.dtype
-    s = send.shape
-    T_pad = s[1]
-    assert s[0] == P and s[3] == D
-    x = Xchg(P, h, h_kv, D, _dtype_code(qkv))
-    _check(lib().shiftattn_pack_seq2head(_ptr(qkv), _ptr(send), T, T_pad, ctypes.byref(x), _stream()))
+    _check(_native().pack_seq2head(qkv, send, P, h, h_kv))
 
 
 def unpack_head2seq(recv: torch.Tensor, out: torch.Tensor) -> None:
     """recv [P, T_pad, h/P, D] -> out [T, h, D]."""
-    P, T_pad, hq_l, D = recv.shape
-    T, h, D2 = out.shape
-    assert D2 == D and h == P * hq_l and recv.is_contiguous() and out.is_contiguous() and out.dtype == recv.dtype
-    x = Xchg(P, h, 0, D, _dtype_code(recv))
-    _check(lib().shiftattn_unpack_head2seq(_ptr(recv), _ptr(out), T, T_pad, ctypes.byref(x), _stream()))
+    _check(_native().unpack_head2seq(recv, out))
 
 
 # ---- KV cache and attention -------------------------------------------------------------------------
@@ -247,79 +250,34 @@ def proj_workspace_bytes(rows: int, n_features: int, k: int, fp8: bool = False) 
 def qkv_proj_pack(x: torch.Tensor, w_qkv: torch.Tensor, send: torch.Tensor, P: int, h: int, h_kv: int,
                   workspace: Optional[torch.Tensor] = None) -> None:
     """x [T, d_model], w_qkv [(h + 2 h_kv) D, d_model] -> send [P, T_pad, hq_l + 2 hkv_l, D] (projection + pack)."""
-    T, d_model = x.shape
-    s = send.shape
-    T_pad, D = s[1], s[3]
-    assert w_qkv.shape == ((h + 2 * h_kv) * D, d_model) and x.is_contiguous() and w_qkv.is_contiguous() and send.is_contiguous()
-    assert s[0] == P and s[2] == h // P + 2 * local_kv_heads(P, h_kv) and x.dtype == w_qkv.dtype == send.dtype
-    xc = Xchg(P, h, h_kv, D, _dtype_code(x))
-    if workspace is None:
-        _check(lib().shiftattn_qkv_proj_pack(_ptr(x), _ptr(w_qkv), _ptr(send), T, T_pad, d_model, ctypes.byref(xc), _stream()))
-    else:
-        _check(lib().shiftattn_qkv_proj_pack_ws(_ptr(x), _ptr(w_qkv), _ptr(send), T, T_pad, d_model, ctypes.byref(xc), _ptr(workspace),
-                                                workspace.nbytes, _stream()))
+    _check(_native().qkv_proj_pack(x, w_qkv, send, P, h, h_kv, workspace))
 
 
 def unpack_o_proj(recv: torch.Tensor, w_o: torch.Tensor, out: torch.Tensor, workspace: Optional[torch.Tensor] = None) -> None:
     """recv [P, T_pad, hq_l, D], w_o [d_model, h D] -> out [T, d_model] (unpack + projection)."""
-    P, T_pad, hq_l, D = recv.shape
-    T, d_model = out.shape
-    assert w_o.shape == (d_model, P * hq_l * D) and recv.is_contiguous() and w_o.is_contiguous() and out.is_contiguous()
-    assert recv.dtype == w_o.dtype == out.dtype
-    xc = Xchg(P, P * hq_l, 0, D, _dtype_code(recv))
-    if workspace is None:
-        _check(lib().shiftattn_unpack_o_proj(_ptr(recv), _ptr(w_o), _ptr(out), T, T_pad, d_model, ctypes.byref(xc), _stream()))
-    else:
-        _check(lib().shiftattn_unpack_o_proj_ws(_ptr(recv), _ptr(w_o), _ptr(out), T, T_pad, d_model, ctypes.byref(xc), _ptr(workspace),
-                                                workspace.nbytes, _stream()))
+    _check(_native().unpack_o_proj(recv, w_o, out, workspace))
 
 
 def quantize_rows_fp8(x: torch.Tensor, codes: torch.Tensor, scales: torch.Tensor) -> None:
     """x [rows, cols] bf16 -> codes [rows, cols] uint8 (FP8 E4M3), scales [rows] float32 (amax / 448)."""
-    rows, cols = x.shape
-    assert x.dtype == torch.bfloat16 and codes.dtype == torch.uint8 and scales.dtype == torch.float32
-    assert codes.shape == x.shape and scales.shape == (rows,) and x.is_contiguous() and codes.is_contiguous() and scales.is_contiguous()
-    _check(lib().shiftattn_quantize_rows_fp8(_ptr(x), _ptr(codes), _ptr(scales), rows, cols, _stream()))
+    _check(_native().quantize_rows_fp8(x, codes, scales))
 
 
 def quantize_recv_fp8(recv: torch.Tensor, codes: torch.Tensor, scales: torch.Tensor) -> None:
     """recv [P, T_pad, hq_l, D] bf16 -> codes of the same shape (uint8), scales [T]: one scale per token over all buffers."""
-    P, T_pad, hq_l, D = recv.shape
-    T = scales.shape[0]
-    assert recv.dtype == torch.bfloat16 and codes.dtype == torch.uint8 and scales.dtype == torch.float32 and codes.shape == recv.shape
-    assert recv.is_contiguous() and codes.is_contiguous() and scales.is_contiguous()
-    xc = Xchg(P, P * hq_l, 0, D, BF16)
-    _check(lib().shiftattn_quantize_recv_fp8(_ptr(recv), _ptr(codes), _ptr(scales), T, T_pad, ctypes.byref(xc), _stream()))
+    _check(_native().quantize_recv_fp8(recv, codes, scales))
 
 
 def qkv_proj_pack_fp8(x_codes: torch.Tensor, x_scales: torch.Tensor, w_codes: torch.Tensor, w_scales: torch.Tensor,
                       send: torch.Tensor, P: int, h: int, h_kv: int, workspace: Optional[torch.Tensor] = None) -> None:
     """FP8 E4M3 codes x [T, d_model] and w [(h + 2 h_kv) D, d_model] with their row scales -> bf16 send buffers."""
-    T, d_model = x_codes.shape
-    s, w = send.shape, w_codes.shape
-    T_pad, D = s[1], s[3]
-    assert x_codes.dtype == w_codes.dtype == torch.uint8 and x_scales.dtype == w_scales.dtype == torch.float32 and send.dtype == torch.bfloat16
-    assert w == ((h + 2 * h_kv) * D, d_model) and x_scales.shape == (T,) and w_scales.shape == (w[0],)
-    assert s[0] == P and s[2] == h // P + 2 * local_kv_heads(P, h_kv)
-    assert all(t.is_contiguous() for t in (x_codes, x_scales, w_codes, w_scales, send))
-    xc = Xchg(P, h, h_kv, D, BF16)
-    _check(lib().shiftattn_qkv_proj_pack_fp8_ws(_ptr(x_codes), _ptr(x_scales), _ptr(w_codes), _ptr(w_scales), _ptr(send), T, T_pad,
-                                                d_model, ctypes.byref(xc), _ptr(workspace) if workspace is not None else None,
-                                                workspace.nbytes if workspace is not None else 0, _stream()))
+    _check(_native().qkv_proj_pack_fp8(x_codes, x_scales, w_codes, w_scales, send, P, h, h_kv, workspace))
 
 
 def unpack_o_proj_fp8(recv_codes: torch.Tensor, a_scales: torch.Tensor, w_codes: torch.Tensor, w_scales: torch.Tensor,
                       out: torch.Tensor, workspace: Optional[torch.Tensor] = None) -> None:
     """FP8 E4M3 codes recv [P, T_pad, hq_l, D] (one scale per token) and w [d_model, h D] (one per feature) -> out [T, d_model] bf16."""
-    P, T_pad, hq_l, D = recv_codes.shape
-    T, d_model = out.shape
-    assert recv_codes.dtype == w_codes.dtype == torch.uint8 and a_scales.dtype == w_scales.dtype == torch.float32 and out.dtype == torch.bfloat16
-    assert w_codes.shape == (d_model, P * hq_l * D) and a_scales.shape[0] >= T and w_scales.shape == (d_model,)
-    assert all(t.is_contiguous() for t in (recv_codes, a_scales, w_codes, w_scales, out))
-    xc = Xchg(P, P * hq_l, 0, D, BF16)
-    _check(lib().shiftattn_unpack_o_proj_fp8_ws(_ptr(recv_codes), _ptr(a_scales), _ptr(w_codes), _ptr(w_scales), _ptr(out), T, T_pad,
-                                                d_model, ctypes.byref(xc), _ptr(workspace) if workspace is not None else None,
-                                                workspace.nbytes if workspace is not None else 0, _stream()))
+    _check(_native().unpack_o_proj_fp8(recv_codes, a_scales, w_codes, w_scales, out, workspace))
 
 
 def attn_desc(q: torch.Tensor, kv_cache: torch.Tensor, block_table: torch.Tensor, softmax_scale: float,
@@ -340,16 +298,7 @@ def attn_desc(q: torch.Tensor, kv_cache: torch.Tensor, block_table: torch.Tensor
 
 def kv_write(k_new: torch.Tensor, v_new: torch.Tensor, slot_mapping: torch.Tensor, kv_cache: torch.Tensor,
              k_scale: float = 1.0, v_scale: float = 1.0) -> None:
-    n, hkv_l, D = k_new.shape
-    assert v_new.shape == k_new.shape and slot_mapping.dtype == torch.int64 and slot_mapping.shape[0] == n
-    assert _row_stride(v_new) == _row_stride(k_new)
-    num_blocks = kv_cache.shape[0]
-    assert kv_cache.shape[1:] == (hkv_l, 2, BLOCK_SIZE * D) and kv_cache.is_contiguous()
-    fp8 = kv_cache.dtype == torch.uint8
-    a = Attn(hkv_l, hkv_l, D, _dtype_code(k_new), BLOCK_SIZE, num_blocks, 0, 1.0, 0, _row_stride(k_new), 0,
-             KV_FP8_E4M3 if fp8 else KV_SAME, float(k_scale), float(v_scale), 0)
-    _check(lib().shiftattn_kv_write(_ptr(k_new), _ptr(v_new), _ptr(slot_mapping), n, _ptr(kv_cache), ctypes.byref(a),
-                                    _stream()))
+    _check(_native().kv_write(k_new, v_new, slot_mapping, kv_cache, k_scale, v_scale))
 
 
 def prefill_workspace_bytes(num_seqs: int, total_q: int, max_q_len: int, max_seq_len: int, a: Attn) -> int:
@@ -360,26 +309,21 @@ def decode_workspace_bytes(num_seqs: int, max_seq_len: int, a: Attn) -> int:
     return int(lib().shiftattn_decode_workspace_bytes(num_seqs, max_seq_len, ctypes.byref(a)))
 
 
+def _workspace(need: int, like: torch.Tensor) -> Optional[torch.Tensor]:
+    return torch.empty(need, dtype=torch.uint8, device=like.device) if need else None
+
+
 def prefill(q: torch.Tensor, kv_cache: torch.Tensor, block_table: torch.Tensor, cu_seqlens_q: torch.Tensor,
             seq_lens: torch.Tensor, max_q_len: int, max_seq_len: int, out: torch.Tensor, softmax_scale: float,
             k_new: Optional[torch.Tensor] = None, v_new: Optional[torch.Tensor] = None,
             slot_mapping: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None, k_scale: float = 1.0,
             v_scale: float = 1.0) -> None:
     """Causal attention of prefill chunks; q/out [total_q, hq_l, D] (row-strided views allowed)."""
-    shape = q.shape
-    total_q, num_seqs = shape[0], seq_lens.shape[0]
-    assert cu_seqlens_q.dtype == torch.int32 and seq_lens.dtype == torch.int32 and cu_seqlens_q.shape[0] == num_seqs + 1
-    assert out.shape == shape and out.dtype == q.dtype
-    a = attn_desc(q, kv_cache, block_table, softmax_scale, k_new, out, k_scale, v_scale)
     if workspace is None:
-        need = prefill_workspace_bytes(num_seqs, total_q, max_q_len, max_seq_len, a)
-        if need:
-            workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
-    ws_bytes = 0 if workspace is None else workspace.nbytes
-    _check(lib().shiftattn_prefill(_ptr(q), _ptr(k_new), _ptr(v_new), _ptr(slot_mapping), _ptr(kv_cache),
-                                   _ptr(block_table), _ptr(cu_seqlens_q), _ptr(seq_lens), num_seqs, total_q,
-                                   max_q_len, max_seq_len, _ptr(out), _ptr(workspace), ws_bytes, ctypes.byref(a),
-                                   _stream()))
+        a = attn_desc(q, kv_cache, block_table, softmax_scale, k_new, out, k_scale, v_scale)
+        workspace = _workspace(prefill_workspace_bytes(seq_lens.shape[0], q.shape[0], max_q_len, max_seq_len, a), q)
+    _check(_native().prefill(q, kv_cache, block_table, cu_seqlens_q, seq_lens, max_q_len, max_seq_len, out, softmax_scale, k_new, v_new,
+                             slot_mapping, workspace, k_scale, v_scale))
 
 
 def decode(q: torch.Tensor, kv_cache: torch.Tensor, block_table: torch.Tensor, seq_lens: torch.Tensor,
@@ -387,19 +331,11 @@ def decode(q: torch.Tensor, kv_cache: torch.Tensor, block_table: torch.Tensor, s
            v_new: Optional[torch.Tensor] = None, slot_mapping: Optional[torch.Tensor] = None,
            workspace: Optional[torch.Tensor] = None, k_scale: float = 1.0, v_scale: float = 1.0) -> None:
     """One new token per sequence; q/out [num_seqs, hq_l, D]."""
-    shape = q.shape
-    num_seqs = shape[0]
-    assert seq_lens.dtype == torch.int32 and seq_lens.shape[0] == num_seqs
-    assert out.shape == shape and out.dtype == q.dtype
-    a = attn_desc(q, kv_cache, block_table, softmax_scale, k_new, out, k_scale, v_scale)
     if workspace is None:
-        need = decode_workspace_bytes(num_seqs, max_seq_len, a)
-        if need:
-            workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
-    ws_bytes = 0 if workspace is None else workspace.nbytes
-    _check(lib().shiftattn_decode(_ptr(q), _ptr(k_new), _ptr(v_new), _ptr(slot_mapping), _ptr(kv_cache),
-                                  _ptr(block_table), _ptr(seq_lens), num_seqs, max_seq_len, _ptr(out),
-                                  _ptr(workspace), ws_bytes, ctypes.byref(a), _stream()))
+        a = attn_desc(q, kv_cache, block_table, softmax_scale, k_new, out, k_scale, v_scale)
+        workspace = _workspace(decode_workspace_bytes(q.shape[0], max_seq_len, a), q)
+    _check(_native().decode(q, kv_cache, block_table, seq_lens, max_seq_len, out, softmax_scale, k_new, v_new, slot_mapping, workspace,
+                            k_scale, v_scale))
 
 
 STATIC_SCRATCH_BYTES = 16 << 20
@@ -410,14 +346,8 @@ def decode_static(q: torch.Tensor, kv_cache: torch.Tensor, block_table: torch.Te
                   v_new: Optional[torch.Tensor] = None, slot_mapping: Optional[torch.Tensor] = None, k_scale: float = 1.0,
                   v_scale: float = 1.0) -> None:
     """decode() without a workspace: the library's own static device array takes the split partials."""
-    shape = q.shape
-    num_seqs = shape[0]
-    assert seq_lens.dtype == torch.int32 and seq_lens.shape[0] == num_seqs
-    assert out.shape == shape and out.dtype == q.dtype
-    a = attn_desc(q, kv_cache, block_table, softmax_scale, k_new, out, k_scale, v_scale)
-    _check(lib().shiftattn_decode_static(_ptr(q), _ptr(k_new), _ptr(v_new), _ptr(slot_mapping), _ptr(kv_cache),
-                                         _ptr(block_table), _ptr(seq_lens), num_seqs, max_seq_len, _ptr(out),
-                                         ctypes.byref(a), _stream()))
+    _check(_native().decode_static(q, kv_cache, block_table, seq_lens, max_seq_len, out, softmax_scale, k_new, v_new, slot_mapping, None,
+                                   k_scale, v_scale))
 
 
 def mixed_workspace_bytes(num_prefill_seqs: int, total_prefill_q: int, max_q_len: int, max_prefill_seq_len: int,
@@ -433,22 +363,13 @@ def mixed(q: torch.Tensor, kv_cache: torch.Tensor, block_table: torch.Tensor, cu
           workspace: Optional[torch.Tensor] = None, k_scale: float = 1.0, v_scale: float = 1.0) -> None:
     """Unified batch: the first num_prefill_seqs sequences are chunks (cu_seqlens_q [num_prefill_seqs + 1]), the
     others carry one row each; q/out hold the chunk rows first, then the decode rows."""
-    num_decode_seqs = seq_lens.shape[0] - num_prefill_seqs
-    total_prefill_q = q.shape[0] - num_decode_seqs
-    assert num_decode_seqs >= 0 and total_prefill_q >= 0 and cu_seqlens_q.shape[0] == num_prefill_seqs + 1
-    assert cu_seqlens_q.dtype == torch.int32 and seq_lens.dtype == torch.int32
-    assert out.shape == q.shape and out.dtype == q.dtype and block_table.shape[0] == seq_lens.shape[0]
-    a = attn_desc(q, kv_cache, block_table, softmax_scale, k_new, out, k_scale, v_scale)
     if workspace is None:
-        need = mixed_workspace_bytes(num_prefill_seqs, total_prefill_q, max_q_len, max_prefill_seq_len, num_decode_seqs,
-                                     max_decode_seq_len, a)
-        if need:
-            workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
-    ws_bytes = 0 if workspace is None else workspace.nbytes
-    _check(lib().shiftattn_mixed(_ptr(q), _ptr(k_new), _ptr(v_new), _ptr(slot_mapping), _ptr(kv_cache), _ptr(block_table),
-                                 _ptr(cu_seqlens_q), _ptr(seq_lens), num_prefill_seqs, total_prefill_q, max_q_len,
-                                 max_prefill_seq_len, num_decode_seqs, max_decode_seq_len, _ptr(out), _ptr(workspace),
-                                 ws_bytes, ctypes.byref(a), _stream()))
+        num_decode_seqs = seq_lens.shape[0] - num_prefill_seqs
+        a = attn_desc(q, kv_cache, block_table, softmax_scale, k_new, out, k_scale, v_scale)
+        workspace = _workspace(mixed_workspace_bytes(num_prefill_seqs, q.shape[0] - num_decode_seqs, max_q_len, max_prefill_seq_len,
+                                                     num_decode_seqs, max_decode_seq_len, a), q)
+    _check(_native().mixed(q, kv_cache, block_table, cu_seqlens_q, seq_lens, num_prefill_seqs, max_q_len, max_prefill_seq_len,
+                           max_decode_seq_len, out, softmax_scale, k_new, v_new, slot_mapping, workspace, k_scale, v_scale))
 
 
 # ---- numpy <-> device helpers for tests and benchmarks (storage only) ------------------------------------

@@ -1,0 +1,97 @@
+"""What the Python binding's native calls refuse, and with which exception (no GPU work: the checks come before the launch)."""
+import os
+
+import numpy as np
+import pytest
+import torch
+
+BF, F32, U8, I32, I64 = torch.bfloat16, torch.float32, torch.uint8, torch.int32, torch.int64
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2509_16495_amd import binding
+    if not os.path.exists(binding.LIB_PATH):
+        import __graft_entry__
+        __graft_entry__.build()
+    binding.lib()
+    return binding
+
+
+def _z(*shape, dtype=BF):
+    return torch.zeros(shape, dtype=dtype)
+
+
+def _attn(**kw):
+    a = dict(q=_z(5, 4, 64), cache=_z(3, 1, 2, 16 * 64), table=_z(2, 2, dtype=I32), cu=_z(3, dtype=I32), lens=_z(2, dtype=I32), out=_z(5, 4, 64),
+             k=_z(5, 1, 64), v=_z(5, 1, 64), slots=_z(5, dtype=I64), scale=0.1)
+    a.update(kw)
+    return a
+
+
+def _prefill(B, **kw):
+    a = _attn(**kw)
+    B.prefill(a["q"], a["cache"], a["table"], a["cu"], a["lens"], 3, 32, a["out"], a["scale"], a["k"], a["v"], a["slots"], workspace=_z(64, dtype=U8))
+
+
+def _decode(B, **kw):
+    a = _attn(**{"lens": _z(5, dtype=I32), **kw})
+    B.decode(a["q"], a["cache"], a["table"], a["lens"], 32, a["out"], a["scale"], workspace=_z(64, dtype=U8))
+
+
+def _mixed(B, **kw):
+    a = _attn(**{"cu": _z(2, dtype=I32), **kw})
+    B.mixed(a["q"], a["cache"], a["table"], a["cu"], a["lens"], kw.get("chunks", 1), 4, 32, 32, a["out"], a["scale"], workspace=_z(64, dtype=U8))
+
+
+@pytest.mark.parametrize("call", [_prefill, _decode, _mixed])
+@pytest.mark.parametrize("kw,error", [
+    (dict(q=_z(5, 4, 64, dtype=torch.float16), out=_z(5, 4, 64, dtype=torch.float16), cache=_z(3, 1, 2, 1024, dtype=U8)), TypeError),
+    (dict(out=_z(5, 4, 64, dtype=F32)), AssertionError),
+    (dict(out=_z(5, 5, 64)), AssertionError),
+    (dict(q=_z(5, 64), out=_z(5, 64)), ValueError),
+    (dict(q=_z(4, 5, 64).transpose(0, 1)), AssertionError),               # heads not dense
+    (dict(cache=_z(3, 1, 2, 1000)), AssertionError),
+    (dict(cache=_z(3, 1, 2, 1024, dtype=F32)), AssertionError),
+    (dict(cache=_z(3, 1, 2, 2048)[..., ::2]), AssertionError),            # not contiguous
+    (dict(table=_z(2, 2, dtype=I64)), AssertionError),
+    (dict(table=_z(4, dtype=I32)), AssertionError),
+    (dict(lens=_z(2, dtype=I64)), AssertionError),
+    (dict(scale="x"), TypeError),
+    (dict(q=np.zeros((5, 4, 64), np.float32)), TypeError),
+])
+def test_attention_calls_refuse(B, call, kw, error):
+    with pytest.raises(error):
+        call(B, **kw)
+
+
+def test_other_calls_refuse(B):
+    with pytest.raises(AssertionError):
+        _prefill(B, cu=_z(2, dtype=I32))
+    with pytest.raises(AssertionError):
+        _prefill(B, k=_z(1, 5, 64).transpose(0, 1).expand(5, 2, 64))
+    with pytest.raises(AssertionError):
+        _mixed(B, chunks=3)
+    for args in ((_z(4, 6, 64), _z(2, 4, 3, 64), 2, 4, 2), (_z(4, 6, 64), _z(2, 4, 4, 64, dtype=F32), 2, 4, 1), (_z(4, 6, 64), _z(3, 4, 4, 64), 2, 4, 1),
+                 (_z(6, 4, 64).transpose(0, 1), _z(2, 4, 4, 64), 2, 4, 1)):
+        with pytest.raises(AssertionError):
+            B.pack_seq2head(*args)
+    with pytest.raises(TypeError):
+        B.pack_seq2head(_z(4, 6, 64), _z(2, 4, 4, 64), 2.0, 4, 1)
+    for args in ((_z(2, 4, 2, 64), _z(4, 5, 64)), (_z(2, 4, 2, 64), _z(4, 4, 64, dtype=F32)), (_z(2, 4, 2, 64), _z(4, 4, 32))):
+        with pytest.raises(AssertionError):
+            B.unpack_head2seq(*args)
+    with pytest.raises(AssertionError):
+        B.kv_write(_z(5, 1, 64), _z(5, 1, 64), _z(5, dtype=I32), _z(3, 1, 2, 1024))
+    with pytest.raises(AssertionError):
+        B.qkv_proj_pack(_z(4, 256), _z(768, 128), _z(1, 4, 6, 128), 1, 4, 1)
+    with pytest.raises(AssertionError):
+        B.unpack_o_proj(_z(1, 4, 2, 128), _z(256, 128), _z(4, 256))
+    with pytest.raises(AssertionError):
+        B.quantize_rows_fp8(_z(4, 64), _z(4, 64, dtype=U8), _z(5, dtype=F32))
+    with pytest.raises(AssertionError):
+        B.quantize_recv_fp8(_z(1, 4, 2, 128), _z(1, 4, 2, 64, dtype=U8), _z(4, dtype=F32))
+    with pytest.raises(AssertionError):
+        B.qkv_proj_pack_fp8(_z(4, 256, dtype=U8), _z(3, dtype=F32), _z(768, 256, dtype=U8), _z(768, dtype=F32), _z(1, 4, 6, 128), 1, 4, 1)
+    with pytest.raises(AssertionError):
+        B.unpack_o_proj_fp8(_z(1, 4, 2, 128, dtype=U8), _z(3, dtype=F32), _z(256, 256, dtype=U8), _z(256, dtype=F32), _z(4, 256))
