@@ -832,9 +832,12 @@ double launch_us(const TileKernel& k, bool paired, int splits, int tile_tokens, 
     if (paired) d_hi = d_lo = k.pass + heavy * step + (tiles > 1 ? k.second_pass + light * step : 0.0);
     else d_hi = k.pass + heavy * step, d_lo = k.pass + light * step;
     // A grid beyond the chip takes whole rounds of its shortest workgroup at least.  Workgroups of sequences shorter than
-    // the longest leave at once, but up to two rounds their places are not free soon enough: the dispatcher hands
-    // workgroups to shader engines in turn (measured: 204 busy of 288 workgroups took 37 us, 170 of 240 took 25).
-    const double counted = grid <= 2 * kCus ? grid : wgs;
+    // the longest leave at once, but the dispatcher hands workgroups to shader engines in turn, and up to two rounds the
+    // busy ones fit the places of one only where they leave an engine some room: four chunks of up to 392 tokens on 22459, 8
+    // heads, 194 of 400 workgroups busy 90.8 us, 242 of 500 129; of up to 110 on 19635, 16 heads, 166 of 336 56.4 and 221 of 448
+    // 82.  Held to whole rounds of the grid from where on: at 0.6 / 0.7 / 0.75 / 0.8 / 0.85 / 0.9 of the chip the choices among 320
+    // batches of 2 .. 12 sequences are 0.76 / 0.69 / 0.67 / 0.63 / 0.60 / 1.03 % slower than the best plan, 0.86 always.
+    const double counted = grid <= 2 * kCus && wgs > 0.8 * kCus ? grid : wgs;
     const double rounds = static_cast<double>(static_cast<long>((counted + kCus - 1) / kCus));
     double span = (grid > kCus ? kSlack : 1.0) * (d_hi + d_lo) / 2 * wgs / kCus;
     if (span < d_hi) span = d_hi;

@@ -74,3 +74,18 @@ def test_workspace_of_any_size_between_the_least_and_the_best(oracle, G, kv):
         torch.cuda.synchronize()
         _check(B.to_host(out), want)
         assert torch.all(ws[size:] == 0x5A)
+
+
+@pytest.mark.parametrize("last,ranges", [(199, 4), (201, 3)])
+def test_unequal_chunks_at_the_line_to_whole_rounds(oracle, G, last, ranges):
+    """Four chunks of up to 392 tokens: 204.6 and 205.1 of the 400 workgroups that four key ranges make are busy, and the
+    line lies at 204.8."""
+    from paper_2509_16495_amd import binding as B
+    seqs = [(392, 3000), (70, 2000), (141, 150), (last, 1111)]
+    case = W.make_attn_case("t", 101, "bf16", seqs, 8, 1, 128, pool_factor=1.1)
+    want = oracle.attention_case(case, oracle.cache_for_case(case))
+    cache = G.cache_for_case(case)
+    q, table = G.t(case.q, "bf16"), G.ti(case.block_table, np.int32)
+    total = sum(n for n, _ in seqs)
+    assert B.prefill_workspace_bytes(4, total, 392, 3000, B.attn_desc(q, cache, table, case.softmax_scale, None, q)) == ranges * total * 8 * 130 * 4
+    _check(G.prefill_case(case, cache), want)
