@@ -126,30 +126,55 @@ __global__ __launch_bounds__(kThreads) void kv_write_kernel(const Elem* __restri
 // write the part of each V row they own.  Every token belongs to exactly one run, so every cache
 // element is written once and every input row read once; padding rows (negative slots) start no run.
 // kFp8: the cache holds FP8 E4M3 codes (one byte per element) of x / scale instead of the bf16 values.
+// Bound: bytes for large launches, the chain of round trips for those that fit the chip at once.  Slots are therefore read
+// once, a lane each, and runs are taken from ballots over them (reading first slot and run again was a trip more), and with
+// rows_first the rows of the window are requested together with the slots.  Where runs are shifted against the windows that
+// reads rows twice (half of them on average), so launches beyond one round of the chip ask for them when the runs are known.
+// Measured, us a launch, slots read again and rows behind them -> now (aligned / shifted runs, blocks in random order): 16384
+// tokens 4.52 -> 3.84 / 5.19 -> 4.32, of two heads 6.99 -> 6.69 / 8.49 -> 6.78; 32768 tokens (2048 workgroups, the last with
+// rows_first) 7.31 -> 6.68 / 8.31 -> 7.15; without it 32768 of two heads 13.3 -> 10.3 / 14.5 -> 11.0, 600000 tokens 117.5 -> 104.1
+// / 118.5 -> 105.9 (5.9 TB/s); FP8 cache, 600000 tokens 99.0 -> 92.6.
+constexpr int64_t kRowsFirstWorkgroups = 2048;   // eight workgroups of 256 threads per CU
 template <bool kFp8>
 __global__ __launch_bounds__(kThreads) void kv_write_block_kernel(const uint16_t* __restrict__ k_new,
                                                                   const uint16_t* __restrict__ v_new,
                                                                   const int64_t* __restrict__ slots, int n_tokens,
                                                                   void* __restrict__ cache_v, int hkv_l,
-                                                                  int64_t kv_stride, float k_scale, float v_scale) {
+                                                                  int64_t kv_stride, float k_scale, float v_scale,
+                                                                  bool rows_first) {
     using CE = typename std::conditional<kFp8, uint8_t, uint16_t>::type;    // cache element
     using Piece = typename std::conditional<kFp8, u32x2, u32x4>::type;       // eight cache elements
     constexpr int D = 128, kPitch = D + 16 / sizeof(CE);  // LDS row pitch in elements: 16-byte aligned, 4-bank skew per row
     __shared__ __attribute__((aligned(16))) CE tile[kBlockSize * kPitch];
     CE* cache = static_cast<CE*>(cache_v);
     const int g = blockIdx.y;
-    const int lane16 = threadIdx.x & 15;
     const int64_t w0 = static_cast<int64_t>(blockIdx.x) * kBlockSize;
-    // which tokens of the window start a run (every wavefront computes the same 16 bits)
-    uint32_t starts;
-    {
-        const int64_t i = w0 + lane16;
-        const int64_t s = i < n_tokens ? slots[i] : -1;
-        const int64_t sp = i > 0 && i <= n_tokens ? slots[i - 1] : -2;
-        const bool st = s >= 0 && ((s % kBlockSize) == 0 || sp != s - 1);
-        starts = static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(st)) & 0xFFFFu;
+    const int t_loc = threadIdx.x >> 4, dv = threadIdx.x & 15;    // loader: token of the window, eight elements of its row
+    // the window's own rows, requested before it is known which of them start a run here
+    u32x4 k_own = {0u, 0u, 0u, 0u}, v_own = {0u, 0u, 0u, 0u};
+    if (rows_first && w0 + t_loc < n_tokens) {
+        const size_t src = static_cast<size_t>(w0 + t_loc) * kv_stride + static_cast<size_t>(g) * D + dv * 8;
+        k_own = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(k_new + src));
+        v_own = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(v_new + src));
     }
-    const int t_loc = threadIdx.x >> 4, dv = lane16;    // loader: token of the run, eight elements of its row
+    // Slots of the window and of the next one, a token per lane (every wavefront holds the same 32): bit t of `starts` says
+    // that token t of the window starts a run, bit t of `breaks` that token t does not continue the run of the one before.
+    const int64_t i_lane = w0 + (threadIdx.x & 31);
+    const int64_t s_lane = i_lane < n_tokens ? slots[i_lane] : -1;
+    uint32_t starts, breaks;
+    {
+        const int64_t sp = i_lane > 0 && i_lane < n_tokens ? slots[i_lane - 1] : -2;
+        const bool st = s_lane >= 0 && ((s_lane % kBlockSize) == 0 || sp != s_lane - 1);
+        starts = static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(st)) & 0xFFFFu;
+        breaks = static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(st || s_lane < 0));
+    }
+    auto slot_of = [&](int t) -> int64_t {   // t: uniform
+        const int lo = __builtin_amdgcn_readlane(static_cast<int>(static_cast<uint64_t>(s_lane)), t);
+        const int hi = __builtin_amdgcn_readlane(static_cast<int>(static_cast<uint64_t>(s_lane) >> 32), t);
+        return static_cast<int64_t>((static_cast<uint64_t>(static_cast<uint32_t>(hi)) << 32) | static_cast<uint32_t>(lo));
+    };
+    // tokens of the run that starts at token t of the window: at most 16, since a multiple of 16 starts the next one
+    auto run_length = [&](int t) -> int { return __builtin_ctz((breaks >> 1) >> t) + 1; };
     const int d = threadIdx.x >> 1, h = threadIdx.x & 1;  // writer of V: head-dim row, half of its 16 positions
     auto encode = [&](u32x4 x, float scale) -> Piece {
         if constexpr (kFp8) {
@@ -167,24 +192,22 @@ __global__ __launch_bounds__(kThreads) void kv_write_block_kernel(const uint16_t
             return x;
         }
     };
-    auto run_length = [&](int64_t i0, int64_t slot0) -> int {   // tokens from i0 on that continue slot0 inside its block
-        const int64_t i = i0 + lane16;
-        const bool cont = static_cast<int>(slot0 % kBlockSize) + lane16 < kBlockSize && i < n_tokens && slots[i] == slot0 + lane16;
-        const uint32_t m = static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(cont)) & 0xFFFFu;
-        return __builtin_ctz(~m);
-    };
-    auto write_run = [&](int64_t i0, int64_t slot0, int len) {   // tokens i0 .. i0 + len - 1 into slots slot0 .. of one block
+    auto write_run = [&](int t0, int64_t slot0, int len) {   // tokens t0 .. t0 + len - 1 from the window's first on, slots slot0 .. of one block
         const int off = static_cast<int>(slot0 % kBlockSize);
         const int64_t blk = slot0 / kBlockSize;
-        if (t_loc < len) {
-            const size_t src = static_cast<size_t>(i0 + t_loc) * kv_stride + static_cast<size_t>(g) * D + dv * 8;
-            // rows and cache lines are touched once by this kernel: streaming loads and stores
-            const u32x4 kvec = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(k_new + src));
-            const u32x4 vvec = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(v_new + src));
+        const int p = (t_loc - t0) & (kBlockSize - 1);   // position in the run: tokens of the window stay with their loaders
+        if (p < len) {
+            u32x4 kvec = k_own, vvec = v_own;
+            if (!rows_first || t0 + p >= kBlockSize) {
+                const size_t src = static_cast<size_t>(w0 + t0 + p) * kv_stride + static_cast<size_t>(g) * D + dv * 8;
+                // rows and cache lines are touched once by this kernel: streaming loads and stores
+                kvec = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(k_new + src));
+                vvec = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(v_new + src));
+            }
             __builtin_nontemporal_store(encode(kvec, k_scale),
                                         reinterpret_cast<Piece*>(cache + cache_part_offset(blk, g, 0, hkv_l, D) +
-                                                                 static_cast<size_t>(off + t_loc) * D + dv * 8));
-            *reinterpret_cast<Piece*>(tile + t_loc * kPitch + dv * 8) = encode(vvec, v_scale);
+                                                                 static_cast<size_t>(off + p) * D + dv * 8));
+            *reinterpret_cast<Piece*>(tile + p * kPitch + dv * 8) = encode(vvec, v_scale);
         }
         __syncthreads();
         // positions 8 h .. 8 h + 7 of V row d; position p holds token p - off of the run
@@ -206,9 +229,7 @@ __global__ __launch_bounds__(kThreads) void kv_write_block_kernel(const uint16_t
         while (starts) {   // uniform
             const int t0 = __builtin_ctz(starts);
             starts &= starts - 1;
-            const int64_t i0 = w0 + t0;
-            const int64_t slot0 = slots[i0];
-            write_run(i0, slot0, run_length(i0, slot0));
+            write_run(t0, slot_of(t0), run_length(t0));
             if (starts) __syncthreads();   // the next run reuses the tile
         }
         return;
@@ -222,9 +243,12 @@ __global__ __launch_bounds__(kThreads) void kv_write_block_kernel(const uint16_t
         const int64_t i = w0 + t_loc;
         const int64_t slot = t_loc >= t_first && i < n_tokens ? slots[i] : -1;
         if (slot >= 0) {
-            const size_t src = static_cast<size_t>(i) * kv_stride + static_cast<size_t>(g) * D + dv * 8;
-            const u32x4 kvec = *reinterpret_cast<const u32x4*>(k_new + src);
-            const u32x4 vvec = *reinterpret_cast<const u32x4*>(v_new + src);
+            u32x4 kvec = k_own, vvec = v_own;
+            if (!rows_first) {
+                const size_t src = static_cast<size_t>(i) * kv_stride + static_cast<size_t>(g) * D + dv * 8;
+                kvec = *reinterpret_cast<const u32x4*>(k_new + src);
+                vvec = *reinterpret_cast<const u32x4*>(v_new + src);
+            }
             *reinterpret_cast<Piece*>(cache + cache_part_offset(slot / kBlockSize, g, 0, hkv_l, D) +
                                       static_cast<size_t>(slot % kBlockSize) * D + dv * 8) = encode(kvec, k_scale);
             *reinterpret_cast<Piece*>(tile + t_loc * kPitch + dv * 8) = encode(vvec, v_scale);
@@ -239,11 +263,10 @@ __global__ __launch_bounds__(kThreads) void kv_write_block_kernel(const uint16_t
         if (sl >= 0)
             cache[cache_part_offset(sl / kBlockSize, g, 1, hkv_l, D) + static_cast<size_t>(dd) * kBlockSize + sl % kBlockSize] = tile[t * kPitch + dd];
     }
-    const int64_t i_last = w0 + t_last, slot_last = slots[i_last];
-    const int beyond = t_last + run_length(i_last, slot_last) - kBlockSize;   // tokens of the last run past the window
+    const int beyond = t_last + run_length(t_last) - kBlockSize;   // tokens of the last run past the window
     if (beyond > 0) {
         __syncthreads();
-        write_run(w0 + kBlockSize, slot_last + (kBlockSize - t_last), beyond);
+        write_run(kBlockSize, slot_of(t_last) + (kBlockSize - t_last), beyond);
     }
 }
 
@@ -489,6 +512,7 @@ hipError_t launch_quantize_rows_fp8(const void* x, void* codes, float* scales, i
 
 hipError_t launch_kv_write(const void* k_new, const void* v_new, const int64_t* slots, int n_tokens, void* cache,
                            const AttnShape& a, hipStream_t st) {
+    const bool rows_first = static_cast<int64_t>((n_tokens + kBlockSize - 1) / kBlockSize) * a.hkv_l <= kRowsFirstWorkgroups;
     if (a.kv_fp8()) {
         const int64_t items = static_cast<int64_t>(n_tokens) * a.hkv_l * (a.D / 8);
         if (items == 0) return hipSuccess;
@@ -497,7 +521,7 @@ hipError_t launch_kv_write(const void* k_new, const void* v_new, const int64_t* 
             dim3 g2(static_cast<unsigned>((n_tokens + kBlockSize - 1) / kBlockSize), static_cast<unsigned>(a.hkv_l));
             kv_write_block_kernel<true><<<g2, kThreads, 0, st>>>(static_cast<const uint16_t*>(k_new),
                                                                  static_cast<const uint16_t*>(v_new), slots, n_tokens, cache,
-                                                                 a.hkv_l, a.kv_stride, a.k_scale, a.v_scale);
+                                                                 a.hkv_l, a.kv_stride, a.k_scale, a.v_scale, rows_first);
         } else if (a.elem == 2)
             kv_write_fp8_kernel<uint16_t><<<grid8, kThreads, 0, st>>>(
                 static_cast<const uint16_t*>(k_new), static_cast<const uint16_t*>(v_new), slots, n_tokens,
@@ -515,7 +539,7 @@ hipError_t launch_kv_write(const void* k_new, const void* v_new, const int64_t* 
         dim3 g2(static_cast<unsigned>((n_tokens + kBlockSize - 1) / kBlockSize), static_cast<unsigned>(a.hkv_l));
         kv_write_block_kernel<false><<<g2, kThreads, 0, st>>>(static_cast<const uint16_t*>(k_new),
                                                               static_cast<const uint16_t*>(v_new), slots, n_tokens, cache,
-                                                              a.hkv_l, a.kv_stride, 1.f, 1.f);
+                                                              a.hkv_l, a.kv_stride, 1.f, 1.f, rows_first);
         return hipGetLastError();
     }
     if (a.elem == 2)

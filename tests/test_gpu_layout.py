@@ -134,6 +134,37 @@ def test_kv_write_arbitrary_slot_patterns(oracle, G, seed, fp8):
     assert B.to_host(cache).tobytes() == want.tobytes()
 
 
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("n", [512, 513])
+def test_kv_write_rows_before_slots_and_after(oracle, G, n, fp8):
+    """bf16, D=128, 64 KV heads: 2048 workgroups, the most that request their window's rows before its slots are known, and
+    one window more.  Stretches at every offset against windows and blocks, single tokens, padding; bit-exact cache."""
+    from paper_2509_16495_amd import binding as B
+    rng = np.random.Generator(np.random.PCG64(49))
+    hkv_l, D, n_blocks = 64, 128, 160
+    free = list(rng.permutation(n_blocks))
+    slots = np.empty(0, dtype=np.int64)
+    while len(slots) < n:
+        pos = int(rng.integers(0, 16)) + np.arange(int(rng.choice([1, 1, 3, 15, 16, 17, 40])))
+        blocks = [free.pop() for _ in range(pos[-1] // 16 + 1)]
+        pad = np.full(int(rng.choice([0, 0, 0, 1, 2])), -1)
+        slots = np.concatenate([slots, [blocks[q // 16] * 16 + q % 16 for q in pos], pad]).astype(np.int64)
+    slots = slots[:n]
+    k = W.f32_to_bf16_bits(rng.standard_normal((n, hkv_l, D), dtype=np.float32))
+    v = W.f32_to_bf16_bits(rng.standard_normal((n, hkv_l, D), dtype=np.float32))
+    if fp8:
+        want = oracle.new_cache(n_blocks, hkv_l, 16, D, "fp8_e4m3", fill_byte=0x7F)
+        oracle.kv_write_fp8(want, k, v, slots, 16, "bf16", 0.037, 0.021)
+        cache = G.new_cache_fp8(n_blocks, hkv_l, D, fill_byte=0x7F)
+        G.kv_write(cache, k, v, slots, "bf16", fp8_scales=(0.037, 0.021))
+    else:
+        want = oracle.new_cache(n_blocks, hkv_l, 16, D, "bf16", fill_byte=0x7F)
+        oracle.kv_write(want, k, v, slots, 16, "bf16")
+        cache = G.new_cache(n_blocks, hkv_l, D, "bf16", fill_byte=0x7F)
+        G.kv_write(cache, k, v, slots, "bf16")
+    assert B.to_host(cache).tobytes() == want.tobytes()
+
+
 @pytest.mark.parametrize("sp,tp,H,H_kv", [(3, 2, 12, 6), (8, 1, 32, 4), (4, 2, 16, 8), (4, 2, 40, 8)])
 def test_sp_cache_equals_tp_cache_on_gpu(oracle, G, sp, tp, H, H_kv):
     """KV-cache invariance through the GPU kernels: pack -> exchange -> fused KV write in SP mode
