@@ -137,8 +137,9 @@ inline double longest_chunk_equivalents(int num_seqs, int total_q, int max_q_len
 // for a long prompt among short ones (measured: one 4096-token prompt with seven of 700 tokens took twice the time of
 // the long prompt alone).  Batches whose chunks are not near equal, and whose (sequence, head) count is a multiple of
 // four (a sequence then sees one or two dies), therefore rotate the (sequence, head) index from one (tile rank, key range)
-// to the next (rotation() in tile_order.h), so that a die meets all of them; other counts spread by
-// themselves, and rotating them only costs L2 hits.  Near equal is 0.9 of the longest (between 0.9 and 0.98 twelve
+// to the next (rotation() in tile_order.h), so that a die meets all of them; odd counts spread by
+// themselves, and rotating them only costs L2 hits.  Counts of two more than a multiple of four do not rotate either, though with one
+// head a sequence then sees every second die only: plans of such batches are priced for that (launch_us() in prefill_mfma.hip).  Near equal is 0.9 of the longest (between 0.9 and 0.98 twelve
 // (sequence, head) or more were 3 to 5 % slower rotated), 0.98 where there are four, each on two dies only (21 batches between 0.9
 // and 0.98 1.8 % faster, two of 6754 and 5424 tokens x 2 heads 367 -> 318 us).  Fifty unified batches of unequal chunks, decode
 // rows beside them, took 5 % longer without a rotation (up to twice the time).

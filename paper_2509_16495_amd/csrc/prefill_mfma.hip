@@ -832,12 +832,23 @@ double launch_us(const TileKernel& k, bool paired, int splits, int tile_tokens, 
     if (paired) d_hi = d_lo = k.pass + heavy * step + (tiles > 1 ? k.second_pass + light * step : 0.0);
     else d_hi = k.pass + heavy * step, d_lo = k.pass + light * step;
     // A grid beyond the chip takes whole rounds of its shortest workgroup at least.  Workgroups of sequences shorter than
-    // the longest leave at once, but the dispatcher hands workgroups to shader engines in turn, and up to two rounds the
-    // busy ones fit the places of one only where they leave an engine some room: four chunks of up to 392 tokens on 22459, 8
-    // heads, 194 of 400 workgroups busy 90.8 us, 242 of 500 129; of up to 110 on 19635, 16 heads, 166 of 336 56.4 and 221 of 448
-    // 82.  Held to whole rounds of the grid from where on: at 0.6 / 0.7 / 0.75 / 0.8 / 0.85 / 0.9 of the chip the choices among 320
-    // batches of 2 .. 12 sequences are 0.76 / 0.69 / 0.67 / 0.63 / 0.60 / 1.03 % slower than the best plan, 0.86 always.
-    const double counted = grid <= 2 * kCus && wgs > 0.8 * kCus ? grid : wgs;
+    // the longest leave at once, but the dispatcher hands workgroups to the 32 shader engines in turn, and up to two rounds the
+    // busy ones fit the places of one only where no engine gets more than its eight: of 320 batches of 2 .. 12 unequal chunks those
+    // with at most seven on the fullest engine took 0.9 of the time of the plan priced by whole rounds, those with nine or more 1.2
+    // to 1.4 of it (six chunks of 19 to 95 tokens, 5 heads, ten ranges: all 300 workgroups busy, 1.39).  Busy are a sequence's own tiles,
+    // its ragged last one among them, so n tokens are counted as n / tile + 1.
+    const double rest = num_seqs > 1 ? (total_q - max_q_len) / (num_seqs - 1.0) : 0.0;
+    double other = rest / tile_tokens + 1.0;   // tiles of a sequence but the longest, the ragged one among them
+    if (other > tiles) other = tiles;
+    const double other_ranks = paired ? (other + 1.0) / 2 : other;
+    double busy = (ranks + (num_seqs - 1) * other_ranks) * heads * splits;
+    // Where nothing rotates and the (sequence, head) count is even, the workgroups of one (sequence, head) see every second engine
+    // (375 + 123 tokens on 29041, 8 heads: 144 workgroups of the long chunk on 128 compute units 132 us, 120 91).
+    if ((static_cast<long>(num_seqs) * heads) % 2 == 0 && heads % 2 != 0 && !rotate_sequences_over_dies(num_seqs, heads, total_q, max_q_len))
+        busy += (ranks - other_ranks) * splits;
+    // Held to whole rounds of the grid from where on: at 0.7 / 0.75 / 0.8 / 0.85 / 0.9 / 0.95 of the chip the choices among 350 batches for
+    // which it matters are 9.3 / 8.5 / 7.5 / 6.1 / 8.0 / 9.1 % slower than the best plan, 10.3 always.
+    const double counted = grid <= 2 * kCus && busy > 0.85 * kCus ? grid : wgs;
     const double rounds = static_cast<double>(static_cast<long>((counted + kCus - 1) / kCus));
     double span = (grid > kCus ? kSlack : 1.0) * (d_hi + d_lo) / 2 * wgs / kCus;
     if (span < d_hi) span = d_hi;

@@ -118,6 +118,27 @@ def test_launch_plans_follow_the_shape_of_the_batch(B):
                     assert need == 0, (rows, feats, kk)
 
 
+@pytest.mark.parametrize("lens,cached,hq,hkv,tile", [
+    ([58, 177], 7559, 8, 1, 16), ([222, 85], 8071, 8, 1, 16), ([533, 129], 2897, 4, 1, 32), ([88, 14], 12938, 8, 1, 16),
+])
+def test_two_unequal_chunks_fit_the_dies_they_run_on(B, lens, cached, hq, hkv, tile):
+    """With two (sequence, head) every second die is one sequence's: the long chunk's workgroups are planned for 128 of the
+    256 compute units, one round of them."""
+    a = _attn(B, num_q_heads=hq, num_kv_heads=hkv, max_blocks_per_seq=(max(lens) + cached + 15) // 16)
+    ranges = B.prefill_workspace_bytes(2, sum(lens), max(lens), max(lens) + cached, a) // (sum(lens) * hq * 130 * 4)
+    assert 1 < ranges and ranges * ((max(lens) + tile - 1) // tile) <= 128
+
+
+@pytest.mark.parametrize("lens,cached,hq,hkv", [
+    ([9, 33, 51, 36, 20, 48, 37], 3715, 5, 1), ([35, 31, 35, 5, 24, 8], 1112, 10, 2), ([18, 63, 3, 57, 24, 30, 7, 34, 42, 20], 5990, 5, 1),
+])
+def test_chunks_shorter_than_a_tile_count_as_busy(B, lens, cached, hq, hkv):
+    """Every chunk fits one 128-token tile, so every workgroup of every key range has work: one round of 256."""
+    a = _attn(B, num_q_heads=hq, num_kv_heads=hkv, max_blocks_per_seq=(max(lens) + cached + 15) // 16)
+    ranges = B.prefill_workspace_bytes(len(lens), sum(lens), max(lens), max(lens) + cached, a) // (sum(lens) * hq * 130 * 4)
+    assert 1 < ranges and ranges * len(lens) * hq <= 256
+
+
 def test_struct_layouts_match_header(B):
     assert ctypes.sizeof(B.Xchg) == 20
     assert ctypes.sizeof(B.Attn) == 72 and B.Attn.q_stride.offset == 32 and B.Attn.kv_format.offset == 56

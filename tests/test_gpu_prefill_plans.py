@@ -76,10 +76,10 @@ def test_workspace_of_any_size_between_the_least_and_the_best(oracle, G, kv):
         assert torch.all(ws[size:] == 0x5A)
 
 
-@pytest.mark.parametrize("last,ranges", [(199, 4), (201, 3)])
+@pytest.mark.parametrize("last,ranges", [(211, 4), (212, 3)])
 def test_unequal_chunks_at_the_line_to_whole_rounds(oracle, G, last, ranges):
-    """Four chunks of up to 392 tokens: 204.6 and 205.1 of the 400 workgroups that four key ranges make are busy, and the
-    line lies at 204.8."""
+    """Four chunks of up to 392 tokens: of the 400 workgroups that four key ranges make 217.5 and 217.8 count as busy, and
+    the line lies at 217.6."""
     from paper_2509_16495_amd import binding as B
     seqs = [(392, 3000), (70, 2000), (141, 150), (last, 1111)]
     case = W.make_attn_case("t", 101, "bf16", seqs, 8, 1, 128, pool_factor=1.1)
