@@ -16,7 +16,9 @@ from typing import Optional
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
-LIB_PATH = os.environ.get("SHIFTATTN_LIB") or os.path.join(_HERE, "libshiftattn.so")  # the variable names another build
+# The variable names another build of the library, of the same interface (include/shiftattn.h); the calls are always the package's.
+LIB_PATH = os.environ.get("SHIFTATTN_LIB") or os.path.join(_HERE, "libshiftattn.so")
+CALLS_PATH = os.path.join(_HERE, "_calls.so")
 
 OK, EINVAL, EUNSUPPORTED, EWORKSPACE, EHIP = 0, -1, -2, -3, -4
 BF16, F32 = 0, 1
@@ -48,18 +50,19 @@ KV_SAME, KV_FP8_E4M3 = 0, 1
 
 _lib: Optional[ctypes.CDLL] = None
 _calls = None  # csrc/python_calls.cpp, bound to _lib
-# the functions that _calls takes the addresses of, in its order
-_BOUND = ("pack_seq2head", "unpack_head2seq", "prefill", "decode", "decode_static", "mixed", "kv_write", "qkv_proj_pack_ws",
-          "unpack_o_proj_ws", "qkv_proj_pack", "unpack_o_proj", "qkv_proj_pack_fp8_ws", "unpack_o_proj_fp8_ws", "quantize_rows_fp8",
-          "quantize_recv_fp8")
+
+
+def is_built() -> bool:
+    return os.path.exists(LIB_PATH) and os.path.exists(CALLS_PATH)
 
 
 def lib() -> ctypes.CDLL:
     """The loaded C library.  Raises if it was never built: there is no other implementation."""
     global _lib, _calls
     if _lib is None:
-        if not os.path.exists(LIB_PATH):
-            raise RuntimeError(f"{LIB_PATH} is missing: build it with `python -m paper_2509_16495_amd.build`")
+        for path in (LIB_PATH, CALLS_PATH):
+            if not os.path.exists(path):
+                raise RuntimeError(f"{path} is missing: build it with `python -m paper_2509_16495_amd.build`")
         L = ctypes.CDLL(LIB_PATH)
         vp, i32, i64p, sz = ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p, ctypes.c_size_t
         xp, ap = ctypes.POINTER(Xchg), ctypes.POINTER(Attn)
@@ -107,7 +110,7 @@ def lib() -> ctypes.CDLL:
         L.shiftattn_get_option.restype = i32
         L.shiftattn_last_error.restype = ctypes.c_char_p
         _calls = importlib.import_module("._calls", __package__)
-        _calls.bind(*[ctypes.cast(getattr(L, "shiftattn_" + name), ctypes.c_void_p).value for name in _BOUND])
+        _calls.bind(*[ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in _calls.names])
         _lib = L
     return _lib
 

@@ -16,24 +16,18 @@
 
 namespace {
 
-// the library's functions, in the order in which binding.py passes their addresses
+// the library's functions: one list for the pointers, the names that binding.py looks them up by, and their order in bind()
+#define SHIFTATTN_FUNCTIONS(F)                                                                                         \
+    F(pack, pack_seq2head) F(unpack, unpack_head2seq) F(prefill, prefill) F(decode, decode) F(decode_static, decode_static) \
+    F(mixed, mixed) F(kv_write, kv_write) F(qkv, qkv_proj_pack_ws) F(o_proj, unpack_o_proj_ws) F(qkv_plain, qkv_proj_pack)   \
+    F(o_proj_plain, unpack_o_proj) F(qkv_fp8, qkv_proj_pack_fp8_ws) F(o_proj_fp8, unpack_o_proj_fp8_ws)                      \
+    F(quantize_rows, quantize_rows_fp8) F(quantize_recv, quantize_recv_fp8)
 struct Library {
-    decltype(&shiftattn_pack_seq2head) pack;
-    decltype(&shiftattn_unpack_head2seq) unpack;
-    decltype(&shiftattn_prefill) prefill;
-    decltype(&shiftattn_decode) decode;
-    decltype(&shiftattn_decode_static) decode_static;
-    decltype(&shiftattn_mixed) mixed;
-    decltype(&shiftattn_kv_write) kv_write;
-    decltype(&shiftattn_qkv_proj_pack_ws) qkv;
-    decltype(&shiftattn_unpack_o_proj_ws) o_proj;
-    decltype(&shiftattn_qkv_proj_pack) qkv_plain;
-    decltype(&shiftattn_unpack_o_proj) o_proj_plain;
-    decltype(&shiftattn_qkv_proj_pack_fp8_ws) qkv_fp8;
-    decltype(&shiftattn_unpack_o_proj_fp8_ws) o_proj_fp8;
-    decltype(&shiftattn_quantize_rows_fp8) quantize_rows;
-    decltype(&shiftattn_quantize_recv_fp8) quantize_recv;
+#define SHIFTATTN_POINTER(member, name) decltype(&shiftattn_##name) member;
+    SHIFTATTN_FUNCTIONS(SHIFTATTN_POINTER)
 };
+#define SHIFTATTN_NAME(member, name) "shiftattn_" #name,
+constexpr const char* kNames[] = {SHIFTATTN_FUNCTIONS(SHIFTATTN_NAME)};
 constexpr Py_ssize_t kFunctions = sizeof(Library) / sizeof(void*);
 Library lib{};
 
@@ -389,4 +383,19 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_calls", nullptr, -1, methods, nul
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__calls() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__calls() {
+    PyObject* m = PyModule_Create(&module);
+    PyObject* names = PyTuple_New(kFunctions);
+    if (m && names) {
+        bool ok = true;
+        for (Py_ssize_t i = 0; i < kFunctions; ++i) {
+            PyObject* name = PyUnicode_FromString(kNames[i]);
+            ok = ok && name;
+            PyTuple_SET_ITEM(names, i, name);
+        }
+        if (ok && PyModule_AddObject(m, "names", names) == 0) return m;   // (takes the reference)
+    }
+    Py_XDECREF(names);
+    Py_XDECREF(m);
+    return nullptr;
+}

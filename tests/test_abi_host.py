@@ -15,7 +15,7 @@ HEADER = os.path.join(ROOT, "include", "shiftattn.h")
 @pytest.fixture(scope="module")
 def B():
     from paper_2509_16495_amd import binding
-    if not os.path.exists(binding.LIB_PATH):
+    if not binding.is_built():
         from paper_2509_16495_amd import build
         build.build_library()
     binding.lib()

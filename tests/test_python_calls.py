@@ -11,7 +11,7 @@ BF, F32, U8, I32, I64 = torch.bfloat16, torch.float32, torch.uint8, torch.int32,
 @pytest.fixture(scope="module")
 def B():
     from paper_2509_16495_amd import binding
-    if not os.path.exists(binding.LIB_PATH):
+    if not binding.is_built():
         import __graft_entry__
         __graft_entry__.build()
     binding.lib()
@@ -95,3 +95,28 @@ def test_other_calls_refuse(B):
         B.qkv_proj_pack_fp8(_z(4, 256, dtype=U8), _z(3, dtype=F32), _z(768, 256, dtype=U8), _z(768, dtype=F32), _z(1, 4, 6, 128), 1, 4, 1)
     with pytest.raises(AssertionError):
         B.unpack_o_proj_fp8(_z(1, 4, 2, 128, dtype=U8), _z(3, dtype=F32), _z(256, 256, dtype=U8), _z(256, dtype=F32), _z(4, 256))
+
+
+def test_functions_are_matched_by_name(B):
+    """The native calls name the functions they want, in their own order; each is one that the header declares."""
+    import re
+    from paper_2509_16495_amd import _calls
+    header = open(os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "include", "shiftattn.h")).read()
+    assert len(set(_calls.names)) == len(_calls.names) >= 15
+    assert all(re.search(rf"\b{name}\s*\(", header) and hasattr(B.lib(), name) for name in _calls.names)
+
+
+@pytest.mark.parametrize("missing", ["libshiftattn.so", "_calls.so"])
+def test_a_missing_file_is_named_with_the_way_to_build_it(B, tmp_path, missing):
+    """A package with one of its two built files only (such files stay behind when the sources move on)."""
+    import subprocess
+    import sys
+    pkg = tmp_path / "paper_2509_16495_amd"
+    pkg.mkdir()
+    here = os.path.dirname(os.path.abspath(B.__file__))
+    for name in {"__init__.py", "binding.py", "libshiftattn.so", "_calls.so"} - {missing}:
+        os.symlink(os.path.join(here, name), pkg / name)
+    src = "from paper_2509_16495_amd import binding\ntry: binding.lib()\nexcept RuntimeError as e: print('RuntimeError', e)"
+    env = {k: v for k, v in os.environ.items() if k != "SHIFTATTN_LIB"}
+    out = subprocess.run([sys.executable, "-c", src], cwd=tmp_path, env={**env, "PYTHONPATH": str(tmp_path)}, capture_output=True, text=True)
+    assert out.stdout.startswith("RuntimeError") and missing in out.stdout and "paper_2509_16495_amd.build" in out.stdout, out.stdout + out.stderr
