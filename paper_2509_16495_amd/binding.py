@@ -56,6 +56,10 @@ def is_built() -> bool:
     return os.path.exists(LIB_PATH) and os.path.exists(CALLS_PATH)
 
 
+def _workspace(need: int, like: torch.Tensor) -> torch.Tensor:
+    return torch.empty(need, dtype=torch.uint8, device=like.device)
+
+
 def lib() -> ctypes.CDLL:
     """The loaded C library.  Raises if it was never built: there is no other implementation."""
     global _lib, _calls
@@ -110,7 +114,7 @@ def lib() -> ctypes.CDLL:
         L.shiftattn_get_option.restype = i32
         L.shiftattn_last_error.restype = ctypes.c_char_p
         _calls = importlib.import_module("._calls", __package__)
-        _calls.bind(*[ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in _calls.names])
+        _calls.bind(_workspace, *[ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in _calls.names])
         _lib = L
     return _lib
 
@@ -140,22 +144,12 @@ def _check(rc: int) -> None:
 
 
 # Small calls are bound by what the host does per launch, so the functions of the path hand their arguments to
-# csrc/python_calls.cpp, which checks them and calls the library, and leave the workspace query to calls that bring none
+# csrc/python_calls.cpp, which checks them and calls the library, and asks for a workspace only where a call brings none
 # (the library checks the size by itself).
 def _native():
     if _lib is None:
         lib()
     return _calls
-
-
-_DTYPE_CODES = {torch.bfloat16: BF16, torch.float32: F32}
-
-
-def _dtype_code(t: torch.Tensor) -> int:
-    code = _DTYPE_CODES.get(t.dtype)
-    if code is None:
-        raise TypeError(f"unsupported tensor dtype {t.dtype}")
-    return code
 
 
 def _ptr(t: Optional[torch.Tensor]):
@@ -168,13 +162,6 @@ if hasattr(torch._C, "_cuda_getCurrentRawStream"):
 else:
     def _stream() -> int:
         return torch.cuda.current_stream().cuda_stream
-
-
-def _row_stride(t: torch.Tensor) -> int:
-    """Elements between consecutive tokens of a [tokens, heads, D] view whose inner two dims are dense."""
-    shape, stride = t.shape, t.stride()
-    assert len(shape) == 3 and stride[2] == 1 and (shape[1] == 1 or stride[1] == shape[2]), "inner dims must be dense"
-    return stride[0] if shape[0] > 1 else shape[1] * shape[2]
 
 
 # ---- host-only helpers --------------------------------------------------------------------------
@@ -288,15 +275,7 @@ def attn_desc(q: torch.Tensor, kv_cache: torch.Tensor, block_table: torch.Tensor
               v_scale: float = 1.0) -> Attn:
     """Descriptor from tensor shapes.  kv_cache is [num_blocks, hkv_l, 2, 16*D] in q's type, or uint8 for an
     FP8 E4M3 cache (then k_scale / v_scale give the value of a code)."""
-    _, hq_l, D = q.shape
-    num_blocks, hkv_l, two, bd = kv_cache.shape
-    table, dtype, kv_dtype = block_table.shape, q.dtype, kv_cache.dtype
-    fp8 = kv_dtype == torch.uint8
-    assert two == 2 and bd == BLOCK_SIZE * D and kv_cache.is_contiguous() and (fp8 or kv_dtype == dtype)
-    assert block_table.dtype == torch.int32 and len(table) == 2 and block_table.is_contiguous()
-    return Attn(hq_l, hkv_l, D, _dtype_code(q), BLOCK_SIZE, num_blocks, table[1], softmax_scale, _row_stride(q),
-                0 if k_new is None else _row_stride(k_new), 0 if out is None else _row_stride(out),
-                KV_FP8_E4M3 if fp8 else KV_SAME, k_scale, v_scale, 0)
+    return Attn.from_buffer_copy(_native().attn_desc(q, kv_cache, block_table, softmax_scale, k_new, out, k_scale, v_scale))
 
 
 def kv_write(k_new: torch.Tensor, v_new: torch.Tensor, slot_mapping: torch.Tensor, kv_cache: torch.Tensor,
@@ -312,19 +291,12 @@ def decode_workspace_bytes(num_seqs: int, max_seq_len: int, a: Attn) -> int:
     return int(lib().shiftattn_decode_workspace_bytes(num_seqs, max_seq_len, ctypes.byref(a)))
 
 
-def _workspace(need: int, like: torch.Tensor) -> Optional[torch.Tensor]:
-    return torch.empty(need, dtype=torch.uint8, device=like.device) if need else None
-
-
 def prefill(q: torch.Tensor, kv_cache: torch.Tensor, block_table: torch.Tensor, cu_seqlens_q: torch.Tensor,
             seq_lens: torch.Tensor, max_q_len: int, max_seq_len: int, out: torch.Tensor, softmax_scale: float,
             k_new: Optional[torch.Tensor] = None, v_new: Optional[torch.Tensor] = None,
             slot_mapping: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None, k_scale: float = 1.0,
             v_scale: float = 1.0) -> None:
     """Causal attention of prefill chunks; q/out [total_q, hq_l, D] (row-strided views allowed)."""
-    if workspace is None:
-        a = attn_desc(q, kv_cache, block_table, softmax_scale, k_new, out, k_scale, v_scale)
-        workspace = _workspace(prefill_workspace_bytes(seq_lens.shape[0], q.shape[0], max_q_len, max_seq_len, a), q)
     _check(_native().prefill(q, kv_cache, block_table, cu_seqlens_q, seq_lens, max_q_len, max_seq_len, out, softmax_scale, k_new, v_new,
                              slot_mapping, workspace, k_scale, v_scale))
 
@@ -334,9 +306,6 @@ def decode(q: torch.Tensor, kv_cache: torch.Tensor, block_table: torch.Tensor, s
            v_new: Optional[torch.Tensor] = None, slot_mapping: Optional[torch.Tensor] = None,
            workspace: Optional[torch.Tensor] = None, k_scale: float = 1.0, v_scale: float = 1.0) -> None:
     """One new token per sequence; q/out [num_seqs, hq_l, D]."""
-    if workspace is None:
-        a = attn_desc(q, kv_cache, block_table, softmax_scale, k_new, out, k_scale, v_scale)
-        workspace = _workspace(decode_workspace_bytes(q.shape[0], max_seq_len, a), q)
     _check(_native().decode(q, kv_cache, block_table, seq_lens, max_seq_len, out, softmax_scale, k_new, v_new, slot_mapping, workspace,
                             k_scale, v_scale))
 
@@ -366,11 +335,6 @@ def mixed(q: torch.Tensor, kv_cache: torch.Tensor, block_table: torch.Tensor, cu
           workspace: Optional[torch.Tensor] = None, k_scale: float = 1.0, v_scale: float = 1.0) -> None:
     """Unified batch: the first num_prefill_seqs sequences are chunks (cu_seqlens_q [num_prefill_seqs + 1]), the
     others carry one row each; q/out hold the chunk rows first, then the decode rows."""
-    if workspace is None:
-        num_decode_seqs = seq_lens.shape[0] - num_prefill_seqs
-        a = attn_desc(q, kv_cache, block_table, softmax_scale, k_new, out, k_scale, v_scale)
-        workspace = _workspace(mixed_workspace_bytes(num_prefill_seqs, q.shape[0] - num_decode_seqs, max_q_len, max_prefill_seq_len,
-                                                     num_decode_seqs, max_decode_seq_len, a), q)
     _check(_native().mixed(q, kv_cache, block_table, cu_seqlens_q, seq_lens, num_prefill_seqs, max_q_len, max_prefill_seq_len,
                            max_decode_seq_len, out, softmax_scale, k_new, v_new, slot_mapping, workspace, k_scale, v_scale))
 

@@ -5,7 +5,7 @@
 // 23.3 -> 17.4 us a pass, a call over 4 sequences 12 -> 10.7, where the kernels bound it.
 //
 // The functions take what binding.py's take, positionally and complete, and return the library's status; what is refused is
-// refused with the same exceptions.  They hold no state but the library's addresses (bind()).
+// refused with the same exceptions.  They hold no state but the library's addresses and the allocator (bind()).
 #include <Python.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -21,7 +21,8 @@ namespace {
     F(pack, pack_seq2head) F(unpack, unpack_head2seq) F(prefill, prefill) F(decode, decode) F(decode_static, decode_static) \
     F(mixed, mixed) F(kv_write, kv_write) F(qkv, qkv_proj_pack_ws) F(o_proj, unpack_o_proj_ws) F(qkv_plain, qkv_proj_pack)   \
     F(o_proj_plain, unpack_o_proj) F(qkv_fp8, qkv_proj_pack_fp8_ws) F(o_proj_fp8, unpack_o_proj_fp8_ws)                      \
-    F(quantize_rows, quantize_rows_fp8) F(quantize_recv, quantize_recv_fp8)
+    F(quantize_rows, quantize_rows_fp8) F(quantize_recv, quantize_recv_fp8)                                                 \
+    F(prefill_bytes, prefill_workspace_bytes) F(decode_bytes, decode_workspace_bytes) F(mixed_bytes, mixed_workspace_bytes)
 struct Library {
 #define SHIFTATTN_POINTER(member, name) decltype(&shiftattn_##name) member;
     SHIFTATTN_FUNCTIONS(SHIFTATTN_POINTER)
@@ -30,6 +31,7 @@ struct Library {
 constexpr const char* kNames[] = {SHIFTATTN_FUNCTIONS(SHIFTATTN_NAME)};
 constexpr Py_ssize_t kFunctions = sizeof(Library) / sizeof(void*);
 Library lib{};
+PyObject* allocate = nullptr;   // binding.py's: (bytes, tensor on the device wanted) -> tensor
 
 struct Refused {
     PyObject* type;
@@ -87,7 +89,7 @@ int64_t local_kv_heads(int64_t P, int64_t h_kv) { return h_kv == 0 ? 0 : h_kv >=
 constexpr int64_t kBlock = 16;
 
 shiftattn_attn describe(const at::Tensor& q, const at::Tensor& cache, const at::Tensor& table, PyObject* scale, const at::Tensor* k_new,
-                        const at::Tensor& out, PyObject* k_scale, PyObject* v_scale) {
+                        const at::Tensor* out, PyObject* k_scale, PyObject* v_scale) {
     dims(q, 3, "q");
     dims(cache, 4, "kv_cache");
     const bool fp8 = cache.scalar_type() == at::kByte;
@@ -98,10 +100,26 @@ shiftattn_attn describe(const at::Tensor& q, const at::Tensor& cache, const at::
     a.num_q_heads = cut(q.size(1)), a.num_kv_heads = cut(cache.size(1)), a.head_dim = cut(q.size(2)), a.dtype = dtype_code(q);
     a.block_size = kBlock, a.num_blocks = cut(cache.size(0)), a.max_blocks_per_seq = cut(table.size(1));
     a.softmax_scale = real(scale);
-    a.q_stride = row_stride(q), a.kv_stride = k_new ? row_stride(*k_new) : 0, a.out_stride = row_stride(out);
+    a.q_stride = row_stride(q), a.kv_stride = k_new ? row_stride(*k_new) : 0, a.out_stride = out ? row_stride(*out) : 0;
     a.kv_format = fp8 ? SHIFTATTN_KV_FP8_E4M3 : SHIFTATTN_KV_SAME;
     a.k_scale = real(k_scale), a.v_scale = real(v_scale);
     return a;
+}
+
+// The workspace of a call: what it brings, else what the library asks for, allocated once the arguments have passed.  Where the
+// library has no size for them it refuses them, so that call goes ahead without one and names the reason.
+struct Owned {
+    PyObject* object = nullptr;
+    ~Owned() { Py_XDECREF(object); }
+};
+template <class Bytes>
+const at::Tensor* workspace(PyObject* given, PyObject* like, Owned& own, Bytes wanted) {
+    if (given != Py_None) return &tensor(given);
+    const size_t n = wanted();
+    if (n == 0 || n == SIZE_MAX) return nullptr;
+    own.object = PyObject_CallFunction(allocate, "KO", static_cast<unsigned long long>(n), like);
+    if (!own.object) throw PythonError{};
+    return &tensor(own.object);
 }
 
 // body() checks and returns the call to make, which runs without the interpreter's lock, as through ctypes
@@ -121,6 +139,8 @@ PyObject* run(Py_ssize_t given, Py_ssize_t wanted, Body body) {
     } catch (const Refused& r) {
         PyErr_SetString(r.type, r.what.c_str());
     } catch (const PythonError&) {
+    } catch (const c10::IndexError& e) {
+        PyErr_SetString(PyExc_IndexError, e.what_without_backtrace());
     } catch (const c10::Error& e) {
         PyErr_SetString(PyExc_RuntimeError, e.what_without_backtrace());
     } catch (const std::exception& e) {
@@ -131,20 +151,23 @@ PyObject* run(Py_ssize_t given, Py_ssize_t wanted, Body body) {
 
 #define SHIFTATTN_CALL(name) PyObject* name(PyObject*, PyObject* const* a, Py_ssize_t n)
 
+// the allocator of workspaces, then the addresses of `names`
 SHIFTATTN_CALL(bind) {
-    if (n != kFunctions) {
-        PyErr_Format(PyExc_TypeError, "%zd addresses wanted, not %zd", kFunctions, n);
+    if (n != 1 + kFunctions) {
+        PyErr_Format(PyExc_TypeError, "an allocator and %zd addresses wanted, not %zd arguments", kFunctions, n);
         return nullptr;
     }
     void* at[kFunctions];
-    for (Py_ssize_t i = 0; i < n; ++i) {
-        at[i] = PyLong_AsVoidPtr(a[i]);
+    for (Py_ssize_t i = 0; i < kFunctions; ++i) {
+        at[i] = PyLong_AsVoidPtr(a[1 + i]);
         if (!at[i]) {
             if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "a function of the library has no address");
             return nullptr;
         }
     }
     memcpy(&lib, at, sizeof(lib));
+    Py_INCREF(a[0]);
+    Py_XSETREF(allocate, a[0]);
     Py_RETURN_NONE;
 }
 
@@ -180,15 +203,18 @@ SHIFTATTN_CALL(unpack_head2seq) {
 // q, kv_cache, block_table, cu_seqlens_q, seq_lens, max_q_len, max_seq_len, out, softmax_scale, k_new, v_new, slot_mapping, workspace,
 // k_scale, v_scale
 SHIFTATTN_CALL(prefill) {
+    Owned own;
     return run(n, 15, [&] {
         const at::Tensor &q = tensor(a[0]), &cache = tensor(a[1]), &table = tensor(a[2]), &cu = tensor(a[3]), &lens = tensor(a[4]), &out = tensor(a[7]);
-        const at::Tensor *k = tensor_or_none(a[9]), *v = tensor_or_none(a[10]), *slots = tensor_or_none(a[11]), *ws = tensor_or_none(a[12]);
+        const at::Tensor *k = tensor_or_none(a[9]), *v = tensor_or_none(a[10]), *slots = tensor_or_none(a[11]);
         const int64_t seqs = lens.size(0);
         need(cu.scalar_type() == at::kInt && lens.scalar_type() == at::kInt && cu.size(0) == seqs + 1, "cu_seqlens_q, seq_lens: int32 [num_seqs + 1], [num_seqs]");
         need(out.sizes() == q.sizes() && out.scalar_type() == q.scalar_type(), "out: shape and type of q");
-        return [d = describe(q, cache, table, a[8], k, out, a[13], a[14]), pq = ptr(q), pk = ptr(k), pv = ptr(v), ps = ptr(slots), pc = ptr(cache),
-                pt = ptr(table), pu = ptr(cu), pl = ptr(lens), seqs = cut(seqs), rows = cut(q.size(0)), mq = whole(a[5]), ms = whole(a[6]), po = ptr(out),
-                pw = ptr(ws), nw = bytes(ws), st = stream()] {
+        const shiftattn_attn d = describe(q, cache, table, a[8], k, &out, a[13], a[14]);
+        const int32_t mq = whole(a[5]), ms = whole(a[6]);
+        const at::Tensor* ws = workspace(a[12], a[0], own, [&] { return lib.prefill_bytes(cut(seqs), cut(q.size(0)), mq, ms, &d); });
+        return [d, pq = ptr(q), pk = ptr(k), pv = ptr(v), ps = ptr(slots), pc = ptr(cache), pt = ptr(table), pu = ptr(cu), pl = ptr(lens), seqs = cut(seqs),
+                rows = cut(q.size(0)), mq, ms, po = ptr(out), pw = ptr(ws), nw = bytes(ws), st = stream()] {
             return lib.prefill(pq, pk, pv, static_cast<int64_t*>(ps), pc, static_cast<int32_t*>(pt), static_cast<int32_t*>(pu), static_cast<int32_t*>(pl),
                                seqs, rows, mq, ms, po, pw, nw, &d, st);
         };
@@ -198,14 +224,18 @@ SHIFTATTN_CALL(prefill) {
 // q, kv_cache, block_table, seq_lens, max_seq_len, out, softmax_scale, k_new, v_new, slot_mapping, workspace, k_scale, v_scale; owned: the
 // library's scratch memory instead of a workspace
 PyObject* decode_call(PyObject* const* a, Py_ssize_t n, bool owned) {
+    Owned own;
     return run(n, 13, [&] {
         const at::Tensor &q = tensor(a[0]), &cache = tensor(a[1]), &table = tensor(a[2]), &lens = tensor(a[3]), &out = tensor(a[5]);
-        const at::Tensor *k = tensor_or_none(a[7]), *v = tensor_or_none(a[8]), *slots = tensor_or_none(a[9]), *ws = tensor_or_none(a[10]);
+        const at::Tensor *k = tensor_or_none(a[7]), *v = tensor_or_none(a[8]), *slots = tensor_or_none(a[9]);
         dims(q, 3, "q");
         need(lens.scalar_type() == at::kInt && lens.size(0) == q.size(0), "seq_lens: int32 [num_seqs]");
         need(out.sizes() == q.sizes() && out.scalar_type() == q.scalar_type(), "out: shape and type of q");
-        return [d = describe(q, cache, table, a[6], k, out, a[11], a[12]), pq = ptr(q), pk = ptr(k), pv = ptr(v), ps = ptr(slots), pc = ptr(cache),
-                pt = ptr(table), pl = ptr(lens), seqs = cut(q.size(0)), ms = whole(a[4]), po = ptr(out), pw = ptr(ws), nw = bytes(ws), st = stream(), owned] {
+        const shiftattn_attn d = describe(q, cache, table, a[6], k, &out, a[11], a[12]);
+        const int32_t ms = whole(a[4]);
+        const at::Tensor* ws = owned ? nullptr : workspace(a[10], a[0], own, [&] { return lib.decode_bytes(cut(q.size(0)), ms, &d); });
+        return [d, pq = ptr(q), pk = ptr(k), pv = ptr(v), ps = ptr(slots), pc = ptr(cache), pt = ptr(table), pl = ptr(lens), seqs = cut(q.size(0)), ms,
+                po = ptr(out), pw = ptr(ws), nw = bytes(ws), st = stream(), owned] {
             const auto* slot = static_cast<int64_t*>(ps);
             const auto *blocks = static_cast<int32_t*>(pt), *len = static_cast<int32_t*>(pl);
             return owned ? lib.decode_static(pq, pk, pv, slot, pc, blocks, len, seqs, ms, po, &d, st)
@@ -219,21 +249,37 @@ SHIFTATTN_CALL(decode_static) { return decode_call(a, n, true); }
 // q, kv_cache, block_table, cu_seqlens_q, seq_lens, num_prefill_seqs, max_q_len, max_prefill_seq_len, max_decode_seq_len, out, softmax_scale,
 // k_new, v_new, slot_mapping, workspace, k_scale, v_scale
 SHIFTATTN_CALL(mixed) {
+    Owned own;
     return run(n, 17, [&] {
         const at::Tensor &q = tensor(a[0]), &cache = tensor(a[1]), &table = tensor(a[2]), &cu = tensor(a[3]), &lens = tensor(a[4]), &out = tensor(a[9]);
-        const at::Tensor *k = tensor_or_none(a[11]), *v = tensor_or_none(a[12]), *slots = tensor_or_none(a[13]), *ws = tensor_or_none(a[14]);
+        const at::Tensor *k = tensor_or_none(a[11]), *v = tensor_or_none(a[12]), *slots = tensor_or_none(a[13]);
         dims(q, 3, "q");
         const int64_t chunks = whole(a[5]), rows = lens.size(0) - chunks, chunk_rows = q.size(0) - rows;
         need(rows >= 0 && chunk_rows >= 0 && cu.size(0) == chunks + 1, "cu_seqlens_q: [num_prefill_seqs + 1], one row of q per other sequence");
         need(cu.scalar_type() == at::kInt && lens.scalar_type() == at::kInt, "cu_seqlens_q, seq_lens: int32");
         need(out.sizes() == q.sizes() && out.scalar_type() == q.scalar_type() && table.size(0) == lens.size(0), "out: shape and type of q; block_table: a row per sequence");
-        return [d = describe(q, cache, table, a[10], k, out, a[15], a[16]), pq = ptr(q), pk = ptr(k), pv = ptr(v), ps = ptr(slots), pc = ptr(cache),
-                pt = ptr(table), pu = ptr(cu), pl = ptr(lens), chunks = cut(chunks), chunk_rows = cut(chunk_rows), mq = whole(a[6]), mp = whole(a[7]),
-                rows = cut(rows), md = whole(a[8]), po = ptr(out), pw = ptr(ws), nw = bytes(ws), st = stream()] {
+        const shiftattn_attn d = describe(q, cache, table, a[10], k, &out, a[15], a[16]);
+        const int32_t mq = whole(a[6]), mp = whole(a[7]), md = whole(a[8]);
+        const at::Tensor* ws = workspace(a[14], a[0], own, [&] { return lib.mixed_bytes(cut(chunks), cut(chunk_rows), mq, mp, cut(rows), md, &d); });
+        return [d, pq = ptr(q), pk = ptr(k), pv = ptr(v), ps = ptr(slots), pc = ptr(cache), pt = ptr(table), pu = ptr(cu), pl = ptr(lens),
+                chunks = cut(chunks), chunk_rows = cut(chunk_rows), mq, mp, rows = cut(rows), md, po = ptr(out), pw = ptr(ws), nw = bytes(ws), st = stream()] {
             return lib.mixed(pq, pk, pv, static_cast<int64_t*>(ps), pc, static_cast<int32_t*>(pt), static_cast<int32_t*>(pu), static_cast<int32_t*>(pl),
                              chunks, chunk_rows, mq, mp, rows, md, po, pw, nw, &d, st);
         };
     });
+}
+
+// q, kv_cache, block_table, softmax_scale, k_new, out, k_scale, v_scale -> the descriptor's bytes
+SHIFTATTN_CALL(attn_desc) {
+    PyObject* bytes = nullptr;
+    PyObject* done = run(n, 8, [&] {
+        const shiftattn_attn d = describe(tensor(a[0]), tensor(a[1]), tensor(a[2]), a[3], tensor_or_none(a[4]), tensor_or_none(a[5]), a[6], a[7]);
+        bytes = PyBytes_FromStringAndSize(reinterpret_cast<const char*>(&d), sizeof(d));
+        if (!bytes) throw PythonError{};
+        return [] { return 0; };
+    });
+    Py_XDECREF(done);
+    return bytes;
 }
 
 // k_new, v_new, slot_mapping, kv_cache, k_scale, v_scale
@@ -378,6 +424,7 @@ PyMethodDef methods[] = {SHIFTATTN_METHOD(bind), SHIFTATTN_METHOD(pack_seq2head)
                          SHIFTATTN_METHOD(decode), SHIFTATTN_METHOD(decode_static), SHIFTATTN_METHOD(mixed), SHIFTATTN_METHOD(kv_write),
                          SHIFTATTN_METHOD(qkv_proj_pack), SHIFTATTN_METHOD(unpack_o_proj), SHIFTATTN_METHOD(quantize_rows_fp8),
                          SHIFTATTN_METHOD(quantize_recv_fp8), SHIFTATTN_METHOD(qkv_proj_pack_fp8), SHIFTATTN_METHOD(unpack_o_proj_fp8),
+                         SHIFTATTN_METHOD(attn_desc),
                          {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_calls", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 

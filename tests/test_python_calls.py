@@ -1,4 +1,6 @@
 """What the Python binding's native calls refuse, and with which exception (no GPU work: the checks come before the launch)."""
+import contextlib
+import ctypes
 import os
 
 import numpy as np
@@ -29,23 +31,34 @@ def _attn(**kw):
     return a
 
 
-def _prefill(B, **kw):
+@contextlib.contextmanager
+def _no_allocation(B):
+    def refused(need, like):
+        pytest.fail(f"{need} bytes asked for")
+    rebind = lambda f: B._calls.bind(f, *[ctypes.cast(getattr(B.lib(), name), ctypes.c_void_p).value for name in B._calls.names])
+    rebind(refused)
+    try:
+        yield
+    finally:
+        rebind(B._workspace)
+
+
+def _prefill(B, ws=_z(64, dtype=U8), **kw):
     a = _attn(**kw)
-    B.prefill(a["q"], a["cache"], a["table"], a["cu"], a["lens"], 3, 32, a["out"], a["scale"], a["k"], a["v"], a["slots"], workspace=_z(64, dtype=U8))
+    B.prefill(a["q"], a["cache"], a["table"], a["cu"], a["lens"], 3, 32, a["out"], a["scale"], a["k"], a["v"], a["slots"], workspace=ws)
 
 
-def _decode(B, **kw):
+def _decode(B, ws=_z(64, dtype=U8), **kw):
     a = _attn(**{"lens": _z(5, dtype=I32), **kw})
-    B.decode(a["q"], a["cache"], a["table"], a["lens"], 32, a["out"], a["scale"], workspace=_z(64, dtype=U8))
+    B.decode(a["q"], a["cache"], a["table"], a["lens"], 32, a["out"], a["scale"], workspace=ws)
 
 
-def _mixed(B, **kw):
+def _mixed(B, ws=_z(64, dtype=U8), **kw):
     a = _attn(**{"cu": _z(2, dtype=I32), **kw})
-    B.mixed(a["q"], a["cache"], a["table"], a["cu"], a["lens"], kw.get("chunks", 1), 4, 32, 32, a["out"], a["scale"], workspace=_z(64, dtype=U8))
+    B.mixed(a["q"], a["cache"], a["table"], a["cu"], a["lens"], kw.get("chunks", 1), 4, 32, 32, a["out"], a["scale"], workspace=ws)
 
 
-@pytest.mark.parametrize("call", [_prefill, _decode, _mixed])
-@pytest.mark.parametrize("kw,error", [
+REFUSED = [
     (dict(q=_z(5, 4, 64, dtype=torch.float16), out=_z(5, 4, 64, dtype=torch.float16), cache=_z(3, 1, 2, 1024, dtype=U8)), TypeError),
     (dict(out=_z(5, 4, 64, dtype=F32)), AssertionError),
     (dict(out=_z(5, 5, 64)), AssertionError),
@@ -59,10 +72,31 @@ def _mixed(B, **kw):
     (dict(lens=_z(2, dtype=I64)), AssertionError),
     (dict(scale="x"), TypeError),
     (dict(q=np.zeros((5, 4, 64), np.float32)), TypeError),
-])
+]
+
+
+@pytest.mark.parametrize("call", [_prefill, _decode, _mixed])
+@pytest.mark.parametrize("kw,error", REFUSED)
 def test_attention_calls_refuse(B, call, kw, error):
     with pytest.raises(error):
         call(B, **kw)
+
+
+@pytest.mark.parametrize("call", [_prefill, _decode, _mixed])
+@pytest.mark.parametrize("kw,error", REFUSED + [(dict(lens=torch.tensor(3, dtype=I32)), IndexError)])
+def test_attention_calls_refuse_before_they_ask_for_a_workspace(B, call, kw, error):
+    """Without a workspace the refusals are the same, and nothing is allocated before them."""
+    with pytest.raises(error):
+        call(B, **kw)
+    with _no_allocation(B), pytest.raises(error):
+        call(B, ws=None, **kw)
+
+
+def test_batches_whose_counts_do_not_fit_are_refused_before_a_size_is_asked_for(B):
+    for kw in (dict(chunks=3), dict(lens=_z(9, dtype=I32), table=_z(9, 2, dtype=I32)), dict(cu=_z(3, dtype=I32)), dict(table=_z(3, 2, dtype=I32))):
+        for ws in (_z(64, dtype=U8), None):
+            with _no_allocation(B), pytest.raises(AssertionError):
+                _mixed(B, ws=ws, **kw)
 
 
 def test_other_calls_refuse(B):
@@ -120,3 +154,16 @@ def test_a_missing_file_is_named_with_the_way_to_build_it(B, tmp_path, missing):
     env = {k: v for k, v in os.environ.items() if k != "SHIFTATTN_LIB"}
     out = subprocess.run([sys.executable, "-c", src], cwd=tmp_path, env={**env, "PYTHONPATH": str(tmp_path)}, capture_output=True, text=True)
     assert out.stdout.startswith("RuntimeError") and missing in out.stdout and "paper_2509_16495_amd.build" in out.stdout, out.stdout + out.stderr
+
+
+@pytest.mark.gpu
+def test_a_size_that_the_library_does_not_have_is_left_to_its_own_refusal(B):
+    """No workspace given and none computed (head_dim 4): the library says what it refuses."""
+    t = lambda *shape, dtype=BF: torch.zeros(shape, dtype=dtype, device="cuda:0")
+    q, cache, table, lens, out = t(5, 4, 4), t(3, 1, 2, 64), t(5, 2, dtype=I32), t(5, dtype=I32), t(5, 4, 4)
+    with pytest.raises(B.ShiftAttnError, match="head_dim"):
+        B.prefill(q, cache, table, t(6, dtype=I32), lens, 3, 32, out, 0.1)
+    with pytest.raises(B.ShiftAttnError, match="head_dim"):
+        B.decode(q, cache, table, lens, 32, out, 0.1)
+    with pytest.raises(B.ShiftAttnError, match="head_dim"):
+        B.mixed(q, cache, table, t(2, dtype=I32), lens, 1, 1, 32, 32, out, 0.1)
