@@ -47,8 +47,19 @@ const at::Tensor& tensor(PyObject* o) {
     return THPVariable_Unpack(o);
 }
 const at::Tensor* tensor_or_none(PyObject* o) { return o == Py_None ? nullptr : &tensor(o); }
-void* ptr(const at::Tensor& t) { return t.data_ptr(); }
-void* ptr(const at::Tensor* t) { return t ? t->data_ptr() : nullptr; }
+// (the last check of an argument: kernels reach device memory and pinned host memory, an empty tensor has none)
+void* ptr(const at::Tensor& t) {
+    if (!t.is_cuda() && t.numel() != 0 && !(t.device().is_cpu() && t.is_pinned()))
+        throw Refused{PyExc_RuntimeError, "a tensor on the GPU is wanted, not on " + t.device().str()};
+    return t.data_ptr();
+}
+void* ptr(const at::Tensor* t) { return t ? ptr(*t) : nullptr; }
+// a workspace: its bytes in one piece
+const at::Tensor& dense(const at::Tensor& t) {
+    need(t.is_non_overlapping_and_dense(), "workspace: without gaps or overlaps");
+    return t;
+}
+const at::Tensor* dense_or_none(PyObject* o) { return o == Py_None ? nullptr : &dense(tensor(o)); }
 size_t bytes(const at::Tensor* t) { return t ? t->nbytes() : 0; }
 // (as ctypes takes them: anything with __index__ / __float__, whole numbers cut to 32 bits)
 int32_t whole(PyObject* o) {
@@ -114,12 +125,29 @@ struct Owned {
 };
 template <class Bytes>
 const at::Tensor* workspace(PyObject* given, PyObject* like, Owned& own, Bytes wanted) {
-    if (given != Py_None) return &tensor(given);
+    if (given != Py_None) return &dense(tensor(given));
+    ptr(tensor(like));   // (nothing is allocated for host tensors)
     const size_t n = wanted();
     if (n == 0 || n == SIZE_MAX) return nullptr;
     own.object = PyObject_CallFunction(allocate, "KO", static_cast<unsigned long long>(n), like);
     if (!own.object) throw PythonError{};
     return &tensor(own.object);
+}
+
+// rows that share memory: their stride of 0 would stand for dense rows in the library
+void apart(const at::Tensor& t) { need(t.size(0) <= 1 || t.stride(0) > 0, "rows must not share memory"); }
+// the rows that a call reads and writes, and those that it appends to the cache where it brings all three tensors of them (the
+// library refuses one or two)
+void rows_of(const at::Tensor& q, const at::Tensor& out, const at::Tensor* k, const at::Tensor* v, const at::Tensor* slots, const at::Tensor& cache) {
+    apart(q);
+    apart(out);
+    if (!k || !v || !slots) return;
+    apart(*k);
+    dims(*k, 3, "k_new");
+    need(k->size(0) >= q.size(0) && k->size(1) == cache.size(1) && k->size(2) == q.size(2) && k->scalar_type() == q.scalar_type(),
+         "k_new: [a row per row of q, hkv_l, D] of its type");
+    need(v->sizes() == k->sizes() && v->scalar_type() == k->scalar_type() && row_stride(*v) == row_stride(*k), "v_new: shape, type and row stride of k_new");
+    need(slots->scalar_type() == at::kLong && slots->size(0) >= q.size(0) && slots->is_contiguous(), "slot_mapping: contiguous int64, one per row of q");
 }
 
 // body() checks and returns the call to make, which runs without the interpreter's lock, as through ctypes
@@ -181,6 +209,9 @@ SHIFTATTN_CALL(pack_seq2head) {
         need(qkv.size(1) == h + 2 * static_cast<int64_t>(h_kv) && qkv.is_contiguous() && send.is_contiguous() && send.scalar_type() == qkv.scalar_type() &&
                  send.size(0) == P && send.size(3) == qkv.size(2),
              "qkv: contiguous [T, h + 2 h_kv, D], send: contiguous [P, T_pad, .., D] of its type");
+        // (heads that P ranks cannot share are the library's to refuse)
+        if (P > 0 && h % P == 0 && h_kv >= 0 && (h_kv % P == 0 || P % h_kv == 0))
+            need(send.size(2) == h / P + 2 * local_kv_heads(P, h_kv), "send: [P, T_pad, hq_l + 2 hkv_l, D]");
         return [x = exchange(P, h, h_kv, qkv.size(2), dtype_code(qkv)), in = ptr(qkv), out = ptr(send), T = cut(qkv.size(0)), T_pad = cut(send.size(1)),
                 st = stream()] { return lib.pack(in, out, T, T_pad, &x, st); };
     });
@@ -208,9 +239,12 @@ SHIFTATTN_CALL(prefill) {
         const at::Tensor &q = tensor(a[0]), &cache = tensor(a[1]), &table = tensor(a[2]), &cu = tensor(a[3]), &lens = tensor(a[4]), &out = tensor(a[7]);
         const at::Tensor *k = tensor_or_none(a[9]), *v = tensor_or_none(a[10]), *slots = tensor_or_none(a[11]);
         const int64_t seqs = lens.size(0);
-        need(cu.scalar_type() == at::kInt && lens.scalar_type() == at::kInt && cu.size(0) == seqs + 1, "cu_seqlens_q, seq_lens: int32 [num_seqs + 1], [num_seqs]");
+        need(cu.scalar_type() == at::kInt && lens.scalar_type() == at::kInt && cu.size(0) == seqs + 1 && cu.is_contiguous() && lens.is_contiguous(),
+             "cu_seqlens_q, seq_lens: contiguous int32 [num_seqs + 1], [num_seqs]");
         need(out.sizes() == q.sizes() && out.scalar_type() == q.scalar_type(), "out: shape and type of q");
         const shiftattn_attn d = describe(q, cache, table, a[8], k, &out, a[13], a[14]);
+        need(table.size(0) >= seqs, "block_table: a row per sequence");
+        rows_of(q, out, k, v, slots, cache);
         const int32_t mq = whole(a[5]), ms = whole(a[6]);
         const at::Tensor* ws = workspace(a[12], a[0], own, [&] { return lib.prefill_bytes(cut(seqs), cut(q.size(0)), mq, ms, &d); });
         return [d, pq = ptr(q), pk = ptr(k), pv = ptr(v), ps = ptr(slots), pc = ptr(cache), pt = ptr(table), pu = ptr(cu), pl = ptr(lens), seqs = cut(seqs),
@@ -229,9 +263,11 @@ PyObject* decode_call(PyObject* const* a, Py_ssize_t n, bool owned) {
         const at::Tensor &q = tensor(a[0]), &cache = tensor(a[1]), &table = tensor(a[2]), &lens = tensor(a[3]), &out = tensor(a[5]);
         const at::Tensor *k = tensor_or_none(a[7]), *v = tensor_or_none(a[8]), *slots = tensor_or_none(a[9]);
         dims(q, 3, "q");
-        need(lens.scalar_type() == at::kInt && lens.size(0) == q.size(0), "seq_lens: int32 [num_seqs]");
+        need(lens.scalar_type() == at::kInt && lens.size(0) == q.size(0) && lens.is_contiguous(), "seq_lens: contiguous int32 [num_seqs]");
         need(out.sizes() == q.sizes() && out.scalar_type() == q.scalar_type(), "out: shape and type of q");
         const shiftattn_attn d = describe(q, cache, table, a[6], k, &out, a[11], a[12]);
+        need(table.size(0) >= q.size(0), "block_table: a row per sequence");
+        rows_of(q, out, k, v, slots, cache);
         const int32_t ms = whole(a[4]);
         const at::Tensor* ws = owned ? nullptr : workspace(a[10], a[0], own, [&] { return lib.decode_bytes(cut(q.size(0)), ms, &d); });
         return [d, pq = ptr(q), pk = ptr(k), pv = ptr(v), ps = ptr(slots), pc = ptr(cache), pt = ptr(table), pl = ptr(lens), seqs = cut(q.size(0)), ms,
@@ -256,9 +292,10 @@ SHIFTATTN_CALL(mixed) {
         dims(q, 3, "q");
         const int64_t chunks = whole(a[5]), rows = lens.size(0) - chunks, chunk_rows = q.size(0) - rows;
         need(rows >= 0 && chunk_rows >= 0 && cu.size(0) == chunks + 1, "cu_seqlens_q: [num_prefill_seqs + 1], one row of q per other sequence");
-        need(cu.scalar_type() == at::kInt && lens.scalar_type() == at::kInt, "cu_seqlens_q, seq_lens: int32");
+        need(cu.scalar_type() == at::kInt && lens.scalar_type() == at::kInt && cu.is_contiguous() && lens.is_contiguous(), "cu_seqlens_q, seq_lens: contiguous int32");
         need(out.sizes() == q.sizes() && out.scalar_type() == q.scalar_type() && table.size(0) == lens.size(0), "out: shape and type of q; block_table: a row per sequence");
         const shiftattn_attn d = describe(q, cache, table, a[10], k, &out, a[15], a[16]);
+        rows_of(q, out, k, v, slots, cache);
         const int32_t mq = whole(a[6]), mp = whole(a[7]), md = whole(a[8]);
         const at::Tensor* ws = workspace(a[14], a[0], own, [&] { return lib.mixed_bytes(cut(chunks), cut(chunk_rows), mq, mp, cut(rows), md, &d); });
         return [d, pq = ptr(q), pk = ptr(k), pv = ptr(v), ps = ptr(slots), pc = ptr(cache), pt = ptr(table), pu = ptr(cu), pl = ptr(lens),
@@ -287,11 +324,14 @@ SHIFTATTN_CALL(kv_write) {
     return run(n, 6, [&] {
         const at::Tensor &k = tensor(a[0]), &v = tensor(a[1]), &slots = tensor(a[2]), &cache = tensor(a[3]);
         dims(k, 3, "k_new");
-        need(v.sizes() == k.sizes() && slots.scalar_type() == at::kLong && slots.size(0) == k.size(0) && row_stride(v) == row_stride(k),
-             "v_new: shape and row stride of k_new; slot_mapping: int64 [n_tokens]");
+        apart(k);
+        need(v.sizes() == k.sizes() && v.scalar_type() == k.scalar_type() && slots.scalar_type() == at::kLong && slots.size(0) == k.size(0) &&
+                 slots.is_contiguous() && row_stride(v) == row_stride(k),
+             "v_new: shape, type and row stride of k_new; slot_mapping: contiguous int64 [n_tokens]");
         dims(cache, 4, "kv_cache");
-        need(cache.size(1) == k.size(1) && cache.size(2) == 2 && cache.size(3) == kBlock * k.size(2) && cache.is_contiguous(),
-             "kv_cache: contiguous [num_blocks, hkv_l, 2, 16 * D]");
+        need(cache.size(1) == k.size(1) && cache.size(2) == 2 && cache.size(3) == kBlock * k.size(2) && cache.is_contiguous() &&
+                 (cache.scalar_type() == at::kByte || cache.scalar_type() == k.scalar_type()),
+             "kv_cache: contiguous [num_blocks, hkv_l, 2, 16 * D] of k_new's type or uint8");
         shiftattn_attn d{};
         d.num_q_heads = d.num_kv_heads = cut(k.size(1)), d.head_dim = cut(k.size(2)), d.dtype = dtype_code(k), d.block_size = kBlock;
         d.num_blocks = cut(cache.size(0)), d.softmax_scale = 1.0f, d.kv_stride = row_stride(k);
@@ -307,7 +347,7 @@ SHIFTATTN_CALL(kv_write) {
 SHIFTATTN_CALL(qkv_proj_pack) {
     return run(n, 7, [&] {
         const at::Tensor &x = tensor(a[0]), &w = tensor(a[1]), &send = tensor(a[2]);
-        const at::Tensor* ws = tensor_or_none(a[6]);
+        const at::Tensor* ws = dense_or_none(a[6]);
         const int64_t P = whole(a[3]), h = whole(a[4]), h_kv = whole(a[5]);
         dims(x, 2, "x");
         dims(w, 2, "w_qkv");
@@ -329,7 +369,7 @@ SHIFTATTN_CALL(qkv_proj_pack) {
 SHIFTATTN_CALL(unpack_o_proj) {
     return run(n, 4, [&] {
         const at::Tensor &recv = tensor(a[0]), &w = tensor(a[1]), &out = tensor(a[2]);
-        const at::Tensor* ws = tensor_or_none(a[3]);
+        const at::Tensor* ws = dense_or_none(a[3]);
         dims(recv, 4, "recv");
         dims(w, 2, "w_o");
         dims(out, 2, "out");
@@ -377,7 +417,7 @@ SHIFTATTN_CALL(quantize_recv_fp8) {
 SHIFTATTN_CALL(qkv_proj_pack_fp8) {
     return run(n, 9, [&] {
         const at::Tensor &x = tensor(a[0]), &xs = tensor(a[1]), &w = tensor(a[2]), &ws = tensor(a[3]), &send = tensor(a[4]);
-        const at::Tensor* work = tensor_or_none(a[8]);
+        const at::Tensor* work = dense_or_none(a[8]);
         const int64_t P = whole(a[5]), h = whole(a[6]), h_kv = whole(a[7]);
         dims(x, 2, "x_codes");
         dims(w, 2, "w_codes");
@@ -401,7 +441,7 @@ SHIFTATTN_CALL(qkv_proj_pack_fp8) {
 SHIFTATTN_CALL(unpack_o_proj_fp8) {
     return run(n, 6, [&] {
         const at::Tensor &recv = tensor(a[0]), &as = tensor(a[1]), &w = tensor(a[2]), &ws = tensor(a[3]), &out = tensor(a[4]);
-        const at::Tensor* work = tensor_or_none(a[5]);
+        const at::Tensor* work = dense_or_none(a[5]);
         dims(recv, 4, "recv_codes");
         dims(w, 2, "w_codes");
         dims(out, 2, "out");

@@ -49,13 +49,14 @@ def _prefill(B, ws=_z(64, dtype=U8), **kw):
 
 
 def _decode(B, ws=_z(64, dtype=U8), **kw):
-    a = _attn(**{"lens": _z(5, dtype=I32), **kw})
-    B.decode(a["q"], a["cache"], a["table"], a["lens"], 32, a["out"], a["scale"], workspace=ws)
+    a = _attn(**{"lens": _z(5, dtype=I32), "table": _z(5, 2, dtype=I32), **kw})
+    B.decode(a["q"], a["cache"], a["table"], a["lens"], 32, a["out"], a["scale"], a["k"], a["v"], a["slots"], workspace=ws)
 
 
 def _mixed(B, ws=_z(64, dtype=U8), **kw):
     a = _attn(**{"cu": _z(2, dtype=I32), **kw})
-    B.mixed(a["q"], a["cache"], a["table"], a["cu"], a["lens"], kw.get("chunks", 1), 4, 32, 32, a["out"], a["scale"], workspace=ws)
+    B.mixed(a["q"], a["cache"], a["table"], a["cu"], a["lens"], kw.get("chunks", 1), 4, 32, 32, a["out"], a["scale"], a["k"], a["v"],
+            a["slots"], workspace=ws)
 
 
 REFUSED = [
@@ -97,6 +98,65 @@ def test_batches_whose_counts_do_not_fit_are_refused_before_a_size_is_asked_for(
         for ws in (_z(64, dtype=U8), None):
             with _no_allocation(B), pytest.raises(AssertionError):
                 _mixed(B, ws=ws, **kw)
+
+
+def _accepted():
+    """Any call's arguments are fine but for the place they are in: the last thing asked about."""
+    return pytest.raises(RuntimeError, match="a tensor on the GPU is wanted")
+
+
+@pytest.mark.parametrize("ws", [_z(64, dtype=U8), None])
+def test_what_the_refusals_start_from_is_accepted(B, ws):
+    for call in (_prefill, _decode, _mixed):
+        with _no_allocation(B), _accepted():
+            call(B, ws=ws)
+        with _no_allocation(B), _accepted():   # more rows than are used, rows of a wider tensor, a single row of whatever stride
+            call(B, ws=ws, table=_z(9, 2, dtype=I32) if call is not _mixed else _z(2, 2, dtype=I32), q=_z(5, 6, 64)[:, :4],
+                 k=_z(7, 3, 64)[:, :1], v=_z(7, 3, 64)[:, 1:2], slots=_z(8, dtype=I64))
+
+
+@pytest.mark.parametrize("call", [_prefill, _decode, _mixed])
+@pytest.mark.parametrize("kw", [
+    dict(table=_z(1, 2, dtype=I32)),                                                           # fewer rows than sequences
+    dict(k=_z(4, 1, 64), v=_z(4, 1, 64)), dict(k=_z(5, 2, 64), v=_z(5, 2, 64)),                # fewer new rows than rows, more heads than the cache
+    dict(k=_z(5, 1, 64, dtype=F32), v=_z(5, 1, 64, dtype=F32)),
+    dict(v=_z(4, 1, 64)), dict(v=_z(5, 2, 64)[:, :1]), dict(v=_z(5, 1, 64, dtype=F32)),          # not as k_new
+    dict(slots=_z(5, dtype=I32)), dict(slots=_z(4, dtype=I64)), dict(slots=_z(10, dtype=I64)[::2]),
+    dict(q=_z(1, 4, 64).expand(5, 4, 64)), dict(k=_z(1, 1, 64).expand(5, 1, 64), v=_z(1, 1, 64).expand(5, 1, 64)),
+    dict(out=_z(1, 4, 64).expand(5, 4, 64)), dict(ws=_z(1, dtype=U8).expand(64)), dict(ws=_z(128, dtype=U8)[::2]),
+    dict(lens="every second"), dict(cu="every second"),
+])
+def test_attention_calls_refuse_what_lies_outside_their_tensors(B, call, kw):
+    sizes = {"lens": 5 if call is _decode else 2, "cu": 3 if call is _prefill else 2}
+    kw = {k: _z(2 * sizes[k], dtype=I32)[::2] if isinstance(v, str) else v for k, v in kw.items()}
+    if call is _decode and "cu" in kw:
+        return   # (takes none)
+    for ws in (_z(64, dtype=U8), None):
+        with _no_allocation(B), pytest.raises(AssertionError):
+            call(B, **{"ws": ws, **kw})
+
+
+def test_layout_calls_refuse_what_lies_outside_their_tensors(B):
+    with _accepted():
+        B.pack_seq2head(_z(4, 6, 64), _z(2, 4, 4, 64), 2, 4, 1)
+    with _accepted():
+        B.pack_seq2head(_z(4, 4, 64), _z(2, 4, 2, 64), 2, 4, 0)
+    for heads in (1, 3, 5):
+        with pytest.raises(AssertionError):
+            B.pack_seq2head(_z(4, 6, 64), _z(2, 4, heads, 64), 2, 4, 1)
+    k, slots, cache = _z(5, 1, 64), _z(5, dtype=I64), _z(3, 1, 2, 1024)
+    for good in (cache, _z(3, 1, 2, 1024, dtype=U8)):
+        with _accepted():
+            B.kv_write(k, k, slots, good)
+    for args in ((_z(5, 1, 64, dtype=F32), _z(5, 1, 64, dtype=F32), slots, cache), (k, _z(5, 1, 64, dtype=F32), slots, cache),
+                 (k, k, _z(10, dtype=I64)[::2], cache), (_z(1, 1, 64).expand(5, 1, 64), _z(1, 1, 64).expand(5, 1, 64), slots, cache)):
+        with pytest.raises(AssertionError):
+            B.kv_write(*args)
+    for ws, error in ((None, _accepted()), (_z(64, dtype=U8), _accepted()), (_z(128, dtype=U8)[::2], pytest.raises(AssertionError))):
+        with error:
+            B.qkv_proj_pack(_z(4, 256), _z(768, 256), _z(1, 4, 6, 128), 1, 4, 1, ws)
+        with error:
+            B.unpack_o_proj(_z(1, 4, 2, 128), _z(256, 256), _z(4, 256), ws)
 
 
 def test_other_calls_refuse(B):
@@ -167,3 +227,16 @@ def test_a_size_that_the_library_does_not_have_is_left_to_its_own_refusal(B):
         B.decode(q, cache, table, lens, 32, out, 0.1)
     with pytest.raises(B.ShiftAttnError, match="head_dim"):
         B.mixed(q, cache, table, t(2, dtype=I32), lens, 1, 1, 32, 32, out, 0.1)
+
+
+@pytest.mark.gpu
+def test_host_memory_is_refused_unless_the_gpu_can_reach_it(B):
+    x = torch.arange(4 * 6 * 64, dtype=torch.int32).remainder(251).to(BF).view(4, 6, 64)
+    want, send = torch.zeros((2, 4, 4, 64), dtype=BF, device="cuda:0"), torch.zeros((2, 4, 4, 64), dtype=BF, device="cuda:0")
+    B.pack_seq2head(x.to("cuda:0"), want, 2, 4, 1)
+    with _accepted():
+        B.pack_seq2head(x, send, 2, 4, 1)
+    pinned = torch.empty(x.shape, dtype=BF, pin_memory=True)
+    pinned.copy_(x)
+    B.pack_seq2head(pinned, send, 2, 4, 1)
+    assert torch.equal(send, want) and bool(want.any())
