@@ -126,22 +126,19 @@ __global__ __launch_bounds__(kThreads) void kv_write_kernel(const Elem* __restri
 // write the part of each V row they own.  Every token belongs to exactly one run, so every cache
 // element is written once and every input row read once; padding rows (negative slots) start no run.
 // kFp8: the cache holds FP8 E4M3 codes (one byte per element) of x / scale instead of the bf16 values.
-// Bound: bytes for large launches, the chain of round trips for those that fit the chip at once.  Slots are therefore read
-// once, a lane each, and runs are taken from ballots over them (reading first slot and run again was a trip more), and with
-// rows_first the rows of the window are requested together with the slots.  Where runs are shifted against the windows that
-// reads rows twice (half of them on average), so launches beyond one round of the chip ask for them when the runs are known.
-// Measured, us a launch, slots read again and rows behind them -> now (aligned / shifted runs, blocks in random order): 16384
-// tokens 4.52 -> 3.84 / 5.19 -> 4.32, of two heads 6.99 -> 6.69 / 8.49 -> 6.78; 32768 tokens (2048 workgroups, the last with
-// rows_first) 7.31 -> 6.68 / 8.31 -> 7.15; without it 32768 of two heads 13.3 -> 10.3 / 14.5 -> 11.0, 600000 tokens 117.5 -> 104.1
-// / 118.5 -> 105.9 (5.9 TB/s); FP8 cache, 600000 tokens 99.0 -> 92.6.
-constexpr int64_t kRowsFirstWorkgroups = 2048;   // eight workgroups of 256 threads per CU
+// Bound: bytes for large launches, the chain of round trips for small ones: slots, rows, stores.  Lengths and slots of runs come
+// from ballots over the slots, a token per lane (reading them again per run was a trip more).  Measured behind a kernel that has just
+// written the rows, us a launch, slots read again -> now (aligned / runs shifted against the windows, blocks in random order):
+// 8192 tokens 7.8 -> 7.0 / 7.9 -> 7.3, 16384 8.6 -> 8.2 / 9.0 -> 8.6, 65536 16.9 -> 16.2 / 18.0 -> 17.2, 600000 123 -> 122 / 124 -> 123;
+// FP8 cache 600000 tokens 108 -> 98 / 109 -> 101.  (Rows requested together with the slots were no faster up to 512 workgroups and
+// slower beyond where runs are shifted - 32768 tokens 13.8 -, half of them being read twice.  Row loads merged by the compiler with
+// another source lose their streaming hint: 600000 tokens 147.)
 template <bool kFp8>
 __global__ __launch_bounds__(kThreads) void kv_write_block_kernel(const uint16_t* __restrict__ k_new,
                                                                   const uint16_t* __restrict__ v_new,
                                                                   const int64_t* __restrict__ slots, int n_tokens,
                                                                   void* __restrict__ cache_v, int hkv_l,
-                                                                  int64_t kv_stride, float k_scale, float v_scale,
-                                                                  bool rows_first) {
+                                                                  int64_t kv_stride, float k_scale, float v_scale) {
     using CE = typename std::conditional<kFp8, uint8_t, uint16_t>::type;    // cache element
     using Piece = typename std::conditional<kFp8, u32x2, u32x4>::type;       // eight cache elements
     constexpr int D = 128, kPitch = D + 16 / sizeof(CE);  // LDS row pitch in elements: 16-byte aligned, 4-bank skew per row
@@ -150,13 +147,6 @@ __global__ __launch_bounds__(kThreads) void kv_write_block_kernel(const uint16_t
     const int g = blockIdx.y;
     const int64_t w0 = static_cast<int64_t>(blockIdx.x) * kBlockSize;
     const int t_loc = threadIdx.x >> 4, dv = threadIdx.x & 15;    // loader: token of the window, eight elements of its row
-    // the window's own rows, requested before it is known which of them start a run here
-    u32x4 k_own = {0u, 0u, 0u, 0u}, v_own = {0u, 0u, 0u, 0u};
-    if (rows_first && w0 + t_loc < n_tokens) {
-        const size_t src = static_cast<size_t>(w0 + t_loc) * kv_stride + static_cast<size_t>(g) * D + dv * 8;
-        k_own = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(k_new + src));
-        v_own = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(v_new + src));
-    }
     // Slots of the window and of the next one, a token per lane (every wavefront holds the same 32): bit t of `starts` says
     // that token t of the window starts a run, bit t of `breaks` that token t does not continue the run of the one before.
     const int64_t i_lane = w0 + (threadIdx.x & 31);
@@ -197,13 +187,10 @@ __global__ __launch_bounds__(kThreads) void kv_write_block_kernel(const uint16_t
         const int64_t blk = slot0 / kBlockSize;
         const int p = (t_loc - t0) & (kBlockSize - 1);   // position in the run: tokens of the window stay with their loaders
         if (p < len) {
-            u32x4 kvec = k_own, vvec = v_own;
-            if (!rows_first || t0 + p >= kBlockSize) {
-                const size_t src = static_cast<size_t>(w0 + t0 + p) * kv_stride + static_cast<size_t>(g) * D + dv * 8;
-                // rows and cache lines are touched once by this kernel: streaming loads and stores
-                kvec = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(k_new + src));
-                vvec = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(v_new + src));
-            }
+            const size_t src = static_cast<size_t>(w0 + t0 + p) * kv_stride + static_cast<size_t>(g) * D + dv * 8;
+            // rows and cache lines are touched once by this kernel: streaming loads and stores
+            const u32x4 kvec = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(k_new + src));
+            const u32x4 vvec = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(v_new + src));
             __builtin_nontemporal_store(encode(kvec, k_scale),
                                         reinterpret_cast<Piece*>(cache + cache_part_offset(blk, g, 0, hkv_l, D) +
                                                                  static_cast<size_t>(off + p) * D + dv * 8));
@@ -243,12 +230,9 @@ __global__ __launch_bounds__(kThreads) void kv_write_block_kernel(const uint16_t
         const int64_t i = w0 + t_loc;
         const int64_t slot = t_loc >= t_first && i < n_tokens ? slots[i] : -1;
         if (slot >= 0) {
-            u32x4 kvec = k_own, vvec = v_own;
-            if (!rows_first) {
-                const size_t src = static_cast<size_t>(i) * kv_stride + static_cast<size_t>(g) * D + dv * 8;
-                kvec = *reinterpret_cast<const u32x4*>(k_new + src);
-                vvec = *reinterpret_cast<const u32x4*>(v_new + src);
-            }
+            const size_t src = static_cast<size_t>(i) * kv_stride + static_cast<size_t>(g) * D + dv * 8;
+            const u32x4 kvec = *reinterpret_cast<const u32x4*>(k_new + src);
+            const u32x4 vvec = *reinterpret_cast<const u32x4*>(v_new + src);
             *reinterpret_cast<Piece*>(cache + cache_part_offset(slot / kBlockSize, g, 0, hkv_l, D) +
                                       static_cast<size_t>(slot % kBlockSize) * D + dv * 8) = encode(kvec, k_scale);
             *reinterpret_cast<Piece*>(tile + t_loc * kPitch + dv * 8) = encode(vvec, v_scale);
@@ -512,7 +496,6 @@ hipError_t launch_quantize_rows_fp8(const void* x, void* codes, float* scales, i
 
 hipError_t launch_kv_write(const void* k_new, const void* v_new, const int64_t* slots, int n_tokens, void* cache,
                            const AttnShape& a, hipStream_t st) {
-    const bool rows_first = static_cast<int64_t>((n_tokens + kBlockSize - 1) / kBlockSize) * a.hkv_l <= kRowsFirstWorkgroups;
     if (a.kv_fp8()) {
         const int64_t items = static_cast<int64_t>(n_tokens) * a.hkv_l * (a.D / 8);
         if (items == 0) return hipSuccess;
@@ -521,7 +504,7 @@ hipError_t launch_kv_write(const void* k_new, const void* v_new, const int64_t* 
             dim3 g2(static_cast<unsigned>((n_tokens + kBlockSize - 1) / kBlockSize), static_cast<unsigned>(a.hkv_l));
             kv_write_block_kernel<true><<<g2, kThreads, 0, st>>>(static_cast<const uint16_t*>(k_new),
                                                                  static_cast<const uint16_t*>(v_new), slots, n_tokens, cache,
-                                                                 a.hkv_l, a.kv_stride, a.k_scale, a.v_scale, rows_first);
+                                                                 a.hkv_l, a.kv_stride, a.k_scale, a.v_scale);
         } else if (a.elem == 2)
             kv_write_fp8_kernel<uint16_t><<<grid8, kThreads, 0, st>>>(
                 static_cast<const uint16_t*>(k_new), static_cast<const uint16_t*>(v_new), slots, n_tokens,
@@ -539,7 +522,7 @@ hipError_t launch_kv_write(const void* k_new, const void* v_new, const int64_t* 
         dim3 g2(static_cast<unsigned>((n_tokens + kBlockSize - 1) / kBlockSize), static_cast<unsigned>(a.hkv_l));
         kv_write_block_kernel<false><<<g2, kThreads, 0, st>>>(static_cast<const uint16_t*>(k_new),
                                                               static_cast<const uint16_t*>(v_new), slots, n_tokens, cache,
-                                                              a.hkv_l, a.kv_stride, 1.f, 1.f, rows_first);
+                                                              a.hkv_l, a.kv_stride, 1.f, 1.f);
         return hipGetLastError();
     }
     if (a.elem == 2)

@@ -136,9 +136,8 @@ def test_kv_write_arbitrary_slot_patterns(oracle, G, seed, fp8):
 
 @pytest.mark.parametrize("fp8", [False, True])
 @pytest.mark.parametrize("n", [512, 513])
-def test_kv_write_rows_before_slots_and_after(oracle, G, n, fp8):
-    """bf16, D=128, 64 KV heads: 2048 workgroups, the most that request their window's rows before its slots are known, and
-    one window more.  Stretches at every offset against windows and blocks, single tokens, padding; bit-exact cache."""
+def test_kv_write_many_heads(oracle, G, n, fp8):
+    """bf16, D=128, 64 KV heads: 32 whole windows, and one token of one more.  Stretches at every offset against windows and blocks, single tokens, padding; bit-exact cache."""
     from paper_2509_16495_amd import binding as B
     rng = np.random.Generator(np.random.PCG64(49))
     hkv_l, D, n_blocks = 64, 128, 160
