@@ -12,15 +12,13 @@ struct TileItem {
 
 // By how much the (sequence, head) index of run `t` of a rotated launch is shifted (runs of n_sh workgroups, for n_sh == 4 pairs of
 // them).  The dispatcher hands workgroup i to die i % 8 and there to shader engine (i / 8) % 4, whatever else is free, so what has
-// to meet every sequence is each of these 32 engines.  Which members of a run an engine gets repeats after `period` runs; the shift
-// grows by `period` + `extra` meanwhile, a number without a common factor with n_sh.  (By `period` alone, which is what one per
-// run gives, an engine sees one sequence of n_sh == 4 only and one in four (sequence, head) of n_sh == 8.)  130 random batches of
-// two to twelve chunks against one per run: n_sh 4 1.13 times on average, 1.7 at most (4305 + 2070 + 1321 + 5987 tokens, 8 heads
-// 240 -> 141 us), 8 1.07, 12 1.03; beyond 16 an engine sees enough of them anyway (2 % slower with it).
-[[gnu::always_inline]] constexpr inline int rotation(int t, int n_sh) {
-    const int lg = n_sh == 16 ? 1 : n_sh == 12 ? 3 : 2, extra = n_sh > 16 ? 0 : n_sh == 12 ? 3 : 1;
-    return t + extra * (t >> lg);
-}
+// to meet every sequence is each of these 32 engines.  Which members of a run an engine gets repeats after four runs; the shift
+// grows by five meanwhile, a number without a common factor with n_sh.  (By four alone, which is what one per run gives, an engine
+// sees one sequence of n_sh == 4 only and two of n_sh == 8.)  Random unequal batches against one per run: 60 of n_sh 4 0.94 of the
+// time, none slower, 0.62 at best (4305 + 2070 + 1321 + 5987 tokens, 8 heads 240 -> 141 us), 160 of n_sh 8 0.96 (14 more than 3 %
+// slower, up to 13).  Beyond 8 an engine sees enough of them by one per run: every engine shown all gave nothing for 12 (160
+// batches, 1.00) and 1.3 % more time for 16 (160, up to 1.34 times), 2 % beyond.
+[[gnu::always_inline]] constexpr inline int rotation(int t, int n_sh) { return n_sh > 8 ? t : t + (t >> 2); }
 
 // Workgroup `block` of a grid whose first `decode_wgs` workgroups take decode rows.  The ones behind them are runs of n_sh
 // workgroups, one per (sequence, head), a run for every (rank, key range).  range_major: the key ranges outermost (launches

@@ -87,9 +87,9 @@ def test_projection_tiles_load_rows_that_exist(maps, tile):
             assert maps.rows_wrong(M, M_out, tile) == 0, (M, M_out)
 
 
-@pytest.mark.parametrize("n_sh", [4, 8, 12, 16])
+@pytest.mark.parametrize("n_sh", [4, 8])
 def test_rotation_shows_every_engine_all_sequences(maps, n_sh):
-    """Workgroup i runs on die i % 8, shader engine (i / 8) % 4 of it: with a rotation each of the 32 meets every (sequence, head)
+    """Workgroup i runs on die i % 8, shader engine (i / 8) % 4 of it: with a rotation of few (sequence, head) each of the 32 meets every (sequence, head)
     about equally often, whatever decode workgroups stand in front and in either order of the grid."""
     for decode_wgs in (0, 67, 96):
         for ranks, n_splits, range_major in ((32 * n_sh, 1, 0), (8 * n_sh, 4, 0), (8 * n_sh, 4, 1)):
@@ -97,3 +97,10 @@ def test_rotation_shows_every_engine_all_sequences(maps, n_sh):
             for b in range(decode_wgs, decode_wgs + n_sh * 32 * n_sh):
                 seen[b % 32][maps.sh_of(b, decode_wgs, n_sh, ranks, n_splits, range_major, 1)] += 1
             assert min(min(x) for x in seen) >= 0.6 * n_sh and max(max(x) for x in seen) <= 1.6 * n_sh, (decode_wgs, ranks, n_splits)
+
+
+@pytest.mark.parametrize("n_sh", [12, 16, 20, 24])
+def test_rotation_of_many_goes_on_by_one_a_run(maps, n_sh):
+    """Every engine shown all of them costs more than it gives from 12 on."""
+    runs = [[maps.sh_of(r * n_sh + i, 0, n_sh, 64, 1, 0, 1) for i in range(n_sh)] for r in range(64)]
+    assert runs == [[(i - r) % n_sh for i in range(n_sh)] for r in range(64)]
