@@ -497,6 +497,11 @@ __global__ __launch_bounds__(kThreads, 2) void prefill_kernel(PrefillParams p, D
         if (n > 0) {
             // prologue: K of the first two tiles, S^T of the first
             // (K of the second is waited for behind the products on the first)
+            // (the ids are uniform; said here, or the key loop forms its addresses from vector registers, eight vector instructions
+            // more in two steps: 0.4 % of 24 kinds of batches)
+            id0 = __builtin_amdgcn_readfirstlane(id0);
+            id1 = __builtin_amdgcn_readfirstlane(id1);
+            id2 = __builtin_amdgcn_readfirstlane(id2);
             if (n > 1) {
                 load_k(block_base(id1), 1);
                 __builtin_amdgcn_s_waitcnt(0x0F74);   // vmcnt(4): all but these four

@@ -85,3 +85,27 @@ def test_kv_append_streams_the_rows_of_runs(tmp_path, fp8):
         elif inside and "global_load_dwordx4" in line:
             loads.append(line.split("//")[0].rstrip().endswith(" nt"))
     assert loads.count(True) >= 4 and loads.count(False) <= 2, loads
+
+
+def test_prefill_key_loop_forms_its_addresses_in_scalar_registers(tmp_path):
+    """128-column kernel, the steady-state loop of two tiles a trip: block ids are uniform, so their addresses cost the vector unit
+    nothing; an id that the compiler takes for different per lane moves three multiplications and the loads' bases there."""
+    out = os.path.join(str(tmp_path), "prefill.s")
+    flags = [f for f in BLD.FLAGS if f not in ("-shared", "-fPIC")]
+    subprocess.check_call(["hipcc", *flags, "--cuda-device-only", "-S", os.path.join(BLD.CSRC, "prefill_mfma.hip"), "-o", out],
+                          cwd=BLD.CSRC, stderr=subprocess.DEVNULL)
+    blocks, kernel = [], ""
+    for line in open(out):
+        m = re.match(r"^([A-Za-z_.$][\w.$]*):", line)
+        if m and not m.group(1).startswith(".L"):
+            kernel = m.group(1)
+        elif m:
+            blocks.append((kernel, []))
+        elif blocks and line.startswith("\t") and line[1:2].isalpha():
+            blocks[-1][1].append(line.split()[0])
+    loops = [i for i, (k, b) in enumerate(blocks) if "prefill_kernelILi" in k and sum("mfma" in x for x in b) >= 16 and b.count("global_load_lds_dwordx4") == 8]
+    assert len(loops) == 3, [(k, len(b)) for k, b in (blocks[i] for i in loops)]   # one of each instance
+    for i in loops:
+        for k, b in blocks[i:i + 2]:
+            assert sum("mfma" in x for x in b) >= 15
+            assert not [x for x in b if x.startswith(("v_readfirstlane", "v_readlane", "v_mul_lo_u32", "v_mad_u64_u32"))], k
