@@ -207,7 +207,7 @@ __global__ __launch_bounds__(kThreads, 2) void prefill_kernel(PrefillParams p, D
     // 1 KiB from src (wavefront-uniform, in scalar registers) + a 32-bit byte offset per lane + kImm into LDS at dst + kImm
     // (dst uniform): written as assembly so that the address is formed by the load itself (scalar base + vector offset)
     // instead of a 64-bit vector addition per load, which would cost MFMA issue time like any vector instruction.
-    // The loads are waited for with explicit vmcnt(0) waits (wait_vm0) only.
+    // The compiler does not count these loads: they are waited for explicitly, with vmcnt(0) (wait_vm0) or, where a pass begins, vmcnt(4).
     auto dma_1k = [&](const unsigned char* src, uint32_t lane_off, auto imm_c, unsigned char* dst) SHIFTATTN_INLINE {
         constexpr int kImm = decltype(imm_c)::value;
         const uint32_t m0v = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(dst));
@@ -496,15 +496,16 @@ __global__ __launch_bounds__(kThreads, 2) void prefill_kernel(PrefillParams p, D
         int barriers = 0;  // barriers this group executes in the pass; both groups must end up equal
         if (n > 0) {
             // prologue: K of the first two tiles, S^T of the first
-            // (K of the second is waited for behind the products on the first)
-            // (the ids are uniform; said here, or the key loop forms its addresses from vector registers, eight vector instructions
+            // (K of the second is waited for behind the products on the first; the ids are uniform: said here, or the key loop forms its addresses from vector registers, eight vector instructions
             // more in two steps: 0.4 % of 24 kinds of batches)
             id0 = __builtin_amdgcn_readfirstlane(id0);
             id1 = __builtin_amdgcn_readfirstlane(id1);
             id2 = __builtin_amdgcn_readfirstlane(id2);
             if (n > 1) {
                 load_k(block_base(id1), 1);
-                __builtin_amdgcn_s_waitcnt(0x0F74);   // vmcnt(4): all but these four
+                // vmcnt(4): all but these four.  Memory operations count down in the order of their issue, and the four are behind those
+                // of the first tile; whatever else is issued behind them only makes the wait a longer one.
+                __builtin_amdgcn_s_waitcnt(0x0F74);
             } else {
                 wait_vm0();
             }

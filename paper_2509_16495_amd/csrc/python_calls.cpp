@@ -1,8 +1,7 @@
 // The Python binding's calls (binding.py), natively: arguments are checked and turned into those of the C ABI here, so that a
 // small call costs the host little more than its launches.  What a call spent in Python - shapes and strides asked one by one,
 // a ctypes structure filled, nineteen ctypes arguments converted - was 2.2 us for an exchange and 4.8 us for an attention call,
-// a third of the whole call where there is little to compute.  Here it is 0.3 and 0.4; pack + fp32 prefill + unpack of 256 tokens
-// 23.3 -> 17.4 us a pass, a call over 4 sequences 12 -> 10.7, where the kernels bound it.
+// a third of the whole call where there is little to compute.  Here it is 0.3 and 0.4.
 //
 // The functions take what binding.py's take, positionally and complete, and return the library's status; what is refused is
 // refused with the same exceptions.  They hold no state but the library's addresses and the allocator (bind()).
