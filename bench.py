@@ -16,7 +16,8 @@ dominant kernel (the chunk's prefill kernel) against the chip's dense bf16 MFMA 
 call alone; `decode_in_step` prices the step's decode part against HBM bandwidth.  `cpu_baseline` is the fp64 CPU
 oracle timed on a stated row sample of the same batch.  Further objects report the other configurations (8B-shaped
 prefill batch, 70B-shaped prefill, 256-sequence decode, small decode batches, the 70B exchange, K/V append, the
-fused projections), each with its own roofline object and an oracle timing.  All timings are medians of
+fused projections), each with its own roofline object and an oracle timing, those named in DETAILS in an object on stderr so that
+the line stays short enough for records that cut long ones.  All timings are medians of
 per-call HIP-event pairs on the launch stream unless stated.  HBM traffic from hardware counters is not measured in
 this run: `traffic` repeats the figure of the profiled runs summarised in profiles/hbm_traffic.md when that table was
 measured on exactly the kernel sources of this tree (it carries their hash), and is null otherwise.
@@ -40,6 +41,11 @@ PEAK_FP8_TFLOPS = 5000.0    # MI355X dense fp8 MFMA
 PEAK_HBM_GBPS = 8000.0      # MI355X HBM3E
 SETTLE_MS = 30.0            # load applied before a timed region so that the chip's clock has settled (main(): settle)
 METRIC = "prefill attn TFLOP/s + decode KV-read GB/s per MI355X (head shard, % roofline)"
+
+
+# measured in the same run, reported on stderr
+DETAILS = ("decode_sized_projections", "decode_small_batches", "chunk_prefill_with_scaled_q", "qkv_proj_pack", "unpack_o_proj", "qkv_proj_pack_fp8",
+           "unpack_o_proj_fp8", "prefill_5q_per_kv", "prefill_unequal_prompts", "decode_kv_read_fp8")
 
 
 def log(*a):
@@ -820,6 +826,9 @@ def main() -> int:
         log(f"[bench] calibration copy: {src.numel() * 2} bytes read and written per launch of torch's elementwise kernel")
         del src, dst
 
+    # (a record of a run keeps the end of some ten KB of output; the whole line was 21)
+    details = {k: result.pop(k) for k in DETAILS if k in result}
+    log("[bench] details: " + json.dumps(details))
     print(json.dumps(result), flush=True)
     return 0
 
