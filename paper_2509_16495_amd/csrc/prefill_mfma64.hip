@@ -38,13 +38,19 @@
 // the correctly rounded value; a pass that is flagged fetches Q^T again as given.
 //
 // Pipeline of iteration j: S^T of tile j+1 (16 MFMAs), softmax of tile j, O^T += V^T P^T of tile j-1 (16 MFMAs).
-// LDS holds a ring of three stages of K (32 keys) + V^T (32 keys), tile t in stage t%3.  During iteration j
-// wavefronts 0 and 1 bring K of tile j+3 (one cache block each) and wavefronts 2 and 3 V^T of tile j+1, by
-// direct-to-LDS loads; what iteration j reads was loaded two iterations earlier and made visible by the barrier of
-// the iteration before, so operand reads and MFMAs run on across the one barrier per iteration (which sits a few
-// slots into the iteration, in front of the loads that overwrite the stage everybody has just left).  With a single
-// wavefront per SIMD every instruction of the iteration - barrier, loads, address updates, the check of the maximum -
-// takes issue time the MFMAs cannot hide behind another wavefront, so all of it is kept to a few instructions.
+// LDS holds a ring of four stages of K (32 keys) + V^T (32 keys), tile t in stage t%4, so that the four iterations of a
+// trip of the loop read and fill stages known at compile time.  During iteration j wavefronts 0 and 1 bring K of tile j+4
+// (one cache block each) and wavefronts 2 and 3 V^T of tile j+2, by direct-to-LDS loads; what iteration j reads was loaded
+// three iterations earlier and made visible by the barrier of the iteration before, so operand reads and MFMAs run on
+// across the one barrier per iteration.
+//
+// What bounds the loop.  A lone wavefront issues an instruction about every four clocks (an exponential takes eight, a
+// v_readlane nine), a 32x32x16 MFMA occupies the matrix pipe for 32: the pipe stays busy if every slot - an MFMA and what
+// follows it - asks for no more than 28 clocks besides, and if an operand read follows the MFMA of its slot instead of
+// standing in front of it (32.1 against 37.1 clocks a slot, everything else alike).  So the work is dealt to the slots
+// evenly, the addresses of the loads are kept ready in a vector register pair, and nothing is moved between register files.
+// MFMA pipe busy 59 -> 77 % of the clocks; what is left is the power limit, the clock settles at 1.76 instead of 2.05 GHz:
+// 16384 tokens of 8 heads 464 -> 424 us, 2048 tokens on 131072 cached with 64 decodes 957 -> 882.
 //
 // Scheduling: tiles of a sequence are processed in pairs (heaviest with lightest) by one workgroup; a short chunk on a
 // long context is taken one tile per workgroup, its keys split into ranges merged by launch_combine.
@@ -71,16 +77,17 @@ constexpr int kKv = 32;                        // keys per iteration
 constexpr int kKBytes = kKv * kD * 2;          // 8192: K tile, 32 rows of 256 B
 constexpr int kVBytes = kD * kKv * 2;          // 8192: V^T tile, 2 blocks of [128 rows][32 B]
 constexpr int kStageBytes = kKBytes + kVBytes; // 16384
-constexpr int kRingBytes = 3 * kStageBytes;    // 49152
+constexpr int kRingBytes = 4 * kStageBytes;    // 65536
 constexpr int kBlockBytes = kBlockSize * kD * 2;  // 4096: K (or V^T) of one cache block and head
 constexpr int kPitch = 272;                    // row pitch of the output staging tile (256 + 16 bytes)
 constexpr int kFlagBytes = 16;                 // one redo flag per wavefront
-constexpr int kLdsBytes = kRingBytes + kCols * kPitch + kFlagBytes;  // 118800
+constexpr int kIdsAt = kRingBytes + kCols * kPitch + kFlagBytes;  // two windows of 64 block ids per wavefront
+constexpr int kLdsBytes = kIdsAt + kPrefill64Waves * 2 * 64 * 4;  // 137232
 // A column's reference maximum may lag its true running maximum by this much (exp2 units): P reaches 2^32 at most, far
 // inside what bf16 and the fp32 sums hold (their relative precision does not depend on magnitude); O^T overflows only
 // for |V| beyond 2^70.
 constexpr float kRefSlack = 32.0f;
-// The first attempt at a pass uses no reference (see the top of the file): the sum of a column that sees keys must end
+// The first attempt on scaled Q^T uses no reference (see the top of the file): the sum of a column that sees keys must end
 // inside this range - its largest P then lies within a factor "number of keys" of the sum, far from bf16's denormals and
 // from overflow (O^T overflows only for |V| beyond 2^87), and every logit that matters lies within 40 + log2(keys) of
 // zero (which also bounds what a second rounding of Q^T can move).  An infinity or a NaN fails the test.
@@ -100,7 +107,7 @@ struct IC {
 #define SHIFTATTN_INLINE __attribute__((always_inline))
 #define SHIFTATTN_FORCE_INLINE inline __attribute__((always_inline))
 
-// s_waitcnt vmcnt(0) with the other counters left alone (gfx9 encoding)
+// s_waitcnt vmcnt(0) with the other counters left alone (gfx9 encoding), and all but the last four
 __device__ inline void wait_vm0() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
 // The matrix instructions are written as assembly to fix where their accumulators live: S^T in ordinary vector
@@ -129,7 +136,12 @@ __device__ SHIFTATTN_FORCE_INLINE void mfma_o_acc(f32x16& d, u32x4 a, u32x4 b) {
     if constexpr (kGuard) asm volatile("s_nop 4\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(a), "v"(b));
     else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(a), "v"(b));
 }
-__device__ SHIFTATTN_FORCE_INLINE void mfma_settle() { asm volatile("s_nop 7\n\ts_nop 7" ::: "memory"); }
+// Wait states in front of compiler-generated reads of accumulators (and of anything else in their registers): the
+// statement takes the accumulators as operands, so that they are read, or their registers used again, behind it only.
+__device__ SHIFTATTN_FORCE_INLINE void mfma_settle(f32x16 (&d)[2]) { asm volatile("s_nop 7\n\ts_nop 7" : "+v"(d[0]), "+v"(d[1])); }
+__device__ SHIFTATTN_FORCE_INLINE void mfma_settle(f32x16 (&d)[2][4]) {
+    asm volatile("s_nop 7\n\ts_nop 7" : "+a"(d[0][0]), "+a"(d[0][1]), "+a"(d[0][2]), "+a"(d[0][3]), "+a"(d[1][0]), "+a"(d[1][1]), "+a"(d[1][2]), "+a"(d[1][3]));
+}
 
 // Q^T of a lane - eight 16-byte pieces for each of its two column blocks, 32 bytes apart - from global memory straight
 // into accumulation registers, where the MFMAs take it as their B operand (a value that is born in ordinary registers
@@ -177,7 +189,6 @@ struct Prefill64Params {
     int n_splits;     // key ranges per tile
     int paired;       // tiles of a sequence taken two per workgroup (see prefill_mfma64_plan)
     int rotate;       // the (sequence, KV head) index is rotated by the (tile rank, key range) index (see internal.h)
-    int scaled_q;     // the first attempt at a pass works on Q^T times the softmax scale, rounded to bf16 again
     int max_blocks;
     float c;          // softmax_scale * log2(e) (times k_scale for a cache widened from FP8)
     float out_scale;  // multiplies the normalised output: v_scale of an FP8 cache, else 1
@@ -189,7 +200,8 @@ struct Prefill64Params {
 static_assert(kThreads == 64 * kPrefill64Waves && decode_flat::kRoleLdsBytes<kPrefill64Waves> <= kLdsBytes);
 
 // kDecode: 0 = prefill only; 1, 2 = the first workgroups take decode rows over a bf16 (1) or FP8 (2) cache
-template <int kDecode>
+// kScaledQ: the first attempt at a pass works on Q^T times the softmax scale, rounded to bf16 again
+template <int kDecode, bool kScaledQ>
 __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params p, DecodeRole dec) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     if constexpr (kDecode != 0) {
@@ -221,20 +233,16 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
     const int hi_tile = n_tiles - 1 - rank;
     if (p.paired ? rank > hi_tile : hi_tile < 0) return;  // uniform
     const int n_pass = (!p.paired || hi_tile == rank) ? 1 : 2;
-    const_i32_ptr table = (const_i32_ptr)(p.block_table + static_cast<size_t>(s) * p.max_blocks);
-    // Inside the key loop the block id of the coming iteration is fetched by a *vector* load: a scalar load shares its
-    // counter with the LDS operand reads and returns out of order with them, so while one is outstanding every wait for
-    // an operand becomes a wait for everything (measured: 5 % of the kernel).  The address is made to look per-lane
-    // (a zero the compiler cannot see through); the id is back in a scalar register by the time the loads need it.
-    const int32_t* table_v = p.block_table + static_cast<size_t>(s) * p.max_blocks;
-    int lane_zero;
-    asm volatile("v_mov_b32 %0, 0" : "=v"(lane_zero));
+    const int32_t* table = p.block_table + static_cast<size_t>(s) * p.max_blocks;
     const int last_block = (ctx - 1) / kBlockSize;
 
     // in the key loop wavefronts 0 and 1 bring K (cache block 0 / 1 of a tile), wavefronts 2 and 3 V^T
     const bool is_k = wave < 2;
     const int ld_blk = wave & 1;
-    const int ld_dst = __builtin_amdgcn_readfirstlane((is_k ? 0 : kKBytes) + ld_blk * kBlockBytes);
+    // LDS address of this wavefront's u-th load: ld_dst for u % 4 = 0, ld_dst2 for 2, one stage further for 1 and 3
+    const int lds_at = static_cast<int>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char*)lds));
+    const int ld_dst = __builtin_amdgcn_readfirstlane(lds_at + (is_k ? 0 : 2 * kStageBytes + kKBytes) + ld_blk * kBlockBytes);
+    const int ld_dst2 = __builtin_amdgcn_readfirstlane(lds_at + (is_k ? 2 * kStageBytes : kKBytes) + ld_blk * kBlockBytes);
     const size_t blk_bytes = static_cast<size_t>(p.hkv_l) * 2 * kBlockBytes;
     // a wavefront-uniform pointer, said explicitly to be in scalar registers
     auto uniform_ptr = [](const unsigned char* ptr) SHIFTATTN_INLINE -> const unsigned char* {
@@ -245,18 +253,14 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
     };
     const unsigned char* cache_g =
         uniform_ptr(reinterpret_cast<const unsigned char*>(p.cache) + static_cast<size_t>(g) * 2 * kBlockBytes);
-    auto block_base = [&](int id) SHIFTATTN_INLINE -> const unsigned char* {
-        return cache_g + static_cast<int64_t>(id) * blk_bytes;
-    };
     // 4 KiB from src (uniform, scalar registers) + a 32-bit byte offset per lane and load into LDS at dst (uniform).
     // Written as assembly so that the address is formed by the load itself (scalar base + vector offset) instead of a
     // 64-bit vector addition per load.  The LDS destination goes through M0; the compiler treats M0 as reserved (it
     // sets it right before each use of its own and keeps no value in it), so writing it here needs no clobber.  The
     // loads are waited for with explicit vmcnt(0) waits (wait_vm0) only.
-    auto dma_4k = [&](const unsigned char* src, const int (&off)[4], unsigned char* dst) SHIFTATTN_INLINE {
-        const uint32_t m0v = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(dst));
+    auto dma_4k = [&](const unsigned char* src, const int (&off)[4], int m0v) SHIFTATTN_INLINE {
         asm volatile(
-            "s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+            "s_mov_b32 m0, %0\n\ts_nop 4\n\t"
             "global_load_lds_dwordx4 %1, %5\n\t"
             "global_load_lds_dwordx4 %2, %5 offset:1024\n\t"
             "global_load_lds_dwordx4 %3, %5 offset:2048\n\t"
@@ -310,7 +314,7 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
         // log2 e, times k_scale of a cache widened from FP8) and rounded to bf16 again, for the attempt that follows no
         // reference: its logits then leave the MFMAs in exp2 units and its loop spends no instruction on scaling them.
         // (the addresses are formed here and not kept: a second fetch is rare)
-        auto fetch_q = [&](bool with_scale) SHIFTATTN_INLINE {
+        auto fetch_q = [&](auto with_scale) SHIFTATTN_INLINE {
             int lane_q = lane;
             asm volatile("" : "+v"(lane_q));
             const uint16_t* q_ptr[2];
@@ -324,7 +328,7 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
                 q_ptr[cb] = p.q + static_cast<size_t>(q_begin + tok_r) * p.q_stride + (g * p.G + cw_r % p.G) * kD + (lane_q >> 5) * 8;
             }
             load_q_to_acc(qf[0], qf[1], q_ptr[0], q_ptr[1]);
-            if (with_scale) {
+            if constexpr (decltype(with_scale)::value != 0) {
 #pragma unroll
                 for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
@@ -362,22 +366,55 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
         float m_rep[2] = {-INFINITY, -INFINITY};
         const float thr = kRefSlack / p.c;  // how far a logit may exceed the reference (attempts that follow the maximum)
 
-        // Ring of three LDS stages: K of tile t and V^T of tile t live in stage t % 3.  Iteration j reads K of tile
-        // j + 1 and V^T of tile j - 1 and loads K of tile j + 3 and V^T of tile j + 1, so everything an iteration reads
-        // was complete before the barrier of the iteration before: operand reads run on across the barrier.
-        int k_cur[8], v_cur;        // LDS addresses of this iteration's operand reads (k_cur[0]: of the next one's)
-        int st0 = 0, st1 = 0, st2 = 0;  // byte offsets of stages j % 3, (j + 1) % 3, (j + 2) % 3 at the top of iteration j
+        // Ring of four LDS stages: K of tile t and V^T of tile t live in stage t % 4.  Iteration j reads K of tile j + 1 and V^T
+        // of tile j - 1 and loads K of tile j + 4 and V^T of tile j + 2, whose stages were read for the last time in iteration
+        // j - 1.  What an iteration reads was loaded three iterations before and complete before the barrier of the iteration
+        // before, so operand reads run on across the barrier and loads have two iterations to land.
         u32x4 pre_a = {0u, 0u, 0u, 0u}, pre_c = pre_a;  // first K and first V^T operand of the coming iteration
-        auto next_stage = [](int st) SHIFTATTN_INLINE { return st == 2 * kStageBytes ? 0 : st + kStageBytes; };
 
-        // cache block this wavefront loads in iteration j: K of tile j + 3 or V^T of tile j + 1
-        auto load_block_index = [&](int j) SHIFTATTN_INLINE -> int {
-            return min(2 * (kt_begin + j + (is_k ? 3 : 1)) + ld_blk, last_block);
+        // Where this wavefront's loads come from.  Its u-th load is K of tile u (wavefronts 0, 1) or V^T of tile u - 2
+        // (2, 3); lanes hold the byte addresses of the loads of a window of 64, lane 0 the next one's: an iteration reads lane 0 and
+        // moves the others down by one, instead of loading a block id, waiting for it and multiplying it out with a dozen scalar
+        // instructions.  The ids of the window after come straight into LDS meanwhile.
+        const int ld_ahead = __builtin_amdgcn_readfirstlane(is_k ? 0 : 2);
+        uint32_t a_lo = 0, a_hi = 0;
+        int u_left = 0, window = 0;   // loads left in the window; its number
+        int* my_ids = reinterpret_cast<int*>(lds + kIdsAt) + __builtin_amdgcn_readfirstlane(wave * 128);
+        auto block_index = [&](int w) SHIFTATTN_INLINE -> int {
+            return min(2 * (kt_begin + max(64 * w + lane_p - ld_ahead, 0)) + ld_blk, last_block);
         };
-        int id_vec = 0;  // block id of the coming iteration's loads, in a vector register until they are issued
-        // iterations in which this wavefront loads: K of tiles 3 .. n - 1, V^T of tiles 1 .. n - 1 (a load beyond the last tile
-        // would be waited for, with its whole latency, in front of the last product)
-        const int ld_limit = n - __builtin_amdgcn_readfirstlane(is_k ? 3 : 1);
+        auto take_window = [&](int id) SHIFTATTN_INLINE {   // ids are those of blocks that exist: not negative
+            const uint64_t a = reinterpret_cast<uint64_t>(cache_g) + static_cast<uint64_t>(static_cast<uint32_t>(id)) * blk_bytes;
+            a_lo = static_cast<uint32_t>(a);
+            a_hi = static_cast<uint32_t>(a >> 32);
+        };
+        auto request_window = [&](int w) SHIFTATTN_INLINE {
+            const uint32_t m0v = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(my_ids + (w & 1) * 64));
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dword %1, %2"
+                         :: "s"(m0v), "v"(block_index(w) * 4), "s"(uniform_ptr(reinterpret_cast<const unsigned char*>(table))) : "memory");
+        };
+        auto join = [](uint32_t lo, uint32_t hi) SHIFTATTN_INLINE -> const unsigned char* {
+            return reinterpret_cast<const unsigned char*>((static_cast<uint64_t>(hi) << 32) | lo);
+        };
+        auto lane_above = [](uint32_t v) SHIFTATTN_INLINE -> uint32_t {   // wave_rol:1, lane i takes lane i + 1's
+            v = __builtin_amdgcn_update_dpp(v, v, 0x134, 0xf, 0xf, false);
+            asm volatile("" : "+v"(v));
+            return v;
+        };
+
+        // logits of keys beyond a column's position in the tile that begins at key0
+        auto mask_tile = [&](f32x16 (&sv)[2], int key0) SHIFTATTN_INLINE {
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb) {
+                int left = pos_col[cb] - key0 - 8 * half;   // (formed here: kept from outside the loop it would cost registers)
+                asm volatile("" : "+v"(left));
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    sv[cb][r] = 16 * (r >> 3) + (r & 7) > left ? -INFINITY : sv[cb][r];
+            }
+        };
+        // first iteration whose tile holds keys beyond the first column's position
+        const int j_diag = __builtin_amdgcn_readfirstlane(((w_pos_min - (kKv - 1) - kt_begin * kKv) >> 5) + 1);
 
         // zero the V^T entries of keys at or past the context in the given stage (tile kt)
         auto clear_ragged_v = [&](int kt, int stage_off) SHIFTATTN_INLINE {
@@ -397,183 +434,139 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
             }
         };
 
-        // One iteration on tile j.  PAR = parity of j: selects the register sets at compile time.
-        // TRACK: the tile's maximum is collected and checked against the reference (off only in the steady-state bodies
-        // of a pass's first attempt, which check the running sums instead)
-        auto body = [&](auto par_c, auto has_a_c, auto has_c_c, auto guard_c, auto track_c, int j) SHIFTATTN_INLINE {
-            constexpr int PAR = decltype(par_c)::value;
-            // track_c: 1 = the maximum is followed (TRACK); 2 = the reference the column's first key tile left is kept and no
-            // maximum followed (KEEP); 0 = no reference at all, on logits that arrive in exp2 units (Q^T carries the scale)
+        // One iteration on tile j.  PH = j % 4: selects the stages and, by its parity, the register sets at compile time.
+        // track_c: 1 = the maximum is followed (TRACK); 2 = the reference the column's first key tile left is kept and no
+        // maximum followed (KEEP); 0 = no reference at all, on logits that arrive in exp2 units (Q^T carries the scale)
+        auto body = [&](auto ph_c, auto guard_c, auto track_c, int j) SHIFTATTN_INLINE {
+            constexpr int PH = decltype(ph_c)::value, PAR = PH & 1;
+            constexpr bool GUARD = decltype(guard_c)::value != 0;  // outside the steady-state loop
             constexpr bool TRACK = decltype(track_c)::value == 1;
             constexpr bool KEEP = decltype(track_c)::value == 2;
-            constexpr bool GUARD = decltype(guard_c)::value != 0;  // outside the steady-state loop
-            constexpr bool HAS_A = decltype(has_a_c)::value != 0;
-            constexpr bool HAS_C = decltype(has_c_c)::value != 0;
             f32x16(&s_cur)[2] = sbuf[PAR];
             f32x16(&s_nxt)[2] = sbuf[1 - PAR];
             u32x4(&p_cur)[2][2] = pw[PAR];
             u32x4(&p_prv)[2][2] = pw[1 - PAR];
-            const int key0 = (kt_begin + j) * kKv;
-            // address steps of this iteration: the reads of this iteration's K move on from stage (j+1)%3 to (j+2)%3,
-            // those that already serve the next iteration (k_cur[0], v_cur) from (j+2)%3 to (j+3)%3 = j%3
-            const int d_now = st2 - st1, d_next = st0 - st2;
 
-            // operand reads: op o feeds the two MFMAs (column blocks 0 and 1) of slots 2 o and 2 o + 1.  Ops beyond this
-            // iteration's are the first two of the next one (its first K operand, its first V^T operand).
-            constexpr int NOPS = (HAS_A ? 8 : 0) + (HAS_C ? 8 : 0);
-            auto read_k = [&](auto ks_c) SHIFTATTN_INLINE -> u32x4 {   // reads with k_cur[ks], then moves it on
-                constexpr int ks = decltype(ks_c)::value;
-                const u32x4 v = lds_read16(k_cur[ks]);
-                k_cur[ks] += ks == 0 ? d_next : d_now;
-                asm volatile("" : "+v"(k_cur[ks]));
-                return v;
-            };
-            auto read_v = [&](auto idx_c) SHIFTATTN_INLINE -> u32x4 {
-                constexpr int idx = decltype(idx_c)::value;
-                return lds_read16(v_cur + (idx / 4) * kBlockBytes + (idx % 4) * 1024);
-            };
-            auto op_read = [&](auto oc) SHIFTATTN_INLINE -> u32x4 {
-                constexpr int o = decltype(oc)::value;
-                constexpr bool is_a = HAS_A && (!HAS_C || (o % 2 == 0));
-                constexpr int idx = (HAS_A && HAS_C) ? o / 2 : o;
-                if constexpr (is_a) return read_k(IC<idx>{});
-                else return read_v(IC<idx>{});
-            };
-            u32x4 opnd[NOPS > 0 ? NOPS : 1];
-            if constexpr (NOPS > 0) {
-                opnd[0] = HAS_A ? pre_a : pre_c;
-                if constexpr (HAS_A && HAS_C) opnd[1] = pre_c;
-                else opnd[1] = op_read(IC<1>{});
-            }
-            if constexpr (!HAS_A) {  // no K reads in this iteration: the addresses move on all the same
-#pragma unroll
-                for (int ks = 1; ks < 8; ++ks) k_cur[ks] += d_now;
-            }
-            if constexpr (!HAS_C) v_cur += d_next;
-
-            if (key0 + kKv - 1 > w_pos_min) {  // tile crosses the diagonal of this wavefront: uniform
+            if (j >= j_diag) {  // tile crosses the diagonal of this wavefront: uniform
                 // (a real branch: the selects below take their inputs from a statement that cannot be moved out of it)
                 asm volatile("; keys beyond a column's position" : "+v"(s_cur[0]), "+v"(s_cur[1]));
-#pragma unroll
-                for (int cb = 0; cb < 2; ++cb)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int key = key0 + 16 * (r >> 3) + 8 * half + (r & 7);
-                        if (key > pos_col[cb]) s_cur[cb][r] = -INFINITY;
-                    }
+                mask_tile(s_cur, (kt_begin + j) * kKv);
             }
 
+            // operand reads: op o feeds the two MFMAs (column blocks 0 and 1) of slots 2 o and 2 o + 1: even ops K of tile j + 1,
+            // odd ones V^T of tile j - 1.  Ops 16 and 17 are the first two of the next iteration.
+            u32x4 opnd[18];
+            opnd[0] = pre_a;
+            opnd[1] = pre_c;
+            auto op_read = [&](auto oc) SHIFTATTN_INLINE -> u32x4 {
+                constexpr int o = decltype(oc)::value, of = o / 16, idx = (o % 16) / 2;   // of: of the next iteration
+                if constexpr (o % 2 == 0) return lds_read16(k_rd[idx] + ((PH + 1 + of) & 3) * kStageBytes);
+                else return lds_read16(v_rd + ((PH + 3 + of) & 3) * kStageBytes + (idx / 4) * kBlockBytes + (idx % 4) * 1024);
+            };
             // ---- interleaved block ------------------------------------------------------------------------
             float mx[2] = {-INFINITY, -INFINITY};
-            // chunk v (0..31): the logit of column block v / 16, accumulator register v % 16.  Slot v takes the
-            // exponential of logit v and finishes logit v - 1 (row sum; on even v the pair (v - 2, v - 1) is packed, on
-            // odd v the pair (v - 1, v) enters the maximum): four vector instructions per slot, the exponential
-            // counting double, and no instruction uses an exponential issued in its own slot.
-            float e_last = 0.f, e_last2 = 0.f;
-            auto finish_prev = [&](auto vc) SHIFTATTN_INLINE {  // finishes logit v - 1
+            // chunk v (0..31): the logit of column block v / 16, accumulator register v % 16.  Slot v takes the exponential of
+            // logit v and adds logit v - 2 to the row sum; odd slots pack logits v - 3 and v - 2, even ones issue an operand read:
+            // no slot then asks for more issue time than its MFMA takes.  No instruction of a slot reads an exponential issued last.
+            // (the empty asm statements pin results to their slots: left free they drift together)
+            float ev[32];
+            auto sum_up = [&](auto vc) SHIFTATTN_INLINE {
                 constexpr int v = decltype(vc)::value;
-                constexpr int pv = v - 1, cb = pv / 16, r = pv % 16;
-                // The row sum runs one logit further behind (logit v - 2): the first vector instruction behind a slot's MFMA
-                // then never reads the exponential issued last, which would cost a wait state.
-                // (the empty asm statement pins the sum to this slot)
-                if constexpr (pv >= 1) {
-                    l_run[(pv - 1) / 16] += e_last2;
-                    asm volatile("" : "+v"(l_run[(pv - 1) / 16]));
-                }
-                if constexpr (pv == 31) {
-                    l_run[1] += e_last;
-                    asm volatile("" : "+v"(l_run[1]));
-                }
-                if constexpr (r % 2 == 1) {
-                    bf16x2 t;
-                    t[0] = static_cast<__bf16>(e_last2);
-                    t[1] = static_cast<__bf16>(e_last);
-                    p_cur[cb][r >> 3][(r & 7) >> 1] = __builtin_bit_cast(uint32_t, t);
-                    // (pinned to this slot: left free, the packing drifts together and the slots lose their balance)
-                    if constexpr (!TRACK) asm volatile("" : "+v"(p_cur[cb][r >> 3]));
-                }
+                l_run[v / 16] += ev[v];
+                asm volatile("" : "+v"(l_run[v / 16]));
+            };
+            auto pack = [&](auto vc) SHIFTATTN_INLINE {   // logits v, v + 1
+                constexpr int v = decltype(vc)::value, cb = v / 16, r = v % 16;
+                bf16x2 t;
+                t[0] = static_cast<__bf16>(ev[v]);
+                t[1] = static_cast<__bf16>(ev[v + 1]);
+                uint32_t w = __builtin_bit_cast(uint32_t, t);
+                if constexpr (!TRACK) asm volatile("" : "+v"(w));
+                p_cur[cb][r >> 3][(r & 7) >> 1] = w;
             };
             auto chunk = [&](auto vc) SHIFTATTN_INLINE {
                 constexpr int v = decltype(vc)::value;
                 constexpr int cb = v / 16, r = v % 16;
                 // (no reference followed: Q^T carries the scale, the logit arrives in exp2 units)
-                const float e = TRACK        ? __builtin_amdgcn_exp2f(fmaf(s_cur[cb][r], p.c, -mc[cb]))
-                                : KEEP       ? __builtin_amdgcn_exp2f(fmaf(s_cur[cb][r], p.c, -mc[cb]))
-                                             : __builtin_amdgcn_exp2f(s_cur[cb][r]);
-                if constexpr (v >= 1) finish_prev(IC<v>{});
+                const float x = TRACK || KEEP ? fmaf(s_cur[cb][r], p.c, -mc[cb]) : s_cur[cb][r];
+                ev[v] = __builtin_amdgcn_exp2f(x);
+                if constexpr (!TRACK) asm volatile("" : "+v"(ev[v]));
+                if constexpr (v >= 2) sum_up(IC<v - 2>{});
+                if constexpr (v >= 3 && v % 2 == 1) pack(IC<v - 3>{});
                 if constexpr (TRACK && r % 2 == 1) {
                     mx[cb] = fmaxf(fmaxf(mx[cb], s_cur[cb][r - 1]), s_cur[cb][r]);
                     asm volatile("" : "+v"(mx[cb]));
                 }
-                e_last2 = e_last;
-                e_last = e;
-                if constexpr (v == 31) finish_prev(IC<32>{});
+                if constexpr (v == 31) {
+                    sum_up(IC<30>{});
+                    sum_up(IC<31>{});
+                    pack(IC<30>{});
+                }
             };
             auto op_mfma = [&](auto tc, u32x4 a) SHIFTATTN_INLINE {
                 constexpr int t = decltype(tc)::value;
-                constexpr int o = t / 2, cb = t % 2;
-                constexpr bool is_a = HAS_A && (!HAS_C || (o % 2 == 0));
-                constexpr int idx = (HAS_A && HAS_C) ? o / 2 : o;
-                if constexpr (is_a) {
+                constexpr int o = t / 2, cb = t % 2, idx = o / 2;
+                if constexpr (o % 2 == 0) {
                     if constexpr (idx == 0) mfma_s_first<GUARD>(s_nxt[cb], a, qf[cb][idx]);
                     else mfma_s_acc<GUARD>(s_nxt[cb], a, qf[cb][idx]);
                 } else {
-                    constexpr int ks2 = idx / 4, mt = idx % 4;
-                    mfma_o_acc<GUARD>(oacc[cb][mt], a, p_prv[cb][ks2]);
+                    mfma_o_acc<GUARD>(oacc[cb][idx % 4], a, p_prv[cb][idx / 4]);
                 }
             };
-            // what runs once per iteration besides the slots: the barrier (with the wait for this wavefront's loads of
-            // the iteration before), then the loads into the stages nobody reads any more, then the next block id
-            auto fill = [&]() SHIFTATTN_INLINE {
-                // a bare barrier: __syncthreads() would first drain every outstanding LDS read.  What has to be complete
-                // is this wavefront's loads of the iteration before (waited for here, and with them the block id
-                // requested then) and its reads of the stages about to be overwritten (their data went into MFMAs one
-                // iteration ago).
-                wait_vm0();
-                asm volatile("s_barrier" ::: "memory");
-                if (j < ld_limit)
-                    dma_4k(uniform_ptr(block_base(__builtin_amdgcn_readfirstlane(id_vec))), ld_off, lds + (is_k ? st0 : st1) + ld_dst);
-                id_vec = table_v[load_block_index(j + 1) + lane_zero];  // for the loads of the next iteration
+            // What runs once per iteration besides, spread over the odd slots: the address of this iteration's loads (slots 1 and 3),
+            // the barrier (slot 2) with the wait for the loads of the iteration before last in front, the address of the next one's
+            // (slots 5 and 7), now and then the next window of them (slot 7), and the loads into the stage nobody reads any more
+            // (slots 9 to 15): all four right behind the barrier hold up the matrix pipe (2048 tokens on 131072 cached beside 64
+            // decodes: 3 % of the launch).  Loads beyond the last tile are made all the same (of the context's last block at most):
+            // the count that the wait relies on then always holds.
+            uint32_t src_lo = 0, src_hi = 0;
+            auto housekeeping = [&](auto tc) SHIFTATTN_INLINE {
+                constexpr int t = decltype(tc)::value;
+                if constexpr (t == 1) {
+                    src_lo = __builtin_amdgcn_readfirstlane(a_lo);
+                    asm volatile("" : "+s"(src_lo));
+                } else if constexpr (t == 2) {
+                    // a bare barrier: __syncthreads() would first drain every outstanding LDS read.  What has to be complete
+                    // is this wavefront's loads of the iteration before last (all but the last four it issued) and its reads of
+                    // the stages about to be overwritten (their data went into MFMAs in the iteration before).
+                    asm volatile("s_waitcnt vmcnt(4)\n\ts_barrier" ::: "memory");
+                } else if constexpr (t == 3) {
+                    src_hi = __builtin_amdgcn_readfirstlane(a_hi);
+                    asm volatile("" : "+s"(src_hi));
+                } else if constexpr (t == 5) {
+                    a_lo = lane_above(a_lo);
+                } else if constexpr (t == 7) {
+                    a_hi = lane_above(a_hi);
+                    if (--u_left == 0) {
+                        take_window(my_ids[(window & 1) * 64 + lane_p]);
+                        request_window(++window);
+                        u_left = 64;
+                    }
+                } else if constexpr (t == 9) {
+                    asm volatile("s_add_i32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                                 :: "s"(PH < 2 ? ld_dst : ld_dst2), "v"(ld_off[0]), "s"(join(src_lo, src_hi)), "n"((PH & 1) * kStageBytes) : "memory", "scc");
+                } else if constexpr (t == 11 || t == 13 || t == 15) {
+                    constexpr int x = (t - 9) / 2;
+                    asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2" :: "v"(ld_off[x]), "s"(join(src_lo, src_hi)), "n"(1024 * x) : "memory");
+                }
             };
-
-            if constexpr (NOPS == 0) {
-                fill();
-                [&]<int... C>(std::integer_sequence<int, C...>) SHIFTATTN_INLINE { (chunk(IC<C>{}), ...); }
-                (std::make_integer_sequence<int, 32>{});
-            } else {
-                constexpr int kFillSlot = 2;
-                [&]<int... T>(std::integer_sequence<int, T...>) SHIFTATTN_INLINE {
-                    (([&]() SHIFTATTN_INLINE {
-                         constexpr int o = T / 2;
-                         if constexpr (T % 2 == 0) {
-                             if constexpr (o + 2 < NOPS) {
-                                 opnd[o + 2] = op_read(IC<o + 2>{});
-                                 // the V^T base moves on once this iteration's last V^T operand is requested
-                                 if constexpr (HAS_C && o + 2 == NOPS - 1) {
-                                     v_cur += d_next;
-                                     asm volatile("" : "+v"(v_cur));
-                                 }
-                             } else if constexpr (o + 2 == NOPS) {
-                                 pre_a = read_k(IC<0>{});
-                             } else {
-                                 pre_c = read_v(IC<0>{});
-                             }
-                         }
-                         op_mfma(IC<T>{}, opnd[o]);
-                         __builtin_amdgcn_sched_barrier(0);  // the softmax work of the slot goes behind its MFMA
-                         if constexpr (T == kFillSlot) fill();
-                         if constexpr (NOPS == 16) {
-                             chunk(IC<T>{});
-                         } else {
-                             chunk(IC<2 * T>{});
-                             chunk(IC<2 * T + 1>{});
-                         }
+            [&]<int... T>(std::integer_sequence<int, T...>) SHIFTATTN_INLINE {
+                (([&]() SHIFTATTN_INLINE {
+                     op_mfma(IC<T>{}, opnd[T / 2]);
+                     __builtin_amdgcn_sched_barrier(0);  // the rest of the slot goes behind its MFMA
+                     if constexpr (T % 2 == 0) {
+                         opnd[T / 2 + 2] = op_read(IC<T / 2 + 2>{});
                          __builtin_amdgcn_sched_barrier(0);
-                     }()),
-                     ...);
-                }
-                (std::make_integer_sequence<int, 2 * NOPS>{});
+                     }
+                     housekeeping(IC<T>{});
+                     chunk(IC<T>{});
+                     __builtin_amdgcn_sched_barrier(0);
+                 }()),
+                 ...);
             }
+            (std::make_integer_sequence<int, 32>{});
+            pre_a = opnd[16];
+            pre_c = opnd[17];
 
             // ---- the tile's maximum against what the reference covers: rarely, a new reference ------------------
             if constexpr (TRACK)
@@ -612,24 +605,25 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
                 }
                 if (__builtin_amdgcn_ballot_w64(bad)) redo = true;
             }
-            const int st_new = st0;  // (j + 3) % 3
-            st0 = st1;
-            st1 = st2;
-            st2 = st_new;
         };
 
-        // prologue loads: K of the first three tiles and V^T of the first (two cache blocks per wavefront)
+        // prologue loads: K of the first four tiles, V^T of the first two
         auto issue_prologue = [&]() SHIFTATTN_INLINE {
-            const int id_p = table[min(2 * (kt_begin + (wave >> 1)) + ld_blk, last_block)];
-            dma_4k(uniform_ptr(block_base(id_p)), k_ld, lds + (wave >> 1) * kStageBytes + ld_blk * kBlockBytes);
-            // the loads "iteration -1" would have issued: K of tile 2 into stage 2, V^T of tile 0 into stage 0
-            const int id_q = table[load_block_index(-1)];
-            dma_4k(uniform_ptr(block_base(id_q)), ld_off, lds + (is_k ? 2 * kStageBytes : 0) + ld_dst);
-            id_vec = table_v[load_block_index(0) + lane_zero];
+            take_window(table[block_index(0)]);
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+            {
+                if (is_k || x >= 2) dma_4k(join(__builtin_amdgcn_readfirstlane(a_lo), __builtin_amdgcn_readfirstlane(a_hi)), ld_off, ((x & 2) ? ld_dst2 : ld_dst) + (x & 1) * kStageBytes);
+                a_lo = lane_above(a_lo);
+                a_hi = lane_above(a_hi);
+            }
+            request_window(1);
+            window = 1;
+            u_left = 60;
         };
         // The first attempt's go out in front of the fetch of Q^T, whose wait then covers both.
         if (n > 0) issue_prologue();
-        fetch_q(p.scaled_q != 0);
+        fetch_q(IC<kScaledQ ? 1 : 0>{});
 
         // Up to three attempts at the pass.  The first follows no maximum behind the first key tile (its steady-state
         // bodies save the instruction per two logits that would collect it; real logits stay within 2^100 of their
@@ -637,23 +631,27 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
         // follows the maximum tile by tile; it can end flagged itself (a column outgrew its reference after it had sums),
         // and then holds, for every column, a reference within the slack of the true maximum: the third attempt starts
         // from that and is not flagged.
-        for (int attempt = 0; attempt < 3; ++attempt) {
-        redo = false;
+        auto reset_sums = [&]() SHIFTATTN_INLINE {
+            redo = false;
 #pragma unroll
-        for (int cb = 0; cb < 2; ++cb) {
-            l_run[cb] = 0.f;
+            for (int cb = 0; cb < 2; ++cb) {
+                l_run[cb] = 0.f;
 #pragma unroll
-            for (int mt = 0; mt < 4; ++mt)
+                for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) oacc[cb][mt][r] = 0.f;
-        }
+                    for (int r = 0; r < 16; ++r) oacc[cb][mt][r] = 0.f;
+            }
+        };
         auto key_loop = [&](auto track_c) SHIFTATTN_INLINE {
-            // prologue: the loads (already on their way in the first attempt), S^T of the first tile
-            if (attempt > 0) issue_prologue();
-            st0 = 0, st1 = kStageBytes, st2 = 2 * kStageBytes;
+            // prologue: S^T of the first tile (the loads are on their way).  Iteration 0 multiplies V^T "of tile -1" (stage 3) by
+            // P = 0: zeros, so that no product of it is a NaN.
 #pragma unroll
-            for (int ks = 0; ks < 8; ++ks) k_cur[ks] = k_rd[ks] + kStageBytes;   // iteration 0 reads K of tile 1
-            v_cur = v_rd + 2 * kStageBytes;                                       // (nothing; iteration 1 reads stage 0)
+            for (int x = 0; x < 2; ++x)
+                *reinterpret_cast<u32x4*>(lds + 3 * kStageBytes + kKBytes + (x * kThreads + tid) * 16) = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+                for (int ks2 = 0; ks2 < 2; ++ks2) pw[1][cb][ks2] = u32x4{0u, 0u, 0u, 0u};
             wait_vm0();
             __syncthreads();
 #pragma unroll
@@ -665,92 +663,97 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
                     else mfma_s_acc<true>(sbuf[0][cb], a, qf[cb][ks]);
                 }
             }
-            pre_a = lds_read16(k_cur[0]);
-            k_cur[0] += kStageBytes;  // on to stage 2: iteration 1's first K operand
-            mfma_settle();
-            // (the attempt that keeps its first tile's reference takes it here, from a tile that follows the maximum)
-            constexpr int kFirst = decltype(track_c)::value == 2 ? 1 : decltype(track_c)::value;
-            if (n == 1) {
-                body(IC<0>{}, IC<0>{}, IC<0>{}, IC<1>{}, IC<kFirst>{}, 0);
-            } else {
-                body(IC<0>{}, IC<1>{}, IC<0>{}, IC<1>{}, IC<kFirst>{}, 0);
-                int j = 1;  // stays odd: the steady-state loop takes two tiles per trip so that the register sets of
-                            // even and odd tiles are fixed at compile time
-                for (; j + 2 < n; j += 2) {
-                    body(IC<1>{}, IC<1>{}, IC<1>{}, IC<0>{}, track_c, j);
-                    body(IC<0>{}, IC<1>{}, IC<1>{}, IC<0>{}, track_c, j + 1);
-                }
-                if (j + 1 < n) {
-                    body(IC<1>{}, IC<1>{}, IC<1>{}, IC<1>{}, track_c, j);
-                    body(IC<0>{}, IC<0>{}, IC<1>{}, IC<1>{}, track_c, j + 1);
-                } else {
-                    body(IC<1>{}, IC<0>{}, IC<1>{}, IC<1>{}, track_c, j);
+            pre_a = lds_read16(k_rd[0] + kStageBytes);
+            pre_c = lds_read16(v_rd + 3 * kStageBytes);
+            mfma_settle(sbuf[0]);
+            if constexpr (decltype(track_c)::value == 2) {   // the reference that is kept: the first tile's maximum
+                if (j_diag <= 0) mask_tile(sbuf[0], kt_begin * kKv);
+#pragma unroll
+                for (int cb = 0; cb < 2; ++cb) {
+                    float mx = -INFINITY;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sbuf[0][cb][r]);
+                    mx = fmaxf(mx, __shfl_xor(mx, 32));
+                    if (mx > -INFINITY) m_used[cb] = mx, mc[cb] = mx * p.c;
                 }
             }
-            // epilogue: O^T += V^T P^T of the last tile (tile n - 1, in stage (n - 1) % 3 = st2 by now)
-            wait_vm0();
-            __syncthreads();
-            const int lp = (n - 1) & 1;
+            // four tiles per trip, so that the stages and the register sets are fixed at compile time
+            int j = 0;
+            for (; j + 4 <= n; j += 4) {
+                body(IC<0>{}, IC<0>{}, track_c, j);
+                body(IC<1>{}, IC<0>{}, track_c, j + 1);
+                body(IC<2>{}, IC<0>{}, track_c, j + 2);
+                body(IC<3>{}, IC<0>{}, track_c, j + 3);
+            }
+            if (j < n) {
+                body(IC<0>{}, IC<1>{}, track_c, j);
+                if (j + 1 < n) {
+                    body(IC<1>{}, IC<1>{}, track_c, j + 1);
+                    if (j + 2 < n) body(IC<2>{}, IC<1>{}, track_c, j + 2);
+                }
+            }
+            // (the S^T of the tile beyond the last is nobody's: its registers are free behind its MFMAs only)
+            asm volatile("s_nop 7\n\ts_nop 3" :: "v"(sbuf[0][0]), "v"(sbuf[0][1]), "v"(sbuf[1][0]), "v"(sbuf[1][1]));
+            // epilogue: O^T += V^T P^T of the last tile (in its stage since the barrier of the last iteration)
+            const int last_stage = ((n - 1) & 3) * kStageBytes;
             if (ragged) {
-                clear_ragged_v(kt_begin + n - 1, st2);
+                clear_ragged_v(kt_begin + n - 1, last_stage);
                 __syncthreads();
             }
-            auto last_c = [&](auto par_c) SHIFTATTN_INLINE {
-                constexpr int PAR = decltype(par_c)::value;
+            const bool odd = ((n - 1) & 1) != 0;
 #pragma unroll
-                for (int ks2 = 0; ks2 < 2; ++ks2)
+            for (int ks2 = 0; ks2 < 2; ++ks2) {
+                u32x4 p_last[2];
 #pragma unroll
-                    for (int mt = 0; mt < 4; ++mt) {
-                        const u32x4 a = lds_read16(st2 + v_rd + ks2 * kBlockBytes + mt * 1024);
+                for (int cb = 0; cb < 2; ++cb) p_last[cb] = odd ? pw[1][cb][ks2] : pw[0][cb][ks2];
 #pragma unroll
-                        for (int cb = 0; cb < 2; ++cb) {
-                            mfma_o_acc<true>(oacc[cb][mt], a, pw[PAR][cb][ks2]);
-                        }
-                    }
-            };
-            if (lp) last_c(IC<1>{});
-            else last_c(IC<0>{});
-            mfma_settle();
-        };
-        if (n > 0) {
-            if (attempt > 0) key_loop(IC<1>{});
-            else if (p.scaled_q) key_loop(IC<0>{});
-            else key_loop(IC<2>{});
-        }
-        if (attempt == 0) {
-            // The first attempt followed no maximum.  That is exact as long as nothing left the range bf16 and the fp32 sums
-            // hold without loss.  With the first tile's reference kept: a column's sum must not exceed 2^100 (P then stays
-            // below it; what underflows is negligible beside the first tile's keys).  With no reference at all: a column that
-            // sees keys of this range must end with a sum inside [2^-40, 2^40].  An infinity or a NaN fails either test; the
-            // pass is then flagged.
+                for (int mt = 0; mt < 4; ++mt) {
+                    const u32x4 a = lds_read16(last_stage + v_rd + ks2 * kBlockBytes + mt * 1024);
 #pragma unroll
-            for (int cb = 0; cb < 2; ++cb) {
-                const float l_tot = l_run[cb] + __shfl_xor(l_run[cb], 32);
-                if (p.scaled_q) {
-                    const bool sees = n > 0 && pos_col[cb] >= kt_begin * kKv;
-                    if (sees && !(l_tot >= kFreeSumLo && l_tot <= kFreeSumHi)) redo = true;
-                    m_rep[cb] = sees ? 0.f : -INFINITY;   // what a partial result reports as its reference (exp2 units)
-                } else {
-                    if (!(l_tot <= kKeepSumBound)) redo = true;
-                    m_rep[cb] = m_used[cb] * p.c;
+                    for (int cb = 0; cb < 2; ++cb) mfma_o_acc<true>(oacc[cb][mt], a, p_last[cb]);
                 }
             }
-            redo = __builtin_amdgcn_ballot_w64(redo) != 0;
-        } else {
+            mfma_settle(oacc);
+            wait_vm0();   // loads that nobody needs any more may still be on their way into LDS
+        };
+        // does a wavefront of the workgroup ask for another attempt?  (also: every wavefront is done with the ring)
+        auto vote = [&]() SHIFTATTN_INLINE -> bool {
+            int* flags = reinterpret_cast<int*>(lds + kRingBytes + kCols * kPitch);
+            if (lane == 0) flags[wave] = redo ? 1 : 0;
+            __syncthreads();
+            return __builtin_amdgcn_readfirstlane(flags[0] | flags[1] | flags[2] | flags[3]) != 0;
+        };
+        reset_sums();
+        if (n > 0) key_loop(IC<kScaledQ ? 0 : 2>{});
+        // The first attempt followed no maximum.  That is exact as long as nothing left the range bf16 and the fp32 sums hold
+        // without loss.  With the first tile's reference kept: a column's sum must not exceed 2^100 (P then stays below it;
+        // what underflows is negligible beside the first tile's keys).  With no reference at all: a column that sees keys of
+        // this range must end with a sum inside [2^-40, 2^40].  An infinity or a NaN fails either test; the pass is then flagged.
 #pragma unroll
-            for (int cb = 0; cb < 2; ++cb) m_rep[cb] = m_used[cb] * p.c;
+        for (int cb = 0; cb < 2; ++cb) {
+            const float l_tot = l_run[cb] + __shfl_xor(l_run[cb], 32);
+            if constexpr (kScaledQ) {
+                const bool sees = n > 0 && pos_col[cb] >= kt_begin * kKv;
+                if (sees && !(l_tot >= kFreeSumLo && l_tot <= kFreeSumHi)) redo = true;
+                m_rep[cb] = sees ? 0.f : -INFINITY;   // what a partial result reports as its reference (exp2 units)
+            } else {
+                if (!(l_tot <= kKeepSumBound)) redo = true;
+                m_rep[cb] = m_used[cb] * p.c;
+            }
         }
-        if (attempt == 2) break;
-        int* flags = reinterpret_cast<int*>(lds + kRingBytes + kCols * kPitch);
-        if (lane == 0) flags[wave] = redo ? 1 : 0;
-        __syncthreads();  // also: every wavefront is done with the ring
-        const int any_redo = flags[0] | flags[1] | flags[2] | flags[3];
-        if (__builtin_expect(__builtin_amdgcn_readfirstlane(any_redo) == 0, 1)) break;
-        if (attempt == 0) {   // the attempts that follow the maximum start without references, on Q^T as given
+        redo = __builtin_amdgcn_ballot_w64(redo) != 0;
+        if (__builtin_expect(vote(), 0)) {   // start over without references, on Q^T as given, and follow the maximum
 #pragma unroll
             for (int cb = 0; cb < 2; ++cb) m_used[cb] = -INFINITY, mc[cb] = 0.f, bound[cb] = -INFINITY;
-            if (p.scaled_q) fetch_q(false);
-        }
+            for (int attempt = 1;; ++attempt) {
+                if (n > 0) issue_prologue();
+                fetch_q(IC<0>{});
+                reset_sums();
+                if (n > 0) key_loop(IC<1>{});
+                if (attempt == 2 || !vote()) break;
+            }
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb) m_rep[cb] = m_used[cb] * p.c;
         }
 
         // ---- results of the pass ----------------------------------------------------------------------------
@@ -907,13 +910,21 @@ size_t prefill_mfma64_workspace(int total_q, const Prefill64Plan& pl, const Attn
 }
 
 hipError_t prefill_mfma64_init() {
-    for (const void* kernel : {reinterpret_cast<const void*>(&prefill64_kernel<0>), reinterpret_cast<const void*>(&prefill64_kernel<1>),
-                               reinterpret_cast<const void*>(&prefill64_kernel<2>)})
+    for (const void* kernel :
+         {reinterpret_cast<const void*>(&prefill64_kernel<0, false>), reinterpret_cast<const void*>(&prefill64_kernel<1, false>),
+          reinterpret_cast<const void*>(&prefill64_kernel<2, false>), reinterpret_cast<const void*>(&prefill64_kernel<0, true>),
+          reinterpret_cast<const void*>(&prefill64_kernel<1, true>), reinterpret_cast<const void*>(&prefill64_kernel<2, true>)})
         if (hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes); e != hipSuccess) return e;
     return hipSuccess;
 }
 
 namespace {
+
+template <int kDecode>
+void enqueue(unsigned grid, const Prefill64Params& p, const DecodeRole& dec, hipStream_t st) {
+    if (option_prefill_scaled_q()) prefill64_kernel<kDecode, true><<<grid, kThreads, kLdsBytes, st>>>(p, dec);
+    else prefill64_kernel<kDecode, false><<<grid, kThreads, kLdsBytes, st>>>(p, dec);
+}
 
 Prefill64Params wide_params(const void* q, const void* cache, const int32_t* block_table, int max_blocks, const int32_t* cu_seqlens_q,
                             const int32_t* seq_lens, int num_seqs, int total_q, const Prefill64Plan& pl, void* out, void* workspace,
@@ -939,7 +950,6 @@ Prefill64Params wide_params(const void* q, const void* cache, const int32_t* blo
     p.n_splits = pl.n_splits;
     p.paired = pl.paired ? 1 : 0;
     p.rotate = pl.rotate ? 1 : 0;
-    p.scaled_q = option_prefill_scaled_q() ? 1 : 0;
     p.max_blocks = max_blocks;
     p.c = c;
     p.out_scale = out_scale;
@@ -956,7 +966,7 @@ hipError_t launch_prefill_mfma64(const void* q, const void* cache, const int32_t
                                  float out_scale, hipStream_t st) {
     const Prefill64Params p = wide_params(q, cache, block_table, max_blocks, cu_seqlens_q, seq_lens, num_seqs, total_q, pl, out, workspace, a,
                                           c, out_scale);
-    prefill64_kernel<0><<<static_cast<unsigned>(pl.workgroups), kThreads, kLdsBytes, st>>>(p, DecodeRole{});
+    enqueue<0>(static_cast<unsigned>(pl.workgroups), p, DecodeRole{}, st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (pl.n_splits > 1)
@@ -972,8 +982,8 @@ hipError_t launch_prefill64_and_decode(const void* q, const void* cache, const i
     Prefill64Params p = wide_params(q, cache, block_table, max_blocks, cu_seqlens_q, seq_lens, num_seqs, total_q, pl, out, workspace, a, c, out_scale);
     p.range_div = range_div;
     const unsigned grid = static_cast<unsigned>(pl.workgroups + dec.n_wg);
-    if (a.kv_fp8()) prefill64_kernel<2><<<grid, kThreads, kLdsBytes, st>>>(p, dec);
-    else prefill64_kernel<1><<<grid, kThreads, kLdsBytes, st>>>(p, dec);
+    if (a.kv_fp8()) enqueue<2>(grid, p, dec, st);
+    else enqueue<1>(grid, p, dec, st);
     return hipGetLastError();
 }
 

@@ -189,3 +189,22 @@ def test_prefill_kernels_agree_on_dispatch(oracle, G, opts):
         want = oracle.attention_case(case, oracle.cache_for_case(case), rows)
         got = G.prefill_case(case, G.cache_for_case(case))
         _check(got[rows], want)
+
+
+# 32-key tiles a pass walks: every remainder of the loop's four tiles a trip from one tile on, and the ends of the 64 addresses
+# that a wavefront holds ready (K runs out after 60 iterations, then after 64 more)
+TILE_COUNTS = [1, 2, 3, 4, 5, 6, 7, 8, 59, 60, 61, 62, 63, 64, 65, 66, 123, 124, 125, 129]
+
+
+@pytest.mark.parametrize("scaled_q", [0, 1])
+@pytest.mark.parametrize("tiles", TILE_COUNTS)
+def test_wide_prefill_kernel_at_the_ends_of_its_loop(oracle, G, opts, tiles, scaled_q):
+    """One workgroup of the 256-column kernel walks exactly `tiles` tiles, the last of them ragged; the scaled-Q bound as above."""
+    opts(tile=256, splits=1, pairing=2, scaled_q=scaled_q)
+    ctx = 32 * tiles - 5
+    case = W.make_attn_case("t", 97 + tiles, "bf16", [(min(20, ctx), ctx)], 8, 1, 128)
+    want = oracle.attention_case(case, oracle.cache_for_case(case))
+    got = W.to_f64(G.prefill_case(case, G.cache_for_case(case, fill_byte=0xFF)), "bf16")
+    assert got.shape == want.shape and np.all(np.isfinite(got))
+    err = np.abs(got - want)
+    assert np.all(err <= BF16_MAX + (2.0 ** -7 * np.abs(want) if scaled_q else 0)) and err.mean() <= BF16_MEAN, (err.max(), err.mean())
