@@ -341,7 +341,8 @@ int32_t shiftattn_use_base_config(int32_t n_tokens, int32_t threshold);
  *   array): call it once per device before capturing calls into a HIP graph.  Thread-safe.
  * shiftattn_set_option / shiftattn_get_option: process-wide switches, 0 = the library decides per call
  *   (the default, and the fastest).  Set them before asking for workspace sizes: the sizes follow them.
- *   SHIFTATTN_OPT_PREFILL_TILE   128 | 256: which prefill kernel takes bf16 / head_dim 128 launches
+ *   SHIFTATTN_OPT_PREFILL_TILE   128 | 256: columns of the prefill tiles that bf16 / head_dim 128 launches take (of 128 there are
+ *                                two kernels, chosen per launch)
  *   SHIFTATTN_OPT_PREFILL_SPLITS 1 .. 64: key ranges per column tile of those kernels
  *   SHIFTATTN_OPT_GENERIC_ONLY   1: every attention call runs the general kernel (any type / head_dim)
  *   SHIFTATTN_OPT_PREFILL_PAIRING 1 | 2: the prefill kernels take a sequence's column tiles two per workgroup,

@@ -99,6 +99,7 @@ bool launch_prefill_and_decode(const void* q, void* cache, const int32_t* block_
 
 // prefill_mfma64.hip : the same operation on 256-column workgroup tiles, one 64-column wavefront per SIMD; bf16 cache
 struct Prefill64Plan {
+    int groups;  // 1: tiles of 256 columns; 2: tiles of 128, two groups of wavefronts that share the keys of a tile
     int tile_tokens, pair_ranks, n_splits;  // pair_ranks: workgroups per (sequence, KV head, key range)
     bool paired;                            // a workgroup takes two tiles of a sequence (heaviest with lightest)
     bool rotate;                            // rotate_sequences_over_dies() of the batch

@@ -760,10 +760,9 @@ bool prefill_mfma_supported(const AttnShape& a, int num_seqs, int max_seq_len) {
 
 namespace {
 
-// Which of the two kernels serves a launch.  The 256-column kernel is the faster one per MFMA (about 12 %), but its tiles
-// are twice as large: a batch like 4 x 4096 tokens with 4 query heads per KV head makes 128 pairs of 256-column tiles and
-// 256 pairs of 128-column tiles, and only the latter cover the chip with equal workgroups and no merge pass.  The choice
-// compares the two plans under the same rough model of a launch.
+// Which kernel serves a launch: the 128-column kernel of this file (narrow) or one of the two forms of the 64-column wavefronts
+// of prefill_mfma64.hip, tiles of 256 columns (wide) and of 128 with two groups of wavefronts (half; w.groups == 2).
+// choose() compares the narrow and the wide plan under a rough model of a launch; see plan_within() for what is launched.
 struct Choice {
     bool wide;
     Plan narrow;
@@ -805,20 +804,31 @@ size_t split_bytes_of(const Choice& c, int total_q, const AttnShape& a) {
 // fill the chip, and a chip left idle where they do not (a few prompts of some hundred tokens, a short chunk behind a
 // long context: 47 tokens on 9062 cached, 4 heads, were one workgroup per key range that walked its range twice).  Its
 // plan stays the least workspace a call is accepted with and the plan of a caller that brings no more; beyond it, one
-// tile or two per workgroup and 1 to 32 key ranges of both kernels are priced with the model below.  Constants in
-// microseconds, fitted to 140 launches times about 40 plans each (prompts of 7 .. 16384 tokens, chunks behind 100 ..
-// 131072 cached, 1 .. 12 sequences, all head geometries): the fit is 5 % off (root mean square of the logarithm), its
-// choices 1 % slower than the best plan measured, where choose() alone was 45 % slower.
+// tile or two per workgroup and 1 to 32 key ranges of the three kernels are priced with the model below.  Constants in
+// microseconds, fitted to 110 launches times about 50 plans each (prompts of 40 .. 14000 tokens, chunks behind 100 ..
+// 60000 cached, 1 .. 12 sequences, all head geometries): the fit is 9 % off (root mean square of the logarithm), its
+// choices 1.3 % slower than the best plan measured (64 times the narrow kernel's, 36 the half, 10 the wide form's; without the
+// half form 3.7 %).
 struct TileKernel {
     double pass, second_pass;  // around the key loop: set-up, Q, first and last tile, write-out
     double step, step_full;    // one step of the key loop, and what it costs more once every compute unit is busy
     int keys_per_step;
-    double several;            // factor where the batch has several sequences: among 70 random batches of 2 .. 12 the choice differs
-                               // from that of a factor 1 by more than 1.5 % in time in eight, two of them slower, the eight 2.7 %
-                               // faster together (two chunks of 1739 tokens on 31682 were 10 % faster)
+    double several;            // factor where the batch has several sequences
 };
-constexpr TileKernel kNarrowCost = {2.65, 3.1, 1.4, 0.335, 2 * kKvTile, 1.0};   // two groups of wavefronts, a tile of 64 keys each
-constexpr TileKernel kWideCost = {10.1, 9.5, 0.77, 0.03, 32, 1.08};
+constexpr TileKernel kNarrowCost = {1.94, 3.35, 1.362, 0.281, 2 * kKvTile, 1.084};   // two groups of wavefronts, a tile of 64 keys each
+constexpr TileKernel kWideCost = {3.9, 3.1, 0.592, 0.039, 32, 1.108};
+constexpr TileKernel kHalfCost = {5.35, 5.3, 0.506, 0.167, 64, 1.089};   // two groups of wavefronts, a tile of 32 keys each: fewer
+    // clocks a key than the narrow kernel's, more around the loop; the cheaper one from about 1200 keys on (4 x 4096 tokens of 4 heads
+    // 73.2 -> 67.6 us without the append, 11 prompts of 149 to 1097 of 5 heads 23.5 -> 26.7)
+// the kernels a launch can take: the 128-column kernel and the two tilings of the 256-column kernel's file
+enum Kind { kNarrow, kWide, kHalf, kKinds };
+const TileKernel& cost_of(Kind k) { return k == kNarrow ? kNarrowCost : k == kWide ? kWideCost : kHalfCost; }
+bool kind_allowed(Kind k, const AttnShape& bf16) {
+    const int forced = option_prefill_tile();
+    if (k == kNarrow) return forced != 256 || !prefill_mfma64_supported(bf16);
+    if (!prefill_mfma64_supported(bf16)) return false;
+    return k == kWide ? forced != 128 : forced != 256 && bf16.hq_l / bf16.hkv_l <= 128;
+}
 
 double launch_us(const TileKernel& k, bool paired, int splits, int tile_tokens, int heads, int num_seqs, int total_q,
                  int max_q_len, int max_seq_len, int hq_l) {
@@ -864,35 +874,52 @@ double launch_us(const TileKernel& k, bool paired, int splits, int tile_tokens, 
     return (span + 6.6) * (1.0 + 0.008 * splits);   // (launch; among equals the plan with fewer ranges)
 }
 
+// What the model must promise before a launch leaves the 128-column kernel: 54 drawn batches and prompts against the launches
+// without the half form are 1.023 times as fast with it (two 2 to 4 % slower, none of the others 2 %), 1.020 without it (five).
+constexpr double kMargin = 1.035;
+// Keys a range of the half form holds at least: what it gains in its loop, it loses around it in shorter ones (110 launches: the
+// same choices with lines from 0 to 1536; below, the model says little about it).
+constexpr int kHalfLeastKeys = 1024;
+
+Kind kind_of(const Choice& c) { return !c.wide ? kNarrow : c.w.groups == 1 ? kWide : kHalf; }
+
+// `c` with one of the kernels, tiles in pairs or one per workgroup, and that many key ranges
+void set_plan(Choice& c, Kind kind, bool paired, int splits, int num_seqs, int max_q_len, const AttnShape& a) {
+    c.wide = kind != kNarrow;
+    if (kind == kNarrow) {
+        const int tiles = (max_q_len + c.narrow.tile_tokens - 1) / c.narrow.tile_tokens;
+        c.narrow.paired = paired, c.narrow.pair_ranks = paired ? (tiles + 1) / 2 : tiles, c.narrow.n_splits = splits;
+        return;
+    }
+    c.w.groups = kind == kWide ? 1 : 2;
+    c.w.tile_tokens = 256 / c.w.groups / (a.hq_l / a.hkv_l);
+    const int tiles = (max_q_len + c.w.tile_tokens - 1) / c.w.tile_tokens;
+    c.w.paired = paired, c.w.pair_ranks = paired ? (tiles + 1) / 2 : tiles, c.w.n_splits = splits;
+    c.w.workgroups = static_cast<long>(c.w.pair_ranks) * splits * num_seqs * a.hkv_l;
+}
+
+double priced(const Choice& c, int num_seqs, int total_q, int max_q_len, int max_seq_len, const AttnShape& a) {
+    return c.wide ? launch_us(cost_of(kind_of(c)), c.w.paired, c.w.n_splits, c.w.tile_tokens, a.hkv_l, num_seqs, total_q, max_q_len, max_seq_len, a.hq_l)
+                  : launch_us(kNarrowCost, c.narrow.paired, c.narrow.n_splits, c.narrow.tile_tokens, c.narrow.head_slots, num_seqs, total_q,
+                              max_q_len, max_seq_len, a.hq_l);
+}
+
 Choice plan_within(size_t split_budget, int num_seqs, int total_q, int max_q_len, int max_seq_len, const AttnShape& a) {
     Choice best = choose(num_seqs, total_q, max_q_len, max_seq_len, a);
     AttnShape b = a;
     b.kv_elem = b.elem;
-    const int forced_tile = option_prefill_tile(), forced_splits = option_prefill_splits(), forced_pairing = option_prefill_pairing();
-    const bool wide_ok = prefill_mfma64_supported(b);
-    auto priced = [&](const Choice& c) {
-        return c.wide ? launch_us(kWideCost, c.w.paired, c.w.n_splits, c.w.tile_tokens, a.hkv_l, num_seqs, total_q, max_q_len, max_seq_len, a.hq_l)
-                      : launch_us(kNarrowCost, c.narrow.paired, c.narrow.n_splits, c.narrow.tile_tokens, c.narrow.head_slots, num_seqs,
-                                  total_q, max_q_len, max_seq_len, a.hq_l);
-    };
-    double best_us = 0.97 * priced(best);   // (what is left of choose()'s plan only for a gain beyond the model's error)
+    const int forced_splits = option_prefill_splits(), forced_pairing = option_prefill_pairing();
+    // (what is left of choose()'s plan only for a gain beyond the model's error)
+    double best_us = 0.97 * priced(best, num_seqs, total_q, max_q_len, max_seq_len, a);
     Choice c = best;
     auto try_ranges = [&](int splits) {
         if (split_bytes(splits, total_q, a) > split_budget) return;
-        for (int wide = 0; wide < 2; ++wide) {
-            if (wide ? !wide_ok || forced_tile == 128 : wide_ok && forced_tile == 256) continue;
+        for (int k = 0; k < kKinds; ++k) {
+            if (!kind_allowed(static_cast<Kind>(k), b) || (k == kHalf && max_seq_len < splits * kHalfLeastKeys)) continue;
             for (int paired = 0; paired < 2; ++paired) {
                 if (forced_pairing != 0 && paired != (forced_pairing == 1)) continue;
-                c.wide = wide != 0;
-                const int tile_tokens = wide ? c.w.tile_tokens : c.narrow.tile_tokens;
-                const int tiles = (max_q_len + tile_tokens - 1) / tile_tokens, ranks = paired ? (tiles + 1) / 2 : tiles;
-                if (wide) {
-                    c.w.paired = paired != 0, c.w.pair_ranks = ranks, c.w.n_splits = splits;
-                    c.w.workgroups = static_cast<long>(ranks) * splits * num_seqs * a.hkv_l;
-                } else {
-                    c.narrow.paired = paired != 0, c.narrow.pair_ranks = ranks, c.narrow.n_splits = splits;
-                }
-                const double us = priced(c);
+                set_plan(c, static_cast<Kind>(k), paired != 0, splits, num_seqs, max_q_len, a);
+                const double us = (k == kNarrow ? 1.0 : kMargin) * priced(c, num_seqs, total_q, max_q_len, max_seq_len, a);
                 if (us < best_us) best = c, best_us = us;
             }
         }
@@ -1029,6 +1056,9 @@ hipError_t launch_prefill_mfma(const void* q, const void* cache, const int32_t* 
 // decodes (256-column kernel): 1028 -> 974; 1536 on 90000 with 100: 670 -> 602.
 namespace {
 
+// the 128-column kernel beside decode rows (fitted before its constants above were: 200 random unified batches)
+constexpr TileKernel kNarrowBesideRows = {2.65, 3.1, 1.4, 0.335, 2 * kKvTile, 1.0};
+
 struct BothPlan {
     bool taken, wide;
     Plan narrow;
@@ -1045,9 +1075,10 @@ double decode_bytes(int num_seqs, int max_seq_len, const AttnShape& a) {
     return 0.6 * num_seqs * static_cast<double>(max_seq_len) * a.hkv_l * 2 * kD * a.kv_elem;
 }
 constexpr double kDecodeStartUs = 5.0, kBf16BytesPerUsWg = 60e3, kFp8BytesPerUsWg = 48e3, kDecodeBytesPerUs = 5.8e6;
-constexpr double kFourWaves = 0.85;   // of that with four wavefronts per workgroup (the 256-column kernel's) instead of eight
+constexpr double kFourWaves = 0.85, kFp8FourWaves = 0.45;   // of that with four wavefronts per workgroup
+// (the kernels of 64-column wavefronts) instead of eight (97 FP8 rows of up to 16000 beside 1000 tokens on 20000: 132 us narrow, 140 wide, 147 half)
 double decode_us(double bytes, double wgs, bool fp8, bool wide) {
-    const double rate = wgs * (fp8 ? kFp8BytesPerUsWg : kBf16BytesPerUsWg) * (wide ? kFourWaves : 1.0);
+    const double rate = wgs * (fp8 ? kFp8BytesPerUsWg : kBf16BytesPerUsWg) * (!wide ? 1.0 : fp8 ? kFp8FourWaves : kFourWaves);
     return kDecodeStartUs + bytes / (rate < kDecodeBytesPerUs ? rate : kDecodeBytesPerUs);
 }
 
@@ -1074,45 +1105,40 @@ BothPlan plan_both(int num_seqs, int total_q, int max_q_len, int max_seq_len, in
     const double bytes = decode_bytes(num_dec, max_dec_len, a);
     if (bytes < 1e6) return best;   // (a few short rows: nothing to share, and the workspace stays the larger of the two parts')
     const Choice alone = plan_within(SIZE_MAX, num_seqs, total_q, max_q_len, max_seq_len, a);
-    const Plan& base = alone.narrow;
-    const double chunks_us = alone.wide ? launch_us(kWideCost, alone.w.paired, alone.w.n_splits, alone.w.tile_tokens, a.hkv_l, num_seqs, total_q,
-                                                    max_q_len, max_seq_len, a.hq_l)
-                                        : launch_us(kNarrowCost, base.paired, base.n_splits, base.tile_tokens, base.head_slots, num_seqs, total_q,
-                                                    max_q_len, max_seq_len, a.hq_l);
+    const double chunks_us = priced(alone, num_seqs, total_q, max_q_len, max_seq_len, a);
     double best_us = 0.97 * (chunks_us + decode_us(bytes, 256, a.kv_fp8(), false) + 9.0), at_least_us = 0.0;
     const double seqs = longest_chunk_equivalents(num_seqs, total_q, max_q_len);
     const int q = max_q_len < max_seq_len ? max_q_len : max_seq_len;
     AttnShape b16 = a;
     b16.kv_elem = b16.elem;
-    for (int wide = 0; wide < 2; ++wide) {
-        if (wide ? !prefill_mfma64_supported(b16) || option_prefill_tile() == 128 : option_prefill_tile() == 256) continue;
-        const TileKernel& k = wide ? kWideCost : kNarrowCost;
-        const int tile_tokens = wide ? alone.w.tile_tokens : base.tile_tokens, heads = wide ? a.hkv_l : base.head_slots;
-        const int tiles = (max_q_len + tile_tokens - 1) / tile_tokens;
+    for (int kind = 0; kind < kKinds; ++kind) {
+        if (!kind_allowed(static_cast<Kind>(kind), b16)) continue;
+        const TileKernel& k = kind == kNarrow ? kNarrowBesideRows : cost_of(static_cast<Kind>(kind));
+        Choice c = alone;
+        set_plan(c, static_cast<Kind>(kind), false, 1, num_seqs, max_q_len, a);
+        const int tile_tokens = c.wide ? c.w.tile_tokens : c.narrow.tile_tokens, heads = c.wide ? a.hkv_l : c.narrow.head_slots;
+        const int tiles = c.wide ? c.w.pair_ranks : c.narrow.pair_ranks;
+        const bool four_waves = c.wide;
         const double lightest = max_seq_len - q + (tile_tokens < q ? tile_tokens : q);
         const double step = (k.step + k.step_full) / k.keys_per_step;   // per key
-        auto rows_us = [&](double x) { return decode_us(bytes, x, a.kv_fp8(), wide != 0); };
+        auto rows_us = [&](double x) { return decode_us(bytes, x, a.kv_fp8(), four_waves); };
         for (int splits : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 24, 32}) {
             if (splits > 1 && max_seq_len < splits * 2 * kKvTile) break;
+            if (kind == kHalf && max_seq_len < splits * kHalfLeastKeys) break;
             const double wgs = tiles * seqs * heads * splits, grid = static_cast<double>(tiles) * num_seqs * heads * splits;
             const double merge = splits > 1 ? splits * static_cast<double>(total_q) * a.hq_l * 1040 / 5.8e6 : 0.0;
             auto consider = [&](double x, double div, double span) {
-                const double us = (span * (num_seqs > 1 ? k.several : 1.0) + merge + 6.6 + 4.5) * (1.0 + 0.008 * splits);
+                const double us = (kind == kNarrow ? 1.0 : kMargin) * (span * (num_seqs > 1 ? k.several : 1.0) + merge + 6.6 + 4.5) * (1.0 + 0.008 * splits);
                 if (us >= best_us) return;
                 best_us = us;
-                at_least_us = decode_us_at_least(bytes, x, a.kv_fp8(), wide != 0) + merge + 6.6 + 4.5;
+                at_least_us = decode_us_at_least(bytes, x, a.kv_fp8(), four_waves) + merge + 6.6 + 4.5;
+                set_plan(c, static_cast<Kind>(kind), false, splits, num_seqs, max_q_len, a);
                 best.taken = true;
-                best.wide = wide != 0;
-                best.narrow = base;
-                best.w = alone.w;
-                if (wide) {
-                    best.w.paired = false, best.w.pair_ranks = tiles, best.w.n_splits = splits;
-                    best.w.workgroups = static_cast<long>(tiles) * splits * num_seqs * a.hkv_l;
-                } else {
-                    best.narrow.paired = false, best.narrow.pair_ranks = tiles, best.narrow.n_splits = splits;
-                }
+                best.wide = c.wide;
+                best.narrow = c.narrow;
+                best.w = c.w;
                 best.dec_wgs = static_cast<int>(x);
-                best.dec_waves = best.dec_wgs * (wide ? kPrefill64Waves : kDecodeWaves);
+                best.dec_waves = best.dec_wgs * (four_waves ? kPrefill64Waves : kDecodeWaves);
                 best.range_div = static_cast<float>(div);
                 best.partial_bytes = split_bytes(splits, total_q, a);
             };

@@ -21,8 +21,8 @@
 //
 // Softmax against a reference that lags.  Softmax does not care which reference its exponentials are shifted by as long
 // as nothing leaves the range of bf16 and the fp32 sums.  The first attempt at a pass takes the reference from the
-// column's first visible key tile (whose maximum then gets P = 1 exactly: a row with few keys, all in that tile, comes
-// out as exactly as the careful way would give it) and follows no maximum behind it: a fused multiply-add, an
+// column's first visible key tile, or the first two (whose maximum then gets P = 1 exactly: a row with few keys, all in
+// those, comes out as exactly as the careful way would give it) and follows no maximum behind it: a fused multiply-add, an
 // exponential and the row sum per logit, one packing per two, is all the loop spends on the softmax.  Real logits stay
 // within 2^100 of their first tile's maximum, and P up to 2^100 is held by bf16 and the fp32 sums without loss; a column
 // whose sum ends beyond that flags the pass, which is then run again the careful way: the exponentials of a tile are
@@ -51,6 +51,12 @@
 // evenly, the addresses of the loads are kept ready in a vector register pair, and nothing is moved between register files.
 // MFMA pipe busy 59 -> 77 % of the clocks; what is left is the power limit, the clock settles at 1.76 instead of 2.05 GHz:
 // 16384 tokens of 8 heads 464 -> 424 us, 2048 tokens on 131072 cached with 64 decodes 957 -> 882.
+//
+// Two groups (kG = 2).  The same wavefronts on a tile of 128 columns: wavefronts 0 and 1 walk the even key tiles, 2 and 3 the odd
+// ones, each pair with a ring of its own and a first-tile reference of its own, and the groups merge through LDS at the end, each
+// finishing one half of the head dimension.  Twice the bytes into LDS per MFMA, half the length of a pass: what batches take whose
+// 256-column tiles would not fill the chip.  4 x 4096 tokens of 4 heads: 73.2 us in the 128-column kernel of eight 32-column
+// wavefronts, 85 in tiles of 256 columns, 67.6 here.
 //
 // Scheduling: tiles of a sequence are processed in pairs (heaviest with lightest) by one workgroup; a short chunk on a
 // long context is taken one tile per workgroup, its keys split into ranges merged by launch_combine.
@@ -81,8 +87,14 @@ constexpr int kRingBytes = 4 * kStageBytes;    // 65536
 constexpr int kBlockBytes = kBlockSize * kD * 2;  // 4096: K (or V^T) of one cache block and head
 constexpr int kPitch = 272;                    // row pitch of the output staging tile (256 + 16 bytes)
 constexpr int kFlagBytes = 16;                 // one redo flag per wavefront
-constexpr int kIdsAt = kRingBytes + kCols * kPitch + kFlagBytes;  // two windows of 64 block ids per wavefront
+constexpr int kFlagsAt = kRingBytes + kCols * kPitch;
+constexpr int kIdsAt = kFlagsAt + kFlagBytes;  // two windows of 64 block ids per wavefront
 constexpr int kLdsBytes = kIdsAt + kPrefill64Waves * 2 * 64 * 4;  // 137232
+// Two groups: a ring each; when the key loops are over the same bytes hold what the groups exchange - parked accumulators, one
+// (reference, sum) pair per column block and lane - and the staged rows.
+constexpr int kParkBytes = kPrefill64Waves * 64 * 64 * 4;                        // 65536
+constexpr int kMlAt = kParkBytes, kStagedAt = kMlAt + kPrefill64Waves * 2 * 64 * 8;  // 69632
+static_assert(2 * kRingBytes <= kFlagsAt && kStagedAt + kCols / 2 * kPitch <= 2 * kRingBytes);
 // A column's reference maximum may lag its true running maximum by this much (exp2 units): P reaches 2^32 at most, far
 // inside what bf16 and the fp32 sums hold (their relative precision does not depend on magnitude); O^T overflows only
 // for |V| beyond 2^70.
@@ -92,7 +104,7 @@ constexpr float kRefSlack = 32.0f;
 // from overflow (O^T overflows only for |V| beyond 2^87), and every logit that matters lies within 40 + log2(keys) of
 // zero (which also bounds what a second rounding of Q^T can move).  An infinity or a NaN fails the test.
 constexpr float kFreeSumLo = 0x1p-40f, kFreeSumHi = 0x1p40f;
-// The default first attempt keeps the reference the column's first key tile left and follows no maximum behind it: P may
+// The default first attempt keeps the reference the column's first key tiles left and follows no maximum behind it: P may
 // then reach 2^100 (still far inside bf16 and fp32 range; O^T overflows only for |V| beyond 2^27), and a sum beyond that
 // sends the pass to the attempts that do follow the maximum.
 constexpr float kKeepSumBound = 0x1p100f;
@@ -123,17 +135,17 @@ __device__ inline void wait_vm0() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 // MFMA outside the steady-state loop is guarded, the loop itself has no such writes (its accumulators never move).
 template <bool kGuard>
 __device__ SHIFTATTN_FORCE_INLINE void mfma_s_first(f32x16& d, u32x4 a, bf16x8 b) {
-    if constexpr (kGuard) asm volatile("s_nop 4\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "a"(b));
+    if constexpr (kGuard) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "a"(b));
     else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "a"(b));
 }
 template <bool kGuard>
 __device__ SHIFTATTN_FORCE_INLINE void mfma_s_acc(f32x16& d, u32x4 a, bf16x8 b) {
-    if constexpr (kGuard) asm volatile("s_nop 4\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "a"(b));
+    if constexpr (kGuard) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "a"(b));
     else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "a"(b));
 }
 template <bool kGuard>
 __device__ SHIFTATTN_FORCE_INLINE void mfma_o_acc(f32x16& d, u32x4 a, u32x4 b) {
-    if constexpr (kGuard) asm volatile("s_nop 4\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(a), "v"(b));
+    if constexpr (kGuard) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(a), "v"(b));
     else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(a), "v"(b));
 }
 // Wait states in front of compiler-generated reads of accumulators (and of anything else in their registers): the
@@ -185,7 +197,8 @@ struct Prefill64Params {
     float* __restrict__ ml_part;
     int64_t q_stride, out_stride;
     int num_seqs, total_q, hq_l, hkv_l, G;
-    int tile_tokens;  // kCols / G
+    int tile_tokens;  // columns of a tile / G
+    int g_magic;      // 2^20 / G rounded up: x * g_magic >> 20 is x / G for the columns x < 256 of a tile
     int n_splits;     // key ranges per tile
     int paired;       // tiles of a sequence taken two per workgroup (see prefill_mfma64_plan)
     int rotate;       // the (sequence, KV head) index is rotated by the (tile rank, key range) index (see internal.h)
@@ -201,7 +214,9 @@ static_assert(kThreads == 64 * kPrefill64Waves && decode_flat::kRoleLdsBytes<kPr
 
 // kDecode: 0 = prefill only; 1, 2 = the first workgroups take decode rows over a bf16 (1) or FP8 (2) cache
 // kScaledQ: the first attempt at a pass works on Q^T times the softmax scale, rounded to bf16 again
-template <int kDecode, bool kScaledQ>
+// kG: groups of wavefronts.  1: a tile of 256 columns, all four wavefronts on the same keys.  2: a tile of 128 columns, wavefronts
+// 0 and 1 on the even key tiles, 2 and 3 on the odd ones, merged through LDS at the end
+template <int kDecode, bool kScaledQ, int kG>
 __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params p, DecodeRole dec) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     if constexpr (kDecode != 0) {
@@ -213,6 +228,9 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int grp = kG == 1 ? 0 : wave >> 1, wcol = kG == 1 ? wave : wave & 1;   // group; 64-column block of the tile
+    constexpr int kGroupThreads = kThreads / kG;
+    const int gtid = tid & (kGroupThreads - 1);
 
     // ---- which (pair rank, key split, sequence, KV head) is this workgroup --------------------------------------
     const int n_sg = p.num_seqs * p.hkv_l;
@@ -226,6 +244,9 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
     const int ctx = p.seq_lens[s];
     const int tile_tokens = p.tile_tokens;
     const int cols_used = tile_tokens * p.G;
+    // token and head of a column of the tile (a division costs some thirty instructions, and a pass has forty of them: 2 us)
+    auto token_of = [&](int col) SHIFTATTN_INLINE -> int { return static_cast<int>(static_cast<uint32_t>(col * p.g_magic) >> 20); };
+    auto head_of = [&](int col) SHIFTATTN_INLINE -> int { return g * p.G + col - token_of(col) * p.G; };
     const int n_tiles = (q_len + tile_tokens - 1) / tile_tokens;
     // paired: the workgroup takes tile n_tiles - 1 - rank and then tile rank (heaviest with lightest); else the former
     // alone - workgroups start in the order of their index, so the heaviest tiles of all sequences go first and the light
@@ -236,14 +257,15 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
     const int32_t* table = p.block_table + static_cast<size_t>(s) * p.max_blocks;
     const int last_block = (ctx - 1) / kBlockSize;
 
-    // in the key loop wavefronts 0 and 1 bring K (cache block 0 / 1 of a tile), wavefronts 2 and 3 V^T
-    const bool is_k = wave < 2;
+    // In the key loop of one group wavefronts 0 and 1 bring K (cache block 0 / 1 of a tile), wavefronts 2 and 3 V^T; of two groups
+    // either wavefront brings K and V^T of its cache block.
+    const bool is_k = kG == 2 || wave < 2;
     const int ld_blk = wave & 1;
-    // LDS address of this wavefront's u-th load: ld_dst for u % 4 = 0, ld_dst2 for 2, one stage further for 1 and 3
-    const int lds_at = static_cast<int>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char*)lds));
+    // LDS address of this wavefront's u-th load: ld_dst for u % 4 = 0, ld_dst2 for 2, one stage further for 1 and 3.  (Of two groups
+    // that is K's; V^T goes kKBytes further, to the stage two before.)
+    const int lds_at = static_cast<int>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char*)lds)) + grp * kRingBytes;
     const int ld_dst = __builtin_amdgcn_readfirstlane(lds_at + (is_k ? 0 : 2 * kStageBytes + kKBytes) + ld_blk * kBlockBytes);
     const int ld_dst2 = __builtin_amdgcn_readfirstlane(lds_at + (is_k ? 2 * kStageBytes : kKBytes) + ld_blk * kBlockBytes);
-    const size_t blk_bytes = static_cast<size_t>(p.hkv_l) * 2 * kBlockBytes;
     // a wavefront-uniform pointer, said explicitly to be in scalar registers
     auto uniform_ptr = [](const unsigned char* ptr) SHIFTATTN_INLINE -> const unsigned char* {
         const uint64_t a = reinterpret_cast<uint64_t>(ptr);
@@ -277,7 +299,7 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
         int lane_p = lane;
         asm volatile("" : "+v"(lane_p));
         const int l32 = lane_p & 31, half = lane_p >> 5;
-        const int lds_base = static_cast<int>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char*)lds));
+        const int lds_base = lds_at;
         // K operand of MFMA row l32 is K row tau (bits 2 and 3 swapped); piece c of row r sits at c ^ (r & 15)
         const int tau = (l32 & 0x13) | ((l32 & 4) << 1) | ((l32 & 8) >> 1);
         int k_rd[8];
@@ -298,15 +320,16 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
             k_ld[x] = r0 * 256 + (((lane_p & 15) ^ r0 ^ (4 * x)) << 4);
         }
         const int v_ld = kBlockBytes + (lane_p >> 1) * 32 + (((lane_p & 1) ^ ((lane_p >> 4) & 1)) << 4);
+        const int v_off[4] = {v_ld, v_ld, v_ld, v_ld};
         int ld_off[4];
 #pragma unroll
-        for (int x = 0; x < 4; ++x) ld_off[x] = is_k ? k_ld[x] : v_ld;
+        for (int x = 0; x < 4; ++x) ld_off[x] = is_k ? k_ld[x] : v_ld;   // (two groups: K's, V^T's is v_ld)
         int pos_col[2];
         bf16x8 qf[2][8];
 #pragma unroll
         for (int cb = 0; cb < 2; ++cb) {
-            const int cw = wave * 64 + cb * 32 + l32;
-            const int tok = tok0 + cw / p.G;
+            const int cw = wcol * 64 + cb * 32 + l32;
+            const int tok = tok0 + token_of(cw);
             const bool valid = cw < cols_used && tok < q_len;
             pos_col[cb] = valid ? ctx - q_len + tok : -1;
         }
@@ -320,12 +343,12 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
             const uint16_t* q_ptr[2];
 #pragma unroll
             for (int cb = 0; cb < 2; ++cb) {
-                const int cw = wave * 64 + cb * 32 + (lane_q & 31);
+                const int cw = wcol * 64 + cb * 32 + (lane_q & 31);
                 // a column beyond the tile's or the sequence's end reads the row of the nearest real one: every one of
                 // its logits is masked (position -1) or its results are dropped, and columns do not mix
                 const int cw_r = min(cw, cols_used - 1);
-                const int tok_r = min(tok0 + cw_r / p.G, q_len - 1);
-                q_ptr[cb] = p.q + static_cast<size_t>(q_begin + tok_r) * p.q_stride + (g * p.G + cw_r % p.G) * kD + (lane_q >> 5) * 8;
+                const int tok_r = min(tok0 + token_of(cw_r), q_len - 1);
+                q_ptr[cb] = p.q + static_cast<size_t>(q_begin + tok_r) * p.q_stride + head_of(cw_r) * kD + (lane_q >> 5) * 8;
             }
             load_q_to_acc(qf[0], qf[1], q_ptr[0], q_ptr[1]);
             if constexpr (decltype(with_scale)::value != 0) {
@@ -342,9 +365,9 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
                     }
             }
         };
-        const int w_tok_first = tok0 + (wave * 64) / p.G;
+        const int w_tok_first = tok0 + token_of(wcol * 64);
         const int w_pos_min =
-            __builtin_amdgcn_readfirstlane((wave * 64 < cols_used && w_tok_first < q_len) ? ctx - q_len + w_tok_first : -1);
+            __builtin_amdgcn_readfirstlane((wcol * 64 < cols_used && w_tok_first < q_len) ? ctx - q_len + w_tok_first : -1);
 
         // ---- key tiles of this (column tile, split) -------------------------------------------------------
         const int tile_pos_max = ctx - q_len + min(tok0 + tile_tokens, q_len) - 1;
@@ -352,9 +375,13 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
         const int per_split = kDecode == 0 ? (kv_tiles + p.n_splits - 1) / p.n_splits : static_cast<int>(ceilf(kv_tiles / p.range_div));
         const int kt_begin = __builtin_amdgcn_readfirstlane(split * per_split);
         const int kt_end = kDecode != 0 && split == p.n_splits - 1 ? kv_tiles : min(kv_tiles, kt_begin + per_split);
-        const int n = __builtin_amdgcn_readfirstlane(max(kt_end - kt_begin, 0));
+        const int n_all = __builtin_amdgcn_readfirstlane(max(kt_end - kt_begin, 0));
+        // this group's tiles: kt_first + kG j, j < n (the first group has as many or one more)
+        const int n = (n_all + kG - 1 - grp) / kG;
+        const int kt_first = kt_begin + grp;
         // the tile that reaches past the context (if any) holds unwritten V slots: cleared in LDS before use
-        const bool ragged = n > 0 && kt_end * kKv > ctx;
+        // (asked where it is needed: kept through the key loop it would cost scalar registers)
+        auto is_ragged = [&]() SHIFTATTN_INLINE -> bool { return n_all > 0 && kt_end * kKv > ctx; };
 
         f32x16 oacc[2][4];
         f32x16 sbuf[2][2];          // [parity][column block]
@@ -362,7 +389,7 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
         // per column block: reference maximum, its product with the scale (0 while there is none), the largest logit
         // the reference covers (reference + slack), running sum
         float m_used[2] = {-INFINITY, -INFINITY}, mc[2] = {0.f, 0.f}, bound[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};
-        bool redo = false;          // uniform: a column of this wavefront needed a rescaling the key loop does not do
+        int redo = 0;               // uniform: a column of this wavefront needed a rescaling the key loop does not do
         float m_rep[2] = {-INFINITY, -INFINITY};
         const float thr = kRefSlack / p.c;  // how far a logit may exceed the reference (attempts that follow the maximum)
 
@@ -381,10 +408,10 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
         int u_left = 0, window = 0;   // loads left in the window; its number
         int* my_ids = reinterpret_cast<int*>(lds + kIdsAt) + __builtin_amdgcn_readfirstlane(wave * 128);
         auto block_index = [&](int w) SHIFTATTN_INLINE -> int {
-            return min(2 * (kt_begin + max(64 * w + lane_p - ld_ahead, 0)) + ld_blk, last_block);
+            return min(2 * (kt_first + kG * max(64 * w + lane_p - ld_ahead, 0)) + ld_blk, last_block);
         };
         auto take_window = [&](int id) SHIFTATTN_INLINE {   // ids are those of blocks that exist: not negative
-            const uint64_t a = reinterpret_cast<uint64_t>(cache_g) + static_cast<uint64_t>(static_cast<uint32_t>(id)) * blk_bytes;
+            const uint64_t a = reinterpret_cast<uint64_t>(cache_g) + static_cast<uint64_t>(static_cast<uint32_t>(id)) * static_cast<uint32_t>(p.hkv_l * 2 * kBlockBytes);
             a_lo = static_cast<uint32_t>(a);
             a_hi = static_cast<uint32_t>(a >> 32);
         };
@@ -414,16 +441,19 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
             }
         };
         // first iteration whose tile holds keys beyond the first column's position
-        const int j_diag = __builtin_amdgcn_readfirstlane(((w_pos_min - (kKv - 1) - kt_begin * kKv) >> 5) + 1);
+        const int j_diag = __builtin_amdgcn_readfirstlane(((w_pos_min - (kKv - 1) - kt_first * kKv) >> (4 + kG)) + 1);
 
         // zero the V^T entries of keys at or past the context in the given stage (tile kt)
         auto clear_ragged_v = [&](int kt, int stage_off) SHIFTATTN_INLINE {
-            const int d = tid >> 1, h = tid & 1;
+            const int h = gtid & 1;
 #pragma unroll
             for (int bi = 0; bi < 2; ++bi) {
                 const int n_valid = ctx - (kt * kKv + bi * 16 + h * 8);
+#pragma unroll
+                for (int d0 = 0; d0 < kD; d0 += kGroupThreads / 2)
                 if (n_valid < 8) {
-                    u32x4* ptr = reinterpret_cast<u32x4*>(lds + stage_off + kKBytes + bi * kBlockBytes + d * 32 +
+                    const int d = d0 + (gtid >> 1);
+                    u32x4* ptr = reinterpret_cast<u32x4*>(lds + grp * kRingBytes + stage_off + kKBytes + bi * kBlockBytes + d * 32 +
                                                           ((h ^ ((d >> 3) & 1)) << 4));
                     u32x4 v = *ptr;
 #pragma unroll
@@ -437,7 +467,8 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
         // One iteration on tile j.  PH = j % 4: selects the stages and, by its parity, the register sets at compile time.
         // track_c: 1 = the maximum is followed (TRACK); 2 = the reference the column's first key tile left is kept and no
         // maximum followed (KEEP); 0 = no reference at all, on logits that arrive in exp2 units (Q^T carries the scale)
-        auto body = [&](auto ph_c, auto guard_c, auto track_c, int j) SHIFTATTN_INLINE {
+        // s_lo, s_hi: addresses of the last four loads of K (two groups: V^T's is K's of two iterations before)
+        auto body = [&](auto ph_c, auto guard_c, auto track_c, int j, uint32_t (&s_lo)[4], uint32_t (&s_hi)[4]) SHIFTATTN_INLINE {
             constexpr int PH = decltype(ph_c)::value, PAR = PH & 1;
             constexpr bool GUARD = decltype(guard_c)::value != 0;  // outside the steady-state loop
             constexpr bool TRACK = decltype(track_c)::value == 1;
@@ -450,7 +481,7 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
             if (j >= j_diag) {  // tile crosses the diagonal of this wavefront: uniform
                 // (a real branch: the selects below take their inputs from a statement that cannot be moved out of it)
                 asm volatile("; keys beyond a column's position" : "+v"(s_cur[0]), "+v"(s_cur[1]));
-                mask_tile(s_cur, (kt_begin + j) * kKv);
+                mask_tile(s_cur, (kt_first + kG * j) * kKv);
             }
 
             // operand reads: op o feeds the two MFMAs (column blocks 0 and 1) of slots 2 o and 2 o + 1: even ops K of tile j + 1,
@@ -519,7 +550,15 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
             // (slots 9 to 15): all four right behind the barrier hold up the matrix pipe (2048 tokens on 131072 cached beside 64
             // decodes: 3 % of the launch).  Loads beyond the last tile are made all the same (of the context's last block at most):
             // the count that the wait relies on then always holds.
-            uint32_t src_lo = 0, src_hi = 0;
+            auto next_window = [&]() SHIFTATTN_INLINE {
+                if (--u_left == 0) {
+                    take_window(my_ids[(window & 1) * 64 + lane_p]);
+                    request_window(++window);
+                    u_left = 64;
+                }
+            };
+            uint32_t& src_lo = s_lo[PH];
+            uint32_t& src_hi = s_hi[PH];
             auto housekeeping = [&](auto tc) SHIFTATTN_INLINE {
                 constexpr int t = decltype(tc)::value;
                 if constexpr (t == 1) {
@@ -529,7 +568,8 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
                     // a bare barrier: __syncthreads() would first drain every outstanding LDS read.  What has to be complete
                     // is this wavefront's loads of the iteration before last (all but the last four it issued) and its reads of
                     // the stages about to be overwritten (their data went into MFMAs in the iteration before).
-                    asm volatile("s_waitcnt vmcnt(4)\n\ts_barrier" ::: "memory");
+                    if constexpr (kG == 1) asm volatile("s_waitcnt vmcnt(4)\n\ts_barrier" ::: "memory");
+                    else asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");
                 } else if constexpr (t == 3) {
                     src_hi = __builtin_amdgcn_readfirstlane(a_hi);
                     asm volatile("" : "+s"(src_hi));
@@ -537,17 +577,25 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
                     a_lo = lane_above(a_lo);
                 } else if constexpr (t == 7) {
                     a_hi = lane_above(a_hi);
-                    if (--u_left == 0) {
-                        take_window(my_ids[(window & 1) * 64 + lane_p]);
-                        request_window(++window);
-                        u_left = 64;
-                    }
+                    if constexpr (!(kG == 2 && TRACK)) next_window();
+                } else if constexpr (t == 8) {
+                    // (two groups, the rare attempts that follow the maximum: a scalar register too few, kept in a vector lane)
+                    if constexpr (kG == 2 && TRACK) next_window();
                 } else if constexpr (t == 9) {
                     asm volatile("s_add_i32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                                  :: "s"(PH < 2 ? ld_dst : ld_dst2), "v"(ld_off[0]), "s"(join(src_lo, src_hi)), "n"((PH & 1) * kStageBytes) : "memory", "scc");
                 } else if constexpr (t == 11 || t == 13 || t == 15) {
                     constexpr int x = (t - 9) / 2;
                     asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2" :: "v"(ld_off[x]), "s"(join(src_lo, src_hi)), "n"(1024 * x) : "memory");
+                } else if constexpr (kG == 2 && (t == 17 || t == 19 || t == 21 || t == 23)) {   // V^T of tile j + 2
+                    constexpr int x = (t - 17) / 2, v2 = (PH + 2) & 3;
+                    const int off = v_off[x], dst = PH < 2 ? ld_dst2 : ld_dst;
+                    const unsigned char* v_src = join(s_lo[v2], s_hi[v2]);
+                    if constexpr (x == 0)
+                        asm volatile("s_add_i32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                                     :: "s"(dst), "v"(off), "s"(v_src), "n"((PH & 1) * kStageBytes + kKBytes) : "memory", "scc");
+                    else
+                        asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2" :: "v"(off), "s"(v_src), "n"(1024 * x) : "memory");
                 }
             };
             [&]<int... T>(std::integer_sequence<int, T...>) SHIFTATTN_INLINE {
@@ -603,7 +651,7 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
                     }
                     if (grow) l_run[cb] = ps;  // (a column that keeps its reference has just recomputed what it had)
                 }
-                if (__builtin_amdgcn_ballot_w64(bad)) redo = true;
+                redo = __builtin_amdgcn_readfirstlane(__builtin_amdgcn_ballot_w64(bad) ? 1 : redo);
             }
         };
 
@@ -611,9 +659,12 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
         auto issue_prologue = [&]() SHIFTATTN_INLINE {
             take_window(table[block_index(0)]);
 #pragma unroll
-            for (int x = 0; x < 4; ++x)
-            {
-                if (is_k || x >= 2) dma_4k(join(__builtin_amdgcn_readfirstlane(a_lo), __builtin_amdgcn_readfirstlane(a_hi)), ld_off, ((x & 2) ? ld_dst2 : ld_dst) + (x & 1) * kStageBytes);
+            for (int x = 0; x < 4; ++x) {
+                const unsigned char* from = join(__builtin_amdgcn_readfirstlane(a_lo), __builtin_amdgcn_readfirstlane(a_hi));
+                const int dst = ((x & 2) ? ld_dst2 : ld_dst) + (x & 1) * kStageBytes;
+                if (is_k || x >= 2) dma_4k(from, ld_off, dst);
+                if constexpr (kG == 2)
+                    if (x < 2) dma_4k(from, v_off, dst + kKBytes);
                 a_lo = lane_above(a_lo);
                 a_hi = lane_above(a_hi);
             }
@@ -632,7 +683,7 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
         // and then holds, for every column, a reference within the slack of the true maximum: the third attempt starts
         // from that and is not flagged.
         auto reset_sums = [&]() SHIFTATTN_INLINE {
-            redo = false;
+            redo = 0;
 #pragma unroll
             for (int cb = 0; cb < 2; ++cb) {
                 l_run[cb] = 0.f;
@@ -646,8 +697,8 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
             // prologue: S^T of the first tile (the loads are on their way).  Iteration 0 multiplies V^T "of tile -1" (stage 3) by
             // P = 0: zeros, so that no product of it is a NaN.
 #pragma unroll
-            for (int x = 0; x < 2; ++x)
-                *reinterpret_cast<u32x4*>(lds + 3 * kStageBytes + kKBytes + (x * kThreads + tid) * 16) = u32x4{0u, 0u, 0u, 0u};
+            for (int x = 0; x < 2 * kG; ++x)
+                *reinterpret_cast<u32x4*>(lds + grp * kRingBytes + 3 * kStageBytes + kKBytes + (x * kGroupThreads + gtid) * 16) = u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
             for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
@@ -667,37 +718,77 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
             pre_c = lds_read16(v_rd + 3 * kStageBytes);
             mfma_settle(sbuf[0]);
             if constexpr (decltype(track_c)::value == 2) {   // the reference that is kept: the first tile's maximum
-                if (j_diag <= 0) mask_tile(sbuf[0], kt_begin * kKv);
+                // (Keys that are their column's reference have P = 1, exact in bf16, and the heaviest keys carry most of the rounding
+                // error: where rows of less than 1000 keys are among the columns, the second tile's keys take part.  Prompts of
+                // 4096 tokens, 2-norm of the error of rows 128 to 256 3.8 % larger without.)
+                const bool second = n > 1 && (kG == 2 || w_pos_min < kt_first * kKv + 1000);
+                if (j_diag <= 0) mask_tile(sbuf[0], kt_first * kKv);
+                if (second) {
+#pragma unroll
+                    for (int ks = 0; ks < 8; ++ks) {
+                        const u32x4 a = lds_read16(k_rd[ks] + kStageBytes);
+#pragma unroll
+                        for (int cb = 0; cb < 2; ++cb) {
+                            if (ks == 0) mfma_s_first<true>(sbuf[1][cb], a, qf[cb][ks]);
+                            else mfma_s_acc<true>(sbuf[1][cb], a, qf[cb][ks]);
+                        }
+                    }
+                    mfma_settle(sbuf[1]);
+                    if (j_diag <= 1) mask_tile(sbuf[1], (kt_first + kG) * kKv);
+                }
 #pragma unroll
                 for (int cb = 0; cb < 2; ++cb) {
                     float mx = -INFINITY;
 #pragma unroll
                     for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sbuf[0][cb][r]);
+                    if (second)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sbuf[1][cb][r]);
                     mx = fmaxf(mx, __shfl_xor(mx, 32));
                     if (mx > -INFINITY) m_used[cb] = mx, mc[cb] = mx * p.c;
                 }
+                // The loop sums P as it was before the rounding to bf16.  Rows of few keys are what that tells on (their outputs are
+                // the large ones): where there are some, the sums begin with what rounding adds to the first tile's P, so that
+                // those rows divide by the sum of what they multiply (2-norm of the error of prompts of 4096 tokens 1.3 %
+                // larger without).
+                if (w_pos_min < kt_first * kKv + 128) {
+#pragma unroll
+                    for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) {
+                            const float e = __builtin_amdgcn_exp2f(fmaf(sbuf[0][cb][r], p.c, -mc[cb]));
+                            l_run[cb] += static_cast<float>(static_cast<__bf16>(e)) - e;
+                        }
+                }
             }
             // four tiles per trip, so that the stages and the register sets are fixed at compile time
+            uint32_t s_lo[4], s_hi[4];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {   // (the prologue's four addresses have gone round to the last lanes)
+                s_lo[x] = __builtin_amdgcn_readlane(a_lo, 60 + x);
+                s_hi[x] = __builtin_amdgcn_readlane(a_hi, 60 + x);
+            }
             int j = 0;
             for (; j + 4 <= n; j += 4) {
-                body(IC<0>{}, IC<0>{}, track_c, j);
-                body(IC<1>{}, IC<0>{}, track_c, j + 1);
-                body(IC<2>{}, IC<0>{}, track_c, j + 2);
-                body(IC<3>{}, IC<0>{}, track_c, j + 3);
+                body(IC<0>{}, IC<0>{}, track_c, j, s_lo, s_hi);
+                body(IC<1>{}, IC<0>{}, track_c, j + 1, s_lo, s_hi);
+                body(IC<2>{}, IC<0>{}, track_c, j + 2, s_lo, s_hi);
+                body(IC<3>{}, IC<0>{}, track_c, j + 3, s_lo, s_hi);
             }
             if (j < n) {
-                body(IC<0>{}, IC<1>{}, track_c, j);
+                body(IC<0>{}, IC<1>{}, track_c, j, s_lo, s_hi);
                 if (j + 1 < n) {
-                    body(IC<1>{}, IC<1>{}, track_c, j + 1);
-                    if (j + 2 < n) body(IC<2>{}, IC<1>{}, track_c, j + 2);
+                    body(IC<1>{}, IC<1>{}, track_c, j + 1, s_lo, s_hi);
+                    if (j + 2 < n) body(IC<2>{}, IC<1>{}, track_c, j + 2, s_lo, s_hi);
                 }
             }
             // (the S^T of the tile beyond the last is nobody's: its registers are free behind its MFMAs only)
             asm volatile("s_nop 7\n\ts_nop 3" :: "v"(sbuf[0][0]), "v"(sbuf[0][1]), "v"(sbuf[1][0]), "v"(sbuf[1][1]));
             // epilogue: O^T += V^T P^T of the last tile (in its stage since the barrier of the last iteration)
             const int last_stage = ((n - 1) & 3) * kStageBytes;
-            if (ragged) {
-                clear_ragged_v(kt_begin + n - 1, last_stage);
+            if (kG == 2 && n < (n_all + kG - 1) / kG) asm volatile("s_barrier" ::: "memory");   // (the other group's last iteration)
+            if (is_ragged()) {
+                if (kG == 1 || ((n_all - 1) & 1) == grp) clear_ragged_v(kt_end - 1, last_stage);
                 __syncthreads();
             }
             const bool odd = ((n - 1) & 1) != 0;
@@ -718,30 +809,37 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
         };
         // does a wavefront of the workgroup ask for another attempt?  (also: every wavefront is done with the ring)
         auto vote = [&]() SHIFTATTN_INLINE -> bool {
-            int* flags = reinterpret_cast<int*>(lds + kRingBytes + kCols * kPitch);
-            if (lane == 0) flags[wave] = redo ? 1 : 0;
+            int* flags = reinterpret_cast<int*>(lds + kFlagsAt);
+            if (lane == 0) flags[wave] = redo;
             __syncthreads();
-            return __builtin_amdgcn_readfirstlane(flags[0] | flags[1] | flags[2] | flags[3]) != 0;
+            const u32x4 all = *reinterpret_cast<const u32x4*>(flags);
+            return __builtin_amdgcn_readfirstlane(all[0] | all[1] | all[2] | all[3]) != 0;
+        };
+        // a group without tiles beside one that has some (one tile in all): its barriers
+        auto idle_group = [&]() SHIFTATTN_INLINE {
+            for (int b = (n_all + kG - 1) / kG + 1 + (is_ragged() ? 1 : 0); b > 0; --b) asm volatile("s_barrier" ::: "memory");
         };
         reset_sums();
         if (n > 0) key_loop(IC<kScaledQ ? 0 : 2>{});
+        else if (kG == 2 && n_all > 0) idle_group();
         // The first attempt followed no maximum.  That is exact as long as nothing left the range bf16 and the fp32 sums hold
         // without loss.  With the first tile's reference kept: a column's sum must not exceed 2^100 (P then stays below it;
         // what underflows is negligible beside the first tile's keys).  With no reference at all: a column that sees keys of
         // this range must end with a sum inside [2^-40, 2^40].  An infinity or a NaN fails either test; the pass is then flagged.
+        bool out_of_range = false;
 #pragma unroll
         for (int cb = 0; cb < 2; ++cb) {
             const float l_tot = l_run[cb] + __shfl_xor(l_run[cb], 32);
             if constexpr (kScaledQ) {
-                const bool sees = n > 0 && pos_col[cb] >= kt_begin * kKv;
-                if (sees && !(l_tot >= kFreeSumLo && l_tot <= kFreeSumHi)) redo = true;
+                const bool sees = n > 0 && pos_col[cb] >= kt_first * kKv;
+                if (sees && !(l_tot >= kFreeSumLo && l_tot <= kFreeSumHi)) out_of_range = true;
                 m_rep[cb] = sees ? 0.f : -INFINITY;   // what a partial result reports as its reference (exp2 units)
             } else {
-                if (!(l_tot <= kKeepSumBound)) redo = true;
+                if (!(l_tot <= kKeepSumBound)) out_of_range = true;
                 m_rep[cb] = m_used[cb] * p.c;
             }
         }
-        redo = __builtin_amdgcn_ballot_w64(redo) != 0;
+        redo = __builtin_amdgcn_ballot_w64(out_of_range) != 0 ? 1 : 0;
         if (__builtin_expect(vote(), 0)) {   // start over without references, on Q^T as given, and follow the maximum
 #pragma unroll
             for (int cb = 0; cb < 2; ++cb) m_used[cb] = -INFINITY, mc[cb] = 0.f, bound[cb] = -INFINITY;
@@ -750,6 +848,7 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
                 fetch_q(IC<0>{});
                 reset_sums();
                 if (n > 0) key_loop(IC<1>{});
+                else if (kG == 2 && n_all > 0) idle_group();
                 if (attempt == 2 || !vote()) break;
             }
 #pragma unroll
@@ -762,7 +861,101 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
         int lane_m = lane;
         asm volatile("" : "+v"(lane_m));
         const int l32_m = lane_m & 31, half_m = lane_m >> 5;
-        if (p.n_splits == 1) {
+        if constexpr (kG == 2) {
+            // Each group finishes one half of the head dimension (group 0 rows 0..63, group 1 rows 64..127): it parks the other
+            // half of its accumulators for the other group, (reference, sum) beside them, and folds in what that group parked.
+            float* ml = reinterpret_cast<float*>(lds + kMlAt);
+            float l_tot[2];
+            auto park_half = [&](auto g_c) SHIFTATTN_INLINE {
+                constexpr int GRP = decltype(g_c)::value;
+                unsigned char* mine = lds + (GRP * 2 + wcol) * (64 * 64 * 4) + lane_m * 16;
+#pragma unroll
+                for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+                    for (int k = 0; k < 2; ++k)
+#pragma unroll
+                        for (int r4 = 0; r4 < 4; ++r4) {
+                            f32x4 v;
+#pragma unroll
+                            for (int x = 0; x < 4; ++x) v[x] = oacc[cb][2 * (1 - GRP) + k][r4 * 4 + x];
+                            *reinterpret_cast<f32x4*>(mine + ((cb * 2 + k) * 4 + r4) * 1024) = v;
+                        }
+            };
+            if (grp == 0) park_half(IC<0>{});
+            else park_half(IC<1>{});
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb) {
+                l_tot[cb] = l_run[cb] + __shfl_xor(l_run[cb], 32);
+                ml[((wave * 2 + cb) * 2 + 0) * 64 + lane_m] = m_rep[cb];
+                ml[((wave * 2 + cb) * 2 + 1) * 64 + lane_m] = l_tot[cb];
+            }
+            __syncthreads();
+            const bool whole = p.n_splits == 1;
+            auto finish_half = [&](auto g_c) SHIFTATTN_INLINE {
+                constexpr int GRP = decltype(g_c)::value;
+                const unsigned char* theirs = lds + ((1 - GRP) * 2 + wcol) * (64 * 64 * 4) + lane_m * 16;
+                const int other = wave ^ 2;
+#pragma unroll
+                for (int cb = 0; cb < 2; ++cb) {
+                    const float m_o = ml[((other * 2 + cb) * 2 + 0) * 64 + lane_m], l_o = ml[((other * 2 + cb) * 2 + 1) * 64 + lane_m];
+                    const float m_star = fmaxf(m_rep[cb], m_o);
+                    const float w_me = m_rep[cb] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_rep[cb] - m_star);
+                    const float w_o = m_o == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_o - m_star);
+                    const float l_all = l_tot[cb] * w_me + l_o * w_o;
+                    const int cw = wcol * 64 + cb * 32 + l32_m;
+                    // accumulator register r of row tile mt is head-dim 32*mt + 8*(r/4) + 4*half + r%4
+                    auto folded = [&](int k, int r4, float a_me, float a_o) SHIFTATTN_INLINE -> f32x4 {
+                        const f32x4 o = *reinterpret_cast<const f32x4*>(theirs + ((cb * 2 + k) * 4 + r4) * 1024);
+                        f32x4 v;
+#pragma unroll
+                        for (int x = 0; x < 4; ++x) v[x] = oacc[cb][2 * GRP + k][r4 * 4 + x] * a_me + o[x] * a_o;
+                        return v;
+                    };
+                    if (whole) {
+                        const float inv = l_all > 0.f ? p.out_scale / l_all : 0.f;
+                        unsigned char* srow = lds + kStagedAt + cw * kPitch + (64 * GRP + 4 * half_m) * 2;
+#pragma unroll
+                        for (int k = 0; k < 2; ++k)
+#pragma unroll
+                            for (int r4 = 0; r4 < 4; ++r4) {
+                                const f32x4 v = folded(k, r4, w_me * inv, w_o * inv);
+                                bf16x4 h;
+#pragma unroll
+                                for (int x = 0; x < 4; ++x) h[x] = static_cast<__bf16>(v[x]);
+                                *reinterpret_cast<u32x2*>(srow + (32 * k + 8 * r4) * 2) = __builtin_bit_cast(u32x2, h);
+                            }
+                    } else if (pos_col[cb] >= 0) {
+                        const size_t prow = (static_cast<size_t>(split) * p.total_q + q_begin + tok0 + token_of(cw)) * p.hq_l + head_of(cw);
+                        float* op = p.o_part + prow * kD + 64 * GRP + 4 * half_m;
+#pragma unroll
+                        for (int k = 0; k < 2; ++k)
+#pragma unroll
+                            for (int r4 = 0; r4 < 4; ++r4) *reinterpret_cast<f32x4*>(op + 32 * k + 8 * r4) = folded(k, r4, w_me, w_o);
+                        if (GRP == 0 && half_m == 0) {
+                            p.ml_part[prow * 2] = m_star;  // -inf when this key range held no visible key
+                            p.ml_part[prow * 2 + 1] = l_all;
+                        }
+                    }
+                }
+            };
+            if (grp == 0) finish_half(IC<0>{});
+            else finish_half(IC<1>{});
+            if (whole) {
+                __syncthreads();
+                int tid_m = tid;
+                asm volatile("" : "+v"(tid_m));
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const int col = (tid_m >> 4) + 16 * i, piece = tid_m & 15;
+                    const int tok_c = tok0 + token_of(col);
+                    if (col < cols_used && tok_c < q_len) {
+                        const u32x4 v = *reinterpret_cast<const u32x4*>(lds + kStagedAt + col * kPitch + piece * 16);
+                        uint16_t* op = p.out + static_cast<size_t>(q_begin + tok_c) * p.out_stride + head_of(col) * kD + piece * 8;
+                        *reinterpret_cast<u32x4*>(op) = v;
+                    }
+                }
+            }
+        } else if (p.n_splits == 1) {
             // normalise, put bf16 rows into this wavefront's part of the staging tile, then write them out in whole
             // 256-byte rows (one 16-byte piece per lane, 1 KiB of consecutive output per 4 rows)
             unsigned char* stage = lds + kRingBytes + wave * 64 * kPitch;
@@ -789,10 +982,10 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
             for (int i = 0; i < 16; ++i) {
                 const int col = 4 * i + (lane_m >> 4), piece = lane_m & 15;
                 const int cw = wave * 64 + col;
-                const int tok_c = tok0 + cw / p.G;
+                const int tok_c = tok0 + token_of(cw);
                 if (cw < cols_used && tok_c < q_len) {
                     const u32x4 v = *reinterpret_cast<const u32x4*>(stage + col * kPitch + piece * 16);
-                    uint16_t* op = p.out + static_cast<size_t>(q_begin + tok_c) * p.out_stride + (g * p.G + cw % p.G) * kD + piece * 8;
+                    uint16_t* op = p.out + static_cast<size_t>(q_begin + tok_c) * p.out_stride + head_of(cw) * kD + piece * 8;
                     *reinterpret_cast<u32x4*>(op) = v;
                 }
             }
@@ -802,9 +995,9 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
             for (int cb = 0; cb < 2; ++cb) {
                 const float l_tot = l_run[cb] + __shfl_xor(l_run[cb], 32);
                 if (pos_col[cb] >= 0) {
-                    const int cw = wave * 64 + cb * 32 + l32_m;
-                    const int row_col = q_begin + tok0 + cw / p.G;
-                    const int head_col = g * p.G + cw % p.G;
+                    const int cw = wcol * 64 + cb * 32 + l32_m;
+                    const int row_col = q_begin + tok0 + token_of(cw);
+                    const int head_col = head_of(cw);
                     const size_t prow = (static_cast<size_t>(split) * p.total_q + row_col) * p.hq_l + head_col;
                     float* op = p.o_part + prow * kD + 4 * half_m;
 #pragma unroll
@@ -841,6 +1034,7 @@ Prefill64Plan prefill_mfma64_plan(int num_seqs, int total_q, int max_q_len, int 
                                   int forced_splits) {
     Prefill64Plan pl;
     const int G = a.hq_l / a.hkv_l;
+    pl.groups = 1;
     pl.tile_tokens = kCols / G;
     const int tiles = (max_q_len + pl.tile_tokens - 1) / pl.tile_tokens;
     // Causal tiles differ in work (tile i sees i + 1 tiles' worth of keys).  Two ways to level it: a workgroup takes the
@@ -911,9 +1105,11 @@ size_t prefill_mfma64_workspace(int total_q, const Prefill64Plan& pl, const Attn
 
 hipError_t prefill_mfma64_init() {
     for (const void* kernel :
-         {reinterpret_cast<const void*>(&prefill64_kernel<0, false>), reinterpret_cast<const void*>(&prefill64_kernel<1, false>),
-          reinterpret_cast<const void*>(&prefill64_kernel<2, false>), reinterpret_cast<const void*>(&prefill64_kernel<0, true>),
-          reinterpret_cast<const void*>(&prefill64_kernel<1, true>), reinterpret_cast<const void*>(&prefill64_kernel<2, true>)})
+         {reinterpret_cast<const void*>(&prefill64_kernel<0, false, 1>), reinterpret_cast<const void*>(&prefill64_kernel<1, false, 1>),
+          reinterpret_cast<const void*>(&prefill64_kernel<2, false, 1>), reinterpret_cast<const void*>(&prefill64_kernel<0, true, 1>),
+          reinterpret_cast<const void*>(&prefill64_kernel<1, true, 1>), reinterpret_cast<const void*>(&prefill64_kernel<2, true, 1>),
+          reinterpret_cast<const void*>(&prefill64_kernel<0, false, 2>), reinterpret_cast<const void*>(&prefill64_kernel<1, false, 2>),
+          reinterpret_cast<const void*>(&prefill64_kernel<2, false, 2>)})
         if (hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes); e != hipSuccess) return e;
     return hipSuccess;
 }
@@ -921,9 +1117,10 @@ hipError_t prefill_mfma64_init() {
 namespace {
 
 template <int kDecode>
-void enqueue(unsigned grid, const Prefill64Params& p, const DecodeRole& dec, hipStream_t st) {
-    if (option_prefill_scaled_q()) prefill64_kernel<kDecode, true><<<grid, kThreads, kLdsBytes, st>>>(p, dec);
-    else prefill64_kernel<kDecode, false><<<grid, kThreads, kLdsBytes, st>>>(p, dec);
+void enqueue(unsigned grid, int groups, const Prefill64Params& p, const DecodeRole& dec, hipStream_t st) {
+    if (groups == 2) prefill64_kernel<kDecode, false, 2><<<grid, kThreads, kLdsBytes, st>>>(p, dec);
+    else if (option_prefill_scaled_q()) prefill64_kernel<kDecode, true, 1><<<grid, kThreads, kLdsBytes, st>>>(p, dec);
+    else prefill64_kernel<kDecode, false, 1><<<grid, kThreads, kLdsBytes, st>>>(p, dec);
 }
 
 Prefill64Params wide_params(const void* q, const void* cache, const int32_t* block_table, int max_blocks, const int32_t* cu_seqlens_q,
@@ -946,6 +1143,7 @@ Prefill64Params wide_params(const void* q, const void* cache, const int32_t* blo
     p.hq_l = a.hq_l;
     p.hkv_l = a.hkv_l;
     p.G = a.hq_l / a.hkv_l;
+    p.g_magic = ((1 << 20) + p.G - 1) / p.G;
     p.tile_tokens = pl.tile_tokens;
     p.n_splits = pl.n_splits;
     p.paired = pl.paired ? 1 : 0;
@@ -966,7 +1164,7 @@ hipError_t launch_prefill_mfma64(const void* q, const void* cache, const int32_t
                                  float out_scale, hipStream_t st) {
     const Prefill64Params p = wide_params(q, cache, block_table, max_blocks, cu_seqlens_q, seq_lens, num_seqs, total_q, pl, out, workspace, a,
                                           c, out_scale);
-    enqueue<0>(static_cast<unsigned>(pl.workgroups), p, DecodeRole{}, st);
+    enqueue<0>(static_cast<unsigned>(pl.workgroups), pl.groups, p, DecodeRole{}, st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (pl.n_splits > 1)
@@ -982,8 +1180,8 @@ hipError_t launch_prefill64_and_decode(const void* q, const void* cache, const i
     Prefill64Params p = wide_params(q, cache, block_table, max_blocks, cu_seqlens_q, seq_lens, num_seqs, total_q, pl, out, workspace, a, c, out_scale);
     p.range_div = range_div;
     const unsigned grid = static_cast<unsigned>(pl.workgroups + dec.n_wg);
-    if (a.kv_fp8()) enqueue<2>(grid, p, dec, st);
-    else enqueue<1>(grid, p, dec, st);
+    if (a.kv_fp8()) enqueue<2>(grid, pl.groups, p, dec, st);
+    else enqueue<1>(grid, pl.groups, p, dec, st);
     return hipGetLastError();
 }
 

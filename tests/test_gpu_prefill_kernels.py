@@ -208,3 +208,30 @@ def test_wide_prefill_kernel_at_the_ends_of_its_loop(oracle, G, opts, tiles, sca
     assert got.shape == want.shape and np.all(np.isfinite(got))
     err = np.abs(got - want)
     assert np.all(err <= BF16_MAX + (2.0 ** -7 * np.abs(want) if scaled_q else 0)) and err.mean() <= BF16_MEAN, (err.max(), err.mean())
+
+
+@pytest.mark.parametrize("pairing", [1, 2])
+@pytest.mark.parametrize("splits", [1, 2])
+@pytest.mark.parametrize("hq_l,hkv_l", [(8, 1), (5, 1), (4, 4), (10, 2)])
+def test_two_groups_of_wavefronts_at_the_ends_of_their_loops(oracle, G, opts, pairing, splits, hq_l, hkv_l):
+    """A batch whose longest sequence makes the two-group form of 64-column wavefronts the cheaper 128-column kernel; the others
+    end after 1, 2, 3, ... tiles of 32 keys, so that one group has a tile more than the other, or none at all, and walks past
+    the end of its 64 addresses."""
+    opts(tile=128, splits=splits, pairing=pairing)
+    seqs = [(1700, 1700)] + [(min(20, 32 * t - 5), 32 * t - 5) for t in (1, 2, 3, 4, 5, 6, 7, 8, 9, 119, 120, 121, 122, 128, 131)]
+    case = W.make_attn_case("t", 99, "bf16", seqs, hq_l, hkv_l, 128)
+    want = oracle.attention_case(case, oracle.cache_for_case(case))
+    got = G.prefill_case(case, G.cache_for_case(case, fill_byte=0xFF))
+    _check(got, want)
+
+
+@pytest.mark.parametrize("beta", [3.0, 9.0])
+def test_two_groups_of_wavefronts_follow_the_maximum(oracle, G, opts, beta):
+    """Logits some 50 and 150 powers of two above everything before them, in tiles of one group or the other: beyond the range of
+    the sums both groups run the pass again."""
+    opts(tile=128, splits=1)
+    case = W.make_attn_case("t", 93, "bf16", [(300, 2500)], 8, 1, 128)
+    first_new = 2200
+    case = _with_late_outliers(case, [5, 5, 120, 299, 17], [700, 1124, 3, first_new + 299, 40], beta=beta)
+    want = oracle.attention_case(case, oracle.cache_for_case(case))
+    _check(G.prefill_case(case, G.cache_for_case(case)), want)
