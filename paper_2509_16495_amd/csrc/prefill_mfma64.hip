@@ -807,7 +807,8 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
             mfma_settle(oacc);
             wait_vm0();   // loads that nobody needs any more may still be on their way into LDS
         };
-        // does a wavefront of the workgroup ask for another attempt?  (also: every wavefront is done with the ring)
+        // Does a wavefront of the workgroup ask for another attempt?  Behind its barrier every wavefront has left its last operand
+        // reads behind and its own loads have landed (wait_vm0): only then may the ring's bytes be written by anything but loads.
         auto vote = [&]() SHIFTATTN_INLINE -> bool {
             int* flags = reinterpret_cast<int*>(lds + kFlagsAt);
             if (lane == 0) flags[wave] = redo;
@@ -849,7 +850,8 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
                 reset_sums();
                 if (n > 0) key_loop(IC<1>{});
                 else if (kG == 2 && n_all > 0) idle_group();
-                if (attempt == 2 || !vote()) break;
+                // (the vote's barrier is asked for behind the last attempt too: what follows writes into the ring of two groups)
+                if (!vote() || attempt == 2) break;
             }
 #pragma unroll
             for (int cb = 0; cb < 2; ++cb) m_rep[cb] = m_used[cb] * p.c;

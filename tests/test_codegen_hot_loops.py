@@ -7,10 +7,12 @@ instruction: a scratch load shares the vector-memory counter with the direct-to-
 256-column prefill kernel's loop made every launch 4-5 % slower, with every test green).  The check compiles the
 source to assembly with the build's own flags and looks at the basic blocks that carry the loops' MFMAs.
 """
+import functools
 import os
 import re
 import shutil
 import subprocess
+import tempfile
 
 import pytest
 
@@ -109,3 +111,80 @@ def test_prefill_key_loop_forms_its_addresses_in_scalar_registers(tmp_path):
         for k, b in blocks[i:i + 2]:
             assert sum("mfma" in x for x in b) >= 15
             assert not [x for x in b if x.startswith(("v_readfirstlane", "v_readlane", "v_mul_lo_u32", "v_mad_u64_u32"))], k
+
+
+@functools.lru_cache(maxsize=None)
+def _assembly(source):
+    """Lines of the source's gfx950 assembly, compiled once with the build's own flags."""
+    flags = [f for f in BLD.FLAGS if f not in ("-shared", "-fPIC")]
+    with tempfile.TemporaryDirectory() as tmp:
+        out = os.path.join(tmp, source + ".s")
+        subprocess.check_call(["hipcc", *flags, "--cuda-device-only", "-S", os.path.join(BLD.CSRC, source), "-o", out],
+                              cwd=BLD.CSRC, stderr=subprocess.DEVNULL)
+        return tuple(open(out))
+
+
+def _unsynchronised_parks(lines):
+    """Of one kernel's assembly: (parks seen, those of them that an MFMA reaches without an s_barrier in between).  A park is a run of
+    sixteen 16-byte LDS stores 1 KiB apart: what a lane leaves for the other group."""
+    blocks, labels = [[]], {}
+    for line in lines:
+        s = line.split(";")[0].strip()
+        m = re.match(r"^(\.LBB[\w.$]*):", line)
+        if m:
+            blocks.append([])
+            labels[m.group(1)] = len(blocks) - 1
+        elif s and not s.startswith(".") and not s.endswith(":"):
+            blocks[-1].append(s.split())
+            if s.startswith(("s_cbranch", "s_branch", "s_endpgm")):
+                blocks.append([])
+
+    def walk(i, dirty):
+        """Through block i, entered with an MFMA behind the last barrier or not: (the same at its end, parks, those that are dirty)."""
+        run = parks = bad = 0
+        for op in blocks[i]:
+            if op[0].startswith("v_mfma"):
+                dirty = True
+            elif op[0] == "s_barrier":
+                dirty, run = False, 0
+            elif op[0] == "ds_write_b128":
+                offset = next((int(x[7:]) for x in op if x.startswith("offset:")), 0)
+                run = run + 1 if offset == 1024 * run else int(offset == 0)
+                parks += run == 16
+                bad += run == 16 and dirty
+        return dirty, parks, bad
+
+    def successors(i):
+        last = blocks[i][-1] if blocks[i] else [""]
+        if last[0].startswith(("s_cbranch", "s_branch")):
+            yield labels[last[1]]
+        if not last[0].startswith(("s_branch", "s_endpgm")) and i + 1 < len(blocks):
+            yield i + 1
+
+    entered, work = [False] * len(blocks), list(range(len(blocks)))
+    while work:
+        i = work.pop()
+        if walk(i, entered[i])[0]:
+            for n in successors(i):
+                if not entered[n]:
+                    entered[n] = True
+                    work.append(n)
+    found = [walk(i, entered[i]) for i in range(len(blocks))]
+    return sum(f[1] for f in found), sum(f[2] for f in found)
+
+
+@pytest.mark.parametrize("decode", [0, 1, 2])
+def test_two_groups_exchange_their_sums_behind_a_barrier(decode):
+    """The two-group form of the 64-column wavefronts parks accumulators in the bytes of its key rings.  Whichever attempt a pass ends
+    with, a barrier lies between the last product of every wavefront and the first parked accumulator: one group may be a whole tile
+    ahead of the other, whose operands it would overwrite."""
+    lines, inside = [], False
+    for line in _assembly("prefill_mfma64.hip"):
+        if re.match(r"^[A-Za-z_$][\w.$]*:", line):
+            inside = f"prefill64_kernelILi{decode}ELb0ELi2E" in line
+        elif line.startswith(".Lfunc_end"):
+            inside = False
+        elif inside:
+            lines.append(line)
+    parks, bad = _unsynchronised_parks(lines)
+    assert parks >= 1 and bad == 0, (parks, bad)
