@@ -1,8 +1,8 @@
 /*
- * shiftattn_probe.h - measurement aids exported by libshiftattn.so for benchmark reports.
+ * shiftattn_probe.h - measurement and test aids exported by libshiftattn.so.
  *
- * Not part of the attention path and not part of the product interface (shiftattn.h): four kernels
- * that show what the chip attains on the resources the path's kernels are priced against, to print
+ * Not part of the attention path and not part of the product interface (shiftattn.h): a host query
+ * that names the launch a prefill call takes, and, for benchmark reports, four kernels that show what the chip attains on the resources the path's kernels are priced against, to print
  * beside the datasheet peaks.  Each call validates its arguments, enqueues one kernel on `stream`
  * (a hipStream_t as void*) and returns SHIFTATTN_OK or a negative code of shiftattn.h; the caller
  * times it.  All buffer pointers are device pointers, 16-byte aligned.
@@ -22,6 +22,11 @@
  * ceiling_hbm_copy: copies `bytes` (rounded down to 16 KiB) from src to dst with 16-byte
  *   non-temporal loads and stores, 16 KiB in flight per wavefront: a read + write stream with no
  *   index arithmetic.  *bytes_copied (host) receives the bytes copied (as many are read as written).
+ *
+ * prefill_plan: host only, nothing is enqueued.  What shiftattn_prefill (num_decode_seqs = 0), or
+ *   shiftattn_mixed for its chunks, launches for a batch of these sizes with the workspace that its
+ *   size query names, under the options as they are set; a test that aims at a kernel can then say so.
+ *   Arguments as for shiftattn_mixed_workspace_bytes.
  */
 #ifndef SHIFTATTN_PROBE_H
 #define SHIFTATTN_PROBE_H
@@ -29,10 +34,23 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "shiftattn.h"
+
 #ifdef __cplusplus
 extern "C" {
 #endif
 
+typedef struct {
+    int32_t tile_columns;     /* (token, query head) pairs of a workgroup's tile: 128 or 256; 0: a kernel without such tiles */
+    int32_t wave_columns;     /* of them per wavefront: 32, or 64 (tiles of 128 then have two groups of wavefronts) */
+    int32_t key_ranges;       /* ranges that a tile's keys are split into; 1: no merge launch for them */
+    int32_t tiles_per_wg;     /* 1, or 2: heaviest with lightest */
+    int32_t decode_wgs;       /* workgroups of the same launch that take the decode rows; 0: the rows have a launch of their own */
+} shiftattn_prefill_plan_t;
+
+int shiftattn_prefill_plan(int32_t num_prefill_seqs, int32_t total_prefill_q, int32_t max_q_len, int32_t max_prefill_seq_len,
+                           int32_t num_decode_seqs, int32_t max_decode_seq_len, const shiftattn_attn *a,
+                           shiftattn_prefill_plan_t *plan);
 int shiftattn_ceiling_mfma_bf16(const void *operands, void *sink, int32_t iters, int64_t *flops, void *stream);
 int shiftattn_ceiling_mfma_bf16_fresh(const void *operands, void *sink, int32_t iters, int64_t *flops, void *stream);
 int shiftattn_ceiling_hbm_read(const void *src, size_t bytes, void *sink, int64_t *bytes_read, void *stream);

@@ -45,6 +45,11 @@ class Attn(ctypes.Structure):
                 ("reserved", ctypes.c_int32)]
 
 
+class PrefillPlan(ctypes.Structure):
+    _fields_ = [("tile_columns", ctypes.c_int32), ("wave_columns", ctypes.c_int32), ("key_ranges", ctypes.c_int32),
+                ("tiles_per_wg", ctypes.c_int32), ("decode_wgs", ctypes.c_int32)]
+
+
 KV_SAME, KV_FP8_E4M3 = 0, 1
 
 
@@ -179,6 +184,16 @@ def padded_tokens(n: int, sp: int) -> int:
 
 def use_base_config(n_tokens: int, threshold: int) -> int:
     return int(lib().shiftattn_use_base_config(n_tokens, threshold))
+
+
+def prefill_plan(num_seqs: int, total_q: int, max_q_len: int, max_seq_len: int, desc: Attn, num_decode_seqs: int = 0,
+                 max_decode_seq_len: int = 0) -> PrefillPlan:
+    """The launch that such a prefill call, or such a unified batch's chunks, takes (host only)."""
+    plan = PrefillPlan()
+    query = lib().shiftattn_prefill_plan
+    query.argtypes = [ctypes.c_int32] * 6 + [ctypes.POINTER(Attn), ctypes.POINTER(PrefillPlan)]
+    _check(query(num_seqs, total_q, max_q_len, max_seq_len, num_decode_seqs, max_decode_seq_len, ctypes.byref(desc), ctypes.byref(plan)))
+    return plan
 
 
 def ceiling_mfma_bf16(operands: torch.Tensor, sink: torch.Tensor, iters: int) -> int:

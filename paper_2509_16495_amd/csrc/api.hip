@@ -629,6 +629,20 @@ size_t shiftattn_mixed_workspace_bytes(int32_t num_prefill_seqs, int32_t total_p
     return need;
 }
 
+int shiftattn_prefill_plan(int32_t num_prefill_seqs, int32_t total_prefill_q, int32_t max_q_len, int32_t max_prefill_seq_len,
+                           int32_t num_decode_seqs, int32_t max_decode_seq_len, const shiftattn_attn* a, shiftattn_prefill_plan_t* plan) {
+    AttnShape s;
+    if (int rc = check_attn(a, &s)) return rc;
+    if (!plan) return fail(SHIFTATTN_EINVAL, "a required pointer is NULL");
+    if (num_prefill_seqs < 0 || total_prefill_q < 0 || max_q_len < 0 || max_prefill_seq_len < 0 || num_decode_seqs < 0 || max_decode_seq_len < 0)
+        return fail(SHIFTATTN_EINVAL, "negative size argument");
+    *plan = shiftattn_prefill_plan_t{0, 0, 1, 1, 0};
+    if (num_prefill_seqs > 0 && total_prefill_q > 0 && max_q_len > 0 && use_prefill_mfma(s, num_prefill_seqs, max_prefill_seq_len))
+        prefill_mfma_describe(num_prefill_seqs, total_prefill_q, max_q_len, max_prefill_seq_len,
+                              use_decode_mfma(s, num_decode_seqs, max_decode_seq_len) ? num_decode_seqs : 0, max_decode_seq_len, s, plan);
+    return SHIFTATTN_OK;
+}
+
 int shiftattn_mixed(const void* q, const void* k_new, const void* v_new, const int64_t* slot_mapping, void* kv_cache,
                     const int32_t* block_table, const int32_t* cu_seqlens_q, const int32_t* seq_lens,
                     int32_t num_prefill_seqs, int32_t total_prefill_q, int32_t max_q_len, int32_t max_prefill_seq_len,

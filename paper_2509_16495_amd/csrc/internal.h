@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "../../include/shiftattn_probe.h"
+
 namespace shiftattn {
 
 constexpr int kBlockSize = 16;         // tokens per KV-cache block
@@ -89,6 +91,10 @@ hipError_t launch_prefill_mfma(const void* q, const void* cache, const int32_t* 
                                const int32_t* cu_seqlens_q, const int32_t* seq_lens, int num_seqs,
                                int total_q, int max_q_len, int max_seq_len, void* out, void* workspace,
                                size_t workspace_bytes, const AttnShape& a, hipStream_t st);
+
+// the launch of a prefill call (num_dec = 0), or of a unified batch's chunks, with the workspace named above (below)
+void prefill_mfma_describe(int num_seqs, int total_q, int max_q_len, int max_seq_len, int num_dec, int max_dec_len, const AttnShape& a,
+                           shiftattn_prefill_plan_t* plan);
 
 // the chunks and the decode rows of a unified batch in one launch: the workspace it needs (0: the parts are launched one
 // after the other), and the launch (false: not taken, nothing enqueued)

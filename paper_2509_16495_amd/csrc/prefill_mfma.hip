@@ -1179,6 +1179,19 @@ size_t prefill_and_decode_workspace(int num_seqs, int total_q, int max_q_len, in
     return plan_both(num_seqs, total_q, max_q_len, max_seq_len, num_dec, max_dec_len, a).bytes;
 }
 
+void prefill_mfma_describe(int num_seqs, int total_q, int max_q_len, int max_seq_len, int num_dec, int max_dec_len, const AttnShape& a,
+                           shiftattn_prefill_plan_t* plan) {
+    Choice c;
+    const BothPlan both = num_dec > 0 ? plan_both(num_seqs, total_q, max_q_len, max_seq_len, num_dec, max_dec_len, a) : BothPlan{};
+    if (both.taken) c.wide = both.wide, c.narrow = both.narrow, c.w = both.w;
+    else c = plan_within(SIZE_MAX, num_seqs, total_q, max_q_len, max_seq_len, a);
+    plan->tile_columns = c.wide && c.w.groups == 1 ? 256 : 128;
+    plan->wave_columns = c.wide ? 64 : 32;
+    plan->key_ranges = c.wide ? c.w.n_splits : c.narrow.n_splits;
+    plan->tiles_per_wg = (c.wide ? c.w.paired : c.narrow.paired) ? 2 : 1;
+    plan->decode_wgs = both.taken ? both.dec_wgs : 0;
+}
+
 bool launch_prefill_and_decode(const void* q, void* cache, const int32_t* block_table, const int32_t* cu_seqlens_q, const int32_t* seq_lens,
                                int num_seqs, int total_q, int max_q_len, int max_seq_len, int num_dec, int max_dec_len, void* out,
                                void* workspace, size_t workspace_bytes, const AttnShape& a, hipStream_t st, hipError_t* err) {
