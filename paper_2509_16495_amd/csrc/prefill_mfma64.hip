@@ -827,16 +827,18 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
         // without loss.  With the first tile's reference kept: a column's sum must not exceed 2^100 (P then stays below it;
         // what underflows is negligible beside the first tile's keys).  With no reference at all: a column that sees keys of
         // this range must end with a sum inside [2^-40, 2^40].  An infinity or a NaN fails either test; the pass is then flagged.
+        // So is one with a column that sees keys but got no reference, every logit of its first tile or two being -inf: what it
+        // summed behind them would be merged as a range without keys.
         bool out_of_range = false;
 #pragma unroll
         for (int cb = 0; cb < 2; ++cb) {
             const float l_tot = l_run[cb] + __shfl_xor(l_run[cb], 32);
+            const bool sees = n > 0 && pos_col[cb] >= kt_first * kKv;
             if constexpr (kScaledQ) {
-                const bool sees = n > 0 && pos_col[cb] >= kt_first * kKv;
                 if (sees && !(l_tot >= kFreeSumLo && l_tot <= kFreeSumHi)) out_of_range = true;
                 m_rep[cb] = sees ? 0.f : -INFINITY;   // what a partial result reports as its reference (exp2 units)
             } else {
-                if (!(l_tot <= kKeepSumBound)) out_of_range = true;
+                if (!(l_tot <= kKeepSumBound) || (sees && m_used[cb] == -INFINITY)) out_of_range = true;
                 m_rep[cb] = m_used[cb] * p.c;
             }
         }

@@ -99,6 +99,17 @@ def prefill_case(case, cache: torch.Tensor, fused_new_kv: bool = False, fp8_scal
     return B.to_host(out)
 
 
+def launch_of(case, n_prefill=None, fp8_scales=None) -> B.PrefillPlan:
+    """The launch that prefill_case(), or mixed_case() with its first n_prefill sequences as chunks, takes for the case."""
+    n = case.num_seqs if n_prefill is None else n_prefill
+    q, ctx = case.q_lens[:n], case.ctx_lens
+    ks, vs = fp8_scales or (1.0, 1.0)
+    cache = torch.empty((0, case.hkv_l, 2, 16 * case.D), dtype=torch_dtype(case.dtype) if fp8_scales is None else torch.uint8)
+    desc = B.attn_desc(torch.empty((0, case.hq_l, case.D), dtype=torch_dtype(case.dtype)), cache, torch.from_numpy(case.block_table),
+                       case.softmax_scale, None, None, ks, vs)
+    return B.prefill_plan(n, int(q.sum()), int(q.max()), int(ctx[:n].max()), desc, case.num_seqs - n, int(ctx[n:].max()) if n < case.num_seqs else 0)
+
+
 def decode_case(case, cache: torch.Tensor, fused_new_kv: bool = False, fp8_scales=None) -> np.ndarray:
     """shiftattn_decode on a case whose sequences all have one new token."""
     assert np.all(case.q_lens == 1)

@@ -37,6 +37,17 @@ def opts():
     B.set_option(B.OPT_PREFILL_SCALED_Q, 0)
 
 
+def _takes(G, case, tile, wave, splits=None, per_wg=None):
+    """Asserts which kernel, and how many key ranges and tiles per workgroup, a prefill call on the case takes."""
+    p = G.launch_of(case)
+    assert (p.tile_columns, p.wave_columns) == (tile, wave)
+    assert splits in (None, p.key_ranges) and per_wg in (None, p.tiles_per_wg), (p.key_ranges, p.tiles_per_wg)
+
+
+# a sequence that makes the two-group form the cheaper 128-column kernel for any batch it joins
+LONG = (3, 9000)
+
+
 def _check(got_bits, want):
     got = W.to_f64(got_bits, "bf16")
     assert got.shape == want.shape
@@ -233,5 +244,23 @@ def test_two_groups_of_wavefronts_follow_the_maximum(oracle, G, opts, beta):
     case = W.make_attn_case("t", 93, "bf16", [(300, 2500)], 8, 1, 128)
     first_new = 2200
     case = _with_late_outliers(case, [5, 5, 120, 299, 17], [700, 1124, 3, first_new + 299, 40], beta=beta)
+    want = oracle.attention_case(case, oracle.cache_for_case(case))
+    _check(G.prefill_case(case, G.cache_for_case(case)), want)
+
+
+@pytest.mark.parametrize("dead", [range(200), list(range(32)) + list(range(64, 96)), list(range(32, 64)) + list(range(96, 128))],
+                         ids=["all", "even_tiles", "odd_tiles"])
+@pytest.mark.parametrize("tile,wave,splits", [(128, 32, 1), (128, 64, 1), (128, 64, 2), (256, 64, 1), (256, 64, 2)])
+def test_keys_whose_logits_overflow_do_not_hide_those_behind_them(oracle, G, opts, tile, wave, splits, dead):
+    """K of the lowest bf16 value in one component, where every query is positive: the logits of the first key tiles (of one group of
+    wavefronts or of both) are minus infinity, their columns have no reference when the key loop begins, and the keys behind them
+    carry the whole result."""
+    opts(tile=tile, splits=splits, pairing=2)
+    case = W.make_attn_case("t", 101, "bf16", [(40, 400), (33, 333)] + ([LONG] if wave == 64 else []), 8, 1, 128)
+    _takes(G, case, tile, wave, splits, 1)
+    q, k = W.bf16_bits_to_f32(case.q).copy(), W.bf16_bits_to_f32(case.k_ctx).copy()
+    q[:, :, 0] = 4.0
+    k[np.array(dead), 0, 0] = -np.float32(2.0 ** 127 * (2 - 2.0 ** -7))       # of the first sequence: k_ctx holds it first
+    case.q, case.k_ctx = W.f32_to_bf16_bits(q), W.f32_to_bf16_bits(k)
     want = oracle.attention_case(case, oracle.cache_for_case(case))
     _check(G.prefill_case(case, G.cache_for_case(case)), want)
