@@ -116,6 +116,51 @@ def test_mixed_launch_of_unequal_chunks(oracle, G, kv, chunks, decodes, hq_l, hk
     assert np.all(np.isfinite(err)) and err.max() <= 2e-2 and err.mean() <= 1e-3, (err.max(), err.mean())
 
 
+# Batches whose chunks go to tiles of 128 columns in two groups of wavefronts beside the decode rows, over either cache.
+TWO_GROUPS = [
+    # chunks, decode contexts, query heads, KV heads, columns of the prefill kernel, key ranges
+    ([(513, 7733)], [1244, 3993, 2715, 2966, 33, 33, 355], 8, 1, 0, 6),                                    # one chunk
+    ([(876, 1240)], [33, 1, 33, 1, 1, 1, 3145, 1134, 1, 1, 1, 4715], 16, 2, 0, 1),                         # one range
+    ([(749, 749), (494, 494), (399, 399), (102, 3663)], [33, 33, 1, 1403, 3078, 1, 3418, 1, 742], 8, 1, 0, 1),   # unequal, rotated
+    ([(109, 109), (276, 5256), (203, 4919), (154, 4766)], [2200, 2178, 1, 778, 33, 33, 1, 33], 5, 1, 0, 5),
+    ([(117, 1189), (216, 1170), (235, 235), (158, 5013)], [1, 3230, 1], 16, 2, 0, 2),
+    ([(757, 757), (112, 6949), (153, 153)], [33, 1, 4769, 33, 1, 33, 526, 3633, 1, 1], 4, 1, 128, 3),
+    ([(192, 1253), (685, 685), (100, 6799)], [1, 4396, 2766], 4, 4, 128, 3),                              # one query head per KV head
+]
+
+
+@pytest.mark.parametrize("kv,late", [("bf16", False), ("bf16", True), ("fp8", False)])   # (codes clamp the keys that late maxima need)
+@pytest.mark.parametrize("chunks,decodes,hq_l,hkv_l,tile,ranges", TWO_GROUPS)
+def test_mixed_launch_of_two_groups_of_wavefronts(oracle, G, kv, chunks, decodes, hq_l, hkv_l, tile, ranges, late):
+    """late: rows of the first chunk meet, far behind their first keys, logits some 150 powers of two above all before, so that their
+    passes are run again, and once more, beside the decode rows."""
+    from paper_2509_16495_amd import binding as B
+    scales = SCALES if kv == "fp8" else None
+    case = W.make_attn_case("t", 108, "bf16", chunks + [(1, c) for c in decodes], hq_l, hkv_l, 128, pool_factor=1.2)
+    if late:
+        q, k = W.bf16_bits_to_f32(case.q), W.bf16_bits_to_f32(case.k_ctx).copy()
+        rows, ctx = chunks[0]
+        for i, row in enumerate(range(rows - 1, 0, -37)):
+            for part in (0.3, 0.5, 0.8):           # visible to the row: keys up to ctx - rows + row
+                k[int(part * (ctx - rows + row)) + i % 5, 0] = 9.0 * q[row, 0]
+        case.k_ctx = W.f32_to_bf16_bits(k)
+    n = len(chunks)
+    cache = G.cache_for_case(case, fill_byte=0xFF, fp8_scales=scales)
+    if scales:
+        want = oracle.attention_case(case, B.to_host(cache), k_scale=scales[0], v_scale=scales[1])
+    else:
+        want = oracle.attention_case(case, oracle.cache_for_case(case))
+    try:
+        B.set_option(B.OPT_PREFILL_TILE, tile)
+        p = G.launch_of(case, n, scales)
+        assert (p.tile_columns, p.wave_columns, p.key_ranges, p.tiles_per_wg) == (128, 64, ranges, 1) and p.decode_wgs > 0
+        got = W.to_f64(G.mixed_case(case, n, cache, fused_new_kv=False, fp8_scales=scales), "bf16")
+    finally:
+        B.set_option(B.OPT_PREFILL_TILE, 0)
+    err = np.abs(got - want)
+    assert np.all(np.isfinite(got)) and err.max() <= 2e-2 and err.mean() <= 1e-3, (err.max(), err.mean())
+
+
 @pytest.mark.parametrize("kv", ["bf16", "fp8"])
 def test_decode_rows_of_the_shared_launch_are_no_further_off_than_alone(oracle, G, kv):
     """The shared launch gives these decode rows a quarter of the wavefronts that a launch of their own has, so a wavefront walks

@@ -1,5 +1,6 @@
-"""Both tuned prefill kernels (128-column and 256-column workgroup tiles) against the fp64 oracle, each forced
-through shiftattn_set_option so that no shape escapes either of them, with and without forced key splits.
+"""The tuned prefill kernels against the fp64 oracle: tiles of 128 columns in 32-column wavefronts, tiles of 256 in 64-column ones, and
+tiles of 128 in two groups of those.  shiftattn_set_option forces the columns of a tile; which of the two 128-column kernels takes a
+launch is the planner's choice, so the tests that aim at one choose batches for which it does and ask shiftattn_prefill_plan.
 
 Tolerances as for all bf16 attention: max |err| <= 2e-2 and mean |err| <= 1e-3 against the oracle.
 """
@@ -85,6 +86,7 @@ def test_prefill_kernel_forced(oracle, G, opts, tile, splits, seqs, hq_l, hkv_l)
     opts(tile=tile, splits=splits)
     assert B.get_option(B.OPT_PREFILL_TILE) == tile and B.get_option(B.OPT_PREFILL_SPLITS) == splits
     case = W.make_attn_case("t", 91, "bf16", seqs, hq_l, hkv_l, 128)
+    _takes(G, case, tile, tile // 4, splits or None)
     want = oracle.attention_case(case, oracle.cache_for_case(case))
     got = G.prefill_case(case, G.cache_for_case(case, fill_byte=0xFF))   # unwritten slots hold NaN patterns
     _check(got, want)
@@ -225,12 +227,12 @@ def test_wide_prefill_kernel_at_the_ends_of_its_loop(oracle, G, opts, tiles, sca
 @pytest.mark.parametrize("splits", [1, 2])
 @pytest.mark.parametrize("hq_l,hkv_l", [(8, 1), (5, 1), (4, 4), (10, 2)])
 def test_two_groups_of_wavefronts_at_the_ends_of_their_loops(oracle, G, opts, pairing, splits, hq_l, hkv_l):
-    """A batch whose longest sequence makes the two-group form of 64-column wavefronts the cheaper 128-column kernel; the others
-    end after 1, 2, 3, ... tiles of 32 keys, so that one group has a tile more than the other, or none at all, and walks past
-    the end of its 64 addresses."""
+    """Sequences that end after 1, 2, 3, ... tiles of 32 keys, so that one group has a tile more than the other, or none at all, and
+    walks past the end of its 64 addresses."""
     opts(tile=128, splits=splits, pairing=pairing)
-    seqs = [(1700, 1700)] + [(min(20, 32 * t - 5), 32 * t - 5) for t in (1, 2, 3, 4, 5, 6, 7, 8, 9, 119, 120, 121, 122, 128, 131)]
+    seqs = [(1700, 1700), LONG] + [(min(20, 32 * t - 5), 32 * t - 5) for t in (1, 2, 3, 4, 5, 6, 7, 8, 9, 119, 120, 121, 122, 128, 131)]
     case = W.make_attn_case("t", 99, "bf16", seqs, hq_l, hkv_l, 128)
+    _takes(G, case, 128, 64, splits, 3 - pairing)
     want = oracle.attention_case(case, oracle.cache_for_case(case))
     got = G.prefill_case(case, G.cache_for_case(case, fill_byte=0xFF))
     _check(got, want)
@@ -242,8 +244,37 @@ def test_two_groups_of_wavefronts_follow_the_maximum(oracle, G, opts, beta):
     the sums both groups run the pass again."""
     opts(tile=128, splits=1)
     case = W.make_attn_case("t", 93, "bf16", [(300, 2500)], 8, 1, 128)
+    _takes(G, case, 128, 64, 1)
     first_new = 2200
     case = _with_late_outliers(case, [5, 5, 120, 299, 17], [700, 1124, 3, first_new + 299, 40], beta=beta)
+    want = oracle.attention_case(case, oracle.cache_for_case(case))
+    _check(G.prefill_case(case, G.cache_for_case(case)), want)
+
+
+@pytest.mark.parametrize("splits", [1, 3])
+@pytest.mark.parametrize("seqs,hq_l,hkv_l", SHAPES)
+def test_two_groups_of_wavefronts_on_all_shapes(oracle, G, opts, splits, seqs, hq_l, hkv_l):
+    opts(tile=128, splits=splits, pairing=2)
+    case = W.make_attn_case("t", 91, "bf16", seqs + [LONG], hq_l, hkv_l, 128)
+    _takes(G, case, 128, 64, splits, 1)
+    want = oracle.attention_case(case, oracle.cache_for_case(case))
+    _check(G.prefill_case(case, G.cache_for_case(case, fill_byte=0xFF)), want)
+
+
+@pytest.mark.parametrize("splits", [1, 2, 3])
+def test_two_groups_of_wavefronts_run_a_pass_three_times(oracle, G, opts, splits):
+    """Late logits some 150 powers of two above everything before them, in every key range, for a row of each of eight tiles that walk
+    101, 103, ... 115 key tiles, all of them full: the attempt that follows the maximum is flagged as well, and the one behind
+    it ends with the first group a tile ahead of or behind the second, at every stage of the ring (its count of tiles takes all four
+    remainders, with one range and with several)."""
+    opts(tile=128, splits=splits, pairing=2)
+    case = W.make_attn_case("t", 107, "bf16", [(600, 3800), LONG], 8, 1, 128)
+    _takes(G, case, 128, 64, splits, 1)
+    rows = [16 * tile + 9 for tile in (0, 4, 8, 12, 16, 20, 24, 28)]
+    assert [(3200 + row // 16 * 16 + 15) // 32 + 1 for row in rows] == list(range(101, 117, 2))
+    at = (500, 900, 1500, 1900, 2700, 3100)        # two or more in each range, in tiles of either group, behind their first ones
+    pairs = [(row, key + 7 * i) for i, row in enumerate(rows) for key in at]
+    case = _with_late_outliers(case, [r for r, _ in pairs], [k for _, k in pairs], beta=9.0)
     want = oracle.attention_case(case, oracle.cache_for_case(case))
     _check(G.prefill_case(case, G.cache_for_case(case)), want)
 
