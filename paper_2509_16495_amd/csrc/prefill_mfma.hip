@@ -806,9 +806,8 @@ size_t split_bytes_of(const Choice& c, int total_q, const AttnShape& a) {
 // plan stays the least workspace a call is accepted with and the plan of a caller that brings no more; beyond it, one
 // tile or two per workgroup and 1 to 32 key ranges of the three kernels are priced with the model below.  Constants in
 // microseconds, fitted to 110 launches times about 50 plans each (prompts of 40 .. 14000 tokens, chunks behind 100 ..
-// 60000 cached, 1 .. 12 sequences, all head geometries): the fit is 9 % off (root mean square of the logarithm), its
-// choices 1.3 % slower than the best plan measured (64 times the narrow kernel's, 36 the half, 10 the wide form's; without the
-// half form 3.7 %).
+// 60000 cached, 1 .. 12 sequences, all head geometries): the fit is 9 % off (root mean square of the logarithm).  On 1330 others
+// the choices are 2.0 % slower than the best plan measured and 2.9 % faster than those among the narrow and the wide form.
 struct TileKernel {
     double pass, second_pass;  // around the key loop: set-up, Q, first and last tile, write-out
     double step, step_full;    // one step of the key loop, and what it costs more once every compute unit is busy
@@ -874,12 +873,18 @@ double launch_us(const TileKernel& k, bool paired, int splits, int tile_tokens, 
     return (span + 6.6) * (1.0 + 0.008 * splits);   // (launch; among equals the plan with fewer ranges)
 }
 
-// What the model must promise before a launch leaves the 128-column kernel: 54 drawn batches and prompts against the launches
-// without the half form are 1.023 times as fast with it (two 2 to 4 % slower, none of the others 2 %), 1.020 without it (five).
-constexpr double kMargin = 1.035;
-// Keys a range of the half form holds at least: what it gains in its loop, it loses around it in shorter ones (110 launches: the
-// same choices with lines from 0 to 1536; below, the model says little about it).
-constexpr int kHalfLeastKeys = 1024;
+// What the model must promise before a launch leaves the 128-column kernel.  Among 2695 unified batches (1 .. 6 equal or unequal chunks
+// of 40 .. 4096 tokens on up to 131072 cached beside 2 .. 128 rows of up to 32768, either cache, about 40 plans each) the choices with 1 /
+// 1.02 / 1.04 / 1.05 are 6.6 / 6.5 / 6.5 / 6.6 % off the best plan, and 164 / 135 / 102 / 98 of them 3 % slower than the choice among
+// the narrow and the wide form.
+constexpr double kMargin = 1.04;
+// Keys a range of the half form holds at least.  Time with it over that of the narrow kernel, same tiles and ranges, by the keys of
+// a range: 768 .. 1024 1.05, 1024 .. 1400 1.02, 1400 .. 2000 0.99, 2000 .. 2800 0.94, 2800 .. 4000 0.93 (tiles one by one; in pairs
+// 1.12 / 1.05 / 0.99 / 0.97 / 0.94, beside decode rows 1.05 / 1.02 / 1.00 / 0.97 / 0.94; a single launch up to 15 % to either side).
+// The line lies behind the crossing, where nearly all gain: with lines at 1024 / 2000 / 2400 / 2700 the same batches are 6.6 / 6.6 / 6.5 /
+// 6.6 % off the best, 162 / 123 / 102 / 96 of them 3 % slower than without the form; of 1440 launches without decode rows 71 are with a
+// line at 1024, 47 here.
+constexpr int kHalfLeastKeys = 2400;
 
 Kind kind_of(const Choice& c) { return !c.wide ? kNarrow : c.w.groups == 1 ? kWide : kHalf; }
 
@@ -1056,7 +1061,9 @@ hipError_t launch_prefill_mfma(const void* q, const void* cache, const int32_t* 
 // decodes (256-column kernel): 1028 -> 974; 1536 on 90000 with 100: 670 -> 602.
 namespace {
 
-// the 128-column kernel beside decode rows (fitted before its constants above were: 200 random unified batches)
+// The 128-column kernel beside decode rows, where the launch is full from its first workgroup on: from 200 random unified batches.  With
+// its constants above, which come from launches of chunks alone, 196 of the 2695 batches are 3 % slower than without the half form
+// instead of 102, and all 0.2 % in the mean.
 constexpr TileKernel kNarrowBesideRows = {2.65, 3.1, 1.4, 0.335, 2 * kKvTile, 1.0};
 
 struct BothPlan {
@@ -1075,8 +1082,11 @@ double decode_bytes(int num_seqs, int max_seq_len, const AttnShape& a) {
     return 0.6 * num_seqs * static_cast<double>(max_seq_len) * a.hkv_l * 2 * kD * a.kv_elem;
 }
 constexpr double kDecodeStartUs = 5.0, kBf16BytesPerUsWg = 60e3, kFp8BytesPerUsWg = 48e3, kDecodeBytesPerUs = 5.8e6;
-constexpr double kFourWaves = 0.85, kFp8FourWaves = 0.45;   // of that with four wavefronts per workgroup
-// (the kernels of 64-column wavefronts) instead of eight (97 FP8 rows of up to 16000 beside 1000 tokens on 20000: 132 us narrow, 140 wide, 147 half)
+// Of that with four wavefronts per workgroup (the kernels of 64-column wavefronts) instead of eight.  Choices among the 1432 batches over a bf16
+// cache with 0.65 / 0.74 / 0.85 / 1: 7.2 / 7.1 / 7.0 / 7.1 % off the best plan; among the 1263 over an FP8 cache with 0.45 / 0.6 / 0.85:
+// 5.9 / 5.9 / 5.9 %, 43 / 46 / 55 of them 3 % slower than without the half form (97 rows of up to 16000 beside 1000 tokens on 20000:
+// 132 us narrow, 140 wide, 147 half).
+constexpr double kFourWaves = 0.85, kFp8FourWaves = 0.45;
 double decode_us(double bytes, double wgs, bool fp8, bool wide) {
     const double rate = wgs * (fp8 ? kFp8BytesPerUsWg : kBf16BytesPerUsWg) * (!wide ? 1.0 : fp8 ? kFp8FourWaves : kFourWaves);
     return kDecodeStartUs + bytes / (rate < kDecodeBytesPerUs ? rate : kDecodeBytesPerUs);
@@ -1105,7 +1115,7 @@ BothPlan plan_both(int num_seqs, int total_q, int max_q_len, int max_seq_len, in
     const double bytes = decode_bytes(num_dec, max_dec_len, a);
     if (bytes < 1e6) return best;   // (a few short rows: nothing to share, and the workspace stays the larger of the two parts')
     const Choice alone = plan_within(SIZE_MAX, num_seqs, total_q, max_q_len, max_seq_len, a);
-    const double chunks_us = priced(alone, num_seqs, total_q, max_q_len, max_seq_len, a);
+    const double chunks_us = (alone.wide ? kMargin : 1.0) * priced(alone, num_seqs, total_q, max_q_len, max_seq_len, a);   // (the scale of the plans below)
     double best_us = 0.97 * (chunks_us + decode_us(bytes, 256, a.kv_fp8(), false) + 9.0), at_least_us = 0.0;
     const double seqs = longest_chunk_equivalents(num_seqs, total_q, max_q_len);
     const int q = max_q_len < max_seq_len ? max_q_len : max_seq_len;

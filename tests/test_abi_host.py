@@ -394,3 +394,17 @@ def test_unified_batches_whose_decode_rows_outweigh_the_chunks_take_two_launches
     for chunks, num_dec, max_dec, hq, hkv in [([(2048, 133120)], 64, 32768, 8, 1), ([(33, 2000)], 7, 5000, 8, 1)]:
         both, larger = sizes(chunks, num_dec, max_dec, hq, hkv)
         assert both > larger, (chunks, num_dec)
+
+
+@pytest.mark.parametrize("chunks,num_dec,max_dec,hq", [
+    ([(244, 39305)], 19, 2209, 5),     # 55.1 us on the 128-column kernel, 59.9 in two groups of 64-column wavefronts
+    ([(1579, 3676)], 31, 5516, 8),     # 53.6 and 58.0
+    ([(120, 32556)], 30, 5061, 8),     # 52.9 and 56.2
+    ([(545, 8155)], 71, 1094, 8),      # 45.3 and 48.0
+    ([(312, 2111)] * 4, 0, 0, 16),     # 39.2 and 42.3
+])
+def test_short_key_ranges_stay_with_the_128_column_kernel(B, chunks, num_dec, max_dec, hq):
+    """What two groups of wavefronts gain in their key loop they lose around it where a range holds less than some 2000 keys."""
+    a = _attn(B, num_q_heads=hq, num_kv_heads=2 if hq == 16 else 1, max_blocks_per_seq=(max(max_dec, max(c[1] for c in chunks)) + 15) // 16)
+    p = B.prefill_plan(len(chunks), sum(c[0] for c in chunks), max(c[0] for c in chunks), max(c[1] for c in chunks), a, num_dec, max_dec)
+    assert (p.tile_columns, p.wave_columns) == (128, 32) and (p.decode_wgs > 0) == (num_dec > 0)

@@ -119,13 +119,13 @@ def test_mixed_launch_of_unequal_chunks(oracle, G, kv, chunks, decodes, hq_l, hk
 # Batches whose chunks go to tiles of 128 columns in two groups of wavefronts beside the decode rows, over either cache.
 TWO_GROUPS = [
     # chunks, decode contexts, query heads, KV heads, columns of the prefill kernel, key ranges
-    ([(513, 7733)], [1244, 3993, 2715, 2966, 33, 33, 355], 8, 1, 0, 6),                                    # one chunk
-    ([(876, 1240)], [33, 1, 33, 1, 1, 1, 3145, 1134, 1, 1, 1, 4715], 16, 2, 0, 1),                         # one range
-    ([(749, 749), (494, 494), (399, 399), (102, 3663)], [33, 33, 1, 1403, 3078, 1, 3418, 1, 742], 8, 1, 0, 1),   # unequal, rotated
-    ([(109, 109), (276, 5256), (203, 4919), (154, 4766)], [2200, 2178, 1, 778, 33, 33, 1, 33], 5, 1, 0, 5),
+    ([(515, 14420)], [2677, 1, 33, 1], 8, 1, 0, 6),                                                              # one chunk
+    ([(749, 749), (494, 494), (399, 399), (102, 3663)], [33, 33, 1, 1403, 3078, 1, 3418, 1, 742], 8, 1, 0, 1),   # one range, rotated
+    ([(512, 512), (98, 98), (90, 2407)], [33, 3417, 1374, 1, 552], 16, 2, 128, 1),
     ([(117, 1189), (216, 1170), (235, 235), (158, 5013)], [1, 3230, 1], 16, 2, 0, 2),
-    ([(757, 757), (112, 6949), (153, 153)], [33, 1, 4769, 33, 1, 33, 526, 3633, 1, 1], 4, 1, 128, 3),
-    ([(192, 1253), (685, 685), (100, 6799)], [1, 4396, 2766], 4, 4, 128, 3),                              # one query head per KV head
+    ([(62, 14108), (450, 450), (253, 253)], [33, 33, 4841, 33, 304, 4998, 1, 1759, 3097, 4255, 1, 1661], 4, 1, 0, 5),
+    ([(225, 225), (404, 404), (63, 11126)], [1, 1, 4285, 1, 3116, 1, 33, 1, 33, 1, 1], 5, 1, 128, 4),
+    ([(62, 14599), (415, 415), (89, 284)], [33, 2466, 1, 1, 3216], 4, 4, 0, 5),                                  # one query head per KV head
 ]
 
 
