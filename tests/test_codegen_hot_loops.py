@@ -2,10 +2,11 @@
 wavefront per SIMD hold no register spills.
 
 Both kernels sit at the edge of the register file, and a spill that lands inside the loop costs far more than its
-instruction: a scratch load shares the vector-memory counter with the direct-to-LDS loads, so the loop's
-`s_waitcnt vmcnt(0)` then waits for it too (a one-line change of a loop bound that moved one scratch load into the
-256-column prefill kernel's loop made every launch 4-5 % slower, with every test green).  The check compiles the
-source to assembly with the build's own flags and looks at the basic blocks that carry the loops' MFMAs.
+instruction: a scratch load shares the vector-memory counter with the direct-to-LDS loads.  A wait for all of them then
+waits for it too (a one-line change of a loop bound that moved one scratch load into the 256-column prefill kernel's loop
+made every launch 4-5 % slower, with every test green), and a wait that counts the newest loads, as the 64-column
+wavefronts' does, would let the tile it needs be one load short.  The check compiles the source to assembly with the
+build's own flags and looks at the basic blocks that carry the loops' MFMAs.
 """
 import functools
 import os
@@ -19,6 +20,30 @@ import pytest
 from paper_2509_16495_amd import build as BLD
 
 pytestmark = pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc to compile to assembly")
+
+
+@functools.lru_cache(maxsize=None)
+def _assembly(source):
+    """Lines of the source's gfx950 assembly, compiled once with the build's own flags."""
+    flags = [f for f in BLD.FLAGS if f not in ("-shared", "-fPIC")]
+    with tempfile.TemporaryDirectory() as tmp:
+        out = os.path.join(tmp, source + ".s")
+        subprocess.check_call(["hipcc", *flags, "--cuda-device-only", "-S", os.path.join(BLD.CSRC, source), "-o", out],
+                              cwd=BLD.CSRC, stderr=subprocess.DEVNULL)
+        return tuple(open(out))
+
+
+def _kernel_lines(source, kernel_substr):
+    """Those of the kernel whose mangled name contains `kernel_substr`."""
+    lines, inside = [], False
+    for line in _assembly(source):
+        if re.match(r"^[A-Za-z_$][\w.$]*:", line):
+            inside = kernel_substr in line
+        elif line.startswith(".Lfunc_end"):
+            inside = False
+        elif inside:
+            lines.append(line)
+    return lines
 
 
 def _blocks_of(source, kernel_substr, tmp_path):
@@ -47,19 +72,41 @@ def _blocks_of(source, kernel_substr, tmp_path):
     return blocks
 
 
-def test_prefill64_steady_state_loop_has_no_spills(tmp_path):
-    blocks = _blocks_of("prefill_mfma64.hip", "prefill64_kernel", tmp_path)
-    heavy = [i for i, b in enumerate(blocks) if b[1] >= 24]      # bodies of an iteration: 32 MFMAs, a few of them in a block in front
-    # the steady-state bodies (two of the attempt that follows no reference, two of those that follow the maximum) are the
-    # short ones; the bodies next to a pass's ends carry wait states in front of every MFMA and are far longer
-    steady = [i for i in heavy if blocks[i][3] < 300]
-    assert len(steady) >= 4, [tuple(b) for b in blocks if b[1]]
-    for i in steady:
-        body = blocks[i]
-        assert body[2] == 0, ("spill traffic in a steady-state body", tuple(body))
-        front = blocks[i - 1]                                   # barrier, refill of the ring and the body's first MFMAs
-        assert front[1] + body[1] == 32, (tuple(front), tuple(body))
-        assert front[2] == 0, ("spill traffic in front of a steady-state body", tuple(front))
+# template arguments <decode role, scaled Q, groups> of the instances of the 64-column wavefronts' kernel
+PREFILL64 = [(d, q, 1) for q in (0, 1) for d in (0, 1, 2)] + [(d, 0, 2) for d in (0, 1, 2)]
+
+
+@pytest.mark.parametrize("decode,scaled_q,groups", PREFILL64)
+def test_prefill64_steady_state_loops_have_no_spills(decode, scaled_q, groups):
+    """Every instance holds fourteen bodies of an iteration, 32 MFMAs each in two blocks (the second with the direct-to-LDS loads of a tile,
+    twice as many with two groups): four of the steady loop and three behind it, whose MFMAs carry wait states, for the first attempt at a
+    pass and as many, with a maximum per two logits, for those that follow the maximum."""
+    blocks = []
+    for line in _kernel_lines("prefill_mfma64.hip", f"prefill64_kernelILi{decode}ELb{scaled_q}ELi{groups}E"):
+        text = line.split(";")[0].strip()
+        if re.match(r"^\.LBB", line):
+            blocks.append([])
+        elif blocks and text and not text.startswith("."):
+            blocks[-1].append(text.split()[0])
+    assert not [op for b in blocks for op in b if op.startswith("scratch_")]
+
+    def count(ops, *names):
+        return sum(op.startswith(names) for op in ops)
+
+    kinds = {}
+    for front, body in zip(blocks, blocks[1:]):
+        if count(body, "global_load_lds_dwordx4") != 4 * groups or count(body, "v_mfma") < 20:
+            continue
+        both = front + body
+        assert count(both, "v_mfma") == 32 and count(front, "s_barrier") == 1
+        waits = sum(a == "s_nop" and b.startswith("v_mfma") for a, b in zip(both, both[1:]))
+        follows = count(both, "v_max3_f32")
+        assert waits in (0, 32) and follows in (0, 16)
+        kinds[waits > 0, follows > 0] = kinds.get((waits > 0, follows > 0), 0) + 1
+        # (the rare attempts of two groups want one scalar register too many: it comes back from a vector lane once a trip)
+        allowed = 0 if follows == 0 or groups == 1 else 1 if waits == 0 else 2
+        assert count(both, "v_readlane", "v_writelane") <= allowed
+    assert kinds == {(False, False): 4, (True, False): 3, (False, True): 4, (True, True): 3}
 
 
 def test_proj_gemm_main_loop_has_no_spills(tmp_path):
@@ -111,17 +158,6 @@ def test_prefill_key_loop_forms_its_addresses_in_scalar_registers(tmp_path):
         for k, b in blocks[i:i + 2]:
             assert sum("mfma" in x for x in b) >= 15
             assert not [x for x in b if x.startswith(("v_readfirstlane", "v_readlane", "v_mul_lo_u32", "v_mad_u64_u32"))], k
-
-
-@functools.lru_cache(maxsize=None)
-def _assembly(source):
-    """Lines of the source's gfx950 assembly, compiled once with the build's own flags."""
-    flags = [f for f in BLD.FLAGS if f not in ("-shared", "-fPIC")]
-    with tempfile.TemporaryDirectory() as tmp:
-        out = os.path.join(tmp, source + ".s")
-        subprocess.check_call(["hipcc", *flags, "--cuda-device-only", "-S", os.path.join(BLD.CSRC, source), "-o", out],
-                              cwd=BLD.CSRC, stderr=subprocess.DEVNULL)
-        return tuple(open(out))
 
 
 def _unsynchronised_parks(lines):
@@ -178,13 +214,5 @@ def test_two_groups_exchange_their_sums_behind_a_barrier(decode):
     """The two-group form of the 64-column wavefronts parks accumulators in the bytes of its key rings.  Whichever attempt a pass ends
     with, a barrier lies between the last product of every wavefront and the first parked accumulator: one group may be a whole tile
     ahead of the other, whose operands it would overwrite."""
-    lines, inside = [], False
-    for line in _assembly("prefill_mfma64.hip"):
-        if re.match(r"^[A-Za-z_$][\w.$]*:", line):
-            inside = f"prefill64_kernelILi{decode}ELb0ELi2E" in line
-        elif line.startswith(".Lfunc_end"):
-            inside = False
-        elif inside:
-            lines.append(line)
-    parks, bad = _unsynchronised_parks(lines)
+    parks, bad = _unsynchronised_parks(_kernel_lines("prefill_mfma64.hip", f"prefill64_kernelILi{decode}ELb0ELi2E"))
     assert parks >= 1 and bad == 0, (parks, bad)
