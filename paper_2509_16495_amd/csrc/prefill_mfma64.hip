@@ -119,7 +119,7 @@ struct IC {
 #define SHIFTATTN_INLINE __attribute__((always_inline))
 #define SHIFTATTN_FORCE_INLINE inline __attribute__((always_inline))
 
-// s_waitcnt vmcnt(0) with the other counters left alone (gfx9 encoding), and all but the last four
+// s_waitcnt vmcnt(0) with the other counters left alone (gfx9 encoding)
 __device__ inline void wait_vm0() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
 // The matrix instructions are written as assembly to fix where their accumulators live: S^T in ordinary vector
@@ -279,7 +279,8 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
     // Written as assembly so that the address is formed by the load itself (scalar base + vector offset) instead of a
     // 64-bit vector addition per load.  The LDS destination goes through M0; the compiler treats M0 as reserved (it
     // sets it right before each use of its own and keeps no value in it), so writing it here needs no clobber.  The
-    // loads are waited for with explicit vmcnt(0) waits (wait_vm0) only.
+    // compiler does not count these loads: around the key loop they are waited for with vmcnt(0) (wait_vm0), in the loop
+    // with a count of the newest ones (see the barrier there).
     auto dma_4k = [&](const unsigned char* src, const int (&off)[4], int m0v) SHIFTATTN_INLINE {
         asm volatile(
             "s_mov_b32 m0, %0\n\ts_nop 4\n\t"
@@ -465,7 +466,7 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
         };
 
         // One iteration on tile j.  PH = j % 4: selects the stages and, by its parity, the register sets at compile time.
-        // track_c: 1 = the maximum is followed (TRACK); 2 = the reference the column's first key tile left is kept and no
+        // track_c: 1 = the maximum is followed (TRACK); 2 = the reference the column's first key tiles left is kept and no
         // maximum followed (KEEP); 0 = no reference at all, on logits that arrive in exp2 units (Q^T carries the scale)
         // s_lo, s_hi: addresses of the last four loads of K (two groups: V^T's is K's of two iterations before)
         auto body = [&](auto ph_c, auto guard_c, auto track_c, int j, uint32_t (&s_lo)[4], uint32_t (&s_hi)[4]) SHIFTATTN_INLINE {
@@ -566,8 +567,11 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
                     asm volatile("" : "+s"(src_lo));
                 } else if constexpr (t == 2) {
                     // a bare barrier: __syncthreads() would first drain every outstanding LDS read.  What has to be complete
-                    // is this wavefront's loads of the iteration before last (all but the last four it issued) and its reads of
-                    // the stages about to be overwritten (their data went into MFMAs in the iteration before).
+                    // is this wavefront's loads of the iteration before last - all but the newest four, or eight of two groups,
+                    // which are the tile loads of the iteration before: nothing else may be issued behind those, so a request
+                    // for the next window of block ids stays in front of its iteration's (slots 7 and 8) and no spill may load
+                    // in here - and its reads of the stages about to be overwritten (their data went into MFMAs in the
+                    // iteration before).
                     if constexpr (kG == 1) asm volatile("s_waitcnt vmcnt(4)\n\ts_barrier" ::: "memory");
                     else asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");
                 } else if constexpr (t == 3) {
@@ -676,9 +680,9 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
         if (n > 0) issue_prologue();
         fetch_q(IC<kScaledQ ? 1 : 0>{});
 
-        // Up to three attempts at the pass.  The first follows no maximum behind the first key tile (its steady-state
+        // Up to three attempts at the pass.  The first follows no maximum behind the first key tile or two (its steady-state
         // bodies save the instruction per two logits that would collect it; real logits stay within 2^100 of their
-        // first tile's maximum).  If some wavefront flags it (see the end of an iteration), the second starts over and
+        // first tiles' maximum).  If some wavefront flags it (behind its key loop), the second starts over and
         // follows the maximum tile by tile; it can end flagged itself (a column outgrew its reference after it had sums),
         // and then holds, for every column, a reference within the slack of the true maximum: the third attempt starts
         // from that and is not flagged.
@@ -717,7 +721,7 @@ __global__ __launch_bounds__(kThreads, 1) void prefill64_kernel(Prefill64Params 
             pre_a = lds_read16(k_rd[0] + kStageBytes);
             pre_c = lds_read16(v_rd + 3 * kStageBytes);
             mfma_settle(sbuf[0]);
-            if constexpr (decltype(track_c)::value == 2) {   // the reference that is kept: the first tile's maximum
+            if constexpr (decltype(track_c)::value == 2) {   // the reference that is kept: the first tile's maximum, or the first two's
                 // (Keys that are their column's reference have P = 1, exact in bf16, and the heaviest keys carry most of the rounding
                 // error: where rows of less than 1000 keys are among the columns, the second tile's keys take part.  Prompts of
                 // 4096 tokens, 2-norm of the error of rows 128 to 256 3.8 % larger without.)
