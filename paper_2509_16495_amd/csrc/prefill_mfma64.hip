@@ -49,7 +49,8 @@
 // follows it - asks for no more than 28 clocks besides, and if an operand read follows the MFMA of its slot instead of
 // standing in front of it (32.1 against 37.1 clocks a slot, everything else alike).  So the work is dealt to the slots
 // evenly, the addresses of the loads are kept ready in a vector register pair, and nothing is moved between register files.
-// MFMA pipe busy 59 -> 77 % of the clocks; what is left is the power limit, the clock settles at 1.76 instead of 2.05 GHz:
+// MFMA pipe busy 60 -> 69 % of a launch's SIMD-clocks (81 % of those with a wavefront resident; 2048 tokens on 131072 cached); what
+// is left is the power limit, the clock settles at 1.76 instead of 2.05 GHz:
 // 16384 tokens of 8 heads 464 -> 424 us, 2048 tokens on 131072 cached with 64 decodes 957 -> 882.
 //
 // Two groups (kG = 2).  The same wavefronts on a tile of 128 columns: wavefronts 0 and 1 walk the even key tiles, 2 and 3 the odd
