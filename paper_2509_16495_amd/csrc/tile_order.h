@@ -25,7 +25,7 @@ struct TileItem {
 // that carry decode rows: their shorter last ranges start last, on the compute units that the decode rows leave), else the
 // ranks.  rotate: rotate_sequences_over_dies() of the batch; the rotation is that of the run, whatever stands in front of it
 // in the grid, so a run holds every (sequence, head) once.
-// (inlined early and with the divisions in this order: other forms leave the 256-column kernel up to 30 more spilled registers)
+// (inlined early and with the divisions in this order: other forms cost the kernels at the edge of the register file up to 30 more)
 [[gnu::always_inline]] constexpr inline TileItem tile_item(int block, int decode_wgs, int n_sh, int ranks, int n_splits,
                                                            bool range_major, bool rotate) {
     const int wg = block - decode_wgs;
