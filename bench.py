@@ -424,7 +424,7 @@ def main() -> int:
         tf = c2.flops() / (ms_k * 1e-3) / 1e12
         result["prefill_8b"] = {"workload": "configs[1]: 4q/1kv, D=128, 4 x 4096-token causal prefill, paged KV", "flops": c2.flops(),
                                 "ms": round(ms_k, 5), "ms_with_kv_write": round(ms_w, 5),
-                                "roofline": roof("prefill_kernel (128-column tiles)", "mfma", tf, PEAK_BF16_TFLOPS, "TFLOP/s", traffic_key="prefill_8b")}
+                                "roofline": roof("prefill64_kernel (128-column tiles in pairs, two groups of wavefronts)", "mfma", tf, PEAK_BF16_TFLOPS, "TFLOP/s", traffic_key="prefill_8b")}
         log(f"[bench] prefill cfg2: {ms_k * 1e3:.1f} us ({ms_w * 1e3:.1f} with K/V write), {tf:.1f} TFLOP/s ({tf / PEAK_BF16_TFLOPS:.1%})")
         if cpu:
             dt, fl, _ = oracle_attention(c2, np.arange(c2.total_q, dtype=np.int64), "cfg2")
