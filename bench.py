@@ -167,6 +167,14 @@ def main() -> int:
 
     traffic_by_key = counter_traffic()
 
+    def prefill_kernel_name(case, q, cache, table):
+        """The kernel and the plan that a prefill call on the case takes, as the library names them."""
+        p = B.prefill_plan(case.num_seqs, case.total_q, int(case.q_lens.max()), int(case.ctx_lens.max()), B.attn_desc(q, cache, table, case.softmax_scale))
+        groups = ", two groups of wavefronts" if (p.tile_columns, p.wave_columns) == (128, 64) else ""
+        per_wg = "in pairs" if p.tiles_per_wg == 2 else "one per workgroup, heaviest first"
+        ranges = f", {p.key_ranges} key ranges" if p.key_ranges > 1 else ""
+        return f"{'prefill64_kernel' if p.wave_columns == 64 else 'prefill_kernel'} ({p.tile_columns}-column tiles {per_wg}{groups}{ranges})"
+
     def roof(kernel, bound, achieved, peak, unit, traffic_key=None, **extra):
         r = {"kernel": kernel, "bound": bound, "achieved": round(achieved, 2), "peak": peak, "unit": unit,
              "frac": round(achieved / peak, 4), "traffic": traffic_by_key.get(traffic_key)}
@@ -424,7 +432,7 @@ def main() -> int:
         tf = c2.flops() / (ms_k * 1e-3) / 1e12
         result["prefill_8b"] = {"workload": "configs[1]: 4q/1kv, D=128, 4 x 4096-token causal prefill, paged KV", "flops": c2.flops(),
                                 "ms": round(ms_k, 5), "ms_with_kv_write": round(ms_w, 5),
-                                "roofline": roof("prefill64_kernel (128-column tiles in pairs, two groups of wavefronts)", "mfma", tf, PEAK_BF16_TFLOPS, "TFLOP/s", traffic_key="prefill_8b")}
+                                "roofline": roof(prefill_kernel_name(c2, q2, cache2, t2), "mfma", tf, PEAK_BF16_TFLOPS, "TFLOP/s", traffic_key="prefill_8b")}
         log(f"[bench] prefill cfg2: {ms_k * 1e3:.1f} us ({ms_w * 1e3:.1f} with K/V write), {tf:.1f} TFLOP/s ({tf / PEAK_BF16_TFLOPS:.1%})")
         if cpu:
             dt, fl, _ = oracle_attention(c2, np.arange(c2.total_q, dtype=np.int64), "cfg2")
@@ -764,8 +772,7 @@ def main() -> int:
             mq3, mc3 = int(case.q_lens.max()), int(case.ctx_lens.max())
             ms = time_events(lambda: B.prefill(q3, cch, t3, cu3, s3, mq3, mc3, o3, case.softmax_scale), reps)
             tf = case.flops() / (ms * 1e-3) / 1e12
-            kname = ("prefill64_kernel (256-column tiles in pairs)" if key == "prefill_70b" else
-                     "prefill64_kernel (256-column tiles one per workgroup, heaviest first" + (", 2 key ranges)" if key == "prefill_5q_per_kv" else ")"))
+            kname = prefill_kernel_name(case, q3, cch, t3)
             result[key] = {"workload": label, "flops": case.flops(), "ms": round(ms, 5),
                            "roofline": roof(kname, "mfma", tf, PEAK_BF16_TFLOPS, "TFLOP/s", traffic_key=key)}
             log(f"[bench] {key}: {ms * 1e3:.1f} us, {tf:.1f} TFLOP/s ({tf / PEAK_BF16_TFLOPS:.1%} of bf16 MFMA peak)")

@@ -829,12 +829,20 @@ bool kind_allowed(Kind k, const AttnShape& bf16) {
     return k == kWide ? forced != 128 : forced != 256 && bf16.hq_l / bf16.hkv_l <= 128;
 }
 
+// The batch counted in sequences of its longest chunk, for `heads` (sequence, head) indices a sequence.  Of two sequences of one
+// each, which never rotate, either sees every second die only: the longer has half the chip, whatever the shorter leaves of the other
+// half (5068 + 8739 tokens, 5 heads: 150 us on the 128-column kernel, whose heads count one by one, 176 in two groups).  200 launches of
+// two or six unequal sequences: choices 3.0 % off the best plan, 3.9 % with the sum over the longest here too.
+double sequences_that_weigh(int num_seqs, int heads, int total_q, int max_q_len) {
+    return num_seqs == 2 && heads == 1 ? 2.0 : longest_chunk_equivalents(num_seqs, total_q, max_q_len);
+}
+
 double launch_us(const TileKernel& k, bool paired, int splits, int tile_tokens, int heads, int num_seqs, int total_q,
                  int max_q_len, int max_seq_len, int hq_l) {
     constexpr double kCus = 256, kSlack = 1.13;  // slack: how far a chip full of unequal workgroups stays from level
     constexpr double kMergeUs = 4.5, kMergeBytesPerUs = 5.8e6, kRowBytes = 1040;  // partials of a (token, head) written and read
     const int tiles = (max_q_len + tile_tokens - 1) / tile_tokens, ranks = paired ? (tiles + 1) / 2 : tiles;
-    const double seqs = longest_chunk_equivalents(num_seqs, total_q, max_q_len);
+    const double seqs = sequences_that_weigh(num_seqs, heads, total_q, max_q_len);
     const double wgs = ranks * seqs * heads * splits, grid = static_cast<double>(ranks) * num_seqs * heads * splits;
     const int q = max_q_len < max_seq_len ? max_q_len : max_seq_len;
     auto steps = [&](int keys) {   // of the range a workgroup takes of a tile that sees `keys` keys
@@ -914,8 +922,9 @@ Choice plan_within(size_t split_budget, int num_seqs, int total_q, int max_q_len
     AttnShape b = a;
     b.kv_elem = b.elem;
     const int forced_splits = option_prefill_splits(), forced_pairing = option_prefill_pairing();
-    // (what is left of choose()'s plan only for a gain beyond the model's error)
-    double best_us = 0.97 * priced(best, num_seqs, total_q, max_q_len, max_seq_len, a);
+    // (choose()'s plan without the margin, whichever kernel it is for: with 3 % in its favour besides 15 of 1254 launches were slower
+    // by that and more, without one is)
+    double best_us = priced(best, num_seqs, total_q, max_q_len, max_seq_len, a);
     Choice c = best;
     auto try_ranges = [&](int splits) {
         if (split_bytes(splits, total_q, a) > split_budget) return;
@@ -1117,7 +1126,6 @@ BothPlan plan_both(int num_seqs, int total_q, int max_q_len, int max_seq_len, in
     const Choice alone = plan_within(SIZE_MAX, num_seqs, total_q, max_q_len, max_seq_len, a);
     const double chunks_us = (alone.wide ? kMargin : 1.0) * priced(alone, num_seqs, total_q, max_q_len, max_seq_len, a);   // (the scale of the plans below)
     double best_us = 0.97 * (chunks_us + decode_us(bytes, 256, a.kv_fp8(), false) + 9.0), at_least_us = 0.0;
-    const double seqs = longest_chunk_equivalents(num_seqs, total_q, max_q_len);
     const int q = max_q_len < max_seq_len ? max_q_len : max_seq_len;
     AttnShape b16 = a;
     b16.kv_elem = b16.elem;
@@ -1135,7 +1143,7 @@ BothPlan plan_both(int num_seqs, int total_q, int max_q_len, int max_seq_len, in
         for (int splits : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 24, 32}) {
             if (splits > 1 && max_seq_len < splits * 2 * kKvTile) break;
             if (kind == kHalf && max_seq_len < splits * kHalfLeastKeys) break;
-            const double wgs = tiles * seqs * heads * splits, grid = static_cast<double>(tiles) * num_seqs * heads * splits;
+            const double wgs = tiles * sequences_that_weigh(num_seqs, heads, total_q, max_q_len) * heads * splits, grid = static_cast<double>(tiles) * num_seqs * heads * splits;
             const double merge = splits > 1 ? splits * static_cast<double>(total_q) * a.hq_l * 1040 / 5.8e6 : 0.0;
             auto consider = [&](double x, double div, double span) {
                 const double us = (kind == kNarrow ? 1.0 : kMargin) * (span * (num_seqs > 1 ? k.several : 1.0) + merge + 6.6 + 4.5) * (1.0 + 0.008 * splits);

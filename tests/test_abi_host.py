@@ -408,3 +408,11 @@ def test_short_key_ranges_stay_with_the_128_column_kernel(B, chunks, num_dec, ma
     a = _attn(B, num_q_heads=hq, num_kv_heads=2 if hq == 16 else 1, max_blocks_per_seq=(max(max_dec, max(c[1] for c in chunks)) + 15) // 16)
     p = B.prefill_plan(len(chunks), sum(c[0] for c in chunks), max(c[0] for c in chunks), max(c[1] for c in chunks), a, num_dec, max_dec)
     assert (p.tile_columns, p.wave_columns) == (128, 32) and (p.decode_wgs > 0) == (num_dec > 0)
+
+
+def test_two_unequal_prompts_are_priced_for_the_half_of_the_chip_that_each_sees(B):
+    """5068 and 8739 tokens of five heads per KV head: in two groups of wavefronts, heads stacked, the longer prompt runs on every second die
+    (176 us); the 128-column kernel takes the heads one by one and meets them all (160)."""
+    a = _attn(B, num_q_heads=5, max_blocks_per_seq=547)
+    p = B.prefill_plan(2, 5068 + 8739, 8739, 8739, a)
+    assert (p.tile_columns, p.wave_columns, p.key_ranges) == (128, 32, 1)
