@@ -295,3 +295,32 @@ def test_keys_whose_logits_overflow_do_not_hide_those_behind_them(oracle, G, opt
     case.q, case.k_ctx = W.f32_to_bf16_bits(q), W.f32_to_bf16_bits(k)
     want = oracle.attention_case(case, oracle.cache_for_case(case))
     _check(G.prefill_case(case, G.cache_for_case(case)), want)
+
+
+@pytest.mark.parametrize("tile", [128, 256])
+def test_wavefronts_without_columns_do_not_hold_up_the_others(G, opts, tile):
+    """A tile of three tokens of eight heads fills half a wavefront, the others of its workgroup have no column; it walks the keys of
+    a full one.  With selects for masked keys in every iteration of those it took 1.35 times as long as the full tile, without them as
+    long (0.99 and 1.00): the bound lies between, a run differs from another by a per cent or two."""
+    import torch
+    from paper_2509_16495_amd import binding as B
+    opts(tile=tile, splits=1, pairing=2)
+    calls = []
+    for tokens in (3, tile // 8):
+        case = W.make_attn_case("t", 109, "bf16", [(tokens, 20000)], 8, 1, 128)
+        _takes(G, case, tile, 64, 1, 1)
+        cache, q, out = G.cache_for_case(case), G.t(case.q, "bf16"), torch.empty(case.q.shape, dtype=torch.bfloat16, device=G.DEV)
+        table, cu, ctx = G.ti(case.block_table, np.int32), G.ti(case.cu_seqlens_q, np.int32), G.ti(case.ctx_lens, np.int32)
+        calls.append(lambda c=(q, cache, table, cu, ctx, tokens, 20000, out, case.softmax_scale): B.prefill(*c))
+    times = [[], []]
+    for _ in range(30):
+        for call, us in zip(calls, times):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            call()
+            end.record()
+            end.synchronize()
+            us.append(start.elapsed_time(end) * 1e3)
+    few, full = (float(np.median(us[5:])) for us in times)
+    print(f"three tokens {few:.1f} us, a full tile {full:.1f} us")
+    assert few < 1.15 * full, (few, full)
