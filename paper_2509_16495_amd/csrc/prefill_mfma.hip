@@ -806,8 +806,8 @@ size_t split_bytes_of(const Choice& c, int total_q, const AttnShape& a) {
 // plan stays the least workspace a call is accepted with and the plan of a caller that brings no more; beyond it, one
 // tile or two per workgroup and 1 to 32 key ranges of the three kernels are priced with the model below.  Constants in
 // microseconds, fitted to 110 launches times about 50 plans each (prompts of 40 .. 14000 tokens, chunks behind 100 ..
-// 60000 cached, 1 .. 12 sequences, all head geometries): the fit is 9 % off (root mean square of the logarithm).  On 1330 others
-// the choices are 2.0 % slower than the best plan measured and 2.9 % faster than those among the narrow and the wide form.
+// 60000 cached, 1 .. 12 sequences, all head geometries): the fit is 9 % off (root mean square of the logarithm).  On 1500 others
+// the choices are 1.4 % slower than the best plan measured and 1.8 % faster than those among the narrow and the wide form.
 struct TileKernel {
     double pass, second_pass;  // around the key loop: set-up, Q, first and last tile, write-out
     double step, step_full;    // one step of the key loop, and what it costs more once every compute unit is busy
@@ -831,8 +831,8 @@ bool kind_allowed(Kind k, const AttnShape& bf16) {
 
 // The batch counted in sequences of its longest chunk, for `heads` (sequence, head) indices a sequence.  Of two sequences of one
 // each, which never rotate, either sees every second die only: the longer has half the chip, whatever the shorter leaves of the other
-// half (5068 + 8739 tokens, 5 heads: 150 us on the 128-column kernel, whose heads count one by one, 176 in two groups).  200 launches of
-// two or six unequal sequences: choices 3.0 % off the best plan, 3.9 % with the sum over the longest here too.
+// half (5068 + 8739 tokens, 5 heads: 150 us on the 128-column kernel, whose heads count one by one, 176 in two groups).  Of the 1500
+// launches below 11 are 3 % slower than without the half form, 20 with the sum over the longest here too.
 double sequences_that_weigh(int num_seqs, int heads, int total_q, int max_q_len) {
     return num_seqs == 2 && heads == 1 ? 2.0 : longest_chunk_equivalents(num_seqs, total_q, max_q_len);
 }
@@ -881,18 +881,19 @@ double launch_us(const TileKernel& k, bool paired, int splits, int tile_tokens, 
     return (span + 6.6) * (1.0 + 0.008 * splits);   // (launch; among equals the plan with fewer ranges)
 }
 
-// What the model must promise before a launch leaves the 128-column kernel.  Among 2695 unified batches (1 .. 6 equal or unequal chunks
-// of 40 .. 4096 tokens on up to 131072 cached beside 2 .. 128 rows of up to 32768, either cache, about 40 plans each) the choices with 1 /
-// 1.02 / 1.04 / 1.05 are 6.6 / 6.5 / 6.5 / 6.6 % off the best plan, and 164 / 135 / 102 / 98 of them 3 % slower than the choice among
-// the narrow and the wide form.
+// What the model must promise before a launch leaves the 128-column kernel.  Among 1500 launches of chunks alone (1 .. 12 equal or unequal
+// chunks of 40 .. 14000 tokens, some behind 100 .. 60000 cached) and 2577 unified batches (1 .. 3 chunks of up to 3000 tokens on up to
+// 100000 cached beside 2 .. 128 rows of up to 32000, either cache) the choices with 1 / 1.02 / 1.04 / 1.05 are 1.1 / 1.2 / 1.4 / 1.6 % and
+// 1.9 / 2.0 / 2.0 / 2.1 % off the best plan measured, and 31 / 14 / 11 / 12 and 58 / 48 / 42 / 44 of them 3 % slower than the choice among
+// the narrow and the wide form (297 / 275 / 238 / 214 and 237 / 200 / 174 / 153 as much faster).
 constexpr double kMargin = 1.04;
 // Keys a range of the half form holds at least.  Time with it over that of the narrow kernel, same tiles and ranges, by the keys of
-// a range: 768 .. 1024 1.05, 1024 .. 1400 1.02, 1400 .. 2000 0.99, 2000 .. 2800 0.94, 2800 .. 4000 0.93 (tiles one by one; in pairs
-// 1.12 / 1.05 / 0.99 / 0.97 / 0.94, beside decode rows 1.05 / 1.02 / 1.00 / 0.97 / 0.94; a single launch up to 15 % to either side).
-// The line lies behind the crossing, where nearly all gain: with lines at 1024 / 2000 / 2400 / 2700 the same batches are 6.6 / 6.6 / 6.5 /
-// 6.6 % off the best, 162 / 123 / 102 / 96 of them 3 % slower than without the form; of 1440 launches without decode rows 71 are with a
-// line at 1024, 47 here.
-constexpr int kHalfLeastKeys = 2400;
+// a range: 512 .. 768 1.09, 768 .. 1024 1.04, 1024 .. 1400 1.02, 1400 .. 2000 0.97, 2000 .. 2800 0.93, beyond 5600 0.79 (tiles one by
+// one; in pairs 1.13 / 1.07 / 1.04 / 1.00 / 0.96 / 0.82).  Of chunks alone the line lies at the crossing: with lines at 1024 / 1400 /
+// 2000 / 2400 the launches are 1.4 / 1.4 / 1.6 / 1.8 % off the best plan, 11 / 11 / 9 / 9 of them 3 % slower than without the form.  Beside
+// decode rows, where the rows' four wavefronts a workgroup weigh too, it lies behind: with lines at 1400 / 2000 / 2400 / 2800 the batches are
+// 1.9 / 2.0 / 2.0 / 2.1 % off, 47 / 45 / 42 / 40 slower (1579 tokens on 2097 beside 31 rows of 5516: narrow 52 us, half in ranges of 1838 60).
+constexpr int kHalfLeastKeys = 1400, kHalfLeastKeysBesideRows = 2400;
 
 Kind kind_of(const Choice& c) { return !c.wide ? kNarrow : c.w.groups == 1 ? kWide : kHalf; }
 
@@ -1071,8 +1072,8 @@ hipError_t launch_prefill_mfma(const void* q, const void* cache, const int32_t* 
 namespace {
 
 // The 128-column kernel beside decode rows, where the launch is full from its first workgroup on: from 200 random unified batches.  With
-// its constants above, which come from launches of chunks alone, 196 of the 2695 batches are 3 % slower than without the half form
-// instead of 102, and all 0.2 % in the mean.
+// its constants above, which come from launches of chunks alone, the 2577 batches are 2.3 instead of 2.0 % off the best plan, and 152 of
+// them instead of 42 are 3 % slower than without the half form.
 constexpr TileKernel kNarrowBesideRows = {2.65, 3.1, 1.4, 0.335, 2 * kKvTile, 1.0};
 
 struct BothPlan {
@@ -1091,10 +1092,9 @@ double decode_bytes(int num_seqs, int max_seq_len, const AttnShape& a) {
     return 0.6 * num_seqs * static_cast<double>(max_seq_len) * a.hkv_l * 2 * kD * a.kv_elem;
 }
 constexpr double kDecodeStartUs = 5.0, kBf16BytesPerUsWg = 60e3, kFp8BytesPerUsWg = 48e3, kDecodeBytesPerUs = 5.8e6;
-// Of that with four wavefronts per workgroup (the kernels of 64-column wavefronts) instead of eight.  Choices among the 1432 batches over a bf16
-// cache with 0.65 / 0.74 / 0.85 / 1: 7.2 / 7.1 / 7.0 / 7.1 % off the best plan; among the 1263 over an FP8 cache with 0.45 / 0.6 / 0.85:
-// 5.9 / 5.9 / 5.9 %, 43 / 46 / 55 of them 3 % slower than without the half form (97 rows of up to 16000 beside 1000 tokens on 20000:
-// 132 us narrow, 140 wide, 147 half).
+// Of that with four wavefronts per workgroup (the kernels of 64-column wavefronts) instead of eight.  Choices among the 1578 batches over a
+// bf16 cache with 0.65 / 0.74 / 0.85 / 1: 2.2 / 2.1 / 2.2 / 2.2 % off the best plan, 35 / 30 / 31 / 41 of them 3 % slower than without the
+// half form; among the 999 over an FP8 cache with 0.45 / 0.6 / 0.85: 1.8 / 1.8 / 1.9 %, 11 / 15 / 30.
 constexpr double kFourWaves = 0.85, kFp8FourWaves = 0.45;
 double decode_us(double bytes, double wgs, bool fp8, bool wide) {
     const double rate = wgs * (fp8 ? kFp8BytesPerUsWg : kBf16BytesPerUsWg) * (!wide ? 1.0 : fp8 ? kFp8FourWaves : kFourWaves);
@@ -1142,7 +1142,7 @@ BothPlan plan_both(int num_seqs, int total_q, int max_q_len, int max_seq_len, in
         auto rows_us = [&](double x) { return decode_us(bytes, x, a.kv_fp8(), four_waves); };
         for (int splits : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 24, 32}) {
             if (splits > 1 && max_seq_len < splits * 2 * kKvTile) break;
-            if (kind == kHalf && max_seq_len < splits * kHalfLeastKeys) break;
+            if (kind == kHalf && max_seq_len < splits * kHalfLeastKeysBesideRows) break;
             const double wgs = tiles * sequences_that_weigh(num_seqs, heads, total_q, max_q_len) * heads * splits, grid = static_cast<double>(tiles) * num_seqs * heads * splits;
             const double merge = splits > 1 ? splits * static_cast<double>(total_q) * a.hq_l * 1040 / 5.8e6 : 0.0;
             auto consider = [&](double x, double div, double span) {
