@@ -361,7 +361,7 @@ int shiftattn_qkv_proj_pack_ws(const void* x, const void* w_qkv, void* send, int
     const int n_feat = (s.h + 2 * s.h_kv) * 128;
     hipError_t e;
     if (s.T > 0 && !force_generic() && proj_stream_takes(s.T_pad, n_feat, d_model, false, workspace_bytes))
-        e = launch_qkv_proj_stream(x, w_qkv, send, d_model, s, nullptr, nullptr, workspace, static_cast<hipStream_t>(stream));
+        e = launch_qkv_proj_stream(x, w_qkv, send, d_model, s, nullptr, nullptr, static_cast<hipStream_t>(stream));
     else
         e = launch_qkv_proj_pack(x, w_qkv, send, d_model, s, nullptr, nullptr, workspace, workspace_bytes, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? SHIFTATTN_OK : hip_fail(e, "qkv_proj_pack launch");
@@ -388,7 +388,7 @@ int shiftattn_unpack_o_proj_ws(const void* recv, const void* w_o, void* out, int
     if (int rc = ensure_device_ready()) return rc;
     hipError_t e;
     if (!force_generic() && proj_stream_takes(s.T, d_model, s.h * 128, false, workspace_bytes))
-        e = launch_o_proj_stream(recv, w_o, out, d_model, s, nullptr, nullptr, workspace, static_cast<hipStream_t>(stream));
+        e = launch_o_proj_stream(recv, w_o, out, d_model, s, nullptr, nullptr, static_cast<hipStream_t>(stream));
     else
         e = launch_unpack_o_proj(recv, w_o, out, d_model, s, nullptr, nullptr, workspace, workspace_bytes, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? SHIFTATTN_OK : hip_fail(e, "unpack_o_proj launch");
@@ -456,7 +456,7 @@ int shiftattn_qkv_proj_pack_fp8_ws(const void* x_codes, const float* x_scales, c
     const int n_feat = (s.h + 2 * s.h_kv) * 128;
     hipError_t e;
     if (s.T > 0 && !force_generic() && proj_stream_takes(s.T_pad, n_feat, d_model, true, workspace_bytes))
-        e = launch_qkv_proj_stream(x_codes, w_codes, send, d_model, s, x_scales, w_scales, workspace, static_cast<hipStream_t>(stream));
+        e = launch_qkv_proj_stream(x_codes, w_codes, send, d_model, s, x_scales, w_scales, static_cast<hipStream_t>(stream));
     else
         e = launch_qkv_proj_pack(x_codes, w_codes, send, d_model, s, x_scales, w_scales, force_generic() ? nullptr : workspace,
                                  workspace_bytes, static_cast<hipStream_t>(stream));
@@ -486,7 +486,7 @@ int shiftattn_unpack_o_proj_fp8_ws(const void* recv_codes, const float* a_scales
     if (int rc = ensure_device_ready()) return rc;
     hipError_t e;
     if (!force_generic() && proj_stream_takes(s.T, d_model, s.h * 128, true, workspace_bytes))
-        e = launch_o_proj_stream(recv_codes, w_codes, out, d_model, s, a_scales, w_scales, workspace, static_cast<hipStream_t>(stream));
+        e = launch_o_proj_stream(recv_codes, w_codes, out, d_model, s, a_scales, w_scales, static_cast<hipStream_t>(stream));
     else
         e = launch_unpack_o_proj(recv_codes, w_codes, out, d_model, s, a_scales, w_scales, force_generic() ? nullptr : workspace,
                                  workspace_bytes, static_cast<hipStream_t>(stream));

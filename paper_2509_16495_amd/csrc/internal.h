@@ -212,9 +212,9 @@ bool proj_stream_takes(int M_out, int N, int K, bool fp8, size_t workspace_bytes
 // the workspace that the size query names (shiftattn_proj_workspace_bytes)
 size_t proj_workspace(int M_out, int N, int K, bool fp8);
 hipError_t launch_qkv_proj_stream(const void* x, const void* w_qkv, void* send, int d_model, const XchgShape& s,
-                                  const float* x_scales, const float* w_scales, void* workspace, hipStream_t st);
+                                  const float* x_scales, const float* w_scales, hipStream_t st);
 hipError_t launch_o_proj_stream(const void* recv, const void* w_o, void* out, int d_model, const XchgShape& s,
-                                const float* a_scales, const float* w_scales, void* workspace, hipStream_t st);
+                                const float* a_scales, const float* w_scales, hipStream_t st);
 // (row_base: the partial results start at this token row of the result; rows below it are not touched)
 hipError_t launch_proj_finish(const float* partial, int kg, int t_rows, void* c, int M, int M_out, int N, int mode,
                               const XchgShape& s, const float* x_scales, const float* w_scales, hipStream_t st,

@@ -1,0 +1,76 @@
+"""The projections of up to 64 token rows at the edges of the weight-streaming kernel against the CPU float64 oracle: every number
+of token pieces (8 rows each) and weight pieces (8 features each) of a workgroup, ragged ones of both, more features than one round of
+the chip takes, and k of fewer steps than wavefronts, of a number of steps that eight does not divide, and beyond one pass of the ring.
+Tolerance as for all bf16 projections: one rounding of the result (2^-8 |ref|) and the fp32 sums (1e-3 sqrt(K) covers them for
+standard normal operands); FP8 operands are exact products of the codes, so the same holds for them."""
+import numpy as np
+import pytest
+
+from paper_2509_16495_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # P, h, h_kv, d_model, T, T_pad
+    (1, 2, 1, 256, 1, 1),          # 512 features, 4 per workgroup; 4 (FP8: 2) steps of k for eight wavefronts
+    (2, 4, 2, 768, 9, 12),         # 12 (6) steps; two token pieces, the second ragged, padding rows
+    (8, 8, 8, 1280, 17, 17),       # three token pieces; 20 (10) steps
+    (8, 32, 8, 4096, 24, 25),      # 24 and 16 features per workgroup; padding row opens the fourth token piece
+    (8, 40, 8, 5120, 31, 32),      # 28 and 20 features per workgroup: ragged weight pieces
+    (8, 64, 8, 1024, 33, 33),      # 40 features per workgroup; five token pieces run as six
+    (8, 64, 8, 4096, 49, 56),      # 13 pieces a step: four wavefronts
+    (1, 64, 8, 512, 64, 64),       # dense rows, one rank
+    (8, 120, 8, 768, 40, 41),      # 17408 features: two rounds of the chip
+]
+
+
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("P,h,h_kv,d_model,T,T_pad", CASES)
+def test_stream_kernel_edges(oracle, P, h, h_kv, d_model, T, T_pad, fp8):
+    import torch
+    import gpu_backend as G
+    from paper_2509_16495_amd import binding as B
+    rng = np.random.Generator(np.random.PCG64(977))
+    D, N, K = 128, (h + 2 * h_kv) * 128, h * 128
+
+    def bf16(shape):
+        return W.f32_to_bf16_bits(rng.standard_normal(shape, dtype=np.float32))
+
+    x, w_qkv, recv, w_o = bf16((T, d_model)), bf16((N, d_model)), bf16((P, T_pad, h // P, D)), bf16((d_model, K))
+    dev = {n: G.t(a, "bf16") for n, a in (("x", x), ("wq", w_qkv), ("recv", recv), ("wo", w_o))}
+    send = torch.empty((P, T_pad, h // P + 2 * B.local_kv_heads(P, h_kv), D), dtype=torch.bfloat16, device=G.DEV)
+    out = torch.empty((T, d_model), dtype=torch.bfloat16, device=G.DEV)
+    send.view(torch.uint8).fill_(0x55)
+    out.view(torch.uint8).fill_(0x55)
+    if fp8:
+        def quantised(a):
+            codes = torch.empty(a.shape, dtype=torch.uint8, device=G.DEV)
+            scales = torch.empty(a.shape[0], dtype=torch.float32, device=G.DEV)
+            B.quantize_rows_fp8(a, codes, scales)
+            return codes, scales
+        (xc, xs), (wqc, wqs), (woc, wos) = quantised(dev["x"]), quantised(dev["wq"]), quantised(dev["wo"])
+        rc, rs = torch.zeros(dev["recv"].shape, dtype=torch.uint8, device=G.DEV), torch.empty(T, dtype=torch.float32, device=G.DEV)
+        B.quantize_recv_fp8(dev["recv"], rc, rs)
+        B.qkv_proj_pack_fp8(xc, xs, wqc, wqs, send, P, h, h_kv)
+        B.unpack_o_proj_fp8(rc, rs, woc, wos, out)
+        f64 = lambda c: c.view(torch.float8_e4m3fn).to(torch.float64).cpu()   # noqa: E731
+        X, WQ, WO = (f64(c) * s.double().cpu()[:, None] for c, s in ((xc, xs), (wqc, wqs), (woc, wos)))
+        R = f64(rc)[:, :T].permute(1, 0, 2, 3).reshape(T, K) * rs.double().cpu()[:, None]
+        qkv, want_out = (X @ WQ.T).view(T, h + 2 * h_kv, D).numpy(), (R @ WO.T).numpy()
+        hl, kl = h // P, B.local_kv_heads(P, h_kv)
+        want_send = np.zeros((P, T_pad, hl + 2 * kl, D))
+        for p in range(P):
+            g = p * h_kv // P
+            want_send[p, :T] = np.concatenate([qkv[:, p * hl:(p + 1) * hl], qkv[:, h + g:h + g + kl], qkv[:, h + h_kv + g:h + h_kv + g + kl]], axis=1)
+    else:
+        B.qkv_proj_pack(dev["x"], dev["wq"], send, P, h, h_kv)
+        B.unpack_o_proj(dev["recv"], dev["wo"], out)
+        want_send = oracle.qkv_proj_pack(x, w_qkv, P, h, h_kv, D, T_pad, "bf16")
+        want_out = oracle.unpack_o_proj(recv, w_o, T, "bf16")
+    torch.cuda.synchronize()
+    for got, want, k in ((send, want_send, d_model), (out, want_out, K)):
+        got = W.to_f64(B.to_host(got), "bf16")
+        assert np.all(np.isfinite(got))
+        err = np.abs(got - want)
+        assert np.all(err <= 2.0 ** -8 * np.abs(want) + 1e-3 * np.sqrt(k)), float(err.max())
+    assert not np.any(B.to_host(send)[:, T:])
