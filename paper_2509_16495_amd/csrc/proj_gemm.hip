@@ -395,8 +395,9 @@ __device__ __attribute__((always_inline)) void proj_gemm_tile(const GemmParams& 
         mfma_settle();
     } else {
         // v_mfma_scale_f32_16x16x128_f8f6f4 with unit block scales: a stage (128 bytes of a row) is one MFMA k step,
-        // 64 MFMAs of 32 clocks; lane -> row lane % 16 of a 16-row tile, pieces 2 (lane / 16) and 2 (lane / 16) + 1 of
-        // its row (which k a lane holds does not matter as long as both operands agree).  Registers hold the eight token
+        // 64 MFMAs of 32 clocks; lane -> row lane % 16 of a 16-row tile, pieces lane / 16 and 4 + lane / 16 of its row (which
+        // k a lane holds does not matter as long as both operands agree; with pieces 2 (lane / 16) and the next one, every read met
+        // two lanes of the sixteen that LDS serves at a time on the same banks).  Registers hold the eight token
         // tiles of the stage (b, 64 registers) and eight weight tiles (a, 64): rows i = 0..3 of the MFMA grid fetch
         // weight tiles 4..7 of the stage, the workgroup meets in front of row 4 (all of the stage's operands are in
         // registers or on their way, the next stage has landed), rows 4..7 fetch weight tiles 0..3 of the next stage and
@@ -405,7 +406,7 @@ __device__ __attribute__((always_inline)) void proj_gemm_tile(const GemmParams& 
         const int r16 = lane & 15, kg = lane >> 4;
         int rd[2];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) rd[h] = r16 * kRowBytes + (((2 * kg + h) ^ ((r16 >> 1) & 7)) << 4);
+        for (int h = 0; h < 2; ++h) rd[h] = r16 * kRowBytes + (((4 * h + kg) ^ ((r16 >> 1) & 7)) << 4);
         i32x8 a[kAT], b[kBT];
         int unit_scale;   // E8M0 code of 1.0, in a vector register as the instruction wants it
         asm volatile("v_mov_b32 %0, 127" : "=v"(unit_scale));
@@ -440,11 +441,11 @@ __device__ __attribute__((always_inline)) void proj_gemm_tile(const GemmParams& 
             asm volatile("s_nop 4" ::: "memory");   // (accumulator moves between two copies of this body, see above)
             if (kLoadMode == 0 && ragged && st == k_steps - 1) {
                 // a half-filled last stage: the upper 64 bytes of its rows repeat the lower ones (see the loads); the
-                // lanes that hold them multiply by zero
+                // second pieces, which lie there, are multiplied by zero
 #pragma unroll
                 for (int j = 0; j < kBT; ++j)
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) b[j][e] = kg >= 2 ? 0 : b[j][e];
+                    for (int e = 4; e < 8; ++e) b[j][e] = 0;
                 asm volatile("s_nop 4" ::: "memory");
             }
             [&]<int... I>(std::integer_sequence<int, I...>) {

@@ -191,12 +191,12 @@ __global__ __launch_bounds__((64 * stream_waves<UX, UW>())) void proj_stream_ker
     for (int g = 0; g < kRing; ++g)
         if (g < n) request();
 
-    // operand reads: row l16 of a tile of 16, piece 4 kb + grp (bf16: k group grp of k block kb) or 2 grp + kb (FP8: the halves of
-    // the lane's 32 k) at position piece ^ key(row); a tile of one piece reads its eight rows twice
+    // operand reads: row l16 of a tile of 16, piece 4 kb + grp (FP8: two of a lane's k halves, in the same order for both
+    // operands) at position piece ^ key(row); a tile of one piece reads its eight rows twice
     int rd[2], rd_half[2];
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
-        const int piece = kFp8 ? 2 * grp + kb : 4 * kb + grp;
+        const int piece = 4 * kb + grp;
         rd[kb] = l16 * kStepRowBytes + ((piece ^ (l16 >> 1)) << 4);
         rd_half[kb] = (l16 & 7) * kStepRowBytes + ((piece ^ ((l16 & 7) >> 1)) << 4);
     }
