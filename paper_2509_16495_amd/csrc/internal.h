@@ -207,7 +207,7 @@ hipError_t launch_unpack_o_proj(const void* recv, const void* w_o, void* out, in
 size_t proj_gemm_workspace(int M_out, int N, int K, bool fp8);
 // what the large-batch kernel is expected to take with a workspace of this size, in microseconds
 double proj_gemm_us(int M_out, int N, int K, bool fp8, size_t workspace_bytes);
-// proj_stream.hip : the same two products for up to 64 token rows, organised around one pass over the weights
+// proj_stream.hip : the same two products for few token rows, organised around one pass over the weights
 bool proj_stream_takes(int M_out, int N, int K, bool fp8, size_t workspace_bytes);
 // the workspace that the size query names (shiftattn_proj_workspace_bytes)
 size_t proj_workspace(int M_out, int N, int K, bool fp8);

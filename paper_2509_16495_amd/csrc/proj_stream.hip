@@ -1,5 +1,5 @@
 // The two projections next to the exchange (Algorithm 1: qkv = embed * W_qkv, embed = attn_o * W_o) for the few
-// tokens of a decode step (Algorithm 2, the small-batch side of the threshold).  With up to 64 token rows the product
+// tokens of a decode step (Algorithm 2, the small-batch side of the threshold).  With few token rows the product
 // is bound by reading the weight matrix once from HBM, not by the matrix cores, so the kernel is organised around
 // that stream:
 //
@@ -7,7 +7,7 @@
 //     compute unit reads the same number of weight bytes; more than 40 features each: several rounds);
 //   * the eight wavefronts of a workgroup split k.  A wavefront multiplies all features of the block in one walk over its
 //     slice: per step of 128 bytes of k (64 bf16 or 128 FP8 elements) it fetches UX pieces of eight token rows and UW
-//     pieces of eight weight rows, and holds the sums of all (token, feature) pairs in at most 48 registers.  The token
+//     pieces of eight weight rows, and holds the sums of all (token, feature) pairs in registers (up to 32 rows at most 24, 128 rows 96).  The token
 //     rows arrive with the weights they meet, so there is no limit on k and nothing to finish in a second launch;
 //   * both arrive by direct-to-LDS loads (1 KiB per instruction: eight rows x 128 bytes, whole cache lines; weights
 //     marked non-temporal: they are used once, the token rows by every workgroup) into a ring private to the wavefront -
@@ -282,7 +282,8 @@ constexpr int stream_lds() { return stream_waves<UX, UW>() * stream_steps<UX, UW
 #define SHIFTATTN_STREAM_SHAPES(X) \
     X(1, 1) X(1, 2) X(1, 3) X(1, 4) X(1, 5) X(2, 1) X(2, 2) X(2, 3) X(2, 4) X(2, 5) \
     X(3, 1) X(3, 2) X(3, 3) X(3, 4) X(3, 5) X(4, 1) X(4, 2) X(4, 3) X(4, 4) X(4, 5) \
-    X(6, 1) X(6, 2) X(6, 3) X(6, 4) X(6, 5) X(8, 1) X(8, 2) X(8, 3) X(8, 4) X(8, 5)
+    X(6, 1) X(6, 2) X(6, 3) X(6, 4) X(6, 5) X(8, 1) X(8, 2) X(8, 3) X(8, 4) X(8, 5) \
+    X(12, 1) X(12, 2) X(12, 3) X(12, 4) X(12, 5) X(16, 1) X(16, 2) X(16, 3) X(16, 4)
 
 // features per workgroup: the chip's compute units read equally many bytes, in as many rounds of at most 40 features as it takes
 int stream_rows(int N) {
@@ -292,7 +293,7 @@ int stream_rows(int N) {
 
 hipError_t run_stream(StreamParams p, hipStream_t st) {
     p.rows_per_block = stream_rows(p.N);
-    const int octets = (p.M_out + 7) / 8, ux = octets <= 4 ? octets : (octets + 1) / 2 * 2, uw = (p.rows_per_block + 7) / 8;
+    const int octets = (p.M_out + 7) / 8, ux = octets <= 4 ? octets : octets <= 8 ? (octets + 1) / 2 * 2 : (octets + 3) / 4 * 4, uw = (p.rows_per_block + 7) / 8;
     const unsigned grid = (p.N + p.rows_per_block - 1) / p.rows_per_block;
 #define SHIFTATTN_STREAM_LAUNCH(ux_, uw_)                                                                   \
     if (ux == ux_ && uw == uw_) {                                                                         \
@@ -377,18 +378,22 @@ hipError_t proj_stream_init() {
     return e;
 }
 
-// Served: up to 64 token rows, and expected to be no slower than the large-batch kernel with its small tiles and k ranges.
+// Served: up to 128 token rows, and expected to be no slower than the large-batch kernel with its small tiles and k ranges.
 // That kernel shares the weights among all of a tile's token rows, so it can win from 33 rows on; every block of features reads all token rows
 // here.  Up to 32 rows, with rows of at most 8 KiB (4096 bf16 or 8192 FP8 elements), or without the workspace that the large-batch
 // kernel's k ranges want, this one is faster throughout (bf16, 64 rows: 6144 x 4096 16.7 against 21.4 us, 5120 x 2048
 // 11.3 / 17.3, 1024-long rows 7.2 / 10.6; FP8 codes 8192 x 8192 18.0 / 23.1, 5120 x 8192 15.5 / 15.5).  Longer rows: 10240 x 8192 wins at 64 rows (35.9 / 37.7;
 // 10240 x 5120 27.6 / 27.7), 8192 x 8192 up to 40 (26.2 / 26.3; 48 rows 27.5 / 26.6), 5120 x 5120 at none (40 rows 16.3 / 15.5),
-// 1280 x 8192 at none (33 rows 14.4 / 14.1): the line is fitted through these.
+// 1280 x 8192 at none (33 rows 14.4 / 14.1): the line is fitted through these.  65 to 128 rows, this kernel / that one: FP8 codes
+// 6144 x 4096, 96 / 128 rows 12.6 / 17.0, 14.7 / 18.6; 10240 x 5120 19.8 / 23.3, 25.4 / 25.5; 1280 x 5120 11.9 / 12.5, 13.8 / 13.6;
+// 8192 x 8192 21.7 / 21.5; bf16 8192 x 1024 8.2 / 11.0, 9.4 / 11.2; 5120 x 2048 14.4 / 15.3, 16.9 / 16.6; 2048 x 4096 15.1 / 13.9.
 bool proj_stream_takes(int M_out, int N, int K, bool fp8, size_t workspace_bytes) {
     const int elem = fp8 ? 1 : 2;
-    if (M_out < 1 || M_out > 64 || N % 4 != 0 || K % (kStepRowBytes / elem) != 0) return false;
-    if (M_out <= 32 || static_cast<int64_t>(K) * elem <= 8192 || M_out <= (N - 4096) / 96) return true;
-    return proj_gemm_us(M_out, N, K, fp8, workspace_bytes) > 1.1 * proj_gemm_us(M_out, N, K, fp8, SIZE_MAX);
+    if (M_out < 1 || M_out > 128 || N % 4 != 0 || K % (kStepRowBytes / elem) != 0) return false;
+    const int64_t k_bytes = static_cast<int64_t>(K) * elem;
+    if (M_out > 64) return M_out <= 96 ? k_bytes <= (fp8 ? 5120 : 4096) : k_bytes <= (fp8 ? 4096 : 2048) && stream_rows(N) <= 32;
+    if (M_out <= 32 || k_bytes <= 8192 || M_out <= (N - 4096) / 96) return true;
+    return proj_gemm_us(M_out, N, K, fp8, workspace_bytes) > 1.4 * proj_gemm_us(M_out, N, K, fp8, SIZE_MAX);
 }
 
 // What the size query names: for up to 64 rows whose k divides by that of eight wavefronts' steps, k groups x token rows x features in

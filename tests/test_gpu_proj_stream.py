@@ -1,4 +1,4 @@
-"""The projections of up to 64 token rows at the edges of the weight-streaming kernel against the CPU float64 oracle: every number
+"""The projections of up to 128 token rows at the edges of the weight-streaming kernel against the CPU float64 oracle: every number
 of token pieces (8 rows each) and weight pieces (8 features each) of a workgroup, ragged ones of both, more features than one round of
 the chip takes, and k of fewer steps than wavefronts, of a number of steps that eight does not divide, and beyond one pass of the ring.
 Tolerance as for all bf16 projections: one rounding of the result (2^-8 |ref|) and the fp32 sums (1e-3 sqrt(K) covers them for
@@ -21,6 +21,10 @@ CASES = [
     (8, 64, 8, 4096, 49, 56),      # 13 pieces a step: four wavefronts
     (1, 64, 8, 512, 64, 64),       # dense rows, one rank
     (8, 120, 8, 768, 40, 41),      # 17408 features: two rounds of the chip
+    (1, 8, 1, 1024, 65, 65),       # twelve token pieces, three of them without a row of their own
+    (8, 16, 8, 2048, 96, 96),      # 16 features per workgroup
+    (2, 8, 2, 768, 97, 103),       # sixteen token pieces, the padding rows open the thirteenth
+    (4, 8, 8, 1024, 128, 128),     # 12 features per workgroup: a ragged weight piece under sixteen token pieces
 ]
 
 
