@@ -393,7 +393,7 @@ bool proj_stream_takes(int M_out, int N, int K, bool fp8, size_t workspace_bytes
     const int64_t k_bytes = static_cast<int64_t>(K) * elem;
     if (M_out > 64) return M_out <= 96 ? k_bytes <= (fp8 ? 5120 : 4096) : k_bytes <= (fp8 ? 4096 : 2048) && stream_rows(N) <= 32;
     if (M_out <= 32 || k_bytes <= 8192 || M_out <= (N - 4096) / 96) return true;
-    return proj_gemm_us(M_out, N, K, fp8, workspace_bytes) > 1.4 * proj_gemm_us(M_out, N, K, fp8, SIZE_MAX);
+    return proj_gemm_us(M_out, N, K, fp8, workspace_bytes) > 1.1 * proj_gemm_us(M_out, N, K, fp8, SIZE_MAX);
 }
 
 // What the size query names: for up to 64 rows whose k divides by that of eight wavefronts' steps, k groups x token rows x features in
