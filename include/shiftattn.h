@@ -157,18 +157,17 @@ int shiftattn_unpack_o_proj(const void *recv, const void *w_o, void *out, int32_
                             int32_t d_model, const shiftattn_xchg *xc, void *stream);
 
 /* ---- The same two projections with a workspace (Algorithm 2: the few-token steps below the threshold) ----
- * With few token rows (T_pad for qkv_proj_pack, T for unpack_o_proj: up to 8, and up to 64 where it is expected to be
- * the faster way) the product is one pass over the weight matrix; from 17 rows on (at d_model = 8192) that pass is split
- * over k between workgroups.  With a few
- * hundred rows the large-batch kernel has too few output tiles to fill the chip and splits k as well, and with
+ * With few token rows (T_pad for qkv_proj_pack, T for unpack_o_proj: up to 32, and up to 128 where it is expected to be
+ * the faster way) the product is one pass over the weight matrix, which needs no workspace.  With a few
+ * hundred rows the large-batch kernel has too few output tiles to fill the chip and splits k, and with
  * a few thousand (a prefill chunk) it does so for the last token rows when the tiles are no multiple of the
- * chip's compute units.  Either way the fp32 partial results need device memory:
+ * chip's compute units.  The fp32 partial results need device memory:
  *   shiftattn_proj_workspace_bytes(rows, n_features, k): bytes for a product of `rows` token rows with a
  *     [n_features][k] weight matrix (qkv: n_features = (h + 2 h_kv) * D, k = d_model; o: n_features =
  *     d_model, k = h * D); 0 when none is needed.
  * workspace (device, scratch): at least that many bytes, 16-byte aligned; NULL / 0 is always accepted and
- *   means "use a kernel that needs none" (the calls above do exactly that) - between 17 rows and a few
- *   hundred that is up to several times slower.  Calls that share a workspace must not overlap.
+ *   means "use a kernel that needs none" (the calls above do exactly that) - between 33 rows and a few
+ *   hundred that can be several times slower.  Calls that share a workspace must not overlap.
  * Results are bitwise reproducible with and without a workspace, not bitwise equal between the two. */
 size_t shiftattn_proj_workspace_bytes(int32_t rows, int32_t n_features, int32_t k);
 int shiftattn_qkv_proj_pack_ws(const void *x, const void *w_qkv, void *send, int32_t T, int32_t T_pad,
@@ -204,9 +203,8 @@ int shiftattn_qkv_proj_pack_fp8(const void *x_codes, const float *x_scales, cons
 int shiftattn_unpack_o_proj_fp8(const void *recv_codes, const float *a_scales, const void *w_codes,
                                 const float *w_scales, void *out, int32_t T, int32_t T_pad, int32_t d_model,
                                 const shiftattn_xchg *xc, void *stream);
-/* The FP8 projections with a workspace, as the bf16 forms above: up to 64 token rows are one pass over the weight
- * codes (k groups, and with them a workspace, from 33 rows on at d_model = 8192), a few hundred rows split k over
- * workgroups; the scales are applied once, after the fp32 sums of all of k are added.
+/* The FP8 projections with a workspace, as the bf16 forms above: up to 64 token rows (128 with short rows of
+ * weights) are one pass over the weight codes, a few hundred rows split k over workgroups; the scales are applied once, after the fp32 sums of all of k are added.
  * shiftattn_proj_workspace_bytes_fp8: the size for FP8 operands (it differs from the bf16 size). */
 size_t shiftattn_proj_workspace_bytes_fp8(int32_t rows, int32_t n_features, int32_t k);
 int shiftattn_qkv_proj_pack_fp8_ws(const void *x_codes, const float *x_scales, const void *w_codes,

@@ -5,10 +5,11 @@
 //
 //   * 256 workgroups, one per compute unit, each owning a contiguous block of output features (N / 256 rows, so every
 //     compute unit reads the same number of weight bytes; more than 40 features each: several rounds);
-//   * the eight wavefronts of a workgroup split k.  A wavefront multiplies all features of the block in one walk over its
-//     slice: per step of 128 bytes of k (64 bf16 or 128 FP8 elements) it fetches UX pieces of eight token rows and UW
-//     pieces of eight weight rows, and holds the sums of all (token, feature) pairs in registers (up to 32 rows at most 24, 128 rows 96).  The token
-//     rows arrive with the weights they meet, so there is no limit on k and nothing to finish in a second launch;
+//   * the eight wavefronts of a workgroup (four where a step is large) split k.  A wavefront multiplies all features of the
+//     block in one walk over its slice: per step of 128 bytes of k (64 bf16 or 128 FP8 elements) it fetches UX pieces of
+//     eight token rows and UW pieces of eight weight rows, and holds the sums of all (token, feature) pairs in registers (at
+//     most 24 up to 32 rows, 96 at 128 rows).  The token rows arrive with the weights they meet, so there is no limit on k
+//     and nothing to finish in a second launch;
 //   * both arrive by direct-to-LDS loads (1 KiB per instruction: eight rows x 128 bytes, whole cache lines; weights
 //     marked non-temporal: they are used once, the token rows by every workgroup) into a ring private to the wavefront -
 //     no workgroup barrier in the stream, a wavefront waits for its own loads by count - and are read back as MFMA
@@ -24,8 +25,10 @@
 // this one): 10240 x 8192 bf16, 1 / 16 / 19 / 32 rows 27.2 / 32.4 / 33.8 / 36.9 -> 27.0 / 26.7 / 27.0 / 29.0 (168 MB: 6.3
 // TB/s at 16 rows); 5120 x 2048 9.1 / 10.2 / 10.8 / 12.3 -> 6.7 / 7.3 / 7.6 / 8.0; FP8 codes, 10240 x 8192 16.1 / 18.3 / 19.8 / 22.4 ->
 // 15.0 / 15.1 / 15.4 / 16.4, 64 rows 26.1 -> 20.8.
-// What is left over the weights' pass at the read probe's 6.9 TB/s: launch, first round trip and the meeting (about 3 us), and with many
-// rows the token rows themselves (rows a power of two apart come from few L2 channels: about 0.1 us per row at k = 8192).
+// What is left over the weights' pass at the read probe's 6.9 TB/s: launch, first round trip and the meeting (about 3 us), and
+// with many rows the token rows, which every workgroup reads whole (about 0.1 us per row at k = 8192).  Tried and not kept: as
+// many wavefronts as hold two steps each (16 at most; small products 2 to 20 % slower), weights requested further ahead than
+// the token rows in what is left of the LDS (within 2 %), at least 16 features a workgroup (up to 17 % slower).
 #include "internal.h"
 
 namespace shiftattn {
@@ -38,7 +41,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 
-constexpr int kSWaves = 8;                         // wavefronts the size query counts with
+constexpr int kSWaves = 8;                         // wavefronts that the size query counts with
 constexpr int kSGrid = 256;                        // workgroups: one per compute unit
 constexpr int kStepRowBytes = 128;                 // bytes of a weight row per step of a wavefront: 64 bf16 or 128 FP8 k
 constexpr int kRotSteps = 3;                       // steps of k between the starts of neighbouring blocks
@@ -48,7 +51,7 @@ constexpr int kHeadDim = 128;
 struct StreamParams {
     const unsigned char* __restrict__ w;   // [N][K] bf16 or FP8 E4M3 codes
     const unsigned char* __restrict__ x;   // token rows, see mode
-    uint16_t* __restrict__ c;              // bf16 result (kg == 1)
+    uint16_t* __restrict__ c;              // bf16 result
     const float* __restrict__ partial;     // finishing kernel: [kg][rows][N] fp32
     const float* __restrict__ xs;          // FP8 products: one scale per token row ...
     const float* __restrict__ ws;          // ... and one per output feature (nullptr: none)
@@ -293,7 +296,8 @@ int stream_rows(int N) {
 
 hipError_t run_stream(StreamParams p, hipStream_t st) {
     p.rows_per_block = stream_rows(p.N);
-    const int octets = (p.M_out + 7) / 8, ux = octets <= 4 ? octets : octets <= 8 ? (octets + 1) / 2 * 2 : (octets + 3) / 4 * 4, uw = (p.rows_per_block + 7) / 8;
+    const int octets = (p.M_out + 7) / 8, uw = (p.rows_per_block + 7) / 8;
+    const int ux = octets <= 4 ? octets : octets <= 8 ? (octets + 1) / 2 * 2 : (octets + 3) / 4 * 4;
     const unsigned grid = (p.N + p.rows_per_block - 1) / p.rows_per_block;
 #define SHIFTATTN_STREAM_LAUNCH(ux_, uw_)                                                                   \
     if (ux == ux_ && uw == uw_) {                                                                         \
@@ -379,14 +383,17 @@ hipError_t proj_stream_init() {
 }
 
 // Served: up to 128 token rows, and expected to be no slower than the large-batch kernel with its small tiles and k ranges.
-// That kernel shares the weights among all of a tile's token rows, so it can win from 33 rows on; every block of features reads all token rows
-// here.  Up to 32 rows, with rows of at most 8 KiB (4096 bf16 or 8192 FP8 elements), or without the workspace that the large-batch
-// kernel's k ranges want, this one is faster throughout (bf16, 64 rows: 6144 x 4096 16.7 against 21.4 us, 5120 x 2048
-// 11.3 / 17.3, 1024-long rows 7.2 / 10.6; FP8 codes 8192 x 8192 18.0 / 23.1, 5120 x 8192 15.5 / 15.5).  Longer rows: 10240 x 8192 wins at 64 rows (35.9 / 37.7;
-// 10240 x 5120 27.6 / 27.7), 8192 x 8192 up to 40 (26.2 / 26.3; 48 rows 27.5 / 26.6), 5120 x 5120 at none (40 rows 16.3 / 15.5),
-// 1280 x 8192 at none (33 rows 14.4 / 14.1): the line is fitted through these.  65 to 128 rows, this kernel / that one: FP8 codes
-// 6144 x 4096, 96 / 128 rows 12.6 / 17.0, 14.7 / 18.6; 10240 x 5120 19.8 / 23.3, 25.4 / 25.5; 1280 x 5120 11.9 / 12.5, 13.8 / 13.6;
-// 8192 x 8192 21.7 / 21.5; bf16 8192 x 1024 8.2 / 11.0, 9.4 / 11.2; 5120 x 2048 14.4 / 15.3, 16.9 / 16.6; 2048 x 4096 15.1 / 13.9.
+// That kernel shares the weights among all of a tile's token rows, so it can win from 33 rows on; every block of features
+// reads all token rows here.  Measured, us, this kernel / that one:
+//   * up to 32 rows, or up to 64 with rows of at most 8 KiB (4096 bf16 or 8192 FP8 elements), this one throughout: bf16, 64
+//     rows, 6144 x 4096 16.7 / 21.4, 5120 x 2048 11.3 / 17.3, 8192 x 1024 7.2 / 10.6; FP8 8192 x 8192 18.0 / 23.1;
+//   * 33 to 64 longer rows: 10240 x 8192, 64 rows 35.9 / 37.7, 10240 x 5120 27.6 / 27.7; 8192 x 8192, 40 / 48 rows
+//     26.2 / 26.3, 27.5 / 26.6; 5120 x 5120, 40 rows 16.3 / 15.5; 1280 x 5120, 40 rows 12.0 / 11.5: the line in N is drawn
+//     through these.  Without the workspace that its k ranges want that kernel is several times slower, with a short one slower:
+//     1280 x 8192, 48 rows, where the query names a quarter of what it wants, 16.4 / 17.9;
+//   * 65 to 128 rows: FP8 6144 x 4096, 96 / 128 rows 12.6 / 17.0, 14.7 / 18.6; 10240 x 5120 19.8 / 23.3, 25.4 / 25.5;
+//     1280 x 5120 11.9 / 12.5, 13.8 / 13.6; 8192 x 8192 21.7 / 21.5; bf16 8192 x 1024 8.2 / 11.0, 9.4 / 11.2; 5120 x 2048
+//     14.4 / 15.3, 16.9 / 16.6; 2048 x 4096 15.1 / 13.9.  (More than 32 features a workgroup and 96 rows: a ring of one step.)
 bool proj_stream_takes(int M_out, int N, int K, bool fp8, size_t workspace_bytes) {
     const int elem = fp8 ? 1 : 2;
     if (M_out < 1 || M_out > 128 || N % 4 != 0 || K % (kStepRowBytes / elem) != 0) return false;
@@ -396,9 +403,9 @@ bool proj_stream_takes(int M_out, int N, int K, bool fp8, size_t workspace_bytes
     return proj_gemm_us(M_out, N, K, fp8, workspace_bytes) > 1.1 * proj_gemm_us(M_out, N, K, fp8, SIZE_MAX);
 }
 
-// What the size query names: for up to 64 rows whose k divides by that of eight wavefronts' steps, k groups x token rows x features in
-// fp32, more than any plan for them takes; else the large-batch kernel's plan.  (Callers allocate by it and tests pin it, see
-// proj_gemm_workspace(); which kernel runs is decided per call by what fits.)
+// What the size query names: for up to 64 rows whose k divides by that of eight wavefronts' steps, room for k ranges of token rows x
+// features in fp32, which the large-batch kernel uses where it takes such a call; else what its own plan wants.  (Callers allocate by
+// it and tests pin it, see proj_gemm_workspace(); which kernel runs is decided per call by what fits.)
 size_t proj_workspace(int M_out, int N, int K, bool fp8) {
     const int per_step = kSWaves * kStepRowBytes / (fp8 ? 1 : 2);
     if (M_out <= 64 && N % 4 == 0 && K % per_step == 0) {
