@@ -44,6 +44,7 @@ typedef int i32x8 __attribute__((ext_vector_type(8)));
 constexpr int kSWaves = 8;                         // wavefronts that the size query counts with
 constexpr int kSGrid = 256;                        // workgroups: one per compute unit
 constexpr int kStepRowBytes = 128;                 // bytes of a weight row per step of a wavefront: 64 bf16 or 128 FP8 k
+constexpr int kMaxRows = 40;                       // features per workgroup at most
 constexpr int kRotSteps = 3;                       // steps of k between the starts of neighbouring blocks
 constexpr int kHeadDim = 128;
 #define SHIFTATTN_STREAM_HINT " nt"   // weights are read once: non-temporal
@@ -288,9 +289,9 @@ constexpr int stream_lds() { return stream_waves<UX, UW>() * stream_steps<UX, UW
     X(6, 1) X(6, 2) X(6, 3) X(6, 4) X(6, 5) X(8, 1) X(8, 2) X(8, 3) X(8, 4) X(8, 5) \
     X(12, 1) X(12, 2) X(12, 3) X(12, 4) X(12, 5) X(16, 1) X(16, 2) X(16, 3) X(16, 4)
 
-// features per workgroup: the chip's compute units read equally many bytes, in as many rounds of at most 40 features as it takes
+// features per workgroup: the chip's compute units read equally many bytes, in as many rounds of at most kMaxRows features as it takes
 int stream_rows(int N) {
-    const int rounds = (N + kSGrid * 40 - 1) / (kSGrid * 40);
+    const int rounds = (N + kSGrid * kMaxRows - 1) / (kSGrid * kMaxRows);
     return ((N + kSGrid * rounds - 1) / (kSGrid * rounds) + 3) / 4 * 4;
 }
 
@@ -385,12 +386,16 @@ hipError_t proj_stream_init() {
 // Served: up to 128 token rows, and expected to be no slower than the large-batch kernel with its small tiles and k ranges.
 // That kernel shares the weights among all of a tile's token rows, so it can win from 33 rows on; every block of features
 // reads all token rows here.  Measured, us, this kernel / that one:
-//   * up to 32 rows, or up to 64 with rows of at most 8 KiB (4096 bf16 or 8192 FP8 elements), this one throughout: bf16, 64
+//   * up to 16 rows, up to 32 but for the sizes of the third point, or up to 64 with rows of at most 8 KiB (4096 bf16 or 8192 FP8 elements), this one throughout: bf16, 64
 //     rows, 6144 x 4096 16.7 / 21.4, 5120 x 2048 11.3 / 17.3, 8192 x 1024 7.2 / 10.6; FP8 8192 x 8192 18.0 / 23.1;
 //   * 33 to 64 longer rows: 10240 x 8192, 64 rows 35.9 / 37.7, 10240 x 5120 27.6 / 27.7; 8192 x 8192, 40 / 48 rows
 //     26.2 / 26.3, 27.5 / 26.6; 5120 x 5120, 40 rows 16.3 / 15.5; 1280 x 5120, 40 rows 12.0 / 11.5: the line in N is drawn
 //     through these.  Without the workspace that its k ranges want that kernel is several times slower, with a short one slower:
 //     1280 x 8192, 48 rows, where the query names a quarter of what it wants, 16.4 / 17.9;
+//   * more features than one round takes, or rows of more than 16 KiB: by a model of both (this one: launch, the weights' pass at
+//     6.4 TB/s, and per round the token rows past the tenth at 66 GB/s a compute unit).  bf16 14336 x 12288, 24 / 32 rows
+//     64.1 / 65.3, 71.1 / 66.1; 18432 x 8192, 32 / 64 rows 54.1 / 63.2, 71.9 / 63.2; 4096 x 15360, 24 rows 29.9 / 27.6; FP8
+//     8192 x 16384, 32 rows 24.5 / 37.6;
 //   * 65 to 128 rows: FP8 6144 x 4096, 96 / 128 rows 12.6 / 17.0, 14.7 / 18.6; 10240 x 5120 19.8 / 23.3, 25.4 / 25.5;
 //     1280 x 5120 11.9 / 12.5, 13.8 / 13.6; 8192 x 8192 21.7 / 21.5; bf16 8192 x 1024 8.2 / 11.0, 9.4 / 11.2; 5120 x 2048
 //     14.4 / 15.3, 16.9 / 16.6; 2048 x 4096 15.1 / 13.9.  (More than 32 features a workgroup and 96 rows: a ring of one step.)
@@ -398,6 +403,11 @@ bool proj_stream_takes(int M_out, int N, int K, bool fp8, size_t workspace_bytes
     const int elem = fp8 ? 1 : 2;
     if (M_out < 1 || M_out > 128 || N % 4 != 0 || K % (kStepRowBytes / elem) != 0) return false;
     const int64_t k_bytes = static_cast<int64_t>(K) * elem;
+    if (M_out > 16 && (N > kSGrid * kMaxRows || k_bytes > 16384)) {
+        const int rounds = (N + kSGrid * kMaxRows - 1) / (kSGrid * kMaxRows);
+        const double us = 3.0 + static_cast<double>(N) * k_bytes / 6.4e6 + static_cast<double>(rounds) * (M_out - 10) * k_bytes / 66e3;
+        return M_out <= 64 && us <= proj_gemm_us(M_out, N, K, fp8, workspace_bytes);
+    }
     if (M_out > 64) return M_out <= 96 ? k_bytes <= (fp8 ? 5120 : 4096) : k_bytes <= (fp8 ? 4096 : 2048) && stream_rows(N) <= 32;
     if (M_out <= 32 || k_bytes <= 8192 || M_out <= (N - 4096) / 96) return true;
     return proj_gemm_us(M_out, N, K, fp8, workspace_bytes) > 1.1 * proj_gemm_us(M_out, N, K, fp8, SIZE_MAX);

@@ -21,6 +21,7 @@ CASES = [
     (8, 64, 8, 4096, 49, 56),      # 13 pieces a step: four wavefronts
     (1, 64, 8, 512, 64, 64),       # dense rows, one rank
     (8, 120, 8, 768, 40, 41),      # 17408 features: two rounds of the chip
+    (8, 120, 8, 768, 12, 12),      # the same, and 15360 k for the output projection: 240 steps
     (1, 8, 1, 1024, 65, 65),       # twelve token pieces, three of them without a row of their own
     (8, 16, 8, 2048, 96, 96),      # 16 features per workgroup
     (2, 8, 2, 768, 97, 103),       # sixteen token pieces, the padding rows open the thirteenth
