@@ -157,7 +157,7 @@ int shiftattn_unpack_o_proj(const void *recv, const void *w_o, void *out, int32_
                             int32_t d_model, const shiftattn_xchg *xc, void *stream);
 
 /* ---- The same two projections with a workspace (Algorithm 2: the few-token steps below the threshold) ----
- * With few token rows (T_pad for qkv_proj_pack, T for unpack_o_proj: up to 32, and up to 128 where it is expected to be
+ * With few token rows (T_pad for qkv_proj_pack, T for unpack_o_proj: up to 16, and up to 128 where it is expected to be
  * the faster way) the product is one pass over the weight matrix, which needs no workspace.  With a few
  * hundred rows the large-batch kernel has too few output tiles to fill the chip and splits k, and with
  * a few thousand (a prefill chunk) it does so for the last token rows when the tiles are no multiple of the
@@ -166,7 +166,7 @@ int shiftattn_unpack_o_proj(const void *recv, const void *w_o, void *out, int32_
  *     [n_features][k] weight matrix (qkv: n_features = (h + 2 h_kv) * D, k = d_model; o: n_features =
  *     d_model, k = h * D); 0 when none is needed.
  * workspace (device, scratch): at least that many bytes, 16-byte aligned; NULL / 0 is always accepted and
- *   means "use a kernel that needs none" (the calls above do exactly that) - between 33 rows and a few
+ *   means "use a kernel that needs none" (the calls above do exactly that) - between 17 rows and a few
  *   hundred that can be several times slower.  Calls that share a workspace must not overlap.
  * Results are bitwise reproducible with and without a workspace, not bitwise equal between the two. */
 size_t shiftattn_proj_workspace_bytes(int32_t rows, int32_t n_features, int32_t k);
