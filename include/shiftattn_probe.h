@@ -1,8 +1,8 @@
 /*
  * shiftattn_probe.h - measurement and test aids exported by libshiftattn.so.
  *
- * Not part of the attention path and not part of the product interface (shiftattn.h): a host query
- * that names the launch a prefill call takes, and, for benchmark reports, four kernels that show what the chip attains on the resources the path's kernels are priced against, to print
+ * Not part of the attention path and not part of the product interface (shiftattn.h): host queries
+ * that name the launch a prefill or projection call takes, and, for benchmark reports, four kernels that show what the chip attains on the resources the path's kernels are priced against, to print
  * beside the datasheet peaks.  Each call validates its arguments, enqueues one kernel on `stream`
  * (a hipStream_t as void*) and returns SHIFTATTN_OK or a negative code of shiftattn.h; the caller
  * times it.  All buffer pointers are device pointers, 16-byte aligned.
@@ -27,6 +27,9 @@
  *   shiftattn_mixed for its chunks, launches for a batch of these sizes with the workspace that its
  *   size query names, under the options as they are set; a test that aims at a kernel can then say so.
  *   Arguments as for shiftattn_mixed_workspace_bytes.
+ * proj_plan: host only, nothing is enqueued.  What a projection of `rows` (>= 1; T_pad for qkv_proj_pack, T for
+ *   unpack_o_proj) token rows with an [n_features][k] weight matrix launches when it is given a workspace of
+ *   workspace_bytes, under the options as they are set.  fp8: the operands are FP8 codes.
  */
 #ifndef SHIFTATTN_PROBE_H
 #define SHIFTATTN_PROBE_H
@@ -51,6 +54,18 @@ typedef struct {
 int shiftattn_prefill_plan(int32_t num_prefill_seqs, int32_t total_prefill_q, int32_t max_q_len, int32_t max_prefill_seq_len,
                            int32_t num_decode_seqs, int32_t max_decode_seq_len, const shiftattn_attn *a,
                            shiftattn_prefill_plan_t *plan);
+
+typedef struct {
+    int32_t streams;          /* 1: the weight-streaming kernel, which takes the call in workgroups of eight or four wavefronts; 0: the tiled kernel */
+    int32_t k_ranges;         /* workgroups that share a block of features or an output tile of the last token rows; 1: no workspace is used */
+    int32_t token_pieces;     /* streaming kernel: pieces of eight token rows and of eight features that a workgroup multiplies */
+    int32_t feature_pieces;
+    int32_t lead_tiles;       /* tiled kernel: token tiles of a launch of their own in front (0: none), and their features x token rows */
+    int32_t lead_features, lead_tokens;
+    int32_t tile_features, tile_tokens;   /* ... and those of the tiles behind them */
+} shiftattn_proj_plan_t;
+
+int shiftattn_proj_plan(int32_t rows, int32_t n_features, int32_t k, int32_t fp8, size_t workspace_bytes, shiftattn_proj_plan_t *plan);
 int shiftattn_ceiling_mfma_bf16(const void *operands, void *sink, int32_t iters, int64_t *flops, void *stream);
 int shiftattn_ceiling_mfma_bf16_fresh(const void *operands, void *sink, int32_t iters, int64_t *flops, void *stream);
 int shiftattn_ceiling_hbm_read(const void *src, size_t bytes, void *sink, int64_t *bytes_read, void *stream);

@@ -50,6 +50,11 @@ class PrefillPlan(ctypes.Structure):
                 ("tiles_per_wg", ctypes.c_int32), ("decode_wgs", ctypes.c_int32)]
 
 
+class ProjPlan(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int32) for n in ("streams", "k_ranges", "token_pieces", "feature_pieces", "lead_tiles", "lead_features",
+                                              "lead_tokens", "tile_features", "tile_tokens")]
+
+
 KV_SAME, KV_FP8_E4M3 = 0, 1
 
 
@@ -193,6 +198,17 @@ def prefill_plan(num_seqs: int, total_q: int, max_q_len: int, max_seq_len: int, 
     query = lib().shiftattn_prefill_plan
     query.argtypes = [ctypes.c_int32] * 6 + [ctypes.POINTER(Attn), ctypes.POINTER(PrefillPlan)]
     _check(query(num_seqs, total_q, max_q_len, max_seq_len, num_decode_seqs, max_decode_seq_len, ctypes.byref(desc), ctypes.byref(plan)))
+    return plan
+
+
+def proj_plan(rows: int, n_features: int, k: int, fp8: bool = False, workspace_bytes: Optional[int] = None) -> ProjPlan:
+    """The launch that a projection of `rows` token rows with an [n_features, k] matrix takes (host only); workspace_bytes
+    None: with the workspace that the size query names."""
+    plan = ProjPlan()
+    query = lib().shiftattn_proj_plan
+    query.argtypes = [ctypes.c_int32] * 4 + [ctypes.c_size_t, ctypes.POINTER(ProjPlan)]
+    given = proj_workspace_bytes(rows, n_features, k, fp8) if workspace_bytes is None else workspace_bytes
+    _check(query(rows, n_features, k, int(fp8), given, ctypes.byref(plan)))
     return plan
 
 

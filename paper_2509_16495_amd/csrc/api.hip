@@ -409,6 +409,19 @@ size_t shiftattn_proj_workspace_bytes_fp8(int32_t rows, int32_t n_features, int3
     return proj_workspace(rows, n_features, k, true);
 }
 
+int shiftattn_proj_plan(int32_t rows, int32_t n_features, int32_t k, int32_t fp8, size_t workspace_bytes, shiftattn_proj_plan_t* plan) {
+    if (!plan) return fail(SHIFTATTN_EINVAL, "a required pointer is NULL");
+    if (rows < 1 || n_features < 1 || k < 1) return fail(SHIFTATTN_EINVAL, "rows = %d, n_features = %d, k = %d", rows, n_features, k);
+    if (n_features % 256 || k % 64) return fail(SHIFTATTN_EUNSUPPORTED, "no projection has n_features = %d, k = %d", n_features, k);
+    if (!force_generic() && proj_stream_takes(rows, n_features, k, fp8 != 0, workspace_bytes)) {
+        if (!proj_stream_describe(rows, n_features, plan))
+            return fail(SHIFTATTN_EUNSUPPORTED, "no kernel is built for rows = %d, n_features = %d", rows, n_features);
+    } else {
+        proj_gemm_describe(rows, n_features, k, fp8 != 0, fp8 && force_generic() ? 0 : workspace_bytes, plan);
+    }
+    return SHIFTATTN_OK;
+}
+
 int shiftattn_quantize_rows_fp8(const void* x, void* codes, float* scales, int32_t rows, int32_t cols, void* stream) {
     if (rows < 0 || cols < 1) return fail(SHIFTATTN_EINVAL, "rows = %d, cols = %d", rows, cols);
     if (cols % 8) return fail(SHIFTATTN_EUNSUPPORTED, "cols = %d is not a multiple of 8", cols);

@@ -209,6 +209,9 @@ size_t proj_gemm_workspace(int M_out, int N, int K, bool fp8);
 double proj_gemm_us(int M_out, int N, int K, bool fp8, size_t workspace_bytes);
 // proj_stream.hip : the same two products for few token rows, organised around one pass over the weights
 bool proj_stream_takes(int M_out, int N, int K, bool fp8, size_t workspace_bytes);
+// what either kernel launches for a call that it takes (host only); false: no such instance of the first one is built
+bool proj_stream_describe(int M_out, int N, shiftattn_proj_plan_t* plan);
+void proj_gemm_describe(int M_out, int N, int K, bool fp8, size_t workspace_bytes, shiftattn_proj_plan_t* plan);
 // the workspace that the size query names (shiftattn_proj_workspace_bytes)
 size_t proj_workspace(int M_out, int N, int K, bool fp8);
 hipError_t launch_qkv_proj_stream(const void* x, const void* w_qkv, void* send, int d_model, const XchgShape& s,

@@ -772,6 +772,12 @@ size_t proj_gemm_workspace(int M_out, int N, int K, bool fp8) {
     return bytes;
 }
 
+void proj_gemm_describe(int M_out, int N, int K, bool fp8, size_t workspace_bytes, shiftattn_proj_plan_t* plan) {
+    const GemmPlan pl = plan_gemm(M_out, N, K, fp8, workspace_bytes);
+    *plan = shiftattn_proj_plan_t{0, pl.splits, 0, 0, pl.lead_tiles, kTileFeatures[pl.lead], kTileTokens[pl.lead],
+                                  kTileFeatures[pl.tail], kTileTokens[pl.tail]};
+}
+
 double proj_gemm_us(int M_out, int N, int K, bool fp8, size_t workspace_bytes) { return plan_gemm(M_out, N, K, fp8, workspace_bytes).us; }
 
 // runs the product in the best way for which the workspace has room

@@ -295,10 +295,25 @@ int stream_rows(int N) {
     return ((N + kSGrid * rounds - 1) / (kSGrid * rounds) + 3) / 4 * 4;
 }
 
+struct StreamShape {
+    int ux, uw;   // pieces of eight token rows and of eight weight rows
+};
+
+StreamShape stream_shape(int M_out, int rows_per_block) {
+    const int octets = (M_out + 7) / 8;
+    return {octets <= 4 ? octets : octets <= 8 ? (octets + 1) / 2 * 2 : (octets + 3) / 4 * 4, (rows_per_block + 7) / 8};
+}
+
+bool stream_built(StreamShape shape) {
+#define SHIFTATTN_STREAM_IS(ux_, uw_) if (shape.ux == ux_ && shape.uw == uw_) return true;
+    SHIFTATTN_STREAM_SHAPES(SHIFTATTN_STREAM_IS)
+#undef SHIFTATTN_STREAM_IS
+    return false;
+}
+
 hipError_t run_stream(StreamParams p, hipStream_t st) {
     p.rows_per_block = stream_rows(p.N);
-    const int octets = (p.M_out + 7) / 8, uw = (p.rows_per_block + 7) / 8;
-    const int ux = octets <= 4 ? octets : octets <= 8 ? (octets + 1) / 2 * 2 : (octets + 3) / 4 * 4;
+    const auto [ux, uw] = stream_shape(p.M_out, p.rows_per_block);
     const unsigned grid = (p.N + p.rows_per_block - 1) / p.rows_per_block;
 #define SHIFTATTN_STREAM_LAUNCH(ux_, uw_)                                                                   \
     if (ux == ux_ && uw == uw_) {                                                                         \
@@ -411,6 +426,13 @@ bool proj_stream_takes(int M_out, int N, int K, bool fp8, size_t workspace_bytes
     if (M_out > 64) return M_out <= 96 ? k_bytes <= (fp8 ? 5120 : 4096) : k_bytes <= (fp8 ? 4096 : 2048) && stream_rows(N) <= 32;
     if (M_out <= 32 || k_bytes <= 8192 || M_out <= (N - 4096) / 96) return true;
     return proj_gemm_us(M_out, N, K, fp8, workspace_bytes) > 1.1 * proj_gemm_us(M_out, N, K, fp8, SIZE_MAX);
+}
+
+// Host query: the instance that a call which this kernel takes launches; false if it is not built
+bool proj_stream_describe(int M_out, int N, shiftattn_proj_plan_t* plan) {
+    const StreamShape shape = stream_shape(M_out, stream_rows(N));
+    *plan = shiftattn_proj_plan_t{1, 1, shape.ux, shape.uw, 0, 0, 0, 0, 0};
+    return stream_built(shape);
 }
 
 // What the size query names: for up to 64 rows whose k divides by that of eight wavefronts' steps, room for k ranges of token rows x

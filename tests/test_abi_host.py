@@ -417,3 +417,33 @@ def test_two_unequal_prompts_are_priced_for_the_half_of_the_chip_that_each_sees(
     a = _attn(B, num_q_heads=5, max_blocks_per_seq=547)
     p = B.prefill_plan(2, 5068 + 8739, 8739, 8739, a)
     assert (p.tile_columns, p.wave_columns, p.key_ranges) == (128, 32, 1)
+
+
+def test_projections_name_a_kernel_that_is_built(B):
+    """Every size takes one of the two projection kernels: the weight-streaming one with as many token pieces as cover the rows, in an
+    instance that is built (the query fails otherwise), or the tiled one.  40 features a workgroup and more than 96 rows have no
+    instance: a ring of one step."""
+    for fp8 in (False, True):
+        for n in (256, 768, 1280, 2304, 4096, 5120, 6144, 8192, 8448, 10240, 10496, 17408, 20480, 20736):
+            for k in (64, 128, 512, 2048, 4096, 5120, 8192, 8256, 16384, 65536):
+                for rows in range(1, 131):
+                    for ws in (None, 0, 1024):
+                        p = B.proj_plan(rows, n, k, fp8, ws)
+                        assert p.k_ranges >= 1
+                        if p.streams:
+                            assert 8 * p.token_pieces >= rows and p.feature_pieces in range(1, 6) and p.token_pieces + p.feature_pieces <= 20
+                        else:
+                            assert rows > 16 or k % (128 if fp8 else 64), (rows, n, k, fp8, ws)
+                            assert p.tile_features in (128, 256) and p.tile_tokens in (128, 256)
+    assert [B.proj_plan(r, 10240, 512).streams for r in (96, 97, 128)] == [1, 0, 0]
+    assert [B.proj_plan(r, 8192, 512).streams for r in (96, 97, 128, 129)] == [1, 1, 1, 0]
+    q = B.lib().shiftattn_proj_plan
+    plan = B.ProjPlan()
+    assert q(8, 256, 512, 0, 0, None) == B.EINVAL
+    assert q(0, 256, 512, 0, 0, ctypes.byref(plan)) == B.EINVAL and q(8, 0, 512, 0, 0, ctypes.byref(plan)) == B.EINVAL
+    assert q(8, 128, 512, 0, 0, ctypes.byref(plan)) == B.EUNSUPPORTED and q(8, 256, 96, 0, 0, ctypes.byref(plan)) == B.EUNSUPPORTED
+    try:
+        B.set_option(B.OPT_GENERIC_ONLY, 1)
+        assert B.proj_plan(1, 10240, 8192).streams == 0
+    finally:
+        B.set_option(B.OPT_GENERIC_ONLY, 0)
