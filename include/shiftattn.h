@@ -158,7 +158,8 @@ int shiftattn_unpack_o_proj(const void *recv, const void *w_o, void *out, int32_
 
 /* ---- The same two projections with a workspace (Algorithm 2: the few-token steps below the threshold) ----
  * With few token rows (T_pad for qkv_proj_pack, T for unpack_o_proj: up to 16, and up to 128 where it is expected to be
- * the faster way) the product is one pass over the weight matrix, which needs no workspace.  With a few
+ * the faster way) the product is one pass over the weight matrix; with few features and long rows of weights (2304 x 16384, say)
+ * that pass is split over k between workgroups, up to 64 rows.  With a few
  * hundred rows the large-batch kernel has too few output tiles to fill the chip and splits k, and with
  * a few thousand (a prefill chunk) it does so for the last token rows when the tiles are no multiple of the
  * chip's compute units.  The fp32 partial results need device memory:

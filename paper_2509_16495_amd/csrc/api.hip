@@ -359,9 +359,10 @@ int shiftattn_qkv_proj_pack_ws(const void* x, const void* w_qkv, void* send, int
         return fail(SHIFTATTN_EINVAL, "workspace is NULL or not 16-byte aligned");
     if (int rc = ensure_device_ready()) return rc;
     const int n_feat = (s.h + 2 * s.h_kv) * 128;
+    const int kg = s.T > 0 && !force_generic() ? proj_stream_ranges(s.T_pad, n_feat, d_model, false, workspace_bytes) : 0;
     hipError_t e;
-    if (s.T > 0 && !force_generic() && proj_stream_takes(s.T_pad, n_feat, d_model, false, workspace_bytes))
-        e = launch_qkv_proj_stream(x, w_qkv, send, d_model, s, nullptr, nullptr, static_cast<hipStream_t>(stream));
+    if (kg > 0)
+        e = launch_qkv_proj_stream(x, w_qkv, send, d_model, s, nullptr, nullptr, kg, workspace, static_cast<hipStream_t>(stream));
     else
         e = launch_qkv_proj_pack(x, w_qkv, send, d_model, s, nullptr, nullptr, workspace, workspace_bytes, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? SHIFTATTN_OK : hip_fail(e, "qkv_proj_pack launch");
@@ -386,9 +387,10 @@ int shiftattn_unpack_o_proj_ws(const void* recv, const void* w_o, void* out, int
     if (workspace_bytes > 0 && (!workspace || !aligned16(workspace)))
         return fail(SHIFTATTN_EINVAL, "workspace is NULL or not 16-byte aligned");
     if (int rc = ensure_device_ready()) return rc;
+    const int kg = force_generic() ? 0 : proj_stream_ranges(s.T, d_model, s.h * 128, false, workspace_bytes);
     hipError_t e;
-    if (!force_generic() && proj_stream_takes(s.T, d_model, s.h * 128, false, workspace_bytes))
-        e = launch_o_proj_stream(recv, w_o, out, d_model, s, nullptr, nullptr, static_cast<hipStream_t>(stream));
+    if (kg > 0)
+        e = launch_o_proj_stream(recv, w_o, out, d_model, s, nullptr, nullptr, kg, workspace, static_cast<hipStream_t>(stream));
     else
         e = launch_unpack_o_proj(recv, w_o, out, d_model, s, nullptr, nullptr, workspace, workspace_bytes, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? SHIFTATTN_OK : hip_fail(e, "unpack_o_proj launch");
@@ -413,8 +415,9 @@ int shiftattn_proj_plan(int32_t rows, int32_t n_features, int32_t k, int32_t fp8
     if (!plan) return fail(SHIFTATTN_EINVAL, "a required pointer is NULL");
     if (rows < 1 || n_features < 1 || k < 1) return fail(SHIFTATTN_EINVAL, "rows = %d, n_features = %d, k = %d", rows, n_features, k);
     if (n_features % 256 || k % 64) return fail(SHIFTATTN_EUNSUPPORTED, "no projection has n_features = %d, k = %d", n_features, k);
-    if (!force_generic() && proj_stream_takes(rows, n_features, k, fp8 != 0, workspace_bytes)) {
-        if (!proj_stream_describe(rows, n_features, plan))
+    const int kg = force_generic() ? 0 : proj_stream_ranges(rows, n_features, k, fp8 != 0, workspace_bytes);
+    if (kg > 0) {
+        if (!proj_stream_describe(rows, n_features, kg, plan))
             return fail(SHIFTATTN_EUNSUPPORTED, "no kernel is built for rows = %d, n_features = %d", rows, n_features);
     } else {
         proj_gemm_describe(rows, n_features, k, fp8 != 0, fp8 && force_generic() ? 0 : workspace_bytes, plan);
@@ -467,9 +470,10 @@ int shiftattn_qkv_proj_pack_fp8_ws(const void* x_codes, const float* x_scales, c
         return fail(SHIFTATTN_EINVAL, "workspace is NULL or not 16-byte aligned");
     if (int rc = ensure_device_ready()) return rc;
     const int n_feat = (s.h + 2 * s.h_kv) * 128;
+    const int kg = s.T > 0 && !force_generic() ? proj_stream_ranges(s.T_pad, n_feat, d_model, true, workspace_bytes) : 0;
     hipError_t e;
-    if (s.T > 0 && !force_generic() && proj_stream_takes(s.T_pad, n_feat, d_model, true, workspace_bytes))
-        e = launch_qkv_proj_stream(x_codes, w_codes, send, d_model, s, x_scales, w_scales, static_cast<hipStream_t>(stream));
+    if (kg > 0)
+        e = launch_qkv_proj_stream(x_codes, w_codes, send, d_model, s, x_scales, w_scales, kg, workspace, static_cast<hipStream_t>(stream));
     else
         e = launch_qkv_proj_pack(x_codes, w_codes, send, d_model, s, x_scales, w_scales, force_generic() ? nullptr : workspace,
                                  workspace_bytes, static_cast<hipStream_t>(stream));
@@ -497,9 +501,10 @@ int shiftattn_unpack_o_proj_fp8_ws(const void* recv_codes, const float* a_scales
     if (workspace_bytes > 0 && (!workspace || !aligned16(workspace)))
         return fail(SHIFTATTN_EINVAL, "workspace is NULL or not 16-byte aligned");
     if (int rc = ensure_device_ready()) return rc;
+    const int kg = force_generic() ? 0 : proj_stream_ranges(s.T, d_model, s.h * 128, true, workspace_bytes);
     hipError_t e;
-    if (!force_generic() && proj_stream_takes(s.T, d_model, s.h * 128, true, workspace_bytes))
-        e = launch_o_proj_stream(recv_codes, w_codes, out, d_model, s, a_scales, w_scales, static_cast<hipStream_t>(stream));
+    if (kg > 0)
+        e = launch_o_proj_stream(recv_codes, w_codes, out, d_model, s, a_scales, w_scales, kg, workspace, static_cast<hipStream_t>(stream));
     else
         e = launch_unpack_o_proj(recv_codes, w_codes, out, d_model, s, a_scales, w_scales, force_generic() ? nullptr : workspace,
                                  workspace_bytes, static_cast<hipStream_t>(stream));

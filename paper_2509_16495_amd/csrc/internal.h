@@ -208,16 +208,18 @@ size_t proj_gemm_workspace(int M_out, int N, int K, bool fp8);
 // what the large-batch kernel is expected to take with a workspace of this size, in microseconds
 double proj_gemm_us(int M_out, int N, int K, bool fp8, size_t workspace_bytes);
 // proj_stream.hip : the same two products for few token rows, organised around one pass over the weights
-bool proj_stream_takes(int M_out, int N, int K, bool fp8, size_t workspace_bytes);
+// (proj_stream_ranges: into how many k ranges that kernel splits such a call, each range's fp32 sums in the workspace; 1: none
+// is used; 0: the large-batch kernel takes the call)
+int proj_stream_ranges(int M_out, int N, int K, bool fp8, size_t workspace_bytes);
 // what either kernel launches for a call that it takes (host only); false: no such instance of the first one is built
-bool proj_stream_describe(int M_out, int N, shiftattn_proj_plan_t* plan);
+bool proj_stream_describe(int M_out, int N, int kg, shiftattn_proj_plan_t* plan);
 void proj_gemm_describe(int M_out, int N, int K, bool fp8, size_t workspace_bytes, shiftattn_proj_plan_t* plan);
 // the workspace that the size query names (shiftattn_proj_workspace_bytes)
 size_t proj_workspace(int M_out, int N, int K, bool fp8);
 hipError_t launch_qkv_proj_stream(const void* x, const void* w_qkv, void* send, int d_model, const XchgShape& s,
-                                  const float* x_scales, const float* w_scales, hipStream_t st);
+                                  const float* x_scales, const float* w_scales, int kg, void* workspace, hipStream_t st);
 hipError_t launch_o_proj_stream(const void* recv, const void* w_o, void* out, int d_model, const XchgShape& s,
-                                const float* a_scales, const float* w_scales, hipStream_t st);
+                                const float* a_scales, const float* w_scales, int kg, void* workspace, hipStream_t st);
 // (row_base: the partial results start at this token row of the result; rows below it are not touched)
 hipError_t launch_proj_finish(const float* partial, int kg, int t_rows, void* c, int M, int M_out, int N, int mode,
                               const XchgShape& s, const float* x_scales, const float* w_scales, hipStream_t st,

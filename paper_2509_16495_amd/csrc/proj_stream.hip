@@ -8,8 +8,10 @@
 //   * the eight wavefronts of a workgroup (four where a step is large) split k.  A wavefront multiplies all features of the
 //     block in one walk over its slice: per step of 128 bytes of k (64 bf16 or 128 FP8 elements) it fetches UX pieces of
 //     eight token rows and UW pieces of eight weight rows, and holds the sums of all (token, feature) pairs in registers (at
-//     most 24 up to 32 rows, 96 at 128 rows).  The token rows arrive with the weights they meet, so there is no limit on k
-//     and nothing to finish in a second launch;
+//     most 24 up to 32 rows, 96 at 128 rows).  The token rows arrive with the weights they meet, so there is no limit on k;
+//   * few features with long rows leave compute units idle or one long walk to each: there k is cut into 2, 4 or 8 ranges, each a
+//     workgroup of its own, if the caller's workspace has room for their fp32 sums, and a small second kernel (4 to 5 us with its
+//     launch, or 2 where the sums are few) adds them in range order;
 //   * both arrive by direct-to-LDS loads (1 KiB per instruction: eight rows x 128 bytes, whole cache lines; weights
 //     marked non-temporal: they are used once, the token rows by every workgroup) into a ring private to the wavefront -
 //     no workgroup barrier in the stream, a wavefront waits for its own loads by count - and are read back as MFMA
@@ -24,12 +26,16 @@
 // other against token rows held in registers, k split over workgroups and a finishing launch where they did not fit - ->
 // this one): 10240 x 8192 bf16, 1 / 16 / 19 / 32 rows 27.2 / 32.4 / 33.8 / 36.9 -> 27.0 / 26.7 / 27.0 / 29.0 (168 MB: 6.3
 // TB/s at 16 rows); 5120 x 2048 9.1 / 10.2 / 10.8 / 12.3 -> 6.7 / 7.3 / 7.6 / 8.0; FP8 codes, 10240 x 8192 16.1 / 18.3 / 19.8 / 22.4 ->
-// 15.0 / 15.1 / 15.4 / 16.4, 64 rows 26.1 -> 20.8.
+// 15.0 / 15.1 / 15.4 / 16.4, 64 rows 26.1 -> 20.8.  Few features, bf16, whole -> in ranges (the kernel before in brackets): 256 x
+// 65536, 1 row 41.9 -> 11.6 (16.4); 2304 x 16384, 32 rows 27.6 -> 17.8 (23.2); 1024 x 8192, 64 rows 18.1 -> 11.0 (16.1, the tiled
+// kernel).
 // What is left over the weights' pass at the read probe's 6.9 TB/s: launch, first round trip and the meeting (about 3 us), and
 // with many rows the token rows, which every workgroup reads whole (about 0.1 us per row at k = 8192).  Tried and not kept: as
 // many wavefronts as hold two steps each (16 at most; small products 2 to 20 % slower), weights requested further ahead than
 // the token rows in what is left of the LDS (within 2 %), at least 16 features a workgroup (up to 17 % slower).
 #include "internal.h"
+
+#include <math.h>
 
 namespace shiftattn {
 
@@ -53,13 +59,13 @@ struct StreamParams {
     const unsigned char* __restrict__ w;   // [N][K] bf16 or FP8 E4M3 codes
     const unsigned char* __restrict__ x;   // token rows, see mode
     uint16_t* __restrict__ c;              // bf16 result
-    const float* __restrict__ partial;     // finishing kernel: [kg][rows][N] fp32
+    float* __restrict__ partial;           // kg > 1: [kg][rows][N] fp32
     const float* __restrict__ xs;          // FP8 products: one scale per token row ...
     const float* __restrict__ ws;          // ... and one per output feature (nullptr: none)
     int M, M_out, N, K;                    // M token rows exist, rows M .. M_out - 1 of the result are zeros
     int mode;                              // 0: x dense [M][K], result into the send buffers; 1: x gathered from the
                                            // receive buffers (k = (p hq_l + j) 128 + e), result dense [M][N]
-    int kg;                                // finishing kernel: k ranges
+    int kg, kg_log2;                       // k ranges, each a workgroup of its own; the streaming kernel's are a power of two
     int rows_per_block;                    // features per block, a multiple of 4
     XchgShape s;
 };
@@ -124,16 +130,19 @@ __global__ __launch_bounds__((64 * stream_waves<UX, UW>())) void proj_stream_ker
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, grp = lane >> 4;
-    const int row_begin = blockIdx.x * p.rows_per_block;
+    // k range and block of features (workgroup i runs on XCD i % 8: a range's token rows enter few L2s)
+    const int kr = blockIdx.x & (p.kg - 1), rb = blockIdx.x >> p.kg_log2;
+    const int row_begin = rb * p.rows_per_block;
     const int row_end = min(p.N, row_begin + p.rows_per_block);   // row_begin < N: the grid has no empty workgroup
     const size_t k_bytes = static_cast<size_t>(p.K) * kElem;
     const int all_steps = p.K / kStepK;
-    const int slice = all_steps * wave / kWaves, n = all_steps * (wave + 1) / kWaves - slice;   // this wavefront's steps (none, if k is that short)
+    const int my_slice = kr * kWaves + wave, slices_log2 = p.kg_log2 + (kWaves == 8 ? 3 : 2);
+    const int slice = all_steps * my_slice >> slices_log2, n = (all_steps * (my_slice + 1) >> slices_log2) - slice;   // this wavefront's steps (none, if k is that short)
     // Neighbouring blocks start their walk kRotSteps apart and wrap around: rows lie k apart, often a power of two, and with
     // the same start everywhere all workgroups ask the same memory channels at the same time (in the kernel before: 8192
     // features x 8192 k, 1 / 16 rows 27.2 / 29.4 us in bf16, 16.6 / 16.8 with FP8 codes; three steps further per block 23.7 /
     // 26.5 and 13.1 / 14.8; other sizes within 1 % or faster, any odd step alike).
-    const int first = static_cast<int>((static_cast<uint32_t>(slice) + static_cast<uint32_t>(blockIdx.x) * kRotSteps) % all_steps);
+    const int first = static_cast<int>((static_cast<uint32_t>(slice) + static_cast<uint32_t>(rb) * kRotSteps) % all_steps);
     unsigned char* const ring_ptr = lds + wave * (kRing * kSlot);
     const uint32_t ring = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds)) + wave * (kRing * kSlot);
 
@@ -268,6 +277,10 @@ __global__ __launch_bounds__((64 * stream_waves<UX, UW>())) void proj_stream_ker
 #pragma unroll
             for (int e = 0; e < 4; ++e) sum[e] += v[e];
         }
+        if (p.kg > 1) {   // rows past the last token are not read
+            if (t < p.M) *reinterpret_cast<f32x4*>(p.partial + (static_cast<size_t>(kr) * p.M_out + t) * p.N + f) = sum;
+            continue;
+        }
         if constexpr (kFp8) {
             if (t < p.M) {
                 const float row_scale = p.xs[t];
@@ -290,9 +303,9 @@ constexpr int stream_lds() { return stream_waves<UX, UW>() * stream_steps<UX, UW
     X(12, 1) X(12, 2) X(12, 3) X(12, 4) X(12, 5) X(16, 1) X(16, 2) X(16, 3) X(16, 4)
 
 // features per workgroup: the chip's compute units read equally many bytes, in as many rounds of at most kMaxRows features as it takes
-int stream_rows(int N) {
-    const int rounds = (N + kSGrid * kMaxRows - 1) / (kSGrid * kMaxRows);
-    return ((N + kSGrid * rounds - 1) / (kSGrid * rounds) + 3) / 4 * 4;
+int stream_rows(int N, int kg) {
+    const int blocks = kSGrid / kg, rounds = (N + blocks * kMaxRows - 1) / (blocks * kMaxRows);
+    return ((N + blocks * rounds - 1) / (blocks * rounds) + 3) / 4 * 4;
 }
 
 struct StreamShape {
@@ -311,10 +324,9 @@ bool stream_built(StreamShape shape) {
     return false;
 }
 
-hipError_t run_stream(StreamParams p, hipStream_t st) {
-    p.rows_per_block = stream_rows(p.N);
+hipError_t launch_stream(const StreamParams& p, hipStream_t st) {
     const auto [ux, uw] = stream_shape(p.M_out, p.rows_per_block);
-    const unsigned grid = (p.N + p.rows_per_block - 1) / p.rows_per_block;
+    const unsigned grid = (p.N + p.rows_per_block - 1) / p.rows_per_block * p.kg;
 #define SHIFTATTN_STREAM_LAUNCH(ux_, uw_)                                                                   \
     if (ux == ux_ && uw == uw_) {                                                                         \
         if (p.xs) proj_stream_kernel<ux_, uw_, true><<<grid, 64 * stream_waves<ux_, uw_>(), stream_lds<ux_, uw_>(), st>>>(p);     \
@@ -326,7 +338,7 @@ hipError_t run_stream(StreamParams p, hipStream_t st) {
     return hipErrorInvalidValue;
 }
 
-// Behind the large-batch kernel with k ranges: result[t][f .. f + 3] = sum over the ranges in their order, rounded once
+// Behind either kernel with k ranges: result[t][f .. f + 3] = sum over the ranges in their order, rounded once
 // (row_base: partial row r is row row_base + r of the result)
 constexpr int kFinishAhead = 4;
 __global__ __launch_bounds__(256) void proj_stream_finish_kernel(StreamParams p, int t_rows, int row_base) {
@@ -372,7 +384,7 @@ hipError_t launch_proj_finish(const float* partial, int kg, int t_rows, void* c,
     StreamParams p = {};
     p.xs = x_scales;
     p.ws = w_scales;
-    p.partial = partial;
+    p.partial = const_cast<float*>(partial);
     p.c = static_cast<uint16_t*>(c);
     p.M = M;
     p.M_out = M_out;
@@ -398,6 +410,20 @@ hipError_t proj_stream_init() {
     return e;
 }
 
+// Microseconds of a call with k in kg ranges (one round of workgroups), for the choice of kg: launch and meeting, the walk of one
+// wavefront or the weights' pass, whichever is longer (rounded off where they are alike), the finishing launch with the sums written and
+// read.  Fitted to 3666 timed launches of 1 .. 64 rows, 256 .. 8192 features and 1024 .. 65536 k of both types, kg = 1, 2, 4, 8: 6 % off in one
+// of ten, 12 to 15 % in one of a hundred.
+static double stream_us(int M_out, int N, int64_t k_bytes, int kg) {
+    const auto [ux, uw] = stream_shape(M_out, stream_rows(N, kg));
+    const bool eight = ux + uw <= 10;   // wavefronts, see stream_waves()
+    const double step = eight ? 0.034 + 0.096 * ux + 0.178 * uw : 0.096 * (ux + uw) - 0.30;
+    const double walk = static_cast<double>(k_bytes) / kStepRowBytes / (kg * (eight ? 8 : 4)) * step;
+    const double weights = static_cast<double>(N) * k_bytes / 7.7e6;
+    const double w2 = walk * walk, b2 = weights * weights;
+    return 3.2 + 0.03 * (ux + uw) + sqrt(sqrt(w2 * w2 + b2 * b2)) + (kg > 1 ? 1.9 + kg * (8.0 * M_out * N) / 2.4e6 : 0.0);
+}
+
 // Served: up to 128 token rows, and expected to be no slower than the large-batch kernel with its small tiles and k ranges.
 // That kernel shares the weights among all of a tile's token rows, so it can win from 33 rows on; every block of features
 // reads all token rows here.  Measured, us, this kernel / that one:
@@ -414,7 +440,7 @@ hipError_t proj_stream_init() {
 //   * 65 to 128 rows: FP8 6144 x 4096, 96 / 128 rows 12.6 / 17.0, 14.7 / 18.6; 10240 x 5120 19.8 / 23.3, 25.4 / 25.5;
 //     1280 x 5120 11.9 / 12.5, 13.8 / 13.6; 8192 x 8192 21.7 / 21.5; bf16 8192 x 1024 8.2 / 11.0, 9.4 / 11.2; 5120 x 2048
 //     14.4 / 15.3, 16.9 / 16.6; 2048 x 4096 15.1 / 13.9.  (More than 32 features a workgroup and 96 rows: a ring of one step.)
-bool proj_stream_takes(int M_out, int N, int K, bool fp8, size_t workspace_bytes) {
+static bool proj_stream_takes(int M_out, int N, int K, bool fp8, size_t workspace_bytes) {
     const int elem = fp8 ? 1 : 2;
     if (M_out < 1 || M_out > 128 || N % 4 != 0 || K % (kStepRowBytes / elem) != 0) return false;
     const int64_t k_bytes = static_cast<int64_t>(K) * elem;
@@ -423,15 +449,39 @@ bool proj_stream_takes(int M_out, int N, int K, bool fp8, size_t workspace_bytes
         const double us = 3.0 + static_cast<double>(N) * k_bytes / 6.4e6 + static_cast<double>(rounds) * (M_out - 10) * k_bytes / 66e3;
         return M_out <= 64 && us <= proj_gemm_us(M_out, N, K, fp8, workspace_bytes);
     }
-    if (M_out > 64) return M_out <= 96 ? k_bytes <= (fp8 ? 5120 : 4096) : k_bytes <= (fp8 ? 4096 : 2048) && stream_rows(N) <= 32;
+    if (M_out > 64) return M_out <= 96 ? k_bytes <= (fp8 ? 5120 : 4096) : k_bytes <= (fp8 ? 4096 : 2048) && stream_rows(N, 1) <= 32;
     if (M_out <= 32 || k_bytes <= 8192 || M_out <= (N - 4096) / 96) return true;
     return proj_gemm_us(M_out, N, K, fp8, workspace_bytes) > 1.1 * proj_gemm_us(M_out, N, K, fp8, SIZE_MAX);
 }
 
+int proj_stream_ranges(int M_out, int N, int K, bool fp8, size_t workspace_bytes) {
+    const int elem = fp8 ? 1 : 2;
+    if (M_out < 1 || N % 4 != 0 || K % (kStepRowBytes / elem) != 0) return 0;
+    // k ranges only where the model has them 5 % ahead of the walk in one piece, or of the tiled kernel where that takes the call.  The
+    // choice over 1424 measured products of up to 64 rows with the workspace of the size query: within 2 % of the best kernel and kg
+    // in nine of ten, 13 % at worst in one of a hundred; none slower than the kernel before (2512 products).  Above 64 rows
+    // the size query's workspace is the tiled kernel's, which uses it.
+    const bool whole = proj_stream_takes(M_out, N, K, fp8, workspace_bytes);
+    if (M_out > 64) return whole ? 1 : 0;
+    const int64_t k_bytes = static_cast<int64_t>(K) * elem;
+    int best = whole ? 1 : 0;
+    double best_us = whole ? stream_us(M_out, N, k_bytes, 1) : proj_gemm_us(M_out, N, K, fp8, workspace_bytes);
+    for (int kg = 2; kg <= 8; kg *= 2) {
+        if (N > kSGrid / kg * kMaxRows || k_bytes < static_cast<int64_t>(kg) * 8 * kStepRowBytes ||
+            static_cast<size_t>(kg) * M_out * N * sizeof(float) > workspace_bytes) break;
+        const double us = 1.05 * stream_us(M_out, N, k_bytes, kg);
+        if (us < best_us && stream_built(stream_shape(M_out, stream_rows(N, kg)))) {
+            best = kg;
+            best_us = us;
+        }
+    }
+    return best;
+}
+
 // Host query: the instance that a call which this kernel takes launches; false if it is not built
-bool proj_stream_describe(int M_out, int N, shiftattn_proj_plan_t* plan) {
-    const StreamShape shape = stream_shape(M_out, stream_rows(N));
-    *plan = shiftattn_proj_plan_t{1, 1, shape.ux, shape.uw, 0, 0, 0, 0, 0};
+bool proj_stream_describe(int M_out, int N, int kg, shiftattn_proj_plan_t* plan) {
+    const StreamShape shape = stream_shape(M_out, stream_rows(N, kg));
+    *plan = shiftattn_proj_plan_t{1, kg, shape.ux, shape.uw, 0, 0, 0, 0, 0};
     return stream_built(shape);
 }
 
@@ -450,9 +500,19 @@ size_t proj_workspace(int M_out, int N, int K, bool fp8) {
     return proj_gemm_workspace(M_out, N, K, fp8);
 }
 
-// x_scales / w_scales: nullptr for bf16 operands, the row scales of FP8 E4M3 codes otherwise
+static hipError_t run_stream(StreamParams& p, int kg, void* workspace, hipStream_t st) {
+    p.kg = kg;
+    p.kg_log2 = __builtin_ctz(kg);
+    p.partial = static_cast<float*>(workspace);
+    p.rows_per_block = stream_rows(p.N, kg);
+    const hipError_t e = launch_stream(p, st);
+    if (e != hipSuccess || kg == 1) return e;
+    return launch_proj_finish(p.partial, kg, p.M_out, p.c, p.M, p.M_out, p.N, p.mode, p.s, p.xs, p.ws, st, 0);
+}
+
+// kg: k ranges, see proj_stream_ranges(); x_scales / w_scales: nullptr for bf16 operands, the row scales of FP8 E4M3 codes otherwise
 hipError_t launch_qkv_proj_stream(const void* x, const void* w_qkv, void* send, int d_model, const XchgShape& s,
-                                  const float* x_scales, const float* w_scales, hipStream_t st) {
+                                  const float* x_scales, const float* w_scales, int kg, void* workspace, hipStream_t st) {
     StreamParams p = {};
     p.w = static_cast<const unsigned char*>(w_qkv);
     p.x = static_cast<const unsigned char*>(x);
@@ -465,11 +525,11 @@ hipError_t launch_qkv_proj_stream(const void* x, const void* w_qkv, void* send, 
     p.K = d_model;
     p.mode = 0;
     p.s = s;
-    return run_stream(p, st);
+    return run_stream(p, kg, workspace, st);
 }
 
 hipError_t launch_o_proj_stream(const void* recv, const void* w_o, void* out, int d_model, const XchgShape& s,
-                                const float* a_scales, const float* w_scales, hipStream_t st) {
+                                const float* a_scales, const float* w_scales, int kg, void* workspace, hipStream_t st) {
     StreamParams p = {};
     p.w = static_cast<const unsigned char*>(w_o);
     p.x = static_cast<const unsigned char*>(recv);
@@ -482,7 +542,7 @@ hipError_t launch_o_proj_stream(const void* recv, const void* w_o, void* out, in
     p.K = s.h * kHeadDim;
     p.mode = 1;
     p.s = s;
-    return run_stream(p, st);
+    return run_stream(p, kg, workspace, st);
 }
 
 }  // namespace shiftattn

@@ -447,3 +447,21 @@ def test_projections_name_a_kernel_that_is_built(B):
         assert B.proj_plan(1, 10240, 8192).streams == 0
     finally:
         B.set_option(B.OPT_GENERIC_ONLY, 0)
+
+
+def test_few_features_with_long_rows_of_weights_split_k(B):
+    """A block's workgroup walks all of k: with few features that is one long chain on part of the chip, so k goes over several
+    workgroups where the workspace that the size query names has room for their sums, and never takes more than was given."""
+    for fp8 in (False, True):
+        e = 1 if fp8 else 2
+        for rows in (17, 24, 32, 33, 48, 64):
+            for n in (256, 512, 1024, 1536, 2304):
+                for k_bytes in (32768, 65536):
+                    p = B.proj_plan(rows, n, k_bytes // e, fp8)
+                    assert p.k_ranges > 1, (rows, n, k_bytes, fp8)
+                    assert not p.streams or p.k_ranges * rows * n * 4 <= B.proj_workspace_bytes(rows, n, k_bytes // e, fp8)
+                    room = 2 * rows * n * 4
+                    assert B.proj_plan(rows, n, k_bytes // e, fp8, room).k_ranges <= 2
+                    assert B.proj_plan(rows, n, k_bytes // e, fp8, room - 1).k_ranges == 1
+    assert [B.proj_plan(r, 256, 65536).k_ranges for r in (1, 8, 16)] == [8, 8, 8]
+    assert B.proj_plan(32, 2304, 16384).streams == 1 and B.proj_plan(64, 1024, 8192).streams == 1

@@ -1,6 +1,7 @@
 """The projections of up to 128 token rows at the edges of the weight-streaming kernel against the CPU float64 oracle: every number
 of token pieces (8 rows each) and weight pieces (8 features each) of a workgroup, ragged ones of both, more features than one round of
-the chip takes, and k of fewer steps than wavefronts, of a number of steps that eight does not divide, and beyond one pass of the ring.
+the chip takes, and k of fewer steps than wavefronts, of a number of steps that eight does not divide, and beyond one pass of the ring; with a
+workspace, k in ranges over several workgroups.  The host query names the kernel, so a change of the rule fails here.
 Tolerance as for all bf16 projections: one rounding of the result (2^-8 |ref|) and the fp32 sums (1e-3 sqrt(K) covers them for
 standard normal operands); FP8 operands are exact products of the codes, so the same holds for them."""
 import numpy as np
@@ -29,9 +30,37 @@ CASES = [
 ]
 
 
+# k in ranges: (projection that has them, k ranges with bf16 and with FP8 operands) beside the sizes
+RANGES = [
+    # P, h, h_kv, d_model, T, T_pad
+    (2, 4, 2, 16384, 9, 12, "qkv", 2, 1),      # padding rows: no partial sums, zeros in the send buffers
+    (2, 4, 2, 12288, 64, 64, "qkv", 8, 4),     # 192 (96) steps over 64 (32) wavefronts
+    (8, 16, 1, 8192, 45, 48, "qkv", 4, 1),     # KV replication; 36 features per workgroup, sixteen pieces a step
+    (8, 64, 8, 512, 32, 33, "o", 2, 1),        # the second range starts in the fifth of eight receive buffers
+    (4, 256, 8, 256, 1, 1, "o", 8, 8),         # one row; the blocks of features start further apart than a range is long
+    (1, 72, 8, 256, 17, 20, "o", 8, 8),        # 144 (72) steps over 64 wavefronts
+]
+
+
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("P,h,h_kv,d_model,T,T_pad,which,bf16_ranges,fp8_ranges", RANGES)
+def test_k_ranges_over_workgroups(oracle, P, h, h_kv, d_model, T, T_pad, which, bf16_ranges, fp8_ranges, fp8):
+    from paper_2509_16495_amd import binding as B
+    n, k, rows = ((h + 2 * h_kv) * 128, d_model, T_pad) if which == "qkv" else (d_model, h * 128, T)
+    plan = B.proj_plan(rows, n, k, fp8)
+    assert plan.streams and plan.k_ranges == (fp8_ranges if fp8 else bf16_ranges)
+    _both_projections(oracle, P, h, h_kv, d_model, T, T_pad, fp8, workspace=True)
+
+
 @pytest.mark.parametrize("fp8", [False, True])
 @pytest.mark.parametrize("P,h,h_kv,d_model,T,T_pad", CASES)
 def test_stream_kernel_edges(oracle, P, h, h_kv, d_model, T, T_pad, fp8):
+    from paper_2509_16495_amd import binding as B
+    assert B.proj_plan(T_pad, (h + 2 * h_kv) * 128, d_model, fp8, 0).streams and B.proj_plan(T, d_model, h * 128, fp8, 0).streams
+    _both_projections(oracle, P, h, h_kv, d_model, T, T_pad, fp8)
+
+
+def _both_projections(oracle, P, h, h_kv, d_model, T, T_pad, fp8, workspace=False):
     import torch
     import gpu_backend as G
     from paper_2509_16495_amd import binding as B
@@ -47,6 +76,11 @@ def test_stream_kernel_edges(oracle, P, h, h_kv, d_model, T, T_pad, fp8):
     out = torch.empty((T, d_model), dtype=torch.bfloat16, device=G.DEV)
     send.view(torch.uint8).fill_(0x55)
     out.view(torch.uint8).fill_(0x55)
+    ws_q = ws_o = guard = None
+    if workspace:   # as large as the size query says, a guard behind it
+        need = max(B.proj_workspace_bytes(T_pad, N, d_model, fp8), B.proj_workspace_bytes(T, d_model, K, fp8))
+        guard = torch.full((need + 4096,), 0x77, dtype=torch.uint8, device=G.DEV)
+        ws_q, ws_o = guard[:B.proj_workspace_bytes(T_pad, N, d_model, fp8)], guard[:B.proj_workspace_bytes(T, d_model, K, fp8)]
     if fp8:
         def quantised(a):
             codes = torch.empty(a.shape, dtype=torch.uint8, device=G.DEV)
@@ -56,8 +90,8 @@ def test_stream_kernel_edges(oracle, P, h, h_kv, d_model, T, T_pad, fp8):
         (xc, xs), (wqc, wqs), (woc, wos) = quantised(dev["x"]), quantised(dev["wq"]), quantised(dev["wo"])
         rc, rs = torch.zeros(dev["recv"].shape, dtype=torch.uint8, device=G.DEV), torch.empty(T, dtype=torch.float32, device=G.DEV)
         B.quantize_recv_fp8(dev["recv"], rc, rs)
-        B.qkv_proj_pack_fp8(xc, xs, wqc, wqs, send, P, h, h_kv)
-        B.unpack_o_proj_fp8(rc, rs, woc, wos, out)
+        B.qkv_proj_pack_fp8(xc, xs, wqc, wqs, send, P, h, h_kv, workspace=ws_q)
+        B.unpack_o_proj_fp8(rc, rs, woc, wos, out, workspace=ws_o)
         f64 = lambda c: c.view(torch.float8_e4m3fn).to(torch.float64).cpu()   # noqa: E731
         X, WQ, WO = (f64(c) * s.double().cpu()[:, None] for c, s in ((xc, xs), (wqc, wqs), (woc, wos)))
         R = f64(rc)[:, :T].permute(1, 0, 2, 3).reshape(T, K) * rs.double().cpu()[:, None]
@@ -68,8 +102,8 @@ def test_stream_kernel_edges(oracle, P, h, h_kv, d_model, T, T_pad, fp8):
             g = p * h_kv // P
             want_send[p, :T] = np.concatenate([qkv[:, p * hl:(p + 1) * hl], qkv[:, h + g:h + g + kl], qkv[:, h + h_kv + g:h + h_kv + g + kl]], axis=1)
     else:
-        B.qkv_proj_pack(dev["x"], dev["wq"], send, P, h, h_kv)
-        B.unpack_o_proj(dev["recv"], dev["wo"], out)
+        B.qkv_proj_pack(dev["x"], dev["wq"], send, P, h, h_kv, workspace=ws_q)
+        B.unpack_o_proj(dev["recv"], dev["wo"], out, workspace=ws_o)
         want_send = oracle.qkv_proj_pack(x, w_qkv, P, h, h_kv, D, T_pad, "bf16")
         want_out = oracle.unpack_o_proj(recv, w_o, T, "bf16")
     torch.cuda.synchronize()
@@ -79,3 +113,4 @@ def test_stream_kernel_edges(oracle, P, h, h_kv, d_model, T, T_pad, fp8):
         err = np.abs(got - want)
         assert np.all(err <= 2.0 ** -8 * np.abs(want) + 1e-3 * np.sqrt(k)), float(err.max())
     assert not np.any(B.to_host(send)[:, T:])
+    assert guard is None or bool((guard[-4096:] == 0x77).all())
