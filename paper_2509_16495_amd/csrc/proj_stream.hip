@@ -457,9 +457,10 @@ static bool proj_stream_takes(int M_out, int N, int K, bool fp8, size_t workspac
 int proj_stream_ranges(int M_out, int N, int K, bool fp8, size_t workspace_bytes) {
     const int elem = fp8 ? 1 : 2;
     if (M_out < 1 || N % 4 != 0 || K % (kStepRowBytes / elem) != 0) return 0;
-    // k ranges only where the model has them 5 % ahead of the walk in one piece, or of the tiled kernel where that takes the call.  The
-    // choice over 1424 measured products of up to 64 rows with the workspace of the size query: within 2 % of the best kernel and kg
-    // in nine of ten, 13 % at worst in one of a hundred; none slower than the kernel before (2512 products).  Above 64 rows
+    // k ranges only where the model has them 5 % ahead of the walk in one piece, or 10 % of the tiled kernel where that takes the call
+    // (with 5 %: 3072 x 12288, 48 rows 23.1 us in two ranges, 21.8 there).  The
+    // choice over 1424 measured products of up to 64 rows with the workspace of the size query: within 3 % of the best kernel and kg
+    // in nine of ten, 15 % off in one of a hundred; none slower than the kernel before (2512 products).  Above 64 rows
     // the size query's workspace is the tiled kernel's, which uses it.
     const bool whole = proj_stream_takes(M_out, N, K, fp8, workspace_bytes);
     if (M_out > 64) return whole ? 1 : 0;
@@ -469,7 +470,7 @@ int proj_stream_ranges(int M_out, int N, int K, bool fp8, size_t workspace_bytes
     for (int kg = 2; kg <= 8; kg *= 2) {
         if (N > kSGrid / kg * kMaxRows || k_bytes < static_cast<int64_t>(kg) * 8 * kStepRowBytes ||
             static_cast<size_t>(kg) * M_out * N * sizeof(float) > workspace_bytes) break;
-        const double us = 1.05 * stream_us(M_out, N, k_bytes, kg);
+        const double us = (whole ? 1.05 : 1.1) * stream_us(M_out, N, k_bytes, kg);
         if (us < best_us && stream_built(stream_shape(M_out, stream_rows(N, kg)))) {
             best = kg;
             best_us = us;

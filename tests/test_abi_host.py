@@ -464,4 +464,5 @@ def test_few_features_with_long_rows_of_weights_split_k(B):
                     assert B.proj_plan(rows, n, k_bytes // e, fp8, room).k_ranges <= 2
                     assert B.proj_plan(rows, n, k_bytes // e, fp8, room - 1).k_ranges == 1
     assert [B.proj_plan(r, 256, 65536).k_ranges for r in (1, 8, 16)] == [8, 8, 8]
+    assert B.proj_plan(48, 3072, 12288).streams == 0   # the tiled kernel is the faster one
     assert B.proj_plan(32, 2304, 16384).streams == 1 and B.proj_plan(64, 1024, 8192).streams == 1
