@@ -60,6 +60,53 @@ def test_stream_kernel_edges(oracle, P, h, h_kv, d_model, T, T_pad, fp8):
     _both_projections(oracle, P, h, h_kv, d_model, T, T_pad, fp8)
 
 
+# Every instance of the kernel: pieces of eight token rows x pieces of eight features per workgroup (4, 12, 20, 28 and 36 features on 256
+# compute units, so the last piece is half empty).  20 and, with FP8 codes, 10 steps of k: the wavefronts have unequal shares, and the
+# rings of two steps of the largest instances turn over.
+FEATURES = {1: 1024, 2: 3072, 3: 5120, 4: 7168, 5: 9216}
+PIECES = [(x, w) for x in (1, 2, 3, 4, 6, 8, 12, 16) for w in FEATURES if (x, w) != (16, 5)]
+
+
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("token_pieces,feature_pieces", PIECES)
+def test_every_instance(token_pieces, feature_pieces, fp8):
+    """Both projections at rows that leave the last token piece ragged, against float64 of the same operands."""
+    import torch
+    import gpu_backend as G
+    from paper_2509_16495_amd import binding as B
+    n, k = FEATURES[feature_pieces], 1280
+    if token_pieces == 16:   # (up to 2 KiB of weights a row in bf16)
+        k = 1024
+    T = 8 * token_pieces - 3
+    plan = B.proj_plan(T, n, k, fp8, 0)
+    assert (plan.streams, plan.k_ranges, plan.token_pieces, plan.feature_pieces) == (1, 1, token_pieces, feature_pieces)
+    g = torch.Generator(device=G.DEV)
+    g.manual_seed(8)
+    a = torch.randn((T, k), device=G.DEV, generator=g).to(torch.bfloat16)
+    w = torch.randn((n, k), device=G.DEV, generator=g).to(torch.bfloat16)
+    out = torch.empty((T, n), dtype=torch.bfloat16, device=G.DEV)
+    send = torch.empty((1, T, n // 128, 128), dtype=torch.bfloat16, device=G.DEV)
+    for b in (out, send):
+        b.view(torch.uint8).fill_(0x55)
+    if fp8:
+        ac, asc = torch.empty(a.shape, dtype=torch.uint8, device=G.DEV), torch.empty(T, dtype=torch.float32, device=G.DEV)
+        wc, wsc = torch.empty(w.shape, dtype=torch.uint8, device=G.DEV), torch.empty(n, dtype=torch.float32, device=G.DEV)
+        B.quantize_rows_fp8(a, ac, asc)
+        B.quantize_rows_fp8(w, wc, wsc)
+        B.unpack_o_proj_fp8(ac.view(1, T, k // 128, 128), asc, wc, wsc, out)
+        B.qkv_proj_pack_fp8(ac, asc, wc, wsc, send, 1, n // 128 - 2, 1)
+        value = lambda c, s: c.view(torch.float8_e4m3fn).to(torch.float64) * s.double()[:, None]   # noqa: E731
+        want = value(ac, asc) @ value(wc, wsc).T
+    else:
+        B.unpack_o_proj(a.view(1, T, k // 128, 128), w, out)
+        B.qkv_proj_pack(a, w, send, 1, n // 128 - 2, 1)
+        want = a.double() @ w.double().T
+    torch.cuda.synchronize()
+    for got in (out, send.view(T, n)):
+        err = (got.double() - want).abs()
+        assert bool((err <= 2.0 ** -8 * want.abs() + 1e-3 * k ** 0.5).all()), float(err.max())
+
+
 def _both_projections(oracle, P, h, h_kv, d_model, T, T_pad, fp8, workspace=False):
     import torch
     import gpu_backend as G
