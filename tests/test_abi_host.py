@@ -67,7 +67,7 @@ def test_options_and_their_bounds(B):
 
 def test_launch_plans_follow_the_shape_of_the_batch(B):
     """Host logic behind the workspace queries (no GPU work): how many key ranges a prefill launch takes, seen through
-    the size of its partial results, `ranges x rows x heads x (128 + 2) x 4` bytes; and the k ranges / k groups of the
+    the size of its partial results, `ranges x rows x heads x (128 + 2) x 4` bytes; and the sizes named for the k ranges of the
     projections.  Shapes: the benchmark's batches (Table 4 head geometries on 8 ranks)."""
     def ranges(num_seqs, total_q, max_q, max_ctx, hq):
         a = _attn(B, num_q_heads=hq, max_blocks_per_seq=(max_ctx + 15) // 16)
@@ -93,8 +93,8 @@ def test_launch_plans_follow_the_shape_of_the_batch(B):
     finally:
         B.set_option(B.OPT_PREFILL_TILE, 0)
         B.set_option(B.OPT_PREFILL_PAIRING, 0)
-    # projections: k groups of the streaming kernel (token slice of a wavefront <= 128 registers), k ranges of the
-    # large-batch kernel while its tiles are few, nothing once they fill the chip
+    # projections: up to 64 rows ranges x rows rounded up to 16, 32 or 64, above them the k ranges of the large-batch kernel while its
+    # tiles are few, nothing once they fill the chip
     n, k = 10240, 8192
     assert [B.proj_workspace_bytes(t, n, k) // (n * 4) for t in (1, 16, 17, 32, 33, 64)] == [0, 0, 2 * 32, 2 * 32, 4 * 64, 4 * 64]
     assert B.proj_workspace_bytes(65, n, k) == 6 * 65 * n * 4 and B.proj_workspace_bytes(512, n, k) == 3 * 512 * n * 4

@@ -94,12 +94,12 @@ QKV_CASES = [
     (2, 8, 4, 1024, 600, 600),
     (2, 8, 4, 192, 9, 10),         # three k tiles: fewer than the ring holds
     (8, 64, 8, 192, 0, 8),         # padding rows only
-    (8, 8, 8, 5120, 20, 24),       # few output tiles, long k no multiple of 1024: with a workspace, k split over workgroups
+    (8, 8, 8, 5120, 20, 24),       # three pieces of eight token rows, the last with padding rows; five steps of k per wavefront
     (8, 32, 8, 2048, 130, 136),
     (8, 8, 8, 8192, 8, 8),         # a decode step's few rows: the weight-streaming kernel (one pass over the codes)
-    (8, 8, 8, 4096, 20, 24),       # two token blocks, one k group
-    (8, 8, 8, 4096, 40, 40),       # four token blocks: two k groups with a workspace, the large-batch kernel without
-    (4, 40, 8, 1024, 5, 8),        # 28 features per workgroup, one step per wavefront
+    (8, 8, 8, 4096, 20, 24),       # three pieces of token rows, the last with padding rows
+    (8, 8, 8, 4096, 40, 40),       # five pieces run as six
+    (4, 40, 8, 1024, 5, 8),        # 28 features per workgroup, one step of k per wavefront
     (8, 32, 4, 2048, 3, 4),        # replication into several send buffers
     (2, 4, 2, 2112, 100, 100),     # k split over two workgroups with a half-filled last stage in the second range
 ]
