@@ -165,10 +165,11 @@ int shiftattn_unpack_o_proj(const void *recv, const void *w_o, void *out, int32_
  * chip's compute units.  The fp32 partial results need device memory:
  *   shiftattn_proj_workspace_bytes(rows, n_features, k): bytes for a product of `rows` token rows with a
  *     [n_features][k] weight matrix (qkv: n_features = (h + 2 h_kv) * D, k = d_model; o: n_features =
- *     d_model, k = h * D); 0 when none is needed.
- * workspace (device, scratch): at least that many bytes, 16-byte aligned; NULL / 0 is always accepted and
- *   means "use a kernel that needs none" (the calls above do exactly that) - between 17 rows and a few
- *   hundred that can be several times slower.  Calls that share a workspace must not overlap.
+ *     d_model, k = h * D).  These sizes stay as they are from version to version: they are what a call makes good use of, or
+ *     more than it uses, up to all of it (17 to 32 rows that are one pass over the weights); 0: the call would use none.
+ * workspace (device, scratch): that many bytes, 16-byte aligned.  Less is accepted too, and NULL / 0: the call then splits k into
+ *   fewer ranges or not at all (the calls above do exactly that), which can be several times slower from 33 rows to a few
+ *   hundred, and from one row on where features are few and rows of weights long.  Calls that share a workspace must not overlap.
  * Results are bitwise reproducible with and without a workspace, not bitwise equal between the two. */
 size_t shiftattn_proj_workspace_bytes(int32_t rows, int32_t n_features, int32_t k);
 int shiftattn_qkv_proj_pack_ws(const void *x, const void *w_qkv, void *send, int32_t T, int32_t T_pad,

@@ -262,7 +262,7 @@ def unpack_head2seq(recv: torch.Tensor, out: torch.Tensor) -> None:
 
 # ---- KV cache and attention -------------------------------------------------------------------------
 def proj_workspace_bytes(rows: int, n_features: int, k: int, fp8: bool = False) -> int:
-    """Bytes of workspace that make a projection of `rows` token rows with an [n_features, k] matrix one pass over the weights."""
+    """Bytes of workspace that a projection of `rows` token rows with an [n_features, k] matrix makes good use of (or more than it uses)."""
     if fp8:
         return int(lib().shiftattn_proj_workspace_bytes_fp8(rows, n_features, k))
     return int(lib().shiftattn_proj_workspace_bytes(rows, n_features, k))

@@ -8,7 +8,7 @@
 //   * the eight wavefronts of a workgroup (four where a step is large) split k.  A wavefront multiplies all features of the
 //     block in one walk over its slice: per step of 128 bytes of k (64 bf16 or 128 FP8 elements) it fetches UX pieces of
 //     eight token rows and UW pieces of eight weight rows, and holds the sums of all (token, feature) pairs in registers (at
-//     most 24 up to 32 rows, 96 at 128 rows).  The token rows arrive with the weights they meet, so there is no limit on k;
+//     most 24 up to 32 rows, 48 up to 64, 72 up to 96, 64 up to 128).  The token rows arrive with the weights they meet, so there is no limit on k;
 //   * few features with long rows leave compute units idle or one long walk to each: there k is cut into 2, 4 or 8 ranges, each a
 //     workgroup of its own, if the caller's workspace has room for their fp32 sums, and a small second kernel (4 to 5 us with its
 //     launch, or 2 where the sums are few) adds them in range order;
@@ -259,7 +259,7 @@ __global__ __launch_bounds__((64 * stream_waves<UX, UW>())) void proj_stream_ker
                         acc[tw][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag(a[tw][kb]), frag(b[tb][kb]), acc[tw][tb], 0, 0, 0);
         }
     }
-    // ---- the eight k slices meet, each in its wavefront's ring, which has been read and into which nothing is on its way
+    // ---- the wavefronts' k slices meet, each in its wavefront's ring, which has been read and into which nothing is on its way
 #pragma unroll
     for (int tw = 0; tw < TW; ++tw)
 #pragma unroll
@@ -436,10 +436,14 @@ static double stream_us(int M_out, int N, int64_t k_bytes, int kg) {
 //   * more features than one round takes, or rows of more than 16 KiB: by a model of both (this one: launch, the weights' pass at
 //     6.4 TB/s, and per round the token rows past the tenth at 66 GB/s a compute unit).  bf16 14336 x 12288, 24 / 32 rows
 //     64.1 / 65.3, 71.1 / 66.1; 18432 x 8192, 32 / 64 rows 54.1 / 63.2, 71.9 / 63.2; 4096 x 15360, 24 rows 29.9 / 27.6; FP8
-//     8192 x 16384, 32 rows 24.5 / 37.6;
+//     8192 x 16384, 32 rows 24.5 / 37.6.  The model prices this one too high near the line, so some calls stay with the tiled kernel
+//     that this one would serve sooner: bf16 8192 x 16384, 32 rows 45.6 / 51.5; 24576 x 8192, 24 rows 67.2 / 71.5; 17408 x 4096, 48
+//     rows 33.0 / 36.0; FP8 14336 x 12288, 17 rows 33.8 / 37.6; 24576 x 8192, 24 rows 37.2 / 40.5;
 //   * 65 to 128 rows: FP8 6144 x 4096, 96 / 128 rows 12.6 / 17.0, 14.7 / 18.6; 10240 x 5120 19.8 / 23.3, 25.4 / 25.5;
 //     1280 x 5120 11.9 / 12.5, 13.8 / 13.6; 8192 x 8192 21.7 / 21.5; bf16 8192 x 1024 8.2 / 11.0, 9.4 / 11.2; 5120 x 2048
 //     14.4 / 15.3, 16.9 / 16.6; 2048 x 4096 15.1 / 13.9.  (More than 32 features a workgroup and 96 rows: a ring of one step.)
+//     The figures of the tiled kernel are those with its workspace; a call without one is not told apart here and takes that kernel
+//     unsplit for longer rows, as it always has (2304 x 5120 in bf16: 65 rows 45 us, 64 rows here 17).
 static bool proj_stream_takes(int M_out, int N, int K, bool fp8, size_t workspace_bytes) {
     const int elem = fp8 ? 1 : 2;
     if (M_out < 1 || M_out > 128 || N % 4 != 0 || K % (kStepRowBytes / elem) != 0) return false;
@@ -486,9 +490,12 @@ bool proj_stream_describe(int M_out, int N, int kg, shiftattn_proj_plan_t* plan)
     return stream_built(shape);
 }
 
-// What the size query names: for up to 64 rows whose k divides by that of eight wavefronts' steps, room for k ranges of token rows x
-// features in fp32, which the large-batch kernel uses where it takes such a call; else what its own plan wants.  (Callers allocate by
-// it and tests pin it, see proj_gemm_workspace(); which kernel runs is decided per call by what fits.)
+// What the size query names: for up to 64 rows whose k divides by that of eight wavefronts' steps, room for k ranges of token rows
+// (rounded up to 16, 32 or 64) x features in fp32, else what the large-batch kernel's plan wants.  Callers allocate by these sizes and
+// tests pin them, so they are part of the interface and no longer follow either kernel: which kernel runs, in how many ranges, is
+// decided per call by what fits.  They are more than a call uses where it streams whole (17 to 32 rows x 10240 x 8192: 2.6 MB, none
+// used), and less than the tiled kernel would take for 33 to 64 rows of 8192 x 8192 and the like (within 2 % there; where features
+// are few the ranges of this kernel make up for it: 48 rows x 1280 x 8192).
 size_t proj_workspace(int M_out, int N, int K, bool fp8) {
     const int per_step = kSWaves * kStepRowBytes / (fp8 ? 1 : 2);
     if (M_out <= 64 && N % 4 == 0 && K % per_step == 0) {
