@@ -675,6 +675,14 @@ def main() -> int:
         wq_rot = [wq] + [(torch.randn(wq.shape, device=dev, generator=gen) * 0.02).to(bf) for _ in range(2)]
         wo_rot = [wo] + [(torch.randn(wo.shape, device=dev, generator=gen) * 0.02).to(bf) for _ in range(2)]
         small_proj = {}
+
+        def proj_kernel_name(call, rows, fp8):
+            n, k = (wq.shape[0], d_model) if call.startswith("qkv") else (d_model, h3 * D)
+            p = B.proj_plan(rows, n, k, fp8)
+            name = (f"proj_stream_kernel<{p.token_pieces},{p.feature_pieces}{',fp8' if fp8 else ''}>" if p.streams
+                    else f"proj_gemm_kernel<{'fp8' if fp8 else 'bf16'}>, {p.tile_features} x {p.tile_tokens} tiles")
+            return name if p.k_ranges == 1 else f"{name}, {p.k_ranges} k ranges, + proj_stream_finish_kernel"
+
         for Ts in (1, 8, 16, 32, 64, 256):
             xs_ = torch.randn((Ts, d_model), device=dev, generator=gen).to(bf)
             snd = torch.empty((x3.P, Ts, h3 // x3.P + 2 * (hkv3 // x3.P), D), dtype=bf, device=dev)
@@ -707,7 +715,7 @@ def main() -> int:
                 gbps = wbytes / (us * 1e-6) / 1e9
                 row[nm] = {"us": round(us, 2), "library_gemm_and_separate_layout_kernel_us": round(us_ref, 2),
                            "weight_bytes": wbytes, "us_to_stream_the_weights_at_peak": round(wbytes / PEAK_HBM_GBPS / 1e3, 2),
-                           "roofline": roof("proj_stream_kernel" if Ts <= 64 else "proj_gemm_kernel<bf16>", "hbm", gbps, PEAK_HBM_GBPS, "GB/s", traffic_key=f"{nm}_T{Ts}")}
+                           "roofline": roof(proj_kernel_name(nm, Ts, False), "hbm", gbps, PEAK_HBM_GBPS, "GB/s", traffic_key=f"{nm}_T{Ts}")}
             small_proj[f"T={Ts}"] = row
             if cpu and Ts == 16:
                 t0 = time.perf_counter()
@@ -739,7 +747,7 @@ def main() -> int:
                                     wo8.numel())):
                 us = time_in_graph(fn, inner=12) * 1e3
                 row[nm] = {"us": round(us, 2), "weight_bytes": wbytes, "us_to_stream_the_weights_at_peak": round(wbytes / PEAK_HBM_GBPS / 1e3, 2),
-                           "roofline": roof("proj_stream_kernel<fp8>" if Ts <= 64 else "proj_gemm_kernel<fp8> (k split over workgroups) + proj_stream_finish_kernel", "hbm",
+                           "roofline": roof(proj_kernel_name(nm, Ts, True), "hbm",
                                             wbytes / (us * 1e-6) / 1e9, PEAK_HBM_GBPS, "GB/s")}
             small_fp8[f"T={Ts}"] = row
             del snd, eo_s, ws_q, ws_o
