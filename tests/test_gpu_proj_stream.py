@@ -60,6 +60,35 @@ def test_stream_kernel_edges(oracle, P, h, h_kv, d_model, T, T_pad, fp8):
     _both_projections(oracle, P, h, h_kv, d_model, T, T_pad, fp8)
 
 
+def test_k_ranges_in_a_replayed_graph():
+    """Both launches of a call in ranges, captured: replays on other inputs of the same buffers, with eager calls between them, give
+    the bits of the eager call."""
+    import torch
+    import gpu_backend as G
+    from paper_2509_16495_amd import binding as B
+    T, n, k = 40, 512, 16384
+    assert B.proj_plan(T, n, k).streams and B.proj_plan(T, n, k).k_ranges > 1
+    g = torch.Generator(device=G.DEV)
+    g.manual_seed(9)
+    recv = torch.randn((8, T, k // 1024, 128), device=G.DEV, generator=g).to(torch.bfloat16)
+    w = torch.randn((n, k), device=G.DEV, generator=g).to(torch.bfloat16)
+    ws = torch.empty(B.proj_workspace_bytes(T, n, k), dtype=torch.uint8, device=G.DEV)
+    out, eager = (torch.empty((T, n), dtype=torch.bfloat16, device=G.DEV) for _ in range(2))
+    B.unpack_o_proj(recv, w, out, workspace=ws)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        B.unpack_o_proj(recv, w, out, workspace=ws)
+    for _ in range(3):
+        recv.copy_(torch.randn(recv.shape, device=G.DEV, generator=g))
+        out.view(torch.uint8).fill_(0x55)
+        graph.replay()
+        torch.cuda.synchronize()
+        B.unpack_o_proj(recv, w, eager, workspace=ws)
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(torch.uint8), eager.view(torch.uint8))
+
+
 # Every instance of the kernel: pieces of eight token rows x pieces of eight features per workgroup (4, 12, 20, 28 and 36 features on 256
 # compute units, so the last piece is half empty).  20 and, with FP8 codes, 10 steps of k: the wavefronts have unequal shares, and the
 # rings of two steps of the largest instances turn over.
